@@ -310,30 +310,37 @@ int quartet_requant_transpose_sr(const uint8_t* src_codes, const uint8_t* src_sc
                                               codes, scales, stream);
 }
 
-int quartet_fwd_operands(const void* x_bf16, const void* w_bf16, int64_t tokens, int64_t in, int64_t out,
-                         uint8_t* xq_codes, uint8_t* xq_scales, uint32_t* x_mask,
-                         uint8_t* wq_codes, uint8_t* wq_scales, uint32_t* w_mask, void* stream) {
+// Hadamard blocks of 32 nb elements
+static int fwd_operands_launch(const void* x_bf16, const void* w_bf16, int64_t tokens, int64_t in, int64_t out, uint32_t nb,
+                               uint8_t* xq_codes, uint8_t* xq_scales, uint32_t* x_mask,
+                               uint8_t* wq_codes, uint8_t* wq_scales, uint32_t* w_mask, void* stream) {
     if (!x_bf16 || !w_bf16 || !xq_codes || !xq_scales || !x_mask || !wq_codes || !wq_scales || !w_mask) return QUARTET_EINVAL;
     if (!aligned16(x_bf16) || !aligned16(w_bf16) || !aligned16(xq_codes) || !aligned16(wq_codes) || !aligned16(x_mask) ||
         !aligned16(w_mask))
         return QUARTET_EINVAL;
     if ((reinterpret_cast<uintptr_t>(xq_scales) | reinterpret_cast<uintptr_t>(wq_scales)) & 3u) return QUARTET_EINVAL;
-    if (in < 0 || (in % 32) != 0) return QUARTET_EINVAL;
+    if (in < 0 || (in % (32 * (int64_t)nb)) != 0) return QUARTET_EINVAL;
     int rc = check_quant_shape(tokens, in, in, 0);
     if (!rc) rc = check_quant_shape(out, in, in, 0);
     if (rc) return rc;
-    SrParams p = make_params(1u, nullptr, 0u, 0u);
+    SrParams p = make_params(nb, nullptr, 0u, 0u);
     ProfileScope prof(QUARTET_KIND_QUANT_FWD, (hipStream_t)stream);
     hipError_t e = quartet::launch_fwd_operands(x_bf16, tokens, w_bf16, out, in, xq_codes, xq_scales, x_mask, wq_codes, wq_scales,
                                                 w_mask, p, (hipStream_t)stream);
     return e == hipSuccess ? QUARTET_OK : hip_fail(e);
 }
 
+int quartet_fwd_operands(const void* x_bf16, const void* w_bf16, int64_t tokens, int64_t in, int64_t out,
+                         uint8_t* xq_codes, uint8_t* xq_scales, uint32_t* x_mask,
+                         uint8_t* wq_codes, uint8_t* wq_scales, uint32_t* w_mask, void* stream) {
+    return fwd_operands_launch(x_bf16, w_bf16, tokens, in, out, 1u, xq_codes, xq_scales, x_mask, wq_codes, wq_scales, w_mask, stream);
+}
+
 // The backward pass's operand conversions in one launch: dy^T, X_q^T, W_q^T, and with g_codes != null also dy itself in
 // row mode (Philox stream 0).
 static int bwd_operands_launch(const void* dy_bf16, int64_t tokens, int64_t in, int64_t out,
                                const uint8_t* xq_codes, const uint8_t* xq_scales, const uint8_t* wq_codes, const uint8_t* wq_scales,
-                               uint32_t sign_word, uint64_t seed, int rounding,
+                               uint32_t nb, const uint32_t* sign_words, uint64_t seed, int rounding,
                                uint8_t* dyt_codes, uint8_t* dyt_scales, uint8_t* xt_codes, uint8_t* xt_scales,
                                uint8_t* wt_codes, uint8_t* wt_scales, uint8_t* g_codes, uint8_t* g_scales, void* stream) {
     if (!dy_bf16 || !xq_codes || !xq_scales || !wq_codes || !wq_scales) return QUARTET_EINVAL;
@@ -345,7 +352,8 @@ static int bwd_operands_launch(const void* dy_bf16, int64_t tokens, int64_t in, 
         return QUARTET_EINVAL;
     if (g_codes && (!g_scales || !aligned16(g_codes) || (reinterpret_cast<uintptr_t>(g_scales) & 3u))) return QUARTET_EINVAL;
     if (rounding != QUARTET_ROUND_STOCHASTIC && rounding != QUARTET_ROUND_NEAREST) return QUARTET_EINVAL;
-    if (tokens < 0 || in < 0 || out < 0 || (tokens % 32) != 0 || (in % 32) != 0 || (out % 32) != 0) return QUARTET_EINVAL;
+    const int64_t hb = 32 * (int64_t)nb;
+    if (tokens < 0 || in < 0 || out < 0 || (tokens % hb) != 0 || (in % 32) != 0 || (out % hb) != 0) return QUARTET_EINVAL;
     // the checks of the calls this launch stands for
     int rc = check_quant_shape(out, tokens, out, 1);
     if (!rc) rc = check_quant_shape(in, tokens, in, 1);
@@ -356,9 +364,9 @@ static int bwd_operands_launch(const void* dy_bf16, int64_t tokens, int64_t in, 
     const int mode = rounding == QUARTET_ROUND_NEAREST ? quartet::kBwdRtn : quartet::kBwdSr;
     ProfileScope prof(QUARTET_KIND_QUANT_BWD, (hipStream_t)stream);
     hipError_t e = quartet::launch_bwd_operands(mode, dy_bf16, tokens, in, out, xq_codes, xq_scales, wq_codes, wq_scales,
-                                                make_params(1u, &sign_word, seed, 2u), make_params(1u, &sign_word, seed, 3u),
-                                                make_params(1u, &sign_word, seed, 1u), dyt_codes, dyt_scales, xt_codes, xt_scales,
-                                                wt_codes, wt_scales, make_params(1u, &sign_word, seed, 0u), g_codes, g_scales,
+                                                make_params(nb, sign_words, seed, 2u), make_params(nb, sign_words, seed, 3u),
+                                                make_params(nb, sign_words, seed, 1u), dyt_codes, dyt_scales, xt_codes, xt_scales,
+                                                wt_codes, wt_scales, make_params(nb, sign_words, seed, 0u), g_codes, g_scales,
                                                 (hipStream_t)stream);
     return e == hipSuccess ? QUARTET_OK : hip_fail(e);
 }
@@ -368,7 +376,7 @@ int quartet_bwd_operands(const void* dy_bf16, int64_t tokens, int64_t in, int64_
                          uint32_t sign_word, uint64_t seed, int rounding,
                          uint8_t* dyt_codes, uint8_t* dyt_scales, uint8_t* xt_codes, uint8_t* xt_scales,
                          uint8_t* wt_codes, uint8_t* wt_scales, void* stream) {
-    return bwd_operands_launch(dy_bf16, tokens, in, out, xq_codes, xq_scales, wq_codes, wq_scales, sign_word, seed, rounding,
+    return bwd_operands_launch(dy_bf16, tokens, in, out, xq_codes, xq_scales, wq_codes, wq_scales, 1u, &sign_word, seed, rounding,
                                dyt_codes, dyt_scales, xt_codes, xt_scales, wt_codes, wt_scales, nullptr, nullptr, stream);
 }
 
@@ -554,16 +562,9 @@ int quartet_linear_fwd_block(const void* x_bf16, const void* w_bf16, int64_t tok
         return QUARTET_EINVAL;
     if (block_groups(hadamard_block) == 0u) return QUARTET_EINVAL;
     if (tokens < 0 || in < 0 || out < 0 || (in % hadamard_block) != 0) return QUARTET_EINVAL;
-    int rc;
-    if (hadamard_block == 32) {
-        rc = quartet_fwd_operands(x_bf16, w_bf16, tokens, in, out, xq_codes, xq_scales, x_mask, wq_codes, wq_scales, w_mask, stream);
-        if (rc) return rc;
-    } else {
-        rc = quartet_quant_fwd_block(x_bf16, tokens, in, in, 0, hadamard_block, xq_codes, xq_scales, x_mask, stream);
-        if (rc) return rc;
-        rc = quartet_quant_fwd_block(w_bf16, out, in, in, 0, hadamard_block, wq_codes, wq_scales, w_mask, stream);
-        if (rc) return rc;
-    }
+    const int rc = fwd_operands_launch(x_bf16, w_bf16, tokens, in, out, block_groups(hadamard_block), xq_codes, xq_scales, x_mask,
+                                       wq_codes, wq_scales, w_mask, stream);
+    if (rc) return rc;
     return quartet_mxfp4_gemm(xq_codes, xq_scales, wq_codes, wq_scales, tokens, out, in, 1.0f, y, y_dtype,
                               out, stream);
 }
@@ -643,28 +644,13 @@ int quartet_linear_bwd_block(const void* dy_bf16, int64_t tokens, int64_t in, in
     int rc;
     // dx = 16/9 H( (Q(dy) Q(W_q^T)^T) . M_x ), inner dimension = out   (operand streams 0, 1)
     // dW = 16/9 H( (Q(dy^T) Q(X_q^T)^T) . M_w ), inner dimension = tokens (operand streams 2, 3)
-    if (hb == 32) {
-        // All four operand conversions in one launch (none depends on another; every operand has its own Philox stream),
-        // then both products in one launch: two launches.  Measured against Q(dy) as a launch of its own between the products:
-        // +4 % on configuration 1, +2.5-5 % on 2, +0.2-2 % on 3, +0.1-0.2 % on 4.
-        rc = bwd_operands_launch(dy_bf16, tokens, in, out, xq_codes, xq_scales, wq_codes, wq_scales, sw[0], seed, rounding,
-                                 gt_codes, gt_scales, bx_codes, bx_scales, bw_codes, bw_scales, g_codes, g_scales, stream);
-        if (rc) return rc;
-        const quartet_gemm_grad_args dw_args = {gt_codes, gt_scales, bx_codes, bx_scales, out, in, tokens, w_mask, c169, dw, in};
-        const quartet_gemm_grad_args dx_args = {g_codes, g_scales, bw_codes, bw_scales, tokens, in, out, x_mask, c169, dx, in};
-        return quartet_mxfp4_gemm_grad_pair(&dw_args, &dx_args, grad_dtype, stream);
-    }
-    // wider Hadamard blocks: one launch per operand conversion
-    rc = quartet_quant_bwd_sr_block(dy_bf16, out, tokens, out, 1, hb, sw, seed, 2u, rounding, gt_codes, gt_scales, stream);
-    if (rc) return rc;
-    rc = quartet_requant_transpose_sr_block(xq_codes, xq_scales, in, tokens, hb, sw, seed, 3u, rounding, bx_codes, bx_scales, stream);
+    // All four operand conversions in one launch (none depends on another; every operand has its own Philox stream), then both
+    // products in one launch.  Measured against Q(dy) as a launch of its own between the products: +4 % on the whole step at
+    // 256 x 512 x 512, +2.5-5 % at 4096 x 2048 x 2048, +0.2-2 % at 8192 x 2048 x 5632, +0.1-0.2 % at 16384 tokens.
+    rc = bwd_operands_launch(dy_bf16, tokens, in, out, xq_codes, xq_scales, wq_codes, wq_scales, block_groups(hb), sw, seed, rounding,
+                             gt_codes, gt_scales, bx_codes, bx_scales, bw_codes, bw_scales, g_codes, g_scales, stream);
     if (rc) return rc;
     if (!big) {
-        // blocks of 64 and 128 columns: the other two conversions, then both products (epilogue inside) in one launch
-        rc = quartet_quant_bwd_sr_block(dy_bf16, tokens, out, out, 0, hb, sw, seed, 0u, rounding, g_codes, g_scales, stream);
-        if (rc) return rc;
-        rc = quartet_requant_transpose_sr_block(wq_codes, wq_scales, in, out, hb, sw, seed, 1u, rounding, bw_codes, bw_scales, stream);
-        if (rc) return rc;
         const quartet_gemm_grad_args dw_args = {gt_codes, gt_scales, bx_codes, bx_scales, out, in, tokens, w_mask, c169, dw, in};
         const quartet_gemm_grad_args dx_args = {g_codes, g_scales, bw_codes, bw_scales, tokens, in, out, x_mask, c169, dx, in};
         return gemm_grad_pair_block(&dw_args, &dx_args, hb, grad_dtype, stream);
@@ -673,10 +659,6 @@ int quartet_linear_bwd_block(const void* dy_bf16, int64_t tokens, int64_t in, in
     rc = quartet_mxfp4_gemm(gt_codes, gt_scales, bx_codes, bx_scales, out, in, tokens, 1.0f, acc, QUARTET_DTYPE_F32, in, stream);
     if (rc) return rc;
     rc = quartet_grad_epilogue_block(acc, w_mask, out, in, hb, c169, dw, grad_dtype, stream);
-    if (rc) return rc;
-    rc = quartet_quant_bwd_sr_block(dy_bf16, tokens, out, out, 0, hb, sw, seed, 0u, rounding, g_codes, g_scales, stream);
-    if (rc) return rc;
-    rc = quartet_requant_transpose_sr_block(wq_codes, wq_scales, in, out, hb, sw, seed, 1u, rounding, bw_codes, bw_scales, stream);
     if (rc) return rc;
     rc = quartet_mxfp4_gemm(g_codes, g_scales, bw_codes, bw_scales, tokens, in, out, 1.0f, acc, QUARTET_DTYPE_F32, in, stream);
     if (rc) return rc;

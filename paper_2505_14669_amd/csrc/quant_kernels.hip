@@ -3,16 +3,17 @@
 // One lane owns one group of 32 values end to end: the five butterfly stages, the group
 // reduction (sum of squares or absmax), the scale and the 32 codes all stay in that lane's
 // registers, so nothing crosses lanes and the fp32 operation order is fixed (Hadamard blocks of
-// 64, 128 or 256 elements add the stages that combine whole groups in front: lane exchanges in row
-// mode, a butterfly tree over the block's source-row groups in the transposed kernels).  HBM traffic
-// is made wave-coalesced on both sides by staging through LDS:
+// 64, 128 or 256 elements add the stages that combine whole groups in front: their groups sit in
+// neighbouring lanes).  HBM traffic is wave-coalesced on both sides:
 //   row mode        : a wave loads 4 KB (64 groups) with 16-byte lane-contiguous loads, swizzles it
 //                     through LDS so each lane gets its own 64 bytes; codes leave as one 16-byte
 //                     store per lane.
-//   transposed mode : a block owns 256 source rows x 128 source columns; lanes read 2 adjacent
-//                     columns per row (4-byte loads, 256 B per wave row), and the 8 groups of codes
-//                     of each output row are gathered in LDS and written as full 128-byte lines.
+//   transposed mode : a block owns 256 source rows (one K-quad of the output).  Large bf16 matrices: lanes read 2 adjacent
+//                     columns per row (256 B per wave row) into registers and the codes are gathered in LDS; otherwise (small
+//                     matrices, wide Hadamard blocks, MXFP4 sources) the rows go through LDS and eight neighbouring lanes hold
+//                     the eight groups of a column.  Both write whole 128-byte lines of codes.
 #include "device_common.h"
+#include "gemm_common.h"
 #include "launchers.h"
 
 namespace quartet {
@@ -28,49 +29,50 @@ __device__ __forceinline__ uint32_t rtn_pack8(const float* v, float scale) {
     return w;
 }
 
-// Encode one rotated group held in v[]: scale, codes, mask.  q_base = (linear output position of
-// element 0)/16 is the Philox call index of the group's first 16 elements.
-template <int MODE>
-__device__ __forceinline__ void encode_group(float (&v)[32], const SrParams& p, uint64_t q_base,
-                                             uint4& codes, uint32_t& scale_byte, uint32_t& mask_word);
-
 __device__ __forceinline__ void flip_signs(float (&v)[32], uint32_t sign_word) {
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = u2f(f2u(v[i]) ^ (((sign_word >> i) & 1u) << 31));
 }
 
-// Quantize one group held in v[] (not yet rotated), Hadamard block = the group.  FLIPPED: the caller has applied the
-// sign vector of the randomized rotation already (where it is cheaper: while unpacking, or on the codes before decoding).
-template <int MODE, bool FLIPPED = false>
-__device__ __forceinline__ void quantize_group(float (&v)[32], const SrParams& p, uint64_t q_base,
-                                               uint4& codes, uint32_t& scale_byte, uint32_t& mask_word) {
-    if (MODE != kFwd && !FLIPPED) flip_signs(v, p.sign_word);
-    fwht32(v);
-    encode_group<MODE>(v, p, q_base, codes, scale_byte, mask_word);
+// Hadamard blocks of 64, 128 or 256 elements (nb = 2, 4, 8 groups): the groups of a K-quad sit in eight consecutive lanes,
+// lane sub = lane % 8 holding group j of the K-quad.  Groups that a group-combining stage pairs up differ in one bit of j;
+// j = sub ^ (sub & 4 ? 3 : 0) makes the partners sub ^ 1, sub ^ 2 and 7 - sub, which DPP reaches inside the arithmetic
+// instruction.
+__device__ __forceinline__ uint32_t kquad_group_of(uint32_t sub) { return sub ^ ((sub & 4u) ? 3u : 0u); }
+
+// sign word of group j of its Hadamard block (nb groups) for a lane
+__device__ __forceinline__ uint32_t lane_sign_word(const SrParams& p, uint32_t j) {
+    uint32_t sw = p.sign_words[0];
+#pragma unroll
+    for (uint32_t q = 1; q < 8; ++q) sw = ((j & (p.nb - 1u)) == q) ? p.sign_words[q] : sw;
+    return sw;
 }
 
-// The same when the Hadamard block spans p.nb groups held by consecutive lanes (lane % nb = the
-// group's place in its block): signs, the group-combining stages across lanes, the stages inside the
-// group, one normalization.  Every lane of the wave must call it.
-template <int MODE>
-__device__ __forceinline__ void quantize_group_lanes(float (&v)[32], const SrParams& p, uint32_t lane, uint64_t q_base,
-                                                     uint4& codes, uint32_t& scale_byte, uint32_t& mask_word) {
-    if (MODE != kFwd) {
-        uint32_t sw = p.sign_words[0];
-#pragma unroll
-        for (uint32_t j = 1; j < 8; ++j) sw = ((lane & (p.nb - 1u)) == j) ? p.sign_words[j] : sw;
-        flip_signs(v, sw);
-    }
-    cross_lane_stages(v, lane, p.nb);
+// 0xFFFFFFFF if bit i of w is set, else 0
+__device__ __forceinline__ uint32_t bit_mask(uint32_t w, uint32_t i) { return (uint32_t)__builtin_amdgcn_sbfe((int)w, i, 1u); }
+
+#define QUARTET_STAGE_ALL(CTRL_TEXT, v, t)                                                          \
+    _Pragma("unroll") for (int i_ = 0; i_ < 32; i_ += 4)                                             \
+        QUARTET_STAGE4_DPP(CTRL_TEXT, v[i_], v[i_ + 1], v[i_ + 2], v[i_ + 3], t);
+
+// Group-combining stages of a Hadamard block of nb = 2, 4 or 8 groups held by lanes as above, the 32-point stages and the
+// normalization.  A group-combining stage leaves -(a - b) in the upper lane and the normalization takes the sign back (see
+// cross_lane_stage); zeros come out as +0.
+__device__ __forceinline__ void rotate_block_lanes(float (&v)[32], uint32_t j, uint32_t nb) {
+    const float t1 = (j & 1u) ? -1.0f : 1.0f, t2 = (j & 2u) ? -1.0f : 1.0f, t4 = (j & 4u) ? -1.0f : 1.0f;
+    QUARTET_STAGE_ALL("quad_perm:[1,0,3,2]", v, t1)
+    if (nb > 2u) { QUARTET_STAGE_ALL("quad_perm:[2,3,0,1]", v, t2) }
+    if (nb > 4u) { QUARTET_STAGE_ALL("row_half_mirror", v, t4) }
     fwht32_unscaled(v);
-    const float c = block_norm_signed(p.nb, lane);
+    const float c = block_norm_signed(nb, j);
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = __builtin_fmaf(v[i], c, 0.0f);
-    encode_group<MODE>(v, p, q_base, codes, scale_byte, mask_word);
 }
 
+// Encode one rotated group held in v[]: scale, codes, mask.  q_base = (linear output position of
+// element 0)/16 is the Philox call index of the group's first 16 elements.
 template <int MODE>
-__device__ __forceinline__ void encode_group(float (&v)[32], const SrParams& p, uint64_t q_base,
+__device__ __forceinline__ void encode_group(float (&v)[32], const SrParams& p, uint32_t stream, uint64_t q_base,
                                              uint4& codes, uint32_t& scale_byte, uint32_t& mask_word) {
     uint32_t c[4] = {0u, 0u, 0u, 0u};
     if (MODE == kFwd) {
@@ -113,7 +115,7 @@ __device__ __forceinline__ void encode_group(float (&v)[32], const SrParams& p, 
             for (int call = 0; call < 2; ++call) {
                 uint64_t q = q_base + (uint64_t)call;
                 uint32_t w[4];
-                philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), p.stream_id, 0u, p.key0, p.key1, w);
+                philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), stream, 0u, p.key0, p.key1, w);
                 c[2 * call] = sr_pack8(&v[16 * call], w[0], w[1]);
                 c[2 * call + 1] = sr_pack8(&v[16 * call + 8], w[2], w[3]);
             }
@@ -158,7 +160,7 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4& q, float* v) {
 template <int MODE, bool MASK, bool BIG>
 __device__ __forceinline__ void quant_row_tile(const uint16_t* __restrict__ x, uint32_t rows, uint32_t gk, int64_t ldx,
                                                uint4* __restrict__ codes, uint8_t* __restrict__ scales, uint32_t* __restrict__ mask,
-                                               const SrParams& p, uint32_t k_blocks, FastDiv div_k_blocks, uint32_t bid,
+                                               const SrParams& p, uint32_t stream, uint32_t k_blocks, FastDiv div_k_blocks, uint32_t bid,
                                                uint4 (*stage)[256], uint32_t* s_scale) {
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     // consecutive blocks walk along K inside the same 8 rows, so the blocks in flight cover one
@@ -180,18 +182,25 @@ __device__ __forceinline__ void quant_row_tile(const uint16_t* __restrict__ x, u
     }
     __syncthreads();
     float v[32];
+    // BIG: the lane's group inside the wave's 64
+    const uint32_t gw = BIG ? (lane & ~7u) | kquad_group_of(lane & 7u) : lane;
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j) {
-        uint4 q = stage[wave][4u * lane + (j ^ ((lane >> 2) & 3u))];
+        uint4 q = stage[wave][4u * gw + (j ^ ((gw >> 2) & 3u))];
         if (MODE != kFwd && !BIG) unpack_bf16x8_signed(q, &v[8 * j], p.sign_word, 8u * j);
         else unpack_bf16x8(q, &v[8 * j]);
     }
-    const uint32_t row_local = wave * 2u + (lane >> 5), gi = lane & 31u;
+    const uint32_t row_local = wave * 2u + (gw >> 5), gi = gw & 31u;
     const uint32_t row = row0 + row_local, g = kq0 * 8u + gi;
     uint4 out;
     uint32_t sb, mw;
-    if (BIG) quantize_group_lanes<MODE>(v, p, lane, ((uint64_t)row * gk + g) * 2u, out, sb, mw);
-    else quantize_group<MODE, true>(v, p, ((uint64_t)row * gk + g) * 2u, out, sb, mw);
+    if (BIG) {
+        if (MODE != kFwd) flip_signs(v, lane_sign_word(p, gi & 7u));
+        rotate_block_lanes(v, gi & 7u, p.nb);
+    } else {
+        fwht32(v);
+    }
+    encode_group<MODE>(v, p, stream, ((uint64_t)row * gk + g) * 2u, out, sb, mw);
     // scale byte of (row, group gi) -> position of the tiled layout inside the block's 256 bytes:
     // [K-quad gi/8][h = gi%2][row_local][p = (gi%8)/2]
     reinterpret_cast<uint8_t*>(s_scale)[(((gi >> 3) * 2u + (gi & 1u)) * 8u + row_local) * 4u + ((gi & 7u) >> 1)] = (uint8_t)sb;
@@ -225,7 +234,7 @@ quant_row_kernel(const uint16_t* __restrict__ x, uint32_t rows, uint32_t gk, int
                  SrParams p, uint32_t k_blocks, FastDiv div_k_blocks) {
     __shared__ uint4 stage[4][256];
     __shared__ uint32_t s_scale[64];
-    quant_row_tile<MODE, MASK, BIG>(x, rows, gk, ldx, codes, scales, mask, p, k_blocks, div_k_blocks, blockIdx.x, stage, s_scale);
+    quant_row_tile<MODE, MASK, BIG>(x, rows, gk, ldx, codes, scales, mask, p, p.stream_id, k_blocks, div_k_blocks, blockIdx.x, stage, s_scale);
 }
 
 // Two matrices with the same inner dimension in one launch (Algorithm 1 Forward quantizes X and W, and neither depends
@@ -240,14 +249,14 @@ struct RowMatrix {
     uint32_t* mask;
 };
 
-template <int MODE, bool MASK>
+template <int MODE, bool MASK, bool BIG>
 __global__ void __launch_bounds__(256)
 quant_row_pair_kernel(RowMatrix a, RowMatrix b, uint32_t split, uint32_t gk, SrParams p, uint32_t k_blocks, FastDiv div_k_blocks) {
     __shared__ uint4 stage[4][256];
     __shared__ uint32_t s_scale[64];
     const bool second = blockIdx.x >= split;
     const RowMatrix& m = second ? b : a;
-    quant_row_tile<MODE, MASK, false>(m.x, m.rows, gk, m.ldx, m.codes, m.scales, m.mask, p, k_blocks, div_k_blocks,
+    quant_row_tile<MODE, MASK, BIG>(m.x, m.rows, gk, m.ldx, m.codes, m.scales, m.mask, p, p.stream_id, k_blocks, div_k_blocks,
                                       second ? blockIdx.x - split : blockIdx.x, stage, s_scale);
 }
 
@@ -262,7 +271,7 @@ __device__ __forceinline__ void transposed_store_tile(const uint4* s_codes, cons
                                                       uint32_t* __restrict__ mask) {
     // full 128-byte lines of codes: 8 lanes per output row
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) {
+    for (uint32_t j = 0; j < 4u; ++j) {
         uint32_t id = threadIdx.x + 256u * j;
         uint32_t lc = id >> 3, part = id & 7u;
         uint32_t r = col0 + lc, grp = grp0 + part;
@@ -300,22 +309,20 @@ __device__ __forceinline__ void transposed_store_tile(const uint4* s_codes, cons
     }
 }
 
-// ------------------------------------------------------------------ transposed mode, bf16 source
-// Logical A[rows x k] = S^T where the source S is bf16 [k x ldx].
-// Block tile: 8 groups (256 source rows, one K-quad of the output) x 128 source columns; wave w owns
-// groups 2w, 2w+1; lane l owns columns 2l, 2l+1.  Blocks are numbered K-quad first: the blocks that
-// run at the same time then write neighbouring 128-byte lines of the same output rows (measured 10 %
-// faster than column-tile first, where every block's lines lie a whole output row apart).  The callers
-// rotate the column tile by the K-quad (transposed_column_tile): with a dense source whose row pitch is a
-// multiple of a few KB, the blocks in flight would otherwise all read the same 4 KB-wide stretch of
-// columns of every row, which the memory channels serve unevenly (measured: 5-9 % slower; a source
-// with 128 bytes of padding per row does not show it).
+// ------------------------------------------------------------------ transposed mode, bf16 source, whole-chip matrices
+// Logical A[rows x k] = S^T where the source S is bf16 [k x ldx], Hadamard block = the group.
+// Block tile: 8 groups (256 source rows, one K-quad of the output) x 128 source columns; wave w owns groups 2w, 2w+1; lane l
+// owns columns 2l, 2l+1.  Bound by memory (nearest) or vector-ALU issue (stochastic).  Every load reads 256 contiguous bytes of one
+// source row into registers, 64 of them in flight per wave: on large matrices that streams faster than the 128-byte pieces
+// through LDS of quant_columns_block, which is the better kernel below about 2000 of its waves and for wider Hadamard blocks
+// (16384 x 11008, stochastic / nearest: 95 / 83 us here, 100 / 88 there; 4096 x 2048: 8.3 / 6.9 here, 7.6 / 6.5 there; 256 x 512:
+// 6.7 / 5.4 here, 3.4 / 3.1 there).
 // bx, by: the block's K-quad and column tile; s_codes (16 KB), s_scales (1 KB), s_mask (4 KB): the block's LDS
 template <int MODE, bool MASK>
 __device__ __forceinline__ void quant_transposed_tile(const uint16_t* __restrict__ src,
                                                       uint32_t rows, uint32_t k, int64_t ldx, uint8_t* __restrict__ codes,
                                                       uint8_t* __restrict__ scales, uint32_t* __restrict__ mask,
-                                                      const SrParams& p, uint32_t bx, uint32_t by,
+                                                      const SrParams& p, uint32_t stream, uint32_t bx, uint32_t by,
                                                       uint4* s_codes, uint8_t* s_scales, uint32_t* s_mask) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     const uint32_t gk = k >> 5;
@@ -359,7 +366,8 @@ __device__ __forceinline__ void quant_transposed_tile(const uint16_t* __restrict
             uint4 q;
             uint32_t sb, m;
             // output position of element 0 of the group: row*k + grp*32, divided by 16
-            quantize_group<MODE, true>(v, p, ((uint64_t)(col + c) * k + grp * 32u) >> 4, q, sb, m);
+            fwht32(v);
+            encode_group<MODE>(v, p, stream, ((uint64_t)(col + c) * k + grp * 32u) >> 4, q, sb, m);
             const uint32_t lc = 2u * lane + c;            // local column
             s_codes[(lc ^ ((lc >> 4) & 1u)) * 8u + (gl ^ sw)] = q;
             s_scales[lc * 8u + gl] = (uint8_t)sb;
@@ -370,7 +378,111 @@ __device__ __forceinline__ void quant_transposed_tile(const uint16_t* __restrict
     transposed_store_tile<MASK>(s_codes, s_scales, s_mask, col0, grp0, rows, gk, k, codes, scales, mask);
 }
 
-// Column tile of the block with K-quad bx and nominal column tile by, of n_ct column tiles (a bijection for every bx).
+// ------------------------------------------------------------------ transposed conversions, lanes along the output's groups
+// A block covers 256 source rows (the 8 groups of one K-quad of the output) by B = 128, 64 or 32 bytes of each row.  The rows
+// go to LDS by LDS-direct loads of 16 bytes per lane (whole pieces of a row, no registers, all of them in flight at once);
+// then a lane owns one group of a column: sub = lane % 8 stands for group j of the K-quad (kquad_group_of), lane / 8 for a
+// chunk of neighbouring columns, and it reads its chunk of the group's 32 rows back.
+//   - The groups of a Hadamard block above 32 sit in neighbouring lanes.
+//   - The eight lanes of a chunk hold the 128 contiguous bytes of codes of one output row and K-quad: every 16-byte store
+//     instruction writes whole lines.
+// STREAM: read non-temporally (large matrices; small ones come out of the caches: 4096 x 2048 7.6 us cached, 8.3 streamed).
+// Group j's 32 rows start at j * kquad_pitch(B): the 32 bytes of padding put the rows i of the eight groups, which one read
+// instruction addresses, on different banks.
+template <uint32_t B> __host__ __device__ constexpr uint32_t kquad_pitch() { return 32u * B + 32u; }
+template <uint32_t B, bool STREAM>
+__device__ __forceinline__ void stage_kquad_rows(const v4i_t& res, uint32_t pitch, const void* lds) {
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr uint32_t CPR = B / 16u, RPI = 64u / CPR, PER_GROUP = 32u / RPI, PER_WAVE = 2u * PER_GROUP;   // wave w: groups 2w, 2w + 1
+    const uint32_t lds0 = (uint32_t)(size_t)(lds_ptr_t)const_cast<void*>(lds);
+    const uint32_t voff = (lane / CPR) * pitch + (lane % CPR) * 16u;
+#pragma unroll
+    for (uint32_t t = 0; t < PER_WAVE; ++t) {
+        const uint32_t grp = 2u * wave + t / PER_GROUP, part = t % PER_GROUP;
+        lds_direct_load16<STREAM>(res, voff + (grp * 32u + part * RPI) * pitch, lds0 + grp * kquad_pitch<B>() + part * 1024u);
+    }
+}
+
+// The scale bytes of a wave's COLS output rows in one K-quad: a lane has put the bytes of its group into s ([h][row][byte],
+// see scale_tile_offset); they leave as whole dwords of a scale tile.  row0 is a multiple of COLS, COLS divides 32.
+template <uint32_t COLS>
+__device__ __forceinline__ void store_kquad_scales(const uint32_t* s, uint8_t* __restrict__ scales, uint32_t row0, uint32_t rows,
+                                                   uint32_t grp0, uint32_t gk, uint32_t lane) {
+    const uint32_t h = lane / COLS, r = row0 + lane % COLS;
+    if (lane < 2u * COLS && r < rows && grp0 + h < gk) {
+        uint8_t* dst = scales + scale_tile_offset(r, grp0 + h, (gk + 7u) >> 3);
+        const uint32_t w = s[lane];
+        if (grp0 + 6u + h < gk) {
+            *reinterpret_cast<uint32_t*>(dst) = w;
+        } else {                                       // ragged last K-quad: only the bytes that exist
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+                if (grp0 + 2u * q + h < gk) dst[q] = (uint8_t)(w >> (8u * q));
+        }
+    }
+}
+
+// bf16 source.  Logical A[rows x k] = S^T where the source S is bf16 [k x ldx]; the block covers 32 * CPL columns from col0 on (CPL
+// = 2: 128-byte pieces of the source rows; CPL = 1: half of that, for matrices too small to fill the chip), K-quad bx.
+// lds: 8 * kquad_pitch<64 CPL>() bytes, s_scale: 64 * CPL dwords.
+template <int MODE, bool MASK, bool BIG, uint32_t CPL>
+__device__ __forceinline__ void quant_columns_block(const uint16_t* __restrict__ src, uint32_t rows, uint32_t k, int64_t ldx,
+                                                    uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
+                                                    uint32_t* __restrict__ mask, const SrParams& p, uint32_t stream, uint32_t bx, uint32_t col0,
+                                                    const void* lds, uint32_t* s_scale) {
+    constexpr uint32_t B = 64u * CPL;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t chunk = lane >> 3, j = kquad_group_of(lane & 7u);
+    const uint32_t gk = k >> 5, grp0 = bx * 8u, grp = grp0 + j;
+    // the block's corner of the source through a buffer resource that ends with the last column of the last source row:
+    // rows past k read as zeros without a predicate; columns past `rows` inside a source row read whatever lies there,
+    // their results are never stored
+    const uint32_t src_rows = (k - grp0 * 32u) < 256u ? (k - grp0 * 32u) : 256u;
+    const uint32_t src_cols = (rows - col0) < 32u * CPL ? (rows - col0) : 32u * CPL;
+    const v4i_t res_x = make_rsrc_words(src + (size_t)grp0 * 32u * ldx + col0, ((src_rows - 1u) * (uint32_t)ldx + src_cols) * 2u);
+    stage_kquad_rows<B, CPL == 2u>(res_x, (uint32_t)ldx * 2u, lds);
+    const uint32_t sw = BIG && MODE != kFwd ? lane_sign_word(p, j) : 0u;
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    const uint8_t* mine = static_cast<const uint8_t*>(lds) + j * kquad_pitch<B>() + (wave * 8u + chunk) * (2u * CPL);
+    uint32_t raw[32];
+#pragma unroll
+    for (uint32_t i = 0; i < 32; ++i) {
+        raw[i] = CPL == 2u ? *reinterpret_cast<const uint32_t*>(mine + i * B) : (uint32_t)*reinterpret_cast<const uint16_t*>(mine + i * B);
+        if (BIG && MODE != kFwd) raw[i] ^= bit_mask(sw, i) & 0x80008000u;      // the lane's sign vector on both halves
+    }
+    uint32_t* s = s_scale + wave * 16u * CPL;
+#pragma unroll
+    for (uint32_t c = 0; c < CPL; ++c) {
+        __builtin_amdgcn_sched_barrier(0);            // one column at a time
+        float v[32];
+#pragma unroll
+        for (uint32_t i = 0; i < 32; ++i) {           // unpacked with the sign vector applied on the way (forward: sign word 0)
+            const uint32_t sbit = (MODE != kFwd && !BIG) ? sign_bit(p.sign_word, i) : 0u;
+            v[i] = c ? u2f((raw[i] & 0xFFFF0000u) ^ sbit) : u2f((raw[i] << 16) + sbit);
+        }
+        if (BIG) rotate_block_lanes(v, j, p.nb);
+        else fwht32(v);
+        const uint32_t lc = chunk * CPL + c, r = col0 + wave * 8u * CPL + lc;
+        uint4 q;
+        uint32_t sb, m;
+        // output position of element 0 of the group: row*k + grp*32, divided by 16
+        encode_group<MODE>(v, p, stream, ((uint64_t)r * k + grp * 32u) >> 4, q, sb, m);
+        reinterpret_cast<uint8_t*>(s)[((j & 1u) * 8u * CPL + lc) * 4u + (j >> 1)] = (uint8_t)sb;
+        if (r < rows && grp < gk) {
+            store_stream16(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q);
+            if (MASK) mask[(size_t)r * gk + grp] = m;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();                  // the bytes are the wave's own and a wave's LDS operations run in order
+    store_kquad_scales<8u * CPL>(s, scales, col0 + wave * 8u * CPL, rows, grp0, gk, lane);
+}
+
+// Column tile of the block with K-quad bx and nominal column tile by, of n_ct column tiles (a bijection for every bx): with
+// a dense source whose row pitch is a multiple of a few KB, the blocks in flight would otherwise all read the same stretch of
+// columns of every row, which the memory channels serve unevenly (measured: 5-9 % slower; a source with 128 bytes of padding
+// per row does not show it).  Blocks are numbered K-quad first: the blocks that run at the same time then write neighbouring
+// 128-byte lines of the same output rows (10 % faster than column-tile first).
 __device__ __forceinline__ uint32_t transposed_column_tile(uint32_t bx, uint32_t by, uint32_t n_ct) { return (by + bx) % n_ct; }
 
 template <int MODE, bool MASK>
@@ -381,429 +493,224 @@ quant_transposed_kernel(const uint16_t* __restrict__ src,
     __shared__ uint4 s_codes[128 * 8];
     __shared__ uint8_t s_scales[128 * 8];
     __shared__ uint32_t s_mask[128 * 8];
-    quant_transposed_tile<MODE, MASK>(src, rows, k, ldx, codes, scales, mask, p, blockIdx.x,
+    quant_transposed_tile<MODE, MASK>(src, rows, k, ldx, codes, scales, mask, p, p.stream_id, blockIdx.x,
                                       transposed_column_tile(blockIdx.x, blockIdx.y, gridDim.y), s_codes, s_scales, s_mask);
 }
 
-// The same tile for Hadamard blocks of NB = 2, 4 or 8 groups.  The groups of a block are whole source
-// row groups, so the group-combining stages come first and work on raw values: for its two groups
-// (places j, j+1 of one block) and each column of its pair a wave reads all NB groups of the block (the
-// other waves of the block read the same lines: the extra reads are cache hits), folds them through the
-// butterfly tree down to that place, and only then runs the 32-point stages.
-template <int MODE, bool MASK, int NB>
-__global__ void __launch_bounds__(256)
-quant_transposed_block_kernel(const uint16_t* __restrict__ src, uint32_t rows, uint32_t k, int64_t ldx,
-                              uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-                              uint32_t* __restrict__ mask, SrParams p) {
-    __shared__ uint4 s_codes[128 * 8];
-    __shared__ uint8_t s_scales[128 * 8];
-    __shared__ uint32_t s_mask[128 * 8];
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-    const uint32_t gk = k >> 5;
-    const uint32_t col0 = transposed_column_tile(blockIdx.x, blockIdx.y, gridDim.y) * 128u;
-    const uint32_t grp0 = blockIdx.x * 8u;
-    const uint32_t col = col0 + 2u * lane;
-    const uint32_t src_rows = (k - grp0 * 32u) < 256u ? (k - grp0 * 32u) : 256u;
-    const uint32_t src_cols = (rows - col0) < 128u ? (rows - col0) : 128u;
-    const __amdgpu_buffer_rsrc_t res_x = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(src + (size_t)grp0 * 32u * ldx + col0), 0,
-        (int)(((src_rows - 1u) * (uint32_t)ldx + src_cols) * 2u), 0x00020000);
-    const uint32_t pitch = (uint32_t)ldx * 2u;
-    const uint32_t gl0 = 2u * wave;                          // the wave's groups gl0, gl0+1 inside the tile
-    const uint32_t jb = gl0 & ~((uint32_t)NB - 1u);           // first group of their Hadamard block
-    const uint32_t j = gl0 - jb;                              // even place of gl0 in the block
-    const uint32_t neg2 = (j & 2u) << 30, neg4 = (j & 4u) << 29;   // sign of the upper operand at the 64- and 128-stages
-    const float norm = block_norm((uint32_t)NB);
-    const uint32_t sw = lane & 7u;                            // 16-byte slot swizzle against bank conflicts
-    // one output group of one column at a time: 32 results and four source rows of every group in flight keep the
-    // kernel at four waves per SIMD (holding both groups of a column pair took all 512 registers of a lane)
-#pragma unroll 1
-    for (uint32_t pass = 0; pass < 4; ++pass) {
-        const uint32_t c = pass & 1u, rb = pass >> 1;
-        const uint32_t neg1 = rb << 31;                       // place j + rb: the 32-stage is a sum (rb = 0) or a difference
-        // The loads do not depend on the pass, so the compiler lifts all 32 NB of them out of this loop and keeps
-        // them in registers: good for NB = 2 and 4 (64 and 128 registers, every line read once), too much for
-        // NB = 8 (all 512 registers of a lane, one wave per SIMD), where an offset it cannot see through keeps
-        // them inside the pass.
-        uint32_t lane_off = 4u * lane;
-        if (NB > 4) asm volatile("" : "+v"(lane_off));
-        float v[32];
-#pragma unroll
-        for (uint32_t i = 0; i < 32; ++i) {
-            // at most four source rows of every group in flight: without the fence all 32 NB loads are
-            // hoisted to the top and the kernel runs out of registers
-            if ((i & 3u) == 0u) __builtin_amdgcn_sched_barrier(0);
-            float x[NB];
-#pragma unroll
-            for (uint32_t jj = 0; jj < (uint32_t)NB; ++jj) {
-                const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(res_x, (int)lane_off, (int)(((jb + jj) * 32u + i) * pitch), 0);
-                uint32_t bits = c ? (w & 0xFFFF0000u) : (w << 16);
-                if (MODE != kFwd) bits ^= ((p.sign_words[jj] >> i) & 1u) << 31;
-                x[jj] = u2f(bits);
-            }
-            float y[NB / 2];
-#pragma unroll
-            for (uint32_t m = 0; m < (uint32_t)NB / 2u; ++m) y[m] = x[2 * m] + u2f(f2u(x[2 * m + 1]) ^ neg1);
-            if (NB >= 4) {
-#pragma unroll
-                for (uint32_t m = 0; m < (uint32_t)NB / 4u; ++m) y[m] = y[2 * m] + u2f(f2u(y[2 * m + 1]) ^ neg2);
-            }
-            if (NB >= 8) y[0] = y[0] + u2f(f2u(y[1]) ^ neg4);
-            v[i] = y[0];
-        }
-        fwht32_unscaled(v);
-#pragma unroll
-        for (int i = 0; i < 32; ++i) v[i] = v[i] * norm;
-        const uint32_t gl = gl0 + rb;
-        uint4 q;
-        uint32_t sbyte, m;
-        encode_group<MODE>(v, p, ((uint64_t)(col + c) * k + (grp0 + gl) * 32u) >> 4, q, sbyte, m);
-        const uint32_t lc = 2u * lane + c;
-        s_codes[(lc ^ ((lc >> 4) & 1u)) * 8u + (gl ^ sw)] = q;
-        s_scales[lc * 8u + gl] = (uint8_t)sbyte;
-        if (MASK) s_mask[lc * 8u + gl] = m;
-    }
-    __syncthreads();
-    transposed_store_tile<MASK>(s_codes, s_scales, s_mask, col0, grp0, rows, gk, k, codes, scales, mask);
+template <int MODE, bool MASK, bool BIG, uint32_t CPL>
+__global__ void __launch_bounds__(256, 4)
+quant_columns_kernel(const uint16_t* __restrict__ src,
+                        uint32_t rows, uint32_t k, int64_t ldx, uint8_t* __restrict__ codes,
+                        uint8_t* __restrict__ scales, uint32_t* __restrict__ mask, SrParams p) {
+    __shared__ __align__(16) uint8_t stage[8u * kquad_pitch<64u * CPL>()];
+    __shared__ uint32_t s_scale[64u * CPL];
+    quant_columns_block<MODE, MASK, BIG, CPL>(src, rows, k, ldx, codes, scales, mask, p, p.stream_id, blockIdx.x,
+                                              transposed_column_tile(blockIdx.x, blockIdx.y, gridDim.y) * 32u * CPL, stage, s_scale);
 }
 
-// ------------------------------------------------------------------ MXFP4 source, other dimension
-// Re-quantization of a saved MXFP4 tensor S [k x rows] along its other dimension (Algorithm 1
-// Backward: the operands W_q^T and X_q^T).  A wave covers 256 source rows (one K-quad of the
-// output) x 64 source columns (64 output rows) and works alone, without block barriers; four
-// neighbouring waves make up a 256-column stretch (one scale tile wide).  Per output group (32
-// source rows) a lane fetches 16 bytes of codes (32 columns of one source row; the four waves of a
-// stretch together read whole 128-byte lines),
-// decodes them exactly and writes the 32 values into the wave's LDS stage laid out
-// [column][source row]; then lane c reads the 32 values of column c back, quantizes the group and
-// keeps its 16 bytes of codes; the scale bytes collect in two registers that are, after the eighth
-// group, exactly the two scale-tile dwords of the lane's output row.  Each lane then writes the 128
-// contiguous bytes of codes of its row and its two scale dwords.
-constexpr uint32_t kStageStride = 36;   // floats per column of the stage: 16-byte aligned, b128 reads conflict-free
-
-// WPB = waves per block (the launcher uses 1: the waves of a 256-column stretch never cooperate, and blocks of one
-// wave spread them over more CUs).
-// The work of one wave: `wave` = its place in the 256-column stretch `quad`, kq = the K-quad of the output, stage = the
-// wave's 64 x kStageStride floats of LDS.
-template <int MODE>
-__device__ __forceinline__ void requant_transposed_wave(const uint8_t* __restrict__ src_codes, const uint8_t* __restrict__ src_scales,
-                                                        uint32_t rows, uint32_t k, uint8_t* __restrict__ codes,
-                                                        uint8_t* __restrict__ scales, const SrParams& p,
-                                                        uint32_t wave, uint32_t quad, uint32_t kq, float* stage) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t gk = k >> 5, okq = (k + 255u) >> 8;          // output groups per row, output K-quads
+// MXFP4 source: re-quantization of a saved MXFP4 tensor S [k x rows] along its other dimension (Algorithm 1 Backward: the
+// operands W_q^T and X_q^T).  The block covers 32 * NC source columns from c0 on, K-quad kq of the output; NC = 8, 4, 2: 128, 64, 32
+// bytes of codes of every source row (less work per wave for smaller problems).  Codes are decoded two columns at a time.
+// lds: 8 * kquad_pitch<16 NC>() bytes and at least 9216, s_scale: 64 * NC dwords.
+template <int MODE, bool BIG, uint32_t NC>
+__device__ __forceinline__ void requant_columns_block(const uint8_t* __restrict__ src_codes, const uint8_t* __restrict__ src_scales,
+                                                      uint32_t rows, uint32_t k, uint8_t* __restrict__ codes,
+                                                      uint8_t* __restrict__ scales, const SrParams& p, uint32_t stream, uint32_t kq, uint32_t col0,
+                                                      void* lds, uint32_t* s_scale) {
+    constexpr uint32_t B = 16u * NC;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t chunk = lane >> 3, j = kquad_group_of(lane & 7u);
+    const uint32_t gk = k >> 5, grp0 = kq * 8u, grp = grp0 + j, c0 = col0 + wave * 8u * NC;
     const uint32_t half = rows >> 1, skq = (rows + 255u) >> 8;  // source row pitch in bytes, source K-quads
-    const uint32_t c0 = quad * 256u + wave * 64u, grp0 = kq * 8u;
-    // load role: source row rl of the group, 32-column chunk ch of the wave's 64 columns
-    const uint32_t rl = lane >> 1, ch = lane & 1u, cg = wave * 2u + ch;   // cg: column group inside the source's K-quad
-    // The block's corner of the source codes and the scale tiles below it through buffer resources that
-    // end with the data: source rows past k read as zeros without predicates or branches.  Columns
-    // past `rows` read whatever lies there; the output rows they feed are never stored.
-    const uint32_t cb0 = quad * 256u;
+    // the source codes of the K-quad's rows and the scale tiles of their row blocks, through buffer resources that end with the
+    // data: source rows past k read as zeros; columns past `rows` read whatever lies there, the output rows they feed are
+    // never stored
     const uint32_t src_rows = (k - grp0 * 32u) < 256u ? (k - grp0 * 32u) : 256u;
-    const uint32_t src_cols = (rows - cb0) < 256u ? (rows - cb0) : 256u;
-    const __amdgpu_buffer_rsrc_t res_c = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(src_codes + (size_t)grp0 * 32u * half + (cb0 >> 1)), 0,
-        (int)((src_rows - 1u) * half + (src_cols >> 1)), 0x00020000);
-    // the 32 rows x 8 column groups of one step of the block are exactly one scale tile of the source
-    const size_t tile0 = ((size_t)grp0 * skq + (cb0 >> 8)) * 256u;
-    const __amdgpu_buffer_rsrc_t res_s = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(src_scales + tile0), 0, (int)((size_t)gk * skq * 256u - tile0), 0x00020000);
-    const uint32_t code_off = rl * half + ((wave * 64u + 32u * ch) >> 1);
-    const uint32_t scale_off = (((cg & 1u) << 5) + rl) * 4u + (cg >> 1);
-    const uint32_t code_step = 32u * half, scale_step = skq * 256u;   // wave-uniform: they ride in the scalar offset
-    const uint32_t wr = (rl + 16u * ch) & 31u;                  // rotated row slot: the 32 lanes of a write pass (16 source rows x 2 chunks) land on 32 different banks
-    // quantize role: output row c0 + lane
-    const uint32_t out_row = c0 + lane, rot = (16u * (lane >> 5)) & 31u;
-
-    // sign of element rl of the rotation's sign vector as the sign bits of eight E2M1 codes (sign-magnitude: decoding
-    // the flipped code gives the negated value exactly, zeros included)
-    const uint32_t code_flip = (MODE != kFwd && ((p.sign_word >> rl) & 1u)) ? 0x88888888u : 0u;
-    v4u_t cw = __builtin_amdgcn_raw_buffer_load_b128(res_c, (int)code_off, 0, 0);
-    uint32_t sb_src = __builtin_amdgcn_raw_buffer_load_b8(res_s, (int)scale_off, 0, 0);
-    uint32_t sw0 = 0u, sw1 = 0u;   // the row's scale bytes as the two dwords of the output's scale tile (groups h, 2+h, 4+h, 6+h)
-    uint8_t* crow = codes + (size_t)out_row * (k >> 1) + (size_t)grp0 * 16u;   // the row's 128 bytes of codes in this K-quad
-// One step g: fetch the next step's codes and scale byte (past the eighth step the values are not
-// used), decode this step's, pass them through the wave's stage, quantize column `lane`.
-#define REQUANT_STEP(G, OUT)                                                                            \
+    const v4i_t res_c = make_rsrc_words(src_codes + (size_t)grp0 * 32u * half + (col0 >> 1), src_rows * half - (col0 >> 1));
+    stage_kquad_rows<B, false>(res_c, half, lds);
+    // A lane's 32 scales are one byte of 32 neighbouring dwords of its row block's tile: column group g of the K-quad, dwords of
+    // half h = g % 2, byte g / 2 (the same for the whole wave).  The lanes of the four chunks that may share (j, h) form eight
+    // of them each, as floats, and share them through LDS.
+    const size_t tile0 = ((size_t)grp0 * skq + (c0 >> 8)) * 256u, scale_bytes = (size_t)gk * skq * 256u;
+    const size_t scale_left = tile0 < scale_bytes ? scale_bytes - tile0 : 0;
+    const __amdgpu_buffer_rsrc_t res_s = make_rsrc(src_scales + tile0, (uint32_t)(scale_left < (size_t)8 * skq * 256u ? scale_left : (size_t)8 * skq * 256u));
+    const uint32_t gbyte = (c0 >> 6) & 3u, h = ((c0 + chunk * NC) >> 5) & 1u, h4 = ((c0 >> 5) & 1u) ^ (chunk >> 2);
+    const int scale_off = (int)(j * skq * 256u + h4 * 128u + (chunk & 3u) * 32u);
+    const v4u_t d0 = __builtin_amdgcn_raw_buffer_load_b128(res_s, scale_off, 0, 0);
+    const v4u_t d1 = __builtin_amdgcn_raw_buffer_load_b128(res_s, scale_off, 16, 0);
+    const uint32_t sw = BIG ? lane_sign_word(p, j) : p.sign_word;
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    const uint8_t* mine = static_cast<const uint8_t*>(lds) + j * kquad_pitch<B>() + (wave * 8u + chunk) * (NC / 2u);
+    uint32_t w[32];
+    // the sign vector applied on the codes: all values of a word are element i of their groups (sign-magnitude: decoding the
+    // flipped code gives the negated value exactly, zeros included)
+#pragma unroll
+    for (uint32_t i = 0; i < 32; ++i) {
+        w[i] = NC == 8u ? *reinterpret_cast<const uint32_t*>(mine + i * B)
+             : NC == 4u ? (uint32_t)*reinterpret_cast<const uint16_t*>(mine + i * B) : (uint32_t)mine[i * B];
+        w[i] ^= bit_mask(sw, i) & 0x88888888u;
+    }
+    __syncthreads();                                   // every wave has its codes: their LDS serves the scales from here on
+    constexpr uint32_t SROW = 36u;                     // floats per (h, j): 16-byte aligned, the eight j of a read on different banks
+    float* fs = static_cast<float*>(lds) + wave * 16u * SROW;
+    {
+        const uint32_t d[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+        float f[8];
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) f[i] = u2f(((d[i] >> (8u * gbyte)) & 0xFFu) << 23);
+        float4* dst = reinterpret_cast<float4*>(fs + (h4 * 8u + j) * SROW + (chunk & 3u) * 8u);
+        dst[0] = make_float4(f[0], f[1], f[2], f[3]);
+        dst[1] = make_float4(f[4], f[5], f[6], f[7]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const float4* my_scales = reinterpret_cast<const float4*>(fs + (h * 8u + j) * SROW);
+    uint32_t* s = s_scale + wave * 16u * NC;
+    // of the lane's current column (an output row): linear position / 16 of its group's first element, and its 16 bytes of codes
+    const uint32_t r0 = c0 + chunk * NC;
+    uint64_t q_base = ((uint64_t)r0 * k + grp * 32u) >> 4;
+    uint8_t* dst_codes = codes + (size_t)r0 * (k >> 1) + (size_t)grp * 16u;
+    uint8_t* s_byte = reinterpret_cast<uint8_t*>(s) + ((((chunk * NC) >> 5) * 2u + (j & 1u)) * (NC >= 4u ? 32u : 16u) + ((chunk * NC) & 31u)) * 4u + (j >> 1);
+#define REQUANT_COLUMN(C, V)                                                                            \
     {                                                                                                   \
+        if (BIG) rotate_block_lanes(V, j, p.nb);                                                        \
+        else fwht32(V);                                                                                 \
+        uint4 q;                                                                                        \
+        uint32_t sb, m;                                                                                 \
+        encode_group<MODE>(V, p, stream, q_base, q, sb, m);                                              \
+        s_byte[(C) * 4u] = (uint8_t)sb;                                                                 \
+        if (r0 + (C) < rows && grp < gk) *reinterpret_cast<uint4*>(dst_codes) = q;                       \
+        q_base += k >> 4;                                                                               \
+        dst_codes += k >> 1;                                                                            \
         __builtin_amdgcn_sched_barrier(0);                                                              \
-        v4u_t cw_next = cw;                                                                             \
-        uint32_t sb_next = sb_src;                                                                      \
-        if ((G) + 1u < 8u) {                                                                            \
-            cw_next = __builtin_amdgcn_raw_buffer_load_b128(res_c, (int)code_off, (int)(((G) + 1u) * code_step), 0); \
-            sb_next = __builtin_amdgcn_raw_buffer_load_b8(res_s, (int)scale_off, (int)(((G) + 1u) * scale_step), 0); \
-        }                                                                                               \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-        asm volatile("" : "+v"(sb_src)); /* the scale is formed here, not next to its load: no early wait */ \
-        const float sc = u2f(sb_src << 23);                                                             \
-        /* the sign vector applied on the codes: all 32 values of this lane are element rl of their groups */ \
-        const uint32_t w[4] = {cw.x ^ code_flip, cw.y ^ code_flip, cw.z ^ code_flip, cw.w ^ code_flip}; \
-        float f[32];                                                                                    \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                 \
-            v2f a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], sc, 0);                              \
-            v2f b = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], sc, 1);                              \
-            v2f c = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], sc, 2);                              \
-            v2f d = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], sc, 3);                              \
-            f[8 * i] = a[0]; f[8 * i + 1] = a[1]; f[8 * i + 2] = b[0]; f[8 * i + 3] = b[1];             \
-            f[8 * i + 4] = c[0]; f[8 * i + 5] = c[1]; f[8 * i + 6] = d[0]; f[8 * i + 7] = d[1];         \
-        }                                                                                               \
-        cw = cw_next;                                                                                   \
-        sb_src = sb_next;                                                                               \
-        /* The stage belongs to this wave alone and a wave's LDS operations complete in order, so the   \
-           exchange needs no barrier and no fence (a fence would also wait for the loads just issued):  \
-           only the compiler must keep the writes and the reads in program order. */                    \
-        __builtin_amdgcn_wave_barrier();                                                                \
-        _Pragma("unroll") for (uint32_t j = 0; j < 32; ++j) stage[(32u * ch + j) * kStageStride + wr] = f[j]; \
-        __builtin_amdgcn_wave_barrier();                                                                \
-        float v[32];                                                                                    \
-        _Pragma("unroll") for (uint32_t q = 0; q < 8; ++q) {                                            \
-            const float4 x = *reinterpret_cast<const float4*>(&stage[lane * kStageStride + ((4u * q + rot) & 31u)]); \
-            v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;                 \
-        }                                                                                               \
-        uint32_t sb, mw;                                                                                \
-        quantize_group<MODE, true>(v, p, ((uint64_t)out_row * k + (grp0 + (G)) * 32u) >> 4, OUT, sb, mw); \
-        if ((G) & 1u) sw1 |= sb << (8u * ((G) >> 1));                                                   \
-        else sw0 |= sb << (8u * ((G) >> 1));                                                            \
     }
-    if (MODE == kBwdSr) {
-        // Unrolled, with the instruction scheduler fenced at the step boundaries: each step's codes get
-        // registers of their own, so the wait before decoding them lets the next step's loads stay in
-        // flight; the row's 128 bytes of codes leave together at the end (a store inside the loop makes
-        // every step wait for it before its registers can be reused).
-        uint4 out[8];
-#pragma unroll
-        for (uint32_t g = 0; g < 8; ++g) REQUANT_STEP(g, out[g])
-        __builtin_amdgcn_sched_barrier(0);
-        if (out_row >= rows) return;
-#pragma unroll
-        for (uint32_t g = 0; g < 8; ++g)
-            if (grp0 + g < gk) *reinterpret_cast<uint4*>(crow + 16u * g) = out[g];
+// Columns 2 P and 2 P + 1 of the lane's chunk sit in one byte of its words, and one instruction decodes both.  Keeping the second's
+// 32 values while the first is quantized takes more than 128 registers (a fourth wave per SIMD) with Philox (PARK: 20 of them
+// wait in LDS; this kernel is bound by vector-ALU issue) and with the lanes of a wide Hadamard block (AGAIN: decoded twice).
+#define REQUANT_DECODE(P, FIRST, SECOND)                                                                \
+    _Pragma("unroll") for (uint32_t i4 = 0; i4 < 8; ++i4) {                                             \
+        const float4 s4 = my_scales[i4];                                                                \
+        const float sc[4] = {s4.x, s4.y, s4.z, s4.w};                                                   \
+        _Pragma("unroll") for (uint32_t e = 0; e < 4; ++e) {                                            \
+            const v2f a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4u * i4 + e], sc[e], P);           \
+            FIRST[4u * i4 + e] = a[0];                                                                  \
+            SECOND[4u * i4 + e] = a[1];                                                                 \
+        }                                                                                               \
+    }                                                                                                   \
+    __builtin_amdgcn_sched_barrier(0);
+#define REQUANT_PAIR(P)                                                                                 \
+    if (2u * (P) < NC) {                                                                                \
+        float v0[32], v1[32];                                                                           \
+        REQUANT_DECODE(P, v0, v1)                                                                       \
+        if (PARK) {                                                                                     \
+            _Pragma("unroll") for (uint32_t i = 0; i < 20; ++i) parked[64u * i] = v1[i];                \
+            asm volatile("" ::: "memory");                                                              \
+            __builtin_amdgcn_sched_barrier(0);                                                          \
+        }                                                                                               \
+        REQUANT_COLUMN(2u * (P), v0)                                                                    \
+        if (PARK) {                                                                                     \
+            asm volatile("" ::: "memory");                                                              \
+            _Pragma("unroll") for (uint32_t i = 0; i < 20; ++i) v1[i] = parked[64u * i];                \
+        }                                                                                               \
+        if (AGAIN) {                                                                                    \
+            _Pragma("unroll") for (uint32_t i = 0; i < 32; ++i) asm volatile("" : "+v"(w[i]));          \
+            REQUANT_DECODE(P, v0, v1)                                                                   \
+        }                                                                                               \
+        REQUANT_COLUMN(2u * (P) + 1u, v1)                                                               \
+    }
+    constexpr bool AGAIN = BIG, PARK = !BIG && MODE == kBwdSr && NC == 8u;
+    float* parked = static_cast<float*>(lds) + 4u * 16u * SROW + wave * 20u * 64u + lane;
+    static_assert(!PARK || 4u * 16u * SROW * 4u + 4u * 5u * 1024u <= 8u * kquad_pitch<B>(), "the parked values must fit behind the scales");
+    __builtin_amdgcn_sched_barrier(0);
+    REQUANT_PAIR(0)
+    REQUANT_PAIR(1)
+    REQUANT_PAIR(2)
+    REQUANT_PAIR(3)
+#undef REQUANT_PAIR
+#undef REQUANT_DECODE
+#undef REQUANT_COLUMN
+    __builtin_amdgcn_wave_barrier();
+    if (NC == 8u) {
+        store_kquad_scales<32u>(s, scales, c0, rows, grp0, gk, lane);
+        store_kquad_scales<32u>(s + 64, scales, c0 + 32u, rows, grp0, gk, lane);
     } else {
-        // round-to-nearest: the unrolled form costs this variant more registers than a CU can give four
-        // waves; it keeps the loop, and each step stores its own 16 bytes
-#pragma unroll 1
-        for (uint32_t g = 0; g < 8; ++g) {
-            uint4 out;
-            REQUANT_STEP(g, out)
-            if (out_row < rows && grp0 + g < gk) *reinterpret_cast<uint4*>(crow + 16u * g) = out;
-        }
-        if (out_row >= rows) return;
-    }
-#undef REQUANT_STEP
-    // scales: dwords (row, h = 0) and (row, h = 1) of the output's scale tile; a wave's 64 rows fill two
-    // 128-byte runs per h
-#pragma unroll
-    for (uint32_t h = 0; h < 2; ++h) {
-        const uint32_t w = h ? sw1 : sw0;
-        if (grp0 + h >= gk) continue;
-        uint32_t* dst = reinterpret_cast<uint32_t*>(scales + scale_tile_offset(out_row, grp0 + h, okq));
-        if (grp0 + 6u + h < gk) {
-            *dst = w;
-        } else {
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q)
-                if (grp0 + 2u * q + h < gk) reinterpret_cast<uint8_t*>(dst)[q] = (uint8_t)(w >> (8u * q));
-        }
+        store_kquad_scales<8u * (NC == 8u ? 4u : NC)>(s, scales, c0, rows, grp0, gk, lane);
     }
 }
 
-template <int MODE, int WPB>
-__global__ void __launch_bounds__(64 * WPB, 4)   // 4 waves per SIMD: at most 128 registers
+template <int MODE, bool BIG, uint32_t NC>
+__global__ void __launch_bounds__(256, 4)
 requant_transposed_kernel(const uint8_t* __restrict__ src_codes, const uint8_t* __restrict__ src_scales,
                           uint32_t rows, uint32_t k, uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
                           SrParams p) {
-    __shared__ float s_stage[WPB][64 * kStageStride];
-    // its place in a 256-column stretch, and the stretch
-    uint32_t wave, quad;
-    if (WPB == 1) {
-        // One-wave blocks go to the 8 XCDs in turn.  The four waves of a stretch read the same 128-byte lines, so they
-        // are the blocks b, b+8, b+16, b+24 of a run of 32: same XCD, one L2 fetch per line instead of four.  The grid
-        // is padded to whole runs; the blocks past the last stretch leave at once.
-        quad = (blockIdx.x >> 5) * 8u + (blockIdx.x & 7u);
-        wave = (blockIdx.x >> 3) & 3u;
-        if (quad * 256u >= rows) return;
-    } else {
-        const uint32_t gwave = blockIdx.x * (uint32_t)WPB + (threadIdx.x >> 6);   // wave of the whole launch along the columns
-        wave = gwave & 3u;
-        quad = gwave >> 2;
-    }
-    requant_transposed_wave<MODE>(src_codes, src_scales, rows, k, codes, scales, p, wave, quad, blockIdx.y, s_stage[threadIdx.x >> 6]);
+    __shared__ __align__(16) uint8_t stage[NC == 2u ? 9216u : 8u * kquad_pitch<16u * NC>()];
+    __shared__ uint32_t s_scale[64u * NC];
+    requant_columns_block<MODE, BIG, NC>(src_codes, src_scales, rows, k, codes, scales, p, p.stream_id, blockIdx.y, blockIdx.x * 32u * NC, stage, s_scale);
 }
 
-// ------------------------------------------------------------------ the backward pass's three operand conversions in one launch
-// dy^T quantized along the tokens (quant_transposed_tile), X_q and W_q re-quantized along their other dimension
-// (requant_transposed_wave, four waves = one 256-column stretch per block): Algorithm 1 Backward needs all three before the
-// two gradient products and none depends on another.  Launched one after the other, the re-quantizers leave most of the
-// chip idle on weight-sized tensors and every kernel pays its own ramp-up and drain.  In one grid the re-quantizer blocks
-// come first (W_q's, then X_q's) and the dy^T tiles fill the CUs as those finish.  (Spreading the re-quantizer blocks
-// evenly among the tiles was measured slower than launching the kernels one by one: it breaks up the order in which
-// neighbouring tiles write their lines.)
+// ------------------------------------------------------------------ the backward pass's operand conversions in one launch
+// dy^T quantized along the tokens, X_q and W_q re-quantized along their other dimension, and optionally dy itself along out:
+// Algorithm 1 Backward needs all of them before the two gradient products and none depends on another.  Launched one after the
+// other, the re-quantizers leave most of the chip idle on weight-sized tensors and every kernel pays its own ramp-up and
+// drain.  In one grid the re-quantizer blocks come first (W_q's, then X_q's) and the dy^T tiles fill the CUs as those finish.
+// (Spreading the re-quantizer blocks evenly among the tiles was measured slower than launching the kernels one by one: it
+// breaks up the order in which neighbouring tiles write their lines.)
 struct BwdOperandsMap {
     uint32_t n_rq_w, n_rq;           // re-quantizer blocks of W_q, and of W_q and X_q together: block indices [0, n_rq)
-    uint32_t t_gx, w_quads, x_quads; // dy^T tiles per column tile row (K-quads); 256-column stretches of W_q^T, X_q^T
-    FastDiv div_t_gx, div_w_quads, div_x_quads;
+    uint32_t t_gx, t_gy;             // dy^T tiles: K-quads, column tiles
+    uint32_t quads;                  // re-quantizer blocks along the columns (of W_q and of X_q: both have `in` columns)
+    FastDiv div_t_gx, div_quads;
     uint32_t n_tiles_end;            // blocks [n_rq, n_tiles_end): dy^T tiles; blocks from n_tiles_end on: row tiles of dy (optional)
     uint32_t r_k_blocks;             // row tiles per 8 rows of dy
     FastDiv div_r_k_blocks;
 };
 
-template <int MODE>
-__global__ void __launch_bounds__(256, 4)   // 128 registers: four blocks per CU (their LDS, 4 x 36 KB, fits too)
+// one re-quantized matrix of the launch
+struct RequantMatrix {
+    const uint8_t* src_codes;
+    const uint8_t* src_scales;
+    uint32_t rows, k;
+    uint8_t* codes;
+    uint8_t* scales;
+    uint32_t stream_id;
+};
+
+// CPL, NC: columns per lane of the dy^T tile and of the re-quantizer waves (less work per wave for smaller problems).
+// p: the parameters of all four conversions but for the Philox stream.  Each kind of block is inlined once (W_q's and X_q's
+// blocks share one copy: with one each the kernel outgrew the 64 KB instruction cache).
+template <int MODE, bool BIG, uint32_t CPL, uint32_t NC>
+__global__ void __launch_bounds__(256, 4)
 bwd_operands_kernel(const uint16_t* __restrict__ dy, uint32_t t_rows, uint32_t t_k, int64_t t_ldx,
-                    uint8_t* __restrict__ t_codes, uint8_t* __restrict__ t_scales, SrParams t_p,
-                    const uint8_t* __restrict__ x_src_codes, const uint8_t* __restrict__ x_src_scales, uint32_t x_rows, uint32_t x_k,
-                    uint8_t* __restrict__ x_codes, uint8_t* __restrict__ x_scales, SrParams x_p,
-                    const uint8_t* __restrict__ w_src_codes, const uint8_t* __restrict__ w_src_scales, uint32_t w_rows, uint32_t w_k,
-                    uint8_t* __restrict__ w_codes, uint8_t* __restrict__ w_scales, SrParams w_p,
-                    uint4* __restrict__ r_codes, uint8_t* __restrict__ r_scales, SrParams r_p, BwdOperandsMap map) {
-    __shared__ __align__(16) uint8_t smem[4u * 64u * kStageStride * sizeof(float)];   // 36 KB: four re-quantizer stages
-    static_assert(sizeof(smem) >= 128 * 8 * (16 + 1 + 4), "the dy^T tile's staging must fit as well");
-    static_assert(sizeof(smem) >= 4 * 256 * 16 + 64 * 4, "the row tile's staging must fit as well");
+                    uint8_t* __restrict__ t_codes, uint8_t* __restrict__ t_scales, uint32_t t_stream, RequantMatrix w, RequantMatrix x,
+                    uint4* __restrict__ r_codes, uint8_t* __restrict__ r_scales, uint32_t r_stream, SrParams p, BwdOperandsMap map) {
+    constexpr bool WIDE_TILE = !BIG && CPL == 2u;
+    constexpr uint32_t B = 64u * CPL > 16u * NC ? 64u * CPL : 16u * NC;
+    __shared__ __align__(16) uint8_t smem[8u * kquad_pitch<B>()];
+    __shared__ uint32_t s_scale[64u * (NC > CPL ? NC : CPL)];
+    static_assert(sizeof(smem) >= 4 * 256 * 16 && sizeof(s_scale) >= 64 * 4, "the row tile's staging must fit");
+    static_assert(!WIDE_TILE || (sizeof(smem) >= 128 * 8 * 16 && sizeof(s_scale) >= 128 * 8), "the dy^T tile's staging must fit");
     const uint32_t b = blockIdx.x;
     if (b < map.n_rq) {
-        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        float* stage = reinterpret_cast<float*>(smem) + wave * (64u * kStageStride);
-        if (b < map.n_rq_w) {
-            const uint32_t kq = fast_div(b, map.div_w_quads), quad = b - kq * map.w_quads;
-            requant_transposed_wave<MODE>(w_src_codes, w_src_scales, w_rows, w_k, w_codes, w_scales, w_p, wave, quad, kq, stage);
-        } else {
-            const uint32_t j = b - map.n_rq_w;
-            const uint32_t kq = fast_div(j, map.div_x_quads), quad = j - kq * map.x_quads;
-            requant_transposed_wave<MODE>(x_src_codes, x_src_scales, x_rows, x_k, x_codes, x_scales, x_p, wave, quad, kq, stage);
-        }
+        const bool is_w = b < map.n_rq_w;
+        const RequantMatrix& m = is_w ? w : x;
+        const uint32_t i = is_w ? b : b - map.n_rq_w;
+        const uint32_t kq = fast_div(i, map.div_quads), quad = i - kq * map.quads;
+        requant_columns_block<MODE, BIG, NC>(m.src_codes, m.src_scales, m.rows, m.k, m.codes, m.scales, p, m.stream_id, kq, quad * 32u * NC, smem, s_scale);
     } else if (b >= map.n_tiles_end) {
         // Q(dy) in row mode (the first operand of the dx product), for callers that want all four conversions in one launch:
         // dy is [t_k x t_rows] row-major, groups along its rows
-        uint4 (*stage)[256] = reinterpret_cast<uint4 (*)[256]>(smem);
-        uint32_t* s_scale = reinterpret_cast<uint32_t*>(smem + 4 * 256 * 16);
-        quant_row_tile<MODE, false, false>(dy, t_k, t_rows >> 5, t_ldx, r_codes, r_scales, nullptr, r_p, map.r_k_blocks,
-                                           map.div_r_k_blocks, b - map.n_tiles_end, stage, s_scale);
+        quant_row_tile<MODE, false, BIG>(dy, t_k, t_rows >> 5, t_ldx, r_codes, r_scales, nullptr, p, r_stream, map.r_k_blocks,
+                                         map.div_r_k_blocks, b - map.n_tiles_end, reinterpret_cast<uint4 (*)[256]>(smem), s_scale);
     } else {
         const uint32_t tb = b - map.n_rq;
         const uint32_t by = fast_div(tb, map.div_t_gx), bx = tb - by * map.t_gx;
-        uint4* s_codes = reinterpret_cast<uint4*>(smem);
-        uint32_t* s_mask = reinterpret_cast<uint32_t*>(smem + 128 * 8 * 16);
-        uint8_t* s_scales = smem + 128 * 8 * 20;
-        quant_transposed_tile<MODE, false>(dy, t_rows, t_k, t_ldx, t_codes, t_scales, nullptr, t_p, bx,
-                                           transposed_column_tile(bx, by, (t_rows + 127u) >> 7), s_codes, s_scales, s_mask);
-    }
-}
-
-// Re-quantization for Hadamard blocks of NB = 2, 4 or 8 groups (same tile, same stage).  The groups of
-// a block are whole groups of source rows, so the group-combining stages come first, on the decoded
-// values: for output group G (place j in its block) a lane decodes its 32 columns of the NB source
-// rows (block group jj, row rl), eight values at a time, flips their signs and folds them through the
-// butterfly tree down to place j; the 32-point stages follow after the transposition as usual.
-template <int MODE, int NB>
-__global__ void __launch_bounds__(256)
-requant_transposed_block_kernel(const uint8_t* __restrict__ src_codes, const uint8_t* __restrict__ src_scales,
-                                uint32_t rows, uint32_t k, uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-                                SrParams p) {
-    __shared__ float s_stage[4][64 * kStageStride];
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-    float* stage = s_stage[wave];
-    const uint32_t gk = k >> 5, okq = (k + 255u) >> 8;
-    const uint32_t half = rows >> 1, skq = (rows + 255u) >> 8;
-    const uint32_t c0 = blockIdx.x * 256u + wave * 64u, kq = blockIdx.y, grp0 = kq * 8u;
-    const uint32_t rl = lane >> 1, ch = lane & 1u, cg = wave * 2u + ch;
-    const uint32_t cb0 = blockIdx.x * 256u;
-    const uint32_t src_rows = (k - grp0 * 32u) < 256u ? (k - grp0 * 32u) : 256u;
-    const uint32_t src_cols = (rows - cb0) < 256u ? (rows - cb0) : 256u;
-    const __amdgpu_buffer_rsrc_t res_c = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(src_codes + (size_t)grp0 * 32u * half + (cb0 >> 1)), 0,
-        (int)((src_rows - 1u) * half + (src_cols >> 1)), 0x00020000);
-    const size_t tile0 = ((size_t)grp0 * skq + (cb0 >> 8)) * 256u;
-    const __amdgpu_buffer_rsrc_t res_s = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(src_scales + tile0), 0, (int)((size_t)gk * skq * 256u - tile0), 0x00020000);
-    const uint32_t code_off = rl * half + ((wave * 64u + 32u * ch) >> 1);
-    const uint32_t scale_off = (((cg & 1u) << 5) + rl) * 4u + (cg >> 1);
-    const uint32_t code_step = 32u * half, scale_step = skq * 256u;
-    const uint32_t wr = (rl + 16u * ch) & 31u;
-    const uint32_t out_row = c0 + lane, rot = (16u * (lane >> 5)) & 31u;
-    const float norm = block_norm((uint32_t)NB);
-    uint32_t sw0 = 0u, sw1 = 0u;
-    uint8_t* crow = codes + (size_t)out_row * (k >> 1) + (size_t)grp0 * 16u;
-#pragma unroll 1
-    for (uint32_t g = 0; g < 8; ++g) {
-        const uint32_t jb = g & ~((uint32_t)NB - 1u), j = g - jb;
-        const uint32_t neg1 = (j & 1u) << 31, neg2 = (j & 2u) << 30, neg4 = (j & 4u) << 29;
-        v4u_t cw[NB];
-        float sc[NB];
-        uint32_t flip[NB];
-#pragma unroll
-        for (uint32_t jj = 0; jj < (uint32_t)NB; ++jj) {
-            cw[jj] = __builtin_amdgcn_raw_buffer_load_b128(res_c, (int)code_off, (int)((jb + jj) * code_step), 0);
-            const uint32_t sbyte = __builtin_amdgcn_raw_buffer_load_b8(res_s, (int)scale_off, (int)((jb + jj) * scale_step), 0);
-            sc[jj] = u2f(sbyte << 23);
-            // the loads of a whole block may stay in registers across the steps that share it, the decoded values may
-            // not (NB x 32 floats): a scale the compiler cannot see through keeps the decoding inside the step
-            asm volatile("" : "+v"(sc[jj]));
-            flip[jj] = ((p.sign_words[jj] >> rl) & 1u) << 31;   // element rl of block group jj
-        }
-        float f[32];
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) {
-            __builtin_amdgcn_sched_barrier(0);               // one dword of codes per group at a time
-            float x[NB][8];
-#pragma unroll
-            for (uint32_t jj = 0; jj < (uint32_t)NB; ++jj) {
-                const uint32_t w = cw[jj][q];
-                v2f a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc[jj], 0);
-                v2f b = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc[jj], 1);
-                v2f c = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc[jj], 2);
-                v2f d = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc[jj], 3);
-                const float t[8] = {a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
-#pragma unroll
-                for (uint32_t e = 0; e < 8; ++e) x[jj][e] = u2f(f2u(t[e]) ^ flip[jj]);
-            }
-#pragma unroll
-            for (uint32_t e = 0; e < 8; ++e) {
-                float y[NB / 2];
-#pragma unroll
-                for (uint32_t m = 0; m < (uint32_t)NB / 2u; ++m) y[m] = x[2 * m][e] + u2f(f2u(x[2 * m + 1][e]) ^ neg1);
-                if (NB >= 4) {
-#pragma unroll
-                    for (uint32_t m = 0; m < (uint32_t)NB / 4u; ++m) y[m] = y[2 * m] + u2f(f2u(y[2 * m + 1]) ^ neg2);
-                }
-                if (NB >= 8) y[0] = y[0] + u2f(f2u(y[1]) ^ neg4);
-                f[8 * q + e] = y[0];
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (uint32_t jx = 0; jx < 32; ++jx) stage[(32u * ch + jx) * kStageStride + wr] = f[jx];
-        __builtin_amdgcn_wave_barrier();
-        float v[32];
-#pragma unroll
-        for (uint32_t q = 0; q < 8; ++q) {
-            const float4 xx = *reinterpret_cast<const float4*>(&stage[lane * kStageStride + ((4u * q + rot) & 31u)]);
-            v[4 * q] = xx.x; v[4 * q + 1] = xx.y; v[4 * q + 2] = xx.z; v[4 * q + 3] = xx.w;
-        }
-        __builtin_amdgcn_wave_barrier();
-        fwht32_unscaled(v);
-#pragma unroll
-        for (int i = 0; i < 32; ++i) v[i] = v[i] * norm;
-        uint4 out;
-        uint32_t sb, mw;
-        encode_group<MODE>(v, p, ((uint64_t)out_row * k + (grp0 + g) * 32u) >> 4, out, sb, mw);
-        if (g & 1u) sw1 |= sb << (8u * (g >> 1));
-        else sw0 |= sb << (8u * (g >> 1));
-        if (out_row < rows && grp0 + g < gk) *reinterpret_cast<uint4*>(crow + 16u * g) = out;
-    }
-    if (out_row >= rows) return;
-#pragma unroll
-    for (uint32_t h = 0; h < 2; ++h) {
-        const uint32_t w = h ? sw1 : sw0;
-        if (grp0 + h >= gk) continue;
-        uint32_t* dst = reinterpret_cast<uint32_t*>(scales + scale_tile_offset(out_row, grp0 + h, okq));
-        if (grp0 + 6u + h < gk) {
-            *dst = w;
-        } else {
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q)
-                if (grp0 + 2u * q + h < gk) reinterpret_cast<uint8_t*>(dst)[q] = (uint8_t)(w >> (8u * q));
-        }
+        const uint32_t ct = transposed_column_tile(bx, by, map.t_gy);
+        if (WIDE_TILE)
+            quant_transposed_tile<MODE, false>(dy, t_rows, t_k, t_ldx, t_codes, t_scales, nullptr, p, t_stream, bx, ct,
+                                               reinterpret_cast<uint4*>(smem), reinterpret_cast<uint8_t*>(s_scale), nullptr);
+        else
+            quant_columns_block<MODE, false, BIG, CPL>(dy, t_rows, t_k, t_ldx, t_codes, t_scales, nullptr, p, t_stream, bx, ct * 32u * CPL,
+                                                       smem, s_scale);
     }
 }
 
@@ -862,26 +769,44 @@ static hipError_t launch_row(const void* x, int64_t rows, int64_t k, int64_t ldx
     return hipGetLastError();
 }
 
+// Columns per lane of the re-quantizer waves for a launch that converts `elements` values transposed.  A wave quantizes its columns
+// one after the other, 1-1.5 us each, so while the whole launch is shorter than eight of them the waves take fewer columns; fewer
+// columns also mean shorter pieces of the source rows (128, 64, 32 bytes), which cost memory efficiency once the chip is full.
+// Measured (us, all four conversions of a layer, 8 / 4 / 2 columns, stochastic): 256 x 512 x 512 11.5 / 7.5 / 5.4; 2048^3 (16 M
+// elements) 12.5 / 8.9 / 9.1; 4096 x 4096 x 1024 (25 M) 22.9 / 17.6 / 18.5; 8192 x 2048 x 2048 (38 M) 30.0 / 31.4 / -;
+// 4096^3 (50 M) 37 / 38 / -.
+static uint32_t requant_columns(uint64_t elements) {
+    return elements >= ((uint64_t)32 << 20) ? 8u : elements >= ((uint64_t)10 << 20) ? 4u : 2u;
+}
+
 template <int MODE, bool MASK>
-static void launch_transposed_nb(dim3 grid, hipStream_t st, const void* src, int64_t rows, int64_t k, int64_t ldx,
-                                 uint8_t* codes, uint8_t* scales, uint32_t* mask, const SrParams& p) {
-    dim3 block(256);
+static void launch_transposed_nb(const void* src, int64_t rows, int64_t k, int64_t ldx, uint8_t* codes, uint8_t* scales,
+                                 uint32_t* mask, const SrParams& p, hipStream_t st) {
+    const uint32_t kquads = (uint32_t)((k / 32 + 7) / 8);
     const uint16_t* s = (const uint16_t*)src;
-    switch (p.nb) {
-    case 1u: hipLaunchKernelGGL((quant_transposed_kernel<MODE, MASK>), grid, block, 0, st, s, (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p); break;
-    case 2u: hipLaunchKernelGGL((quant_transposed_block_kernel<MODE, MASK, 2>), grid, block, 0, st, s, (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p); break;
-    case 4u: hipLaunchKernelGGL((quant_transposed_block_kernel<MODE, MASK, 4>), grid, block, 0, st, s, (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p); break;
-    default: hipLaunchKernelGGL((quant_transposed_block_kernel<MODE, MASK, 8>), grid, block, 0, st, s, (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p); break;
+    // below about two of the 256 x 32 waves per SIMD: half the columns per block (4096 x 2048, 1024 waves: 7.5 us against 8.3;
+    // 16384 x 4096, 8192 waves: 35.9 against 34.2)
+    const bool small = (uint64_t)kquads * (uint64_t)((rows + 31) / 32) < 2048u;
+#define QUARTET_TRANSPOSED(COLS, KERNEL, ...)                                                                                    \
+    hipLaunchKernelGGL((KERNEL<MODE, MASK __VA_ARGS__>), dim3(kquads, (uint32_t)((rows + COLS - 1) / COLS)), dim3(256), 0, st, s,  \
+                       (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p)
+    if (p.nb > 1u) {
+        if (small) QUARTET_TRANSPOSED(32, quant_columns_kernel, , true, 1);
+        else QUARTET_TRANSPOSED(64, quant_columns_kernel, , true, 2);
+    } else {
+        if (small) QUARTET_TRANSPOSED(32, quant_columns_kernel, , false, 1);
+        else QUARTET_TRANSPOSED(128, quant_transposed_kernel, );
     }
+#undef QUARTET_TRANSPOSED
 }
 
 template <int MODE>
 static hipError_t launch_transposed(const void* src, int64_t rows, int64_t k, int64_t ldx, uint8_t* codes,
                                     uint8_t* scales, uint32_t* mask, const SrParams& p, hipStream_t st) {
     if (rows == 0 || k == 0) return hipSuccess;
-    dim3 grid((uint32_t)((k / 32 + 7) / 8), (uint32_t)((rows + 127) / 128));
-    if (mask) launch_transposed_nb<MODE, true>(grid, st, src, rows, k, ldx, codes, scales, mask, p);
-    else launch_transposed_nb<MODE, false>(grid, st, src, rows, k, ldx, codes, scales, mask, p);
+    constexpr bool CAN_MASK = MODE == kFwd;           // the backward rules never clip
+    if (CAN_MASK && mask) launch_transposed_nb<MODE, CAN_MASK>(src, rows, k, ldx, codes, scales, mask, p, st);
+    else launch_transposed_nb<MODE, false>(src, rows, k, ldx, codes, scales, nullptr, p, st);
     return hipGetLastError();
 }
 
@@ -901,30 +826,31 @@ hipError_t launch_quant(int mode, const void* x, int64_t rows, int64_t k, int64_
     }
 }
 
-template <int MODE>
-static void launch_requant_nb(dim3 grid, hipStream_t st, const uint8_t* src_codes, const uint8_t* src_scales, int64_t rows,
-                              int64_t k, const SrParams& p, uint8_t* codes, uint8_t* scales) {
-    dim3 block(256);
-    switch (p.nb) {
-    case 1u:
-        // one wave per block (the waves never cooperate): measured equal to four-wave blocks on the large tensors and
-        // 8-20 % faster on weight-sized ones, where it spreads the same waves over four times as many CUs; runs of 32
-        // blocks = 8 stretches x 4 waves, see the kernel
-        hipLaunchKernelGGL((requant_transposed_kernel<MODE, 1>), dim3(((grid.x + 7u) / 8u) * 32u, grid.y), dim3(64), 0, st, src_codes, src_scales, (uint32_t)rows, (uint32_t)k, codes, scales, p);
-        break;
-    case 2u: hipLaunchKernelGGL((requant_transposed_block_kernel<MODE, 2>), grid, block, 0, st, src_codes, src_scales, (uint32_t)rows, (uint32_t)k, codes, scales, p); break;
-    case 4u: hipLaunchKernelGGL((requant_transposed_block_kernel<MODE, 4>), grid, block, 0, st, src_codes, src_scales, (uint32_t)rows, (uint32_t)k, codes, scales, p); break;
-    default: hipLaunchKernelGGL((requant_transposed_block_kernel<MODE, 8>), grid, block, 0, st, src_codes, src_scales, (uint32_t)rows, (uint32_t)k, codes, scales, p); break;
-    }
+template <int MODE, bool BIG>
+static void launch_requant_big(const uint8_t* src_codes, const uint8_t* src_scales, int64_t rows, int64_t k, const SrParams& p,
+                               uint8_t* codes, uint8_t* scales, hipStream_t st) {
+    const uint32_t nc = requant_columns((uint64_t)rows * (uint64_t)k), kquads = (uint32_t)((k + 255) / 256);
+    const dim3 grid((uint32_t)((rows + 32 * nc - 1) / (32 * nc)), kquads);
+#define QUARTET_REQUANT(NC)                                                                                                       \
+    hipLaunchKernelGGL((requant_transposed_kernel<MODE, BIG, NC>), grid, dim3(256), 0, st, src_codes, src_scales, (uint32_t)rows,  \
+                       (uint32_t)k, codes, scales, p)
+    if (nc == 8u) QUARTET_REQUANT(8);
+    else if (nc == 4u) QUARTET_REQUANT(4);
+    else QUARTET_REQUANT(2);
+#undef QUARTET_REQUANT
 }
 
 hipError_t launch_requant_transpose(int mode, const uint8_t* src_codes, const uint8_t* src_scales,
                                     int64_t rows, int64_t k, const SrParams& p, uint8_t* codes,
                                     uint8_t* scales, hipStream_t st) {
     if (rows == 0 || k == 0) return hipSuccess;
-    dim3 grid((uint32_t)((rows + 255) / 256), (uint32_t)((k + 255) / 256));
-    if (mode == kBwdRtn) launch_requant_nb<kBwdRtn>(grid, st, src_codes, src_scales, rows, k, p, codes, scales);
-    else launch_requant_nb<kBwdSr>(grid, st, src_codes, src_scales, rows, k, p, codes, scales);
+    if (mode == kBwdRtn) {
+        if (p.nb > 1u) launch_requant_big<kBwdRtn, true>(src_codes, src_scales, rows, k, p, codes, scales, st);
+        else launch_requant_big<kBwdRtn, false>(src_codes, src_scales, rows, k, p, codes, scales, st);
+    } else {
+        if (p.nb > 1u) launch_requant_big<kBwdSr, true>(src_codes, src_scales, rows, k, p, codes, scales, st);
+        else launch_requant_big<kBwdSr, false>(src_codes, src_scales, rows, k, p, codes, scales, st);
+    }
     return hipGetLastError();
 }
 
@@ -938,8 +864,12 @@ hipError_t launch_fwd_operands(const void* x, int64_t tokens, const void* w, int
     if (na + nb >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;
     RowMatrix a = {(const uint16_t*)x, (uint32_t)tokens, in, (uint4*)xq_codes, xq_scales, x_mask};
     RowMatrix b = {(const uint16_t*)w, (uint32_t)out, in, (uint4*)wq_codes, wq_scales, w_mask};
-    hipLaunchKernelGGL((quant_row_pair_kernel<kFwd, true>), dim3((uint32_t)(na + nb)), dim3(256), 0, st, a, b, (uint32_t)na, gk, p,
-                       k_blocks, make_fast_div(k_blocks));
+    if (p.nb > 1u)
+        hipLaunchKernelGGL((quant_row_pair_kernel<kFwd, true, true>), dim3((uint32_t)(na + nb)), dim3(256), 0, st, a, b, (uint32_t)na,
+                           gk, p, k_blocks, make_fast_div(k_blocks));
+    else
+        hipLaunchKernelGGL((quant_row_pair_kernel<kFwd, true, false>), dim3((uint32_t)(na + nb)), dim3(256), 0, st, a, b, (uint32_t)na,
+                           gk, p, k_blocks, make_fast_div(k_blocks));
     return hipGetLastError();
 }
 
@@ -950,14 +880,19 @@ hipError_t launch_bwd_operands(int mode, const void* dy, int64_t tokens, int64_t
                                uint8_t* wt_codes, uint8_t* wt_scales,
                                const SrParams& p_dy, uint8_t* dy_codes, uint8_t* dy_scales, hipStream_t st) {
     BwdOperandsMap map;
+    const uint32_t kq_t = (uint32_t)((tokens + 255) / 256), kq_o = (uint32_t)((out + 255) / 256);
+    const SrParams& p = p_dyt;        // the four differ in the Philox stream alone
+    const bool big = p.nb > 1u;
+    const uint32_t nc = requant_columns((uint64_t)tokens * (uint64_t)out + (uint64_t)in * (uint64_t)(tokens + out));
+    const int64_t t_cols = nc == 8u ? (big ? 64 : 128) : 32, q_cols = 32 * nc;
     // dy^T: logical [out x tokens]; X_q^T: [in x tokens] from [tokens x in]; W_q^T: [in x out] from [out x in].
     // An empty dimension empties the conversions it belongs to, not the others.
-    map.t_gx = (uint32_t)((tokens / 32 + 7) / 8);
-    const uint32_t t_gy = (uint32_t)((out + 127) / 128);
-    map.w_quads = map.x_quads = (uint32_t)((in + 255) / 256);
-    map.n_rq_w = map.w_quads * (uint32_t)((out + 255) / 256);
-    map.n_rq = map.n_rq_w + map.x_quads * (uint32_t)((tokens + 255) / 256);
-    uint64_t total = (uint64_t)map.t_gx * t_gy + map.n_rq;
+    map.t_gx = kq_t;
+    map.t_gy = (uint32_t)((out + t_cols - 1) / t_cols);
+    map.quads = (uint32_t)((in + q_cols - 1) / q_cols);
+    map.n_rq_w = map.quads * kq_o;
+    map.n_rq = map.n_rq_w + map.quads * kq_t;
+    uint64_t total = (uint64_t)map.t_gx * map.t_gy + map.n_rq;
     if (total >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;
     map.n_tiles_end = (uint32_t)total;
     // optional fourth conversion: dy [tokens x out] in row mode, 8 rows x 1024 columns per block
@@ -966,20 +901,24 @@ hipError_t launch_bwd_operands(int mode, const void* dy, int64_t tokens, int64_t
     if (total == 0) return hipSuccess;
     if (total >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;
     map.div_t_gx = make_fast_div(map.t_gx ? map.t_gx : 1u);
-    map.div_w_quads = make_fast_div(map.w_quads ? map.w_quads : 1u);
-    map.div_x_quads = make_fast_div(map.x_quads ? map.x_quads : 1u);
+    map.div_quads = make_fast_div(map.quads ? map.quads : 1u);
+    const RequantMatrix w = {wq_codes, wq_scales, (uint32_t)in, (uint32_t)out, wt_codes, wt_scales, p_w.stream_id};
+    const RequantMatrix x = {xq_codes, xq_scales, (uint32_t)in, (uint32_t)tokens, xt_codes, xt_scales, p_x.stream_id};
     map.div_r_k_blocks = make_fast_div(map.r_k_blocks ? map.r_k_blocks : 1u);
-    dim3 grid((uint32_t)total), block(256);
-    if (mode == kBwdRtn)
-        hipLaunchKernelGGL((bwd_operands_kernel<kBwdRtn>), grid, block, 0, st, (const uint16_t*)dy, (uint32_t)out, (uint32_t)tokens, out,
-                           dyt_codes, dyt_scales, p_dyt, xq_codes, xq_scales, (uint32_t)in, (uint32_t)tokens, xt_codes, xt_scales, p_x,
-                           wq_codes, wq_scales, (uint32_t)in, (uint32_t)out, wt_codes, wt_scales, p_w,
-                           reinterpret_cast<uint4*>(dy_codes), dy_scales, p_dy, map);
-    else
-        hipLaunchKernelGGL((bwd_operands_kernel<kBwdSr>), grid, block, 0, st, (const uint16_t*)dy, (uint32_t)out, (uint32_t)tokens, out,
-                           dyt_codes, dyt_scales, p_dyt, xq_codes, xq_scales, (uint32_t)in, (uint32_t)tokens, xt_codes, xt_scales, p_x,
-                           wq_codes, wq_scales, (uint32_t)in, (uint32_t)out, wt_codes, wt_scales, p_w,
-                           reinterpret_cast<uint4*>(dy_codes), dy_scales, p_dy, map);
+#define QUARTET_BWD_OPERANDS(MODE, BIG, CPL, NC)                                                                                  \
+    hipLaunchKernelGGL((bwd_operands_kernel<MODE, BIG, CPL, NC>), dim3((uint32_t)total), dim3(256), 0, st, (const uint16_t*)dy,    \
+                       (uint32_t)out, (uint32_t)tokens, out, dyt_codes, dyt_scales, p_dyt.stream_id, w, x,                         \
+                       reinterpret_cast<uint4*>(dy_codes), dy_scales, p_dy.stream_id, p, map)
+#define QUARTET_BWD_OPERANDS_SIZE(MODE, BIG)                                                                                      \
+    do {                                                                                                                          \
+        if (nc == 8u) QUARTET_BWD_OPERANDS(MODE, BIG, 2, 8);                                                                      \
+        else if (nc == 4u) QUARTET_BWD_OPERANDS(MODE, BIG, 1, 4);                                                                 \
+        else QUARTET_BWD_OPERANDS(MODE, BIG, 1, 2);                                                                               \
+    } while (0)
+    if (mode == kBwdRtn) { if (big) QUARTET_BWD_OPERANDS_SIZE(kBwdRtn, true); else QUARTET_BWD_OPERANDS_SIZE(kBwdRtn, false); }
+    else { if (big) QUARTET_BWD_OPERANDS_SIZE(kBwdSr, true); else QUARTET_BWD_OPERANDS_SIZE(kBwdSr, false); }
+#undef QUARTET_BWD_OPERANDS_SIZE
+#undef QUARTET_BWD_OPERANDS
     return hipGetLastError();
 }
 

@@ -689,10 +689,41 @@ static int pick_variant(int64_t m, int64_t n, int fused, uint32_t nb) {
     return variant;
 }
 
+// Problems that the split kernels (gemm_split_kernels.hip) finish sooner: few rows, small layers, long inner dimensions with few
+// tiles.  Compares their estimate with one for the streaming kernel of the variant this size gets (fitted to the same 120 shapes,
+// rms error 6-12 %: launch, first loads and epilogue, the stages of its rounds, the share of the chip that stores results),
+// with a tenth in favour of the streaming kernels; two products in one launch run together there, which the sum of their estimates
+// overstates (60 pairs: a factor of 0.6 misses the faster side by 0.5 % on average).  Measured, streaming against split (us):
+// 256 x 512 x 512 5.8 / 3.5;
+// 24 x 11008 x 4096 12.3 / 6.9; 512 x 512 x 8192 22.3 / 6.9; 1024^3 6.7 / 5.3; 128 x 11008 x 4096 14.5 / 10.7; and on the other
+// side 256 x 11008 x 4096 15.3 / 18.8; 1003 x 5632 x 2048 16.0 / 20.6; 2048 x 2048 x 1024 9.6 / 13.4.  The choice depends on m, n
+// and k alone, so fused and plain products of one size run on the same side.
+static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, int* shape) {
+    if (g_forced_variant >= 0) return false;
+    const double fixed[3] = {5.29, 5.68, 3.36}, per_stage[3] = {0.533, 0.495, 0.240}, per_round[3] = {2.33, 0.0, 1.18},
+                 per_fill[3] = {12.7, 5.06, 4.16};
+    const int64_t bm[3] = {256, 128, 128}, bn[3] = {256, 256, 128}, cus = stream_blocks();
+    double streaming = 0.0;
+    for (int p = 0; p < products; ++p) {
+        const int v = pick_variant(m[p], n[p], 0, 1u);
+        const int64_t tiles = ((m[p] + bm[v] - 1) / bm[v]) * ((n[p] + bn[v] - 1) / bn[v]), rounds = (tiles + cus - 1) / cus;
+        int64_t stages = (k[p] + 255) / 256 * 2;
+        if (stages < 2) stages = 2;
+        streaming += (p == 0 ? fixed[v] : 0.0) + (double)rounds * (per_stage[v] * (double)stages + per_round[v]) +
+                     per_fill[v] * (double)tiles / (double)cus;
+    }
+    return best_split_shape(products, m, n, k, (int)cus, shape) < (products == 1 ? 0.9 : 0.6) * streaming;
+}
+
 hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes,
                        const uint8_t* b_scales, int64_t m, int64_t n, int64_t k, float alpha, void* d,
                        int d_bf16, int64_t ldd, int fused, const uint32_t* mask, uint32_t nb, hipStream_t st) {
     if (m == 0 || n == 0) return hipSuccess;
+    int shape = 0;
+    if (use_split(1, &m, &n, &k, &shape)) {
+        const GemmArgs g = {a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask};
+        return launch_gemm_split(g, nullptr, d_bf16, fused, nb, shape, st);
+    }
     const int variant = pick_variant(m, n, fused, nb);
 #define QUARTET_DISPATCH(FN, ...)                                                                     \
     do {                                                                                              \
@@ -721,6 +752,9 @@ hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_b
         return launch_gemm(g1.a_codes, g1.a_scales, g1.b_codes, g1.b_scales, g1.m, g1.n, g1.k, g1.alpha, g1.d, d_bf16, g1.ldd, 1,
                            g1.mask, nb, st);
     }
+    const int64_t ms[2] = {g0.m, g1.m}, ns[2] = {g0.n, g1.n}, ks[2] = {g0.k, g1.k};
+    int shape = 0;
+    if (use_split(2, ms, ns, ks, &shape)) return launch_gemm_split(g0, &g1, d_bf16, 1, nb, shape, st);
     const int64_t bm[3] = {256, 128, 128}, bn[3] = {256, 256, 128};
     int variant = g_forced_variant;
     if (variant < 0) {

@@ -48,6 +48,10 @@ struct GemmArgs {
     int64_t ldd;
     const uint32_t* mask;
 };
+// In-block split of the inner dimension over small tiles (gemm_split_kernels.hip).  best_split_shape: estimated time in us of one
+// launch for the given products on the best of its tile shapes; launch_gemm_split: g1 = a second product in the same launch, or null.
+double best_split_shape(int products, const int64_t* m, const int64_t* n, const int64_t* k, int compute_units, int* shape);
+hipError_t launch_gemm_split(const GemmArgs& g0, const GemmArgs* g1, int d_bf16, int fused, uint32_t nb, int shape, hipStream_t st);
 hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_bf16, uint32_t nb, hipStream_t st);
 // variant: -1 = size heuristic, 0..2 = force that tile shape (256x256, 128x256, 128x128); band_height: 0 = heuristic, > 0 = tile rows per band
 void set_gemm_plan(int variant, int band_height);

@@ -1,12 +1,15 @@
-"""Build the HIP library (paper_2505_14669_amd/libquartet.so) for gfx950 with hipcc."""
+"""Build the HIP library (paper_2505_14669_amd/libquartet.so) for gfx950 with hipcc and, on top of it, the autograd node of
+the torch layer (paper_2505_14669_amd/_nn_native.so) with g++."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libquartet.so")
+NN_LIB = os.path.join(HERE, "_nn_native.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "quant_kernels.hip", "gemm_kernels.hip", "gemm_split_kernels.hip", "epilogue_kernels.hip", "fp8_kernels.hip", "probe_kernels.hip"]
 
@@ -27,16 +30,38 @@ def _compile(src):
     return obj, out
 
 
+def _compile_nn():
+    """nn_autograd.cpp -> object file: host code against the installed torch's headers."""
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    obj = os.path.join(OBJDIR, "nn_autograd.o")
+    dirs = include_paths(device_type="cuda") + ["/opt/rocm/include", sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for d in dirs:
+        cmd += ["-isystem", d]
+    r = subprocess.run(cmd + ["-c", os.path.join(CSRC, "nn_autograd.cpp"), "-o", obj], stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on nn_autograd.cpp:\n{r.stdout}")
+    return obj, os.path.join(os.path.dirname(torch.__file__), "lib")
+
+
 def build(verbose=False):
     os.makedirs(OBJDIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=5) as ex:
+        nn = ex.submit(_compile_nn)
         results = list(ex.map(_compile, SOURCES))
+        nn_obj, torch_lib = nn.result()
     if verbose:
         for _, out in results:
             if out.strip():
                 print(out)
     objs = [o for o, _ in results]
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, check=True)
+    # the torch libraries are in the process already when this is imported; libquartet.so lies beside it
+    subprocess.run(["g++", "-shared", "-o", NN_LIB, nn_obj, "-L" + HERE, "-l:libquartet.so", "-L" + torch_lib, "-ltorch_python",
+                    "-ltorch_cpu", "-ltorch_hip", "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"], check=True)
     return LIB
 
 

@@ -1,0 +1,168 @@
+// The linear layer's autograd node in native code: what nn.QuartetLinearFunction.apply runs.  Argument checks, output and context
+// allocation, the two C ABI calls (quartet_linear_fwd_block, quartet_linear_bwd_block) and the graph edge; no arithmetic.
+//
+// Why native: a step of a small layer is bound by the host.  As a Python autograd function the step of a 288 x 320 x 352 layer
+// took 163-170 us of host time for 17 us of GPU work: seven output tensors, two crossings into Python, and a backward pass
+// that has to take the interpreter lock on the engine's own thread.  Here the forward context is one allocation and the
+// backward pass never enters Python.
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <c10/core/DeviceGuard.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/functions/utils.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/autograd/saved_variable.h>
+
+#include "../../include/quartet.h"
+
+namespace {
+
+using torch::autograd::Node;
+using torch::autograd::variable_list;
+
+PyObject* g_error = nullptr;   // binding.QuartetError
+
+[[noreturn]] void raise_python(PyObject* type, const std::string& text) {
+    pybind11::gil_scoped_acquire gil;
+    PyErr_SetString(type, text.c_str());
+    python_error e;
+    e.persist();
+    throw e;
+}
+
+void check(int rc) {
+    if (rc == QUARTET_OK) return;
+    std::string text = rc == QUARTET_EINVAL ? "QUARTET_EINVAL" : rc == QUARTET_ENOTSUP ? "QUARTET_ENOTSUP" : "QUARTET_EHIP";
+    if (rc == QUARTET_EHIP) text += " (hipError_t " + std::to_string(quartet_last_hip_error()) + ")";
+    raise_python(g_error, text);
+}
+
+// The forward context {X_q, M_x, W_q, M_w} as byte ranges of one buffer.
+struct Context {
+    size_t x_codes, x_scales, x_mask, w_codes, w_scales, w_mask, total;
+    Context(int64_t tokens, int64_t in, int64_t out) {
+        size_t at = 0;
+        auto take = [&](size_t bytes) { const size_t here = at; at += (bytes + 255) & ~(size_t)255; return here; };
+        x_codes = take((size_t)(tokens * in) / 2);
+        x_scales = take(quartet_scale_bytes(tokens, in));
+        x_mask = take((size_t)(tokens * in) / 8);
+        w_codes = take((size_t)(out * in) / 2);
+        w_scales = take(quartet_scale_bytes(out, in));
+        w_mask = take((size_t)(out * in) / 8);
+        total = at < 256 ? 256 : at;
+    }
+};
+
+uint8_t* bytes_of(const at::Tensor& t) { return static_cast<uint8_t*>(t.data_ptr()); }
+void* stream_of(const at::Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
+
+struct QuartetLinearBackward : public Node {
+    torch::autograd::SavedVariable context;
+    std::vector<int64_t> x_sizes;
+    int64_t tokens, in, out;
+    int hadamard_block, rounding;
+    uint64_t seed;
+
+    std::string name() const override { return "QuartetLinearFunctionBackward"; }
+    void release_variables() override { context.reset_data(); }
+
+    variable_list apply(variable_list&& grads) override {
+        at::NoGradGuard no_grad;
+        const at::Tensor ctx = context.unpack(shared_from_this());
+        c10::DeviceGuard device(ctx.device());
+        const auto bf16 = ctx.options().dtype(at::kBFloat16);
+        const at::Tensor dy = grads[0].defined() ? grads[0].reshape({tokens, out}).to(at::kBFloat16).contiguous() : at::zeros({tokens, out}, bf16);
+        at::Tensor dx = at::empty(x_sizes, bf16), dw = at::empty({out, in}, bf16);
+        const size_t nbytes = quartet_linear_workspace_bytes_block(tokens, in, out, hadamard_block);
+        // from the caching allocator, so calls on several streams or threads never share it
+        const at::Tensor ws = at::empty({(int64_t)(nbytes < 256 ? 256 : nbytes)}, ctx.options());
+        const Context c(tokens, in, out);
+        const uint8_t* b = bytes_of(ctx);
+        check(quartet_linear_bwd_block(dy.data_ptr(), tokens, in, out, hadamard_block, b + c.x_codes, b + c.x_scales,
+                                       reinterpret_cast<const uint32_t*>(b + c.x_mask), b + c.w_codes, b + c.w_scales,
+                                       reinterpret_cast<const uint32_t*>(b + c.w_mask), seed, rounding, dx.data_ptr(), dw.data_ptr(),
+                                       QUARTET_DTYPE_BF16, ws.data_ptr(), nbytes, stream_of(ctx)));
+        return {dx, dw};
+    }
+};
+
+at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, int rounding, int hadamard_block) {
+    if (x.scalar_type() != at::kBFloat16 || weight.scalar_type() != at::kBFloat16)
+        raise_python(PyExc_TypeError, "QuartetLinearFunction takes bf16 activations and weights");
+    if (!x.is_cuda() || !weight.is_cuda()) raise_python(PyExc_RuntimeError, "QuartetLinearFunction runs on the GPU only");
+    if (weight.dim() != 2) raise_python(PyExc_ValueError, "weight must be a matrix [out_features, in_features]");
+    const int64_t out = weight.size(0), in = weight.size(1);
+    if (x.dim() < 1 || x.size(-1) != in)
+        raise_python(PyExc_RuntimeError, "the last dimension of the activations must be in_features = " + std::to_string(in));
+    if (hadamard_block != 32 && hadamard_block != 64 && hadamard_block != 128 && hadamard_block != 256)
+        raise_python(PyExc_ValueError, "hadamard_block must be 32, 64, 128 or 256");
+    const int64_t tokens = in ? x.numel() / in : 0;
+    if (tokens % hadamard_block || in % hadamard_block || out % hadamard_block)
+        raise_python(PyExc_ValueError, "tokens, in_features and out_features must be multiples of " + std::to_string(hadamard_block));
+    const bool track = torch::autograd::compute_requires_grad(x, weight);
+    at::Tensor y, ctx;
+    {
+        at::AutoDispatchBelowADInplaceOrView below_autograd;
+        c10::DeviceGuard device(x.device());
+        const at::Tensor x2 = x.contiguous(), w2 = weight.contiguous();
+        std::vector<int64_t> y_sizes = x.sizes().vec();
+        y_sizes.back() = out;
+        y = at::empty(y_sizes, x.options());
+        const Context c(tokens, in, out);
+        ctx = at::empty({(int64_t)c.total}, x.options().dtype(at::kByte));
+        uint8_t* b = bytes_of(ctx);
+        check(quartet_linear_fwd_block(x2.data_ptr(), w2.data_ptr(), tokens, in, out, hadamard_block, y.data_ptr(), QUARTET_DTYPE_BF16,
+                                       b + c.x_codes, b + c.x_scales, reinterpret_cast<uint32_t*>(b + c.x_mask), b + c.w_codes,
+                                       b + c.w_scales, reinterpret_cast<uint32_t*>(b + c.w_mask), stream_of(x)));
+    }
+    if (track) {
+        auto node = std::shared_ptr<QuartetLinearBackward>(new QuartetLinearBackward(), torch::autograd::deleteNode);
+        node->set_next_edges(torch::autograd::collect_next_edges(x, weight));
+        node->context = torch::autograd::SavedVariable(ctx, false);
+        node->x_sizes = x.sizes().vec();
+        node->tokens = tokens; node->in = in; node->out = out;
+        node->hadamard_block = hadamard_block; node->rounding = rounding; node->seed = seed;
+        torch::autograd::set_history(y, node);
+    }
+    return y;
+}
+
+// linear(x, weight, seed, rounding, hadamard_block)
+PyObject* py_linear(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    if (n != 5 || !THPVariable_Check(args[0]) || !THPVariable_Check(args[1])) {
+        PyErr_SetString(PyExc_TypeError, "linear(x, weight, seed, rounding, hadamard_block): two tensors and three integers");
+        return nullptr;
+    }
+    const uint64_t seed = PyLong_AsUnsignedLongLongMask(args[2]);
+    const long rounding = PyLong_AsLong(args[3]), block = PyLong_AsLong(args[4]);
+    if (PyErr_Occurred()) return nullptr;
+    const at::Tensor x = THPVariable_Unpack(args[0]), w = THPVariable_Unpack(args[1]);
+    at::Tensor y;
+    {
+        pybind11::gil_scoped_release no_gil;
+        y = linear(x, w, seed, (int)rounding, (int)block);
+    }
+    return THPVariable_Wrap(std::move(y));
+    END_HANDLE_TH_ERRORS
+}
+
+PyObject* py_set_error(PyObject*, PyObject* type) {
+    Py_INCREF(type);
+    Py_XDECREF(g_error);
+    g_error = type;
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {
+    {"linear", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(py_linear)), METH_FASTCALL, nullptr},
+    {"set_error", py_set_error, METH_O, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_nn_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__nn_native(void) { return PyModule_Create(&module_def); }

@@ -1,0 +1,72 @@
+"""The native autograd node of the torch layer: gradients asked for one by one, graph freed after use, non-contiguous
+inputs, no graph without gradients, calls on two streams at once."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def qnn():
+    import paper_2505_14669_amd.nn as nn
+    return nn
+
+
+def _case(seed, t=96, i=64, o=160):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return [torch.randn(s, generator=g, device=DEV).to(torch.bfloat16) for s in ((t, i), (o, i), (t, o))]
+
+
+def _grads(qnn, x, w, dy, seed=9):
+    x, w = x.clone().requires_grad_(True), w.clone().requires_grad_(True)
+    y = qnn.QuartetLinearFunction.apply(x, w, seed, 0)
+    y.backward(dy)
+    return y.detach(), x.grad, w.grad
+
+
+@pytest.mark.parametrize("need", [(True, False), (False, True)])
+def test_one_gradient_only(qnn, need):
+    x, w, dy = _case(1)
+    _, dx, dw = _grads(qnn, x, w, dy)
+    x, w = x.clone().requires_grad_(need[0]), w.clone().requires_grad_(need[1])
+    qnn.QuartetLinearFunction.apply(x, w, 9, 0).backward(dy)
+    assert (x.grad is None) == (not need[0]) and (w.grad is None) == (not need[1])
+    assert torch.equal(x.grad, dx) if need[0] else torch.equal(w.grad, dw)
+
+
+def test_graph_is_freed_and_absent_without_gradients(qnn):
+    x, w, dy = _case(2)
+    x.requires_grad_(True)
+    y = qnn.QuartetLinearFunction.apply(x, w, 3, 1)
+    y.backward(dy)
+    with pytest.raises(RuntimeError):
+        y.backward(dy)
+    with torch.no_grad():
+        z = qnn.QuartetLinearFunction.apply(x, w, 3, 1)
+    assert z.grad_fn is None and torch.equal(z, y)
+
+
+def test_non_contiguous_inputs_and_gradient(qnn):
+    x, w, dy = _case(3, 128, 96, 96)
+    y0, dx0, dw0 = _grads(qnn, x, w, dy)
+    xt, wt = x.t().contiguous().t().requires_grad_(True), w.t().contiguous().t().requires_grad_(True)
+    y = qnn.QuartetLinearFunction.apply(xt, wt, 9, 0)
+    y.backward(dy.t().contiguous().t())
+    assert torch.equal(y, y0) and torch.equal(xt.grad, dx0) and torch.equal(wt.grad, dw0)
+
+
+def test_two_streams_do_not_share_scratch(qnn):
+    cases = [_case(10 + s, 2048, 1024, 1024) for s in range(2)]
+    want = [_grads(qnn, *c) for c in cases]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in cases]
+    got = [None, None]
+    for _ in range(4):
+        for s, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                got[s] = _grads(qnn, *cases[s])
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        assert all(torch.equal(a, b) for a, b in zip(g, w))

@@ -485,8 +485,10 @@ __device__ __forceinline__ void quant_columns_block(const uint16_t* __restrict__
 // 128-byte lines of the same output rows (10 % faster than column-tile first).
 __device__ __forceinline__ uint32_t transposed_column_tile(uint32_t bx, uint32_t by, uint32_t n_ct) { return (by + bx) % n_ct; }
 
+// Stochastic: scheduled for two to three waves per SIMD (16384 x 11008: 87.0 us, scheduled for three alone 88.6); nearest: four.
 template <int MODE, bool MASK>
-__global__ void __launch_bounds__(256, MODE == kBwdSr ? 3 : 4)
+__attribute__((amdgpu_waves_per_eu(MODE == kBwdSr ? 2 : 4, MODE == kBwdSr ? 3 : 8)))
+__global__ void __launch_bounds__(256)
 quant_transposed_kernel(const uint16_t* __restrict__ src,
                         uint32_t rows, uint32_t k, int64_t ldx, uint8_t* __restrict__ codes,
                         uint8_t* __restrict__ scales, uint32_t* __restrict__ mask, SrParams p) {

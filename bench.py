@@ -284,7 +284,7 @@ def lower_bound_ms(layers):
 
 def mfma_ceiling(q, torch, layer, cus, wall_khz):
     """What the bare matrix-core instruction sustains on this machine right now: the library's register-only loop of
-    v_mfma_scale_f32_32x32x64_f8f6f4 (one block of 4 waves per compute unit) on the first 32 KiB of the first layer's
+    v_mfma_scale_f32_16x16x128_f8f6f4 (one block of 4 waves per compute unit) on the first 32 KiB of the first layer's
     quantized activations and 8 KiB of their scale bytes, timed by events on the current stream; the shader clock it
     held comes from the kernel's own clock counters."""
     codes = layer.xq_codes.reshape(-1)[:32768].contiguous()
@@ -300,7 +300,7 @@ def mfma_ceiling(q, torch, layer, cus, wall_khz):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
     c = ctr.cpu().tolist()
-    flop = cus * 4.0 * iters * 16 * 2 * 32 * 32 * 64
+    flop = cus * 4.0 * iters * 32 * 2 * 16 * 16 * 128
     return {"TFLOPs": round(flop / ms / 1e9, 1), "ms": round(ms, 2), "blocks": cus, "iterations": iters,
             "clock_ghz": round(c[0] / c[1] * wall_khz / 1e6, 3) if c[1] > 0 and wall_khz > 0 else None,
             "what": "register-only loop of the GEMM's matrix-core instruction on this run's quantized activations: "

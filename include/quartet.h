@@ -99,10 +99,10 @@ int quartet_profile_read(int *kinds, float *ms, int capacity);
  * c[0] / c[1] * quartet_wall_clock_khz() is the shader clock in kHz the chip held under that kernel.  8-byte
  * aligned; process-global, not thread-safe.
  * quartet_wall_clock_khz(): rate of the device's constant clock in kHz (negative: error).
- * quartet_probe_mfma_ceiling: launches `blocks` blocks of 4 waves that each run `iterations` rounds of the 16
- * v_mfma_scale_f32_32x32x64_f8f6f4 instructions of one K-step of the GEMM's 128 x 128 wave tile on operands held in
+ * quartet_probe_mfma_ceiling: launches `blocks` blocks of 4 waves that each run `iterations` rounds of 32
+ * v_mfma_scale_f32_16x16x128_f8f6f4 instructions (half a K-step of the GEMM's 128 x 128 wave tile) on operands held in
  * registers (no LDS or memory traffic inside the loop):
- * blocks * 4 * iterations * 16 * 2 * 32 * 32 * 64 flop.  codes: 32768 device bytes (8 fragments x 256 lanes x 16 B,
+ * blocks * 4 * iterations * 32 * 2 * 16 * 16 * 128 flop.  codes: 32768 device bytes (8 fragments x 256 lanes x 16 B,
  * any E2M1 codes: the rate depends on the data, so pass quantized tensors of the workload), scales: 8192 device
  * bytes (8 x 256 dwords of E8M0 bytes), sink: blocks * 256 floats the kernel writes once at its end,
  * device_counters as for quartet_profile_clock or NULL.  The caller times the launch with events on `stream`.

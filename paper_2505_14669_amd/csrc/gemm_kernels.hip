@@ -1,21 +1,29 @@
 // MXFP4 x MXFP4 -> fp32 GEMM on the gfx950 block-scaled matrix cores (Section 4.4, "Stage 2":
 // D = (A x SFA)(B x SFB)^T with one E8M0 scale per 32 elements along K).
 //
-// v_mfma_scale_f32_32x32x64_f8f6f4 operand layout (FP4, cbsz = blgp = 4), measured on gfx950:
-//   A: lane l holds row l%32, K-elements 32*(l/32) .. +31 as 128 bits, element j in bits [4j,4j+4)
+// v_mfma_scale_f32_16x16x128_f8f6f4 operand layout (FP4, cbsz = blgp = 4), measured on gfx950:
+//   A: lane l holds row l%16, K-elements 32*(l/16) .. +31 as 128 bits, element j in bits [4j,4j+4)
 //      -- exactly the packed row-major code bytes, so a fragment is one 16-byte LDS read;
 //   B: the same with the output column in place of the row;
 //   scale: one byte per lane (selected by op_sel from a 32-bit register) = the E8M0 scale of that
 //      lane's 32 K-elements, i.e. one MX group per lane per instruction;
-//   D: lane l, register r -> row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+//   D: lane l, register r -> row 4*(l/16) + r, column l%16.
+// Why 16 x 16 x 128 and not 32 x 32 x 64 (same rate, same operand bytes per wave tile): the chip is power-limited under FP4 matrix
+// work, and the deeper instruction reads and writes each fp32 accumulator once per 128 K-elements instead of once per 64.
+// Registers only, quantized normal data, 128 x 128 wave tiles: 7.09 PFLOP/s at 1.79 GHz against 6.38 at 1.59 GHz; both give the same bits (compared over 25 binades of scales).
 // The tiled scale layout (see scale_tile_offset) stores, for each block of 32 rows and 256
-// K-elements, one dword per lane whose four bytes are that lane's scales for the four K=64 steps,
-// so a wave's scale fragment is one coalesced 256-byte global load and the paper's separate
-// scale-rearrangement step does not exist here.
+// K-elements, dword 32 h + row with the scales of groups h, 2 + h, 4 + h, 6 + h: lane l reads the dword of its row and h =
+// (l/16) % 2 once per K-quad (128 contiguous bytes twice per wave), and its group of the quad's first and second K-step is byte
+// l/32 and byte 2 + l/32; the paper's separate scale-rearrangement step does not exist here.
 //
 // Kernels: gemm_mxfp4_stream_kernel (256 x 256 tiles) and gemm_mxfp4_stream_tile_kernel (128 x 256 and 128 x 128 tiles
-// for small problems): one block per compute unit streams its tiles through a ring of LDS stages.  Both work
+// for small problems): one block per compute unit streams its tiles through a ring of K-quads (256 elements) in LDS.  Both work
 // through a batch of one or two products per launch (GemmBatch).
+// What bounds them besides power is the way of the operands into the LDS: a cache line is 128 bytes, so a ring of 128-element
+// stages (64 bytes of codes per row) fetched every line twice.  K-quads, whole lines, one barrier per quad and reads and loads spread
+// evenly over the matrix-core instructions took, against that design with 32 x 32 x 64 instructions (layer steps, us): 16384 x
+// 4096 x 11008 1419 -> 1366, 16384 x 4096 x 4096 614 -> 595, 8192 x 5632 x 2048 269 -> 259, 2336 x 1376 x 3168 78.1 -> 73.5,
+// 4096 x 2048 x 2048 88.8 -> 86.8, forward 1003 x 2048 x 5632 25.4 -> 24.8.  (16 x 16 x 128 instructions on the old stages: 0-4 % slower.)
 #include "gemm_common.h"
 #include "launchers.h"
 
@@ -54,11 +62,12 @@ struct GemmBatch {
     GemmProblem p[2];
 };
 
-template <int S>
-__device__ __forceinline__ v16f mfma_fp4(const uint4& a, const uint4& b, v16f c, uint32_t sa, uint32_t sb) {
-    v8i va = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
-    v8i vb = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, vb, c, 4, 4, S, (int)sa, S, (int)sb);
+// Byte selector that turns a lane's raw scale dword of a K-quad (with 0x7F7F7F7F as the other source of v_perm_b32) into its scale
+// operand: byte 0 for the quad's first K-step, byte 2 for its second.  group0: the quad's first group; groups from gk on do not
+// exist, their codes are zero and their scale is 2^0.
+__device__ __forceinline__ uint32_t scale_selector(uint32_t lane, uint32_t group0, uint32_t gk) {
+    const uint32_t hi = lane >> 5, g = group0 + (lane >> 4);
+    return (g < gk ? hi : 4u) | ((g + 4u < gk ? 2u + hi : 4u) << 16);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -70,11 +79,10 @@ template <bool OUT_BF16, bool FUSED>
 __global__ void __launch_bounds__(256)
 gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t TM = 4, TN = 4, BM = 256, BN = 256;
-    constexpr uint32_t CODES = (BM + BN) * 4;            // 16-byte chunks of codes per stage
-    constexpr uint32_t STAGE = CODES + 256;              // + 16 scale tiles of 256 B
-    constexpr uint32_t D = kRing - 1;                    // prefetch distance in stages
+    constexpr uint32_t CODES = (BM + BN) * 8;            // 16-byte chunks of codes per K-quad
+    constexpr uint32_t QUAD = CODES + 256;               // + 16 scale tiles of 256 B
     constexpr uint32_t EPI = 4u * 256u;                  // 16-byte chunks of epilogue scratch (4 KB per wave)
-    __shared__ uint4 lds[kRing * STAGE + EPI];
+    __shared__ v4i_t lds[2u * QUAD + EPI];
 
     // measurement support: shader-clock and constant-clock ticks of this block's run (wave-uniform branch)
     uint64_t clk_t0 = 0, clk_w0 = 0;
@@ -85,7 +93,7 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t lrow = lane & 31u, lhalf = lane >> 5;
+    const uint32_t l16 = lane & 15u, quarter = lane >> 4;
     const uint32_t G = gridDim.x, first_tiles = batch.p[0].total_tiles;
     const uint32_t wm0 = (wave >> 1) * 128u, wn0 = (wave & 1u) * 128u;
     const bool scales_of_a = wave < 2u;
@@ -115,34 +123,35 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
             M0 = (Q).m; N0 = (Q).n;                                                                     \
         }                                                                                               \
     }
-    // issue cursor: the tile and stage the next LDS-direct loads belong to
-    // (its product's inner dimension decides the offsets: kb = bytes per code row, kq = K-quads, S2i = stages per tile)
+    // issue cursor: the tile and K-quad the next LDS-direct loads belong to
+    // (its product's inner dimension decides the offsets: kb = bytes per code row, kq = K-quads per tile)
     // A tile does not start at K = 0: the tiles of XCD class c (tile number mod 8; an XCD's compute units hold tiles of
     // one class at a time and must stay in step to share panels in their L2) start c/8 of the way along K, in whole K-quads,
-    // and wrap around: ikst is the K-stage the cursor's local stage ist stands for.  Otherwise every compute unit of the
+    // and wrap around: ikq is the K-quad the cursor's local quad iq stands for.  Otherwise every compute unit of the
     // chip asks for the same few hundred bytes of its operand rows at the same time, and with a row pitch of a few KB the
     // memory channels behind the L2s serve that unevenly (measured: 1-2 % of the K = 4096 products' time).  fp32 sums are
     // formed in a rotated order then, the same for a tile wherever it runs.  Only for K a multiple of 256: a ragged last
     // K-quad keeps its place at the end.
-    uint32_t iv = blockIdx.x, ist = 0u;
+    // A load instruction brings 8 rows x 128 bytes (whole cache lines: with 16 rows x 64 bytes every line crosses from the L2 twice).
+    uint32_t iv = blockIdx.x, iq = 0u;
     v4i_t res_a, res_b, res_s;
-    uint32_t kb, istages, S2i, goff, gstep, soff, ikst;
-    const uint32_t drow = wave * 16u + (lane >> 2);
-    const uint32_t dcol = (lane & 3u) ^ ((drow >> 2) & 3u);
+    uint32_t kb, kq, goff, gstep, soff, ikq;
+    const uint32_t drow = wave * 8u + (lane >> 3);
+    const uint32_t dcol = (lane & 7u) ^ ((drow >> 1) & 7u);
 #define STREAM_ISSUE_SETUP()                                                                            \
     {                                                                                                   \
         uint32_t sel_, lv_, m0_, n0_;                                                                   \
         STREAM_PRODUCT(iv, sel_, lv_)                                                                   \
         const GemmProblem& q_ = batch.p[sel_];                                                          \
         STREAM_TILE(q_, lv_, m0_, n0_)                                                                  \
-        const uint32_t k_ = q_.k, kq_ = (k_ + 255u) >> 8;                                               \
+        const uint32_t k_ = q_.k;                                                                       \
+        const uint32_t kq_ = (k_ + 255u) >> 8;  /* scale tiles per 32 rows */                           \
+        kq = kq_ ? kq_ : 1u;                                                                            \
         kb = k_ >> 1;                                                                                   \
-        istages = (k_ + 127u) >> 7;                                                                     \
-        S2i = istages < 2u ? 2u : ((istages + 1u) & ~1u);                                               \
-        ikst = ((k_ & 255u) == 0u) ? (((lv_ & 7u) * (S2i >> 1)) >> 3) * 2u : 0u;                        \
-        goff = drow * kb + dcol * 16u;          /* + j*64*kb, + stage*64 */                             \
-        gstep = 64u * kb;                                                                               \
-        soff = (((wave & 1u) * 4u + (lane >> 4)) * kq_) * 256u + (lane & 15u) * 16u;   /* + quad*256 */ \
+        ikq = ((k_ & 255u) == 0u) ? ((lv_ & 7u) * kq) >> 3 : 0u;                                        \
+        goff = drow * kb + dcol * 16u;          /* + j*32*kb, + quad*128 */                             \
+        gstep = 32u * kb;                                                                               \
+        soff = (((wave & 1u) * 4u + (lane >> 4)) * kq_) * 256u + (lane & 15u) * 16u;    /* + quad*256 */ \
         const uint32_t rows_a_ = (q_.m - m0_) < BM ? (q_.m - m0_) : BM, rows_b_ = (q_.n - n0_) < BN ? (q_.n - n0_) : BN; \
         res_a = make_rsrc_words(q_.a_codes + (size_t)m0_ * kb, rows_a_ * kb);                           \
         res_b = make_rsrc_words(q_.b_codes + (size_t)n0_ * kb, rows_b_ * kb);                           \
@@ -153,154 +162,163 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
     STREAM_ISSUE_SETUP()
 
     const uint32_t lds0 = (uint32_t)(size_t)(lds_ptr_t)&lds[0];
-    const uint32_t swz = (lrow >> 2) & 3u;
-    const uint32_t fa_base = (wm0 + lrow) * 4u, fb_base = BM * 4u + (wn0 + lrow) * 4u;
-    const uint32_t sa_base = CODES * 4u + (wm0 >> 5) * 64u + lane;             // dword index in a stage
-    const uint32_t sb_base = CODES * 4u + 8u * 64u + (wn0 >> 5) * 64u + lane;
+    // the lane's 16-byte chunk of a 128-byte code row in the quad's first and second K-step (chunk c of row r lies at c ^ (r/2)%8)
+    const uint32_t chunk0 = quarter ^ (l16 >> 1), chunk1 = chunk0 ^ 4u;
+    const uint32_t fa_pos0 = ((wm0 + l16) * 8u + chunk0) * 16u, fb_pos0 = ((BM + wn0 + l16) * 8u + chunk0) * 16u;
+    const uint32_t fa_pos1 = ((wm0 + l16) * 8u + chunk1) * 16u, fb_pos1 = ((BM + wn0 + l16) * 8u + chunk1) * 16u;
+    const uint8_t* lds_bytes = reinterpret_cast<const uint8_t*>(lds);
+    const uint32_t srow = (quarter & 1u) * 32u + l16;
+    const uint32_t sa_pos = CODES * 16u + ((wm0 >> 5) * 64u + srow) * 4u, sb_pos = CODES * 16u + ((8u + (wn0 >> 5)) * 64u + srow) * 4u;
+    const uint32_t sel_full = scale_selector(lane, 0u, 8u);
 
-    uint32_t sa[TM], sb[TN], ra_n[TM], rb_n[TN];
-    uint4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
+    // fragments: the wave's 8 row blocks of A and 8 column blocks of B, 16 x 128 elements each, of a quad's first and second K-step
+    uint32_t sa[2 * TM], sb[2 * TN], ra_n[2 * TM], rb_n[2 * TN];
+    v4i_t fa0[2 * TM], fb0[2 * TN], fa1[2 * TM], fb1[2 * TN];
 
-// load J (0..3: A rows, 4..7: B rows, 8: scale tiles) of the issue cursor's stage into ring slot SLOT
+// load J (0..7: A rows, 8..15: B rows, 16: scale tiles) of the issue cursor's quad into ring slot SLOT
 #define STREAM_ISSUE(SLOT, J)                                                                           \
     {                                                                                                   \
-        const uint32_t slot_ = lds0 + ((SLOT) * STAGE + wave * 64u) * 16u;                              \
-        if ((J) < 8u) {                                                                                 \
-            const uint32_t base_ = (ikst * 64u + dcol * 16u < kb) ? goff + ikst * 64u : kOutOfRange;      \
-            lds_direct_load16((J) < 4u ? res_a : res_b, base_ + ((J) & 3u) * gstep, slot_ + (J) * 4096u); \
+        const uint32_t slot_ = lds0 + ((SLOT) * QUAD + wave * 64u) * 16u;                               \
+        if ((J) < 16u) {                                                                                \
+            const uint32_t base_ = (ikq * 128u + dcol * 16u < kb) ? goff + ikq * 128u : kOutOfRange;    \
+            lds_direct_load16((J) < 8u ? res_a : res_b, base_ + ((J) & 7u) * gstep, slot_ + (J) * 4096u); \
         } else {                                                                                        \
-            lds_direct_load16(res_s, (ikst < istages) ? soff + (ikst >> 1) * 256u : kOutOfRange, slot_ + CODES * 16u); \
+            lds_direct_load16(res_s, soff + ikq * 256u, slot_ + CODES * 16u);                           \
         }                                                                                               \
     }
-// the stage is issued: move the cursor on (to the next tile of this block after the tile's last stage)
+// the quad is issued: move the cursor on (to the next tile of this block after the tile's last quad)
 #define STREAM_ISSUE_ADVANCE()                                                                          \
     {                                                                                                   \
-        ++ist;                                                                                          \
-        ++ikst;                                                                                         \
-        if (ikst == S2i) ikst = 0u;                                                                     \
-        if (ist == S2i) {                                                                               \
-            ist = 0u;                                                                                   \
+        ++iq;                                                                                           \
+        ++ikq;                                                                                          \
+        if (ikq == kq) ikq = 0u;                                                                        \
+        if (iq == kq) {                                                                                 \
+            iq = 0u;                                                                                    \
             iv += G;                                                                                    \
             STREAM_ISSUE_SETUP()                                                                        \
         }                                                                                               \
     }
-#define STREAM_FRAG_A(SLOT, S, FA, I) FA[I] = lds[(SLOT) * STAGE + fa_base + (I) * 128u + ((2u * (S) + lhalf) ^ swz)];
-#define STREAM_FRAG_B(SLOT, S, FB, J) FB[J] = lds[(SLOT) * STAGE + fb_base + (J) * 128u + ((2u * (S) + lhalf) ^ swz)];
+// LDS positions of the lane's part of the first fragments and scales in ring slot SLOT, kept in one register each (the rest is
+// immediate offsets; left to itself the compiler forms an address per read)
+#define STREAM_AT(NAME, SLOT, POS) uint32_t NAME = (SLOT) * QUAD * 16u + (POS); asm volatile("" : "+v"(NAME));
+// fragment R of a K-step in the order the instructions need them: A 0, B 0..7, A 1..7
+#define STREAM_FRAG(FA, FB, AT_A, AT_B, R)                                                              \
+    {                                                                                                   \
+        if ((R) >= 1u && (R) <= 8u) FB[((R) + 7u) & 7u] = *reinterpret_cast<const v4i_t*>(lds_bytes + (AT_B) + (((R) + 7u) & 7u) * 2048u); \
+        else FA[((R) + 8u) & 7u] = *reinterpret_cast<const v4i_t*>(lds_bytes + (AT_A) + (((R) + 8u) & 7u) * 2048u); \
+    }
 #define STREAM_FENCE() __builtin_amdgcn_sched_barrier(0);
 
-    constexpr uint32_t KEEP2 = 17u;                    // loads of one even and one odd stage stay in flight
-    constexpr uint32_t WAIT2 = 0x0F70u | (KEEP2 & 15u) | ((KEEP2 >> 4) << 14);
+    constexpr uint32_t DRAIN = 0x0070u;                // every LDS-direct load has landed and no LDS read is outstanding
+    constexpr uint32_t DRAIN_BUT_STORES = 0xC07Fu;     // the same when 64 younger stores are on their way (63 operations may be left)
 #pragma unroll
-    for (uint32_t s0 = 0; s0 < D; ++s0) {
-#pragma unroll
-        for (uint32_t j = 0; j < 8u; ++j) STREAM_ISSUE(s0, j)
-        if ((s0 & 1u) == 0u) STREAM_ISSUE(s0, 8u)
-        STREAM_ISSUE_ADVANCE()
-    }
-    __builtin_amdgcn_s_waitcnt(WAIT2);
+    for (uint32_t j = 0; j < 17u; ++j) STREAM_ISSUE(0u, j)
+    STREAM_ISSUE_ADVANCE()
+    __builtin_amdgcn_s_waitcnt(DRAIN);
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (uint32_t i = 0; i < TM; ++i) { STREAM_FRAG_A(0u, 0u, fa0, i) STREAM_FRAG_B(0u, 0u, fb0, i) }
-// Scale dwords of a K-quad, in two steps a few hundred cycles apart: the raw dwords are read from ring slot SLOT right
-// behind the barrier that makes them visible, and turned into the operands of the next pair of stages (the K-quad that
-// starts with the even local stage ST of a tile whose product has GK groups along K; bytes of groups past GK become 2^0)
-// only behind the current pair's last matrix-core instruction.  Used at once, the reads made the wave wait for every LDS
-// read in flight at the end of each odd stage.
-#define STREAM_SCALES_READ(SLOT)                                                                        \
+    for (uint32_t j = 0; j < 17u; ++j) STREAM_ISSUE(1u, j)
+    STREAM_ISSUE_ADVANCE()
+#pragma unroll
+    for (uint32_t r = 0; r < 16u; ++r) STREAM_FRAG(fa0, fb0, fa_pos0, fb_pos0, r)
+// Scale dwords of a K-quad, in two steps: the raw dwords are read from ring slot SLOT behind the barrier and the next
+// quad's first fragments, and turned into operands (of local quad QUADN of a tile whose product has GK groups along K) only behind
+// the current quad's last matrix-core instruction.
+#define STREAM_SCALES_READ_A(SLOT)                                                                      \
     {                                                                                                   \
-        const uint32_t* sbuf_ = reinterpret_cast<const uint32_t*>(&lds[(SLOT) * STAGE]);                \
-        _Pragma("unroll") for (uint32_t i = 0; i < TM; ++i) ra_n[i] = sbuf_[sa_base + i * 64u];         \
-        _Pragma("unroll") for (uint32_t j = 0; j < TN; ++j) rb_n[j] = sbuf_[sb_base + j * 64u];         \
+        STREAM_AT(at_, SLOT, sa_pos)                                                                    \
+        const uint32_t* s_ = reinterpret_cast<const uint32_t*>(lds_bytes + at_);                        \
+        _Pragma("unroll") for (uint32_t i = 0; i < 2u * TM; ++i) ra_n[i] = s_[i / 2u * 64u + i % 2u * 16u]; \
     }
-#define STREAM_SCALES_USE(ST, GK)                                                                       \
+#define STREAM_SCALES_READ_B(SLOT)                                                                      \
     {                                                                                                   \
-        uint32_t keep_ = 0xFFFFFFFFu;                                                                   \
-        if (((ST) + 2u) * 4u > (GK)) {        /* wave-uniform: only a ragged last K-quad */             \
-            const uint32_t ksteps_lane = ((GK) + 1u - lhalf) >> 1;   /* K-steps in which this half-wave has a group */ \
-            const uint32_t done_ = (ST) * 2u;                                                           \
-            const uint32_t nv_ = ksteps_lane > done_ ? (ksteps_lane - done_ < 4u ? ksteps_lane - done_ : 4u) : 0u; \
-            keep_ = nv_ >= 4u ? 0xFFFFFFFFu : ((1u << (8u * nv_)) - 1u);                                \
-        }                                                                                               \
-        _Pragma("unroll") for (uint32_t i = 0; i < TM; ++i) sa[i] = (ra_n[i] & keep_) | (0x7F7F7F7Fu & ~keep_); \
-        _Pragma("unroll") for (uint32_t j = 0; j < TN; ++j) sb[j] = (rb_n[j] & keep_) | (0x7F7F7F7Fu & ~keep_); \
+        STREAM_AT(at_, SLOT, sb_pos)                                                                    \
+        const uint32_t* s_ = reinterpret_cast<const uint32_t*>(lds_bytes + at_);                        \
+        _Pragma("unroll") for (uint32_t j = 0; j < 2u * TN; ++j) rb_n[j] = s_[j / 2u * 64u + j % 2u * 16u]; \
+    }
+#define STREAM_SCALES_USE(QUADN, GK)                                                                    \
+    {                                                                                                   \
+        uint32_t sel_ = sel_full;                                                                       \
+        if (((QUADN) + 1u) * 8u > (GK)) sel_ = scale_selector(lane, (QUADN) * 8u, (GK));   /* wave-uniform: only a ragged last K-quad */ \
+        _Pragma("unroll") for (uint32_t i = 0; i < 2u * TM; ++i) sa[i] = __builtin_amdgcn_perm(0x7F7F7F7Fu, ra_n[i], sel_); \
+        _Pragma("unroll") for (uint32_t j = 0; j < 2u * TN; ++j) sb[j] = __builtin_amdgcn_perm(0x7F7F7F7Fu, rb_n[j], sel_); \
     }
     uint32_t csel, clv;
     STREAM_PRODUCT(blockIdx.x, csel, clv)
-    STREAM_SCALES_READ(0u)
+    STREAM_SCALES_READ_A(0u)
+    STREAM_SCALES_READ_B(0u)
     STREAM_SCALES_USE(0u, batch.p[csel].k >> 5)
-#define STREAM_MF(S, FA, FB, I, J)                                                                      \
-    acc[I][J] = mfma_fp4<S>(FA[I], FB[J], acc[I][J], sa[I], sb[J]);                                     \
-    asm volatile("" : "+a"(acc[I][J]));                                                                 \
+// One K-quad: two K-steps of 64 matrix-core instructions; SL = its ring slot.  The fragments of a K-step are read one by one during the
+// step before it.  The quad's one barrier stands between its steps: every wave has read its last fragment of the slot, so the
+// quad after the next is loaded into it during the second step, and every load of the next quad (issued a whole quad earlier) has
+// landed.  Reads and loads are spread over the instructions: bunched in a quarter of the step they made the matrix cores wait
+// for the LDS.  STORES: the previous tile's result stores, younger than the loads waited for, may still be under way.
+#define STREAM_MF(STEP, I, J)                                                                           \
+    if (STEP) mfma_fp4<1>(fa1[I], fb1[J], acc[I][J], sa[I], sb[J]);                                     \
+    else mfma_fp4<0>(fa0[I], fb0[J], acc[I][J], sa[I], sb[J]);                                          \
     STREAM_FENCE()
-// one stage: PAR = its parity, ST = its local index, slots: SL = its own, SL1 = the next stage's, SLI = the one being filled
-#define STREAM_BODY(PAR, ST, SL, SL1, SLI, NEXT_ST, NEXT_GK)                                            \
+// instruction number N of a step and what follows it: fragment reads of the next K-step behind every third, and in the second step
+// the loads behind the instructions in between
+#define STREAM_AFTER0(N)                                                                                \
+    if ((N) % 3u == 0u && (N) < 48u) { STREAM_FRAG(fa1, fb1, a1_, b1_, (N) / 3u) STREAM_FENCE() }
+#define STREAM_AFTER1(N)                                                                                \
+    if ((N) % 3u == 0u && (N) < 48u) { STREAM_FRAG(fa0, fb0, an_, bn_, (N) / 3u) STREAM_FENCE() }       \
+    if ((N) % 3u == 1u && (N) < 51u) { STREAM_ISSUE(SL_, (N) / 3u) STREAM_FENCE() }                     \
+    if ((N) == 48u) { STREAM_SCALES_READ_A(so_) STREAM_FENCE() }                                        \
+    if ((N) == 51u) { STREAM_SCALES_READ_B(so_) STREAM_FENCE() }
+#define STREAM_ROW(STEP, I)                                                                             \
+    STREAM_MF(STEP, I, 0) STREAM_AFTER##STEP((I) * 8u) STREAM_MF(STEP, I, 1) STREAM_AFTER##STEP((I) * 8u + 1u) \
+    STREAM_MF(STEP, I, 2) STREAM_AFTER##STEP((I) * 8u + 2u) STREAM_MF(STEP, I, 3) STREAM_AFTER##STEP((I) * 8u + 3u) \
+    STREAM_MF(STEP, I, 4) STREAM_AFTER##STEP((I) * 8u + 4u) STREAM_MF(STEP, I, 5) STREAM_AFTER##STEP((I) * 8u + 5u) \
+    STREAM_MF(STEP, I, 6) STREAM_AFTER##STEP((I) * 8u + 6u) STREAM_MF(STEP, I, 7) STREAM_AFTER##STEP((I) * 8u + 7u)
+#define STREAM_BODY(SL, STORES, NEXT_QUAD, NEXT_GK)                                                     \
     {                                                                                                   \
-        STREAM_MF(2 * PAR, fa0, fb0, 0, 0) STREAM_FRAG_B(SL, 1u, fb1, 0) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 0, 1) STREAM_FRAG_B(SL, 1u, fb1, 1) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 0, 2) STREAM_FRAG_B(SL, 1u, fb1, 2) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 0, 3) STREAM_FRAG_B(SL, 1u, fb1, 3) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 1, 0) STREAM_FRAG_A(SL, 1u, fa1, 0) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 1, 1) STREAM_FRAG_A(SL, 1u, fa1, 1) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 1, 2) STREAM_FRAG_A(SL, 1u, fa1, 2) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 1, 3) STREAM_FRAG_A(SL, 1u, fa1, 3) STREAM_FENCE()                 \
-        STREAM_MF(2 * PAR, fa0, fb0, 2, 0) STREAM_ISSUE(SLI, 0u) STREAM_FENCE()                         \
-        STREAM_MF(2 * PAR, fa0, fb0, 2, 1)                                                              \
-        STREAM_MF(2 * PAR, fa0, fb0, 2, 2) STREAM_ISSUE(SLI, 1u) STREAM_FENCE()                         \
-        STREAM_MF(2 * PAR, fa0, fb0, 2, 3)                                                              \
-        STREAM_MF(2 * PAR, fa0, fb0, 3, 0) STREAM_ISSUE(SLI, 2u) STREAM_FENCE()                         \
-        STREAM_MF(2 * PAR, fa0, fb0, 3, 1)                                                              \
-        STREAM_MF(2 * PAR, fa0, fb0, 3, 2) STREAM_ISSUE(SLI, 3u) STREAM_FENCE()                         \
-        STREAM_MF(2 * PAR, fa0, fb0, 3, 3)                                                              \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 0, 0) STREAM_ISSUE(SLI, 4u) STREAM_FENCE()                     \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 0, 1)                                                          \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 0, 2) STREAM_ISSUE(SLI, 5u) STREAM_FENCE()                     \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 0, 3)                                                          \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 1, 0) STREAM_ISSUE(SLI, 6u) STREAM_FENCE()                     \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 1, 1)                                                          \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 1, 2) STREAM_ISSUE(SLI, 7u) STREAM_FENCE()                     \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 1, 3)                                                          \
-        if (PAR == 1) { STREAM_ISSUE(SLI, 8u) STREAM_FENCE() }   /* the stage being filled is even */   \
-        STREAM_ISSUE_ADVANCE()                                                                          \
-        __builtin_amdgcn_s_waitcnt(WAIT2);                                                              \
+        const uint32_t SL_ = (SL), so_ = SL_ ^ 1u;                                                      \
+        STREAM_AT(a1_, SL_, fa_pos1) STREAM_AT(b1_, SL_, fb_pos1)                                       \
+        STREAM_AT(an_, so_, fa_pos0) STREAM_AT(bn_, so_, fb_pos0)                                       \
+        STREAM_ROW(0, 0) STREAM_ROW(0, 1) STREAM_ROW(0, 2) STREAM_ROW(0, 3)                             \
+        STREAM_ROW(0, 4) STREAM_ROW(0, 5) STREAM_ROW(0, 6) STREAM_ROW(0, 7)                             \
+        if (STORES) __builtin_amdgcn_s_waitcnt(DRAIN_BUT_STORES);                                       \
+        else __builtin_amdgcn_s_waitcnt(DRAIN);                                                         \
         __builtin_amdgcn_s_barrier();                                                                   \
         STREAM_FENCE()                                                                                  \
-        if (PAR == 1) { STREAM_SCALES_READ(SL1) STREAM_FENCE() }                                        \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 2, 0) STREAM_FRAG_A(SL1, 0u, fa0, 0) STREAM_FRAG_B(SL1, 0u, fb0, 0) STREAM_FENCE() \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 2, 1) STREAM_FRAG_B(SL1, 0u, fb0, 1) STREAM_FRAG_B(SL1, 0u, fb0, 2) STREAM_FENCE() \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 2, 2) STREAM_FRAG_B(SL1, 0u, fb0, 3) STREAM_FENCE()            \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 2, 3) STREAM_FRAG_A(SL1, 0u, fa0, 1) STREAM_FENCE()            \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 3, 0) STREAM_FRAG_A(SL1, 0u, fa0, 2) STREAM_FENCE()            \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 3, 1) STREAM_FRAG_A(SL1, 0u, fa0, 3) STREAM_FENCE()            \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 3, 2)                                                          \
-        STREAM_MF(2 * PAR + 1, fa1, fb1, 3, 3)                                                          \
-        if (PAR == 1) { STREAM_SCALES_USE(NEXT_ST, NEXT_GK) STREAM_FENCE() }                            \
+        STREAM_ROW(1, 0) STREAM_ROW(1, 1) STREAM_ROW(1, 2) STREAM_ROW(1, 3)                             \
+        STREAM_ROW(1, 4) STREAM_ROW(1, 5) STREAM_ROW(1, 6)                                              \
+        STREAM_ISSUE_ADVANCE()                                                                          \
+        STREAM_FENCE()                                                                                  \
+        STREAM_ROW(1, 7)                                                                                \
+        STREAM_SCALES_USE(NEXT_QUAD, NEXT_GK)                                                           \
+        mfma_operands_written();                                                                        \
+        STREAM_FENCE()                                                                                  \
     }
 
-    v16f acc[TM][TN];
-    float* wbuf = reinterpret_cast<float*>(&lds[kRing * STAGE]) + wave * 1024u;
-    uint32_t g = 0u;                                       // stages done by this block (ring slot = g % kRing)
+    v4f acc[2 * TM][2 * TN];
+    float* wbuf = reinterpret_cast<float*>(&lds[2u * QUAD]) + wave * 1024u;
+    uint32_t sl = 0u;                                      // ring slot of the current quad
+    bool stores = false;                                   // the previous tile's 64 result stores are younger than the loads to wait for
     for (uint32_t cv = blockIdx.x; cv < total_tiles; cv += G) {
         STREAM_PRODUCT(cv, csel, clv)
-        const uint32_t ck = batch.p[csel].k, gk = ck >> 5, stages = (ck + 127u) >> 7;
-        const uint32_t S2 = stages < 2u ? 2u : ((stages + 1u) & ~1u);   // stages per tile, even (extra stages are zero-filled)
-        // the tile's last pair of stages reads the first scales of the block's next tile, which may belong to the other product
+        const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
+        // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
         const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < 2 * (int)TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < 2 * (int)TN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-        for (uint32_t st = 0u; st < S2; st += 2u, g += 2u) {
-            const uint32_t sl = g & 3u;                    // g is even: sl is 0 or 2
-            const uint32_t next_st = st + 2u < S2 ? st + 2u : 0u;   // after the tile's last pair: the next tile's stage 0
-            const uint32_t next_gk = st + 2u < S2 ? gk : gk_after;
-            STREAM_BODY(0, st, sl, sl + 1u, sl ^ 3u, 0u, 0u)                    /* fills slot (g + 3) % 4 */
-            STREAM_BODY(1, st + 1u, sl + 1u, sl ^ 2u, sl, next_st, next_gk)     /* fills slot (g + 4) % 4 */
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+        mfma_operands_written();
+        __builtin_amdgcn_sched_barrier(0);
+        for (uint32_t qd = 0u; qd < quads; ++qd, sl ^= 1u) {
+            const bool last = qd + 1u == quads;            // the next quad is the next tile's first
+            STREAM_BODY(sl, stores, last ? 0u : qd + 1u, last ? gk_after : gk)
+            stores = false;
         }
-        // The ring already holds (or is receiving) the next tile's first stages, and fa0 / fb0 / sa / sb its first
-        // fragments and scales.  The result stores below are older than every load issued from here on and the
-        // vector-memory counter retires in order, so the next tile's first wait also waits for them.
+        mfma_results_written();
+        __builtin_amdgcn_sched_barrier(0);
+        // The ring already holds the next tile's first quad and is receiving its second, and fa0 / fb0 / sa / sb hold its first
+        // fragments and scales.  The vector-memory counter retires in order: the next tile's first barrier waits for loads older than
+        // the result stores below, its second one for the stores as well.
         const GemmProblem& q = batch.p[csel];
         uint32_t m0, n0;
         STREAM_TILE(q, clv, m0, n0)
@@ -310,8 +328,9 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
         if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
         else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
+        stores = full;                                     // 16 passes of four stores each; a ragged tile may have skipped some
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // the stages issued past the last tile (zero-filled) have landed before the LDS is given back
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // the quads issued past the last tile (zero-filled) have landed before the LDS is given back
     if (clock_counters && tid == 0) {
         const uint64_t t1 = __builtin_readcyclecounter(), w1 = __builtin_amdgcn_s_memrealtime();
         atomicAdd(reinterpret_cast<unsigned long long*>(clock_counters), (unsigned long long)(t1 - clk_t0));
@@ -322,41 +341,40 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
 #undef STREAM_ISSUE_SETUP
 #undef STREAM_ISSUE
 #undef STREAM_ISSUE_ADVANCE
-#undef STREAM_FRAG_A
-#undef STREAM_FRAG_B
+#undef STREAM_AT
+#undef STREAM_FRAG
+#undef STREAM_AFTER0
+#undef STREAM_AFTER1
 #undef STREAM_FENCE
-#undef STREAM_SCALES_READ
+#undef STREAM_SCALES_READ_A
+#undef STREAM_SCALES_READ_B
 #undef STREAM_SCALES_USE
 #undef STREAM_MF
+#undef STREAM_ROW
 #undef STREAM_BODY
 }
 
 // ---------------------------------------------------------------------------------------------
 // The streaming design for other tile shapes: wave tile (TM*32) x (TN*32), block tile (64 TM) x (64 TN), for problems
-// whose 256 x 256 tiles would leave compute units idle.  Same ring, same issue cursor, same epilogue; the stage's
-// instruction order is generated from the tile shape instead of written out: after matrix-core instruction number idx of
-// a stage come, in this order, the fragment reads of the stage's second K-step (RPS per slot from slot 0), the stage's
-// LDS-direct loads (spread over the slots up to the barrier), the wait and the barrier POST instructions before the
-// stage's end, and behind the barrier the next stage's first fragments (and, on odd stages, the next K-quad's scales).
+// whose 256 x 256 tiles would leave compute units idle.  Same issue cursor, same two sets of fragments, same barrier between the
+// K-steps of a quad, same epilogue; the instruction order is generated from the tile shape.  A quad of these tiles lasts 0.3-0.6 us,
+// less than a load's way from memory, so the ring has S = 3 or 4 slots (what fits): during the first K-step of quad q go out the
+// loads of quad q + S - 1.  That leaves the slot of a tile's last quad free until the next tile begins: it serves as the
+// epilogue's scratch.
 template <int TM, int TN, bool OUT_BF16, bool FUSED>
 __global__ void __launch_bounds__(256)
 gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t BM = 64 * TM, BN = 64 * TN;
     static_assert(BM % 128 == 0 && BN % 128 == 0, "a wave's four scale tiles must belong to one operand");
-    constexpr uint32_t CODES = (BM + BN) * 4;            // 16-byte chunks of codes per stage
-    constexpr uint32_t STAGE = CODES + 256;              // + room for 16 scale tiles of 256 B (one KB per wave)
-    constexpr uint32_t D = kRing - 1;
-    constexpr uint32_t EPI = 4u * TN * 64u;              // 16-byte chunks of epilogue scratch: 8 rows x TN*32 floats per wave
-    constexpr uint32_t LA = BM / 64, LB = BN / 64, NL = LA + LB;   // LDS-direct loads of codes per wave per stage
+    constexpr uint32_t CODES = (BM + BN) * 8;            // 16-byte chunks of codes per K-quad
+    constexpr uint32_t QUAD = CODES + 256;               // + room for 16 scale tiles of 256 B (one KB per wave)
+    constexpr uint32_t S = BN == 256 ? 3u : 4u;          // ring slots
+    constexpr uint32_t LA = BM / 32, LB = BN / 32, NL = LA + LB;   // LDS-direct loads of codes per wave per quad
     constexpr uint32_t NT = (BM + BN) / 32;              // scale tiles per K-quad: A's, then B's
-    constexpr int NM = TM * TN, R = TM + TN;             // matrix-core instructions and fragment reads per K-step
-    constexpr int POST = NM >= 16 ? 8 : (NM >= 8 ? 6 : 3);   // matrix-core instructions behind the barrier
-    constexpr int P = 2 * NM - POST;                     // slots in front of the barrier
-    constexpr int RPS = (2 * R > NM) ? 2 : 1;            // second-K-step fragment reads per slot
-    constexpr int RS_END = (R + RPS - 1) / RPS;          // first slot without such a read
-    constexpr int XR = R - (POST > 2 ? POST - 2 : 1);    // reads of the next stage's first fragments that must double up
-    static_assert(RS_END <= NM && RS_END < P, "the fragments of the second K-step must be read during the first");
-    __shared__ uint4 lds[kRing * STAGE + EPI];
+    constexpr int TA = 2 * TM, TB = 2 * TN, NM = TA * TB, R = TA + TB;   // matrix-core instructions and fragment reads per K-step
+    constexpr int RSP = NM >= 32 ? 2 : 1;                // instructions per fragment read in the second K-step
+    static_assert(2 * R <= NM + 1 + (RSP == 1 ? R : 0) && (int)NL < NM && R * RSP + 2 < NM, "reads and loads must fit");
+    __shared__ v4i_t lds[S * QUAD];
 
     // measurement support: shader-clock and constant-clock ticks of this block's run (wave-uniform branch)
     uint64_t clk_t0 = 0, clk_w0 = 0;
@@ -367,7 +385,7 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t lrow = lane & 31u, lhalf = lane >> 5;
+    const uint32_t l16 = lane & 15u, quarter = lane >> 4;
     const uint32_t G = gridDim.x, first_tiles = batch.p[0].total_tiles;
     const uint32_t wm0 = (wave >> 1) * (TM * 32u), wn0 = (wave & 1u) * (TN * 32u);
     // scale tiles 4 wave .. 4 wave + 3 of [A's | B's] are this wave's to fetch (waves past the last tile fetch nothing real:
@@ -400,11 +418,11 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
             M0 = (Q).m; N0 = (Q).n;                                                                     \
         }                                                                                               \
     }
-    uint32_t iv = blockIdx.x, ist = 0u;                  // issue cursor: the tile and stage the next loads belong to
+    uint32_t iv = blockIdx.x, iq = 0u;                   // issue cursor: the tile and K-quad the next loads belong to
     v4i_t res_a, res_b, res_s;
-    uint32_t kb, istages, S2i, goff, gstep, soff;        // of the cursor's product
-    const uint32_t drow = wave * 16u + (lane >> 2);
-    const uint32_t dcol = (lane & 3u) ^ ((drow >> 2) & 3u);
+    uint32_t kb, kq, goff, gstep, soff;                  // of the cursor's product
+    const uint32_t drow = wave * 8u + (lane >> 3);
+    const uint32_t dcol = (lane & 7u) ^ ((drow >> 1) & 7u);
 #define ISSUE_SETUP()                                                                                   \
     {                                                                                                   \
         uint32_t sel_, lv_, m0_, n0_;                                                                   \
@@ -412,11 +430,10 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         const GemmProblem& q_ = batch.p[sel_];                                                          \
         TILE_ORIGIN(q_, lv_, m0_, n0_)                                                                  \
         const uint32_t k_ = q_.k, kq_ = (k_ + 255u) >> 8;                                               \
+        kq = kq_ ? kq_ : 1u;                                                                            \
         kb = k_ >> 1;                                                                                   \
-        istages = (k_ + 127u) >> 7;                                                                     \
-        S2i = istages < 2u ? 2u : ((istages + 1u) & ~1u);                                               \
-        goff = drow * kb + dcol * 16u;          /* + j*64*kb, + stage*64 */                             \
-        gstep = 64u * kb;                                                                               \
+        goff = drow * kb + dcol * 16u;          /* + j*32*kb, + quad*128 */                             \
+        gstep = 32u * kb;                                                                               \
         soff = ((stile0 + (lane >> 4)) * kq_) * 256u + (lane & 15u) * 16u;   /* + quad*256 */           \
         const uint32_t rows_a_ = (q_.m - m0_) < BM ? (q_.m - m0_) : BM, rows_b_ = (q_.n - n0_) < BN ? (q_.n - n0_) : BN; \
         res_a = make_rsrc_words(q_.a_codes + (size_t)m0_ * kb, rows_a_ * kb);                           \
@@ -428,146 +445,141 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
     ISSUE_SETUP()
 
     const uint32_t lds0 = (uint32_t)(size_t)(lds_ptr_t)&lds[0];
-    const uint32_t swz = (lrow >> 2) & 3u;
-    const uint32_t fa_base = (wm0 + lrow) * 4u, fb_base = BM * 4u + (wn0 + lrow) * 4u;
-    const uint32_t sa_base = CODES * 4u + (wm0 >> 5) * 64u + lane;             // dword index in a stage
-    const uint32_t sb_base = CODES * 4u + (BM / 32u) * 64u + (wn0 >> 5) * 64u + lane;
+    // LDS positions of the lane's part of the first fragments and scales in a ring slot (see the 256 x 256 kernel)
+    const uint32_t chunk0 = quarter ^ (l16 >> 1), chunk1 = chunk0 ^ 4u, srow = (quarter & 1u) * 32u + l16;
+    const uint32_t fa_pos0 = ((wm0 + l16) * 8u + chunk0) * 16u, fb_pos0 = ((BM + wn0 + l16) * 8u + chunk0) * 16u;
+    const uint32_t fa_pos1 = ((wm0 + l16) * 8u + chunk1) * 16u, fb_pos1 = ((BM + wn0 + l16) * 8u + chunk1) * 16u;
+    const uint32_t sa_pos = CODES * 16u + ((wm0 >> 5) * 64u + srow) * 4u, sb_pos = CODES * 16u + ((BM / 32u + (wn0 >> 5)) * 64u + srow) * 4u;
+    const uint8_t* lds_bytes = reinterpret_cast<const uint8_t*>(lds);
+    const uint32_t sel_full = scale_selector(lane, 0u, 8u);
 
-    uint32_t sa[TM], sb[TN], ra_n[TM], rb_n[TN];
-    uint4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
+    uint32_t sa[TA], sb[TB], ra_n[TA], rb_n[TB];
+    v4i_t fa0[TA], fb0[TB], fa1[TA], fb1[TB];            // fragments of a quad's first and second K-step
 
-// code load J (0 .. LA-1: A rows, LA .. NL-1: B rows) or the scale tiles (J == NL) of the cursor's stage into ring slot SLOT
+// code load J (0 .. LA-1: A rows, LA .. NL-1: B rows) or the scale tiles (J == NL) of the cursor's quad into ring slot SLOT
 #define ISSUE(SLOT, J)                                                                                  \
     {                                                                                                   \
-        const uint32_t slot_ = lds0 + ((SLOT) * STAGE + wave * 64u) * 16u;                              \
+        const uint32_t slot_ = lds0 + ((SLOT) * QUAD + wave * 64u) * 16u;                               \
         if ((uint32_t)(J) < NL) {                                                                       \
-            const uint32_t base_ = (ist * 64u + dcol * 16u < kb) ? goff + ist * 64u : kOutOfRange;      \
+            const uint32_t base_ = (iq * 128u + dcol * 16u < kb) ? goff + iq * 128u : kOutOfRange;      \
             const uint32_t jj_ = (uint32_t)(J) < LA ? (uint32_t)(J) : (uint32_t)(J) - LA;               \
             lds_direct_load16((uint32_t)(J) < LA ? res_a : res_b, base_ + jj_ * gstep, slot_ + (uint32_t)(J) * 4096u); \
         } else {                                                                                        \
-            lds_direct_load16(res_s, (ist < istages) ? soff + (ist >> 1) * 256u : kOutOfRange, slot_ + CODES * 16u); \
+            lds_direct_load16(res_s, soff + iq * 256u, slot_ + CODES * 16u);                            \
         }                                                                                               \
     }
 #define ISSUE_ADVANCE()                                                                                 \
     {                                                                                                   \
-        ++ist;                                                                                          \
-        if (ist == S2i) {                                                                               \
-            ist = 0u;                                                                                   \
+        ++iq;                                                                                           \
+        if (iq == kq) {                                                                                 \
+            iq = 0u;                                                                                    \
             iv += G;                                                                                    \
             ISSUE_SETUP()                                                                               \
         }                                                                                               \
     }
-// fragment number RR of K-step S: B0 .. B(TN-1), then A0 .. A(TM-1)
-#define READ_FRAG(SLOT, S, FA, FB, RR)                                                                  \
+#define LDS_AT(NAME, SLOT, POS) uint32_t NAME = (SLOT) * QUAD * 16u + (POS); asm volatile("" : "+v"(NAME));
+// fragment number RR of a K-step in the order the instructions need them: A0, B0 .. B(TB-1), A1 .. A(TA-1)
+#define READ_FRAG(FA, FB, AT_A, AT_B, RR)                                                               \
     {                                                                                                   \
         const int rr_ = (RR);                                                                           \
-        if (rr_ < TN) FB[rr_] = lds[(SLOT) * STAGE + fb_base + rr_ * 128u + ((2u * (S) + lhalf) ^ swz)]; \
-        else if (rr_ < R) FA[rr_ - TN] = lds[(SLOT) * STAGE + fa_base + (rr_ - TN) * 128u + ((2u * (S) + lhalf) ^ swz)]; \
-    }
-// the next stage's first fragments in the order the first instructions need them: A0, B0 .. B(TN-1), A1 .. A(TM-1)
-#define READ_FRAG_NEXT(SLOT, FA, FB, RR)                                                                \
-    {                                                                                                   \
-        const int rn_ = (RR);                                                                           \
-        READ_FRAG(SLOT, 0u, FA, FB, rn_ == 0 ? TN : (rn_ <= TN ? rn_ - 1 : rn_))                        \
+        if (rr_ >= 1 && rr_ <= TB) FB[rr_ - 1] = *reinterpret_cast<const v4i_t*>(lds_bytes + (AT_B) + (rr_ - 1) * 2048); \
+        else if (rr_ < R) FA[rr_ == 0 ? 0 : rr_ - TB] = *reinterpret_cast<const v4i_t*>(lds_bytes + (AT_A) + (rr_ == 0 ? 0 : rr_ - TB) * 2048); \
     }
 #define FENCE() __builtin_amdgcn_sched_barrier(0);
-// scale dwords of a K-quad: read right behind the barrier, used behind the pair's last matrix-core instruction (see the
-// 256 x 256 kernel)
+// scale dwords of a K-quad: read behind the next quad's first fragments, used behind the quad's last matrix-core instruction
 #define READ_SCALES(SLOT)                                                                               \
     {                                                                                                   \
-        const uint32_t* sbuf_ = reinterpret_cast<const uint32_t*>(&lds[(SLOT) * STAGE]);                \
-        _Pragma("unroll") for (uint32_t i = 0; i < TM; ++i) ra_n[i] = sbuf_[sa_base + i * 64u];         \
-        _Pragma("unroll") for (uint32_t j = 0; j < TN; ++j) rb_n[j] = sbuf_[sb_base + j * 64u];         \
+        LDS_AT(at_a_, SLOT, sa_pos) LDS_AT(at_b_, SLOT, sb_pos)                                         \
+        const uint32_t* s_a_ = reinterpret_cast<const uint32_t*>(lds_bytes + at_a_);                    \
+        const uint32_t* s_b_ = reinterpret_cast<const uint32_t*>(lds_bytes + at_b_);                    \
+        _Pragma("unroll") for (uint32_t i = 0; i < TA; ++i) ra_n[i] = s_a_[i / 2u * 64u + i % 2u * 16u]; \
+        _Pragma("unroll") for (uint32_t j = 0; j < TB; ++j) rb_n[j] = s_b_[j / 2u * 64u + j % 2u * 16u]; \
     }
-#define USE_SCALES(ST, GK)                                                                              \
+#define USE_SCALES(QUADN, GK)                                                                           \
     {                                                                                                   \
-        uint32_t keep_ = 0xFFFFFFFFu;                                                                   \
-        if (((ST) + 2u) * 4u > (GK)) {        /* wave-uniform: only a ragged last K-quad */             \
-            const uint32_t ksteps_lane = ((GK) + 1u - lhalf) >> 1;   /* K-steps in which this half-wave has a group */ \
-            const uint32_t done_ = (ST) * 2u;                                                           \
-            const uint32_t nv_ = ksteps_lane > done_ ? (ksteps_lane - done_ < 4u ? ksteps_lane - done_ : 4u) : 0u; \
-            keep_ = nv_ >= 4u ? 0xFFFFFFFFu : ((1u << (8u * nv_)) - 1u);                                \
-        }                                                                                               \
-        _Pragma("unroll") for (uint32_t i = 0; i < TM; ++i) sa[i] = (ra_n[i] & keep_) | (0x7F7F7F7Fu & ~keep_); \
-        _Pragma("unroll") for (uint32_t j = 0; j < TN; ++j) sb[j] = (rb_n[j] & keep_) | (0x7F7F7F7Fu & ~keep_); \
+        uint32_t sel_ = sel_full;                                                                       \
+        if (((QUADN) + 1u) * 8u > (GK)) sel_ = scale_selector(lane, (QUADN) * 8u, (GK));   /* wave-uniform: only a ragged last K-quad */ \
+        _Pragma("unroll") for (uint32_t i = 0; i < TA; ++i) sa[i] = __builtin_amdgcn_perm(0x7F7F7F7Fu, ra_n[i], sel_); \
+        _Pragma("unroll") for (uint32_t j = 0; j < TB; ++j) sb[j] = __builtin_amdgcn_perm(0x7F7F7F7Fu, rb_n[j], sel_); \
     }
 
-    constexpr uint32_t KEEP2 = 2u * NL + 1u;           // loads of one even and one odd stage stay in flight
-    constexpr uint32_t WAIT2 = 0x0F70u | (KEEP2 & 15u) | ((KEEP2 >> 4) << 14);
+    // vector-memory operations that may be under way at a quad's barrier: the loads of the quads behind the next one, and once after a
+    // tile's end its result stores, which are younger than the next quad's loads
+    constexpr uint32_t AHEAD = (S - 2u) * (NL + 1u), AHEAD_ST = AHEAD + TM * 4u * TN;
+    static_assert(AHEAD_ST < 64u, "the counter has six bits");
+    constexpr uint32_t WAIT = 0x0070u | (AHEAD & 15u) | ((AHEAD >> 4) << 14);      // and no LDS read is outstanding
+    constexpr uint32_t WAIT_ST = 0x0070u | (AHEAD_ST & 15u) | ((AHEAD_ST >> 4) << 14);
 #pragma unroll
-    for (uint32_t s0 = 0; s0 < D; ++s0) {
+    for (uint32_t s0 = 0; s0 < S - 1u; ++s0) {
 #pragma unroll
-        for (uint32_t j = 0; j < NL; ++j) ISSUE(s0, j)
-        if ((s0 & 1u) == 0u) ISSUE(s0, NL)
+        for (uint32_t j = 0; j <= NL; ++j) ISSUE(s0, j)
         ISSUE_ADVANCE()
     }
-    __builtin_amdgcn_s_waitcnt(WAIT2);
+    __builtin_amdgcn_s_waitcnt(WAIT);
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int r = 0; r < R; ++r) READ_FRAG(0u, 0u, fa0, fb0, r)
-    static_assert(XR >= 0 && XR <= R / 2 + 1, "the next stage's fragment reads must fit behind the barrier");
+    for (int r = 0; r < R; ++r) READ_FRAG(fa0, fb0, fa_pos0, fb_pos0, r)
     uint32_t csel, clv;
     PRODUCT_OF(blockIdx.x, csel, clv)
     READ_SCALES(0u)
     USE_SCALES(0u, batch.p[csel].k >> 5)
 
-// one stage: PAR = its parity, slots SL = its own, SL1 = the next stage's, SLI = the one being filled; NEXT_ST: the
-// local index of the stage after the next (odd stages read its K-quad's scales)
-#define STAGE_BODY(PAR, SL, SL1, SLI, NEXT_ST, NEXT_GK)                                                 \
+// one K-quad in slot SL; SL1: the next quad's slot, SLI: the slot being filled
+#define QUAD_BODY(SL, SL1, SLI, STORES, NEXT_QUAD, NEXT_GK)                                             \
     {                                                                                                   \
-        _Pragma("unroll") for (int idx = 0; idx < 2 * NM; ++idx) {                                      \
-            const int ij_ = idx % NM, I_ = ij_ / TN, J_ = ij_ % TN;                                     \
-            if (idx < NM) acc[I_][J_] = mfma_fp4<2 * PAR>(fa0[I_], fb0[J_], acc[I_][J_], sa[I_], sb[J_]); \
-            else acc[I_][J_] = mfma_fp4<2 * PAR + 1>(fa1[I_], fb1[J_], acc[I_][J_], sa[I_], sb[J_]);    \
-            asm volatile("" : "+a"(acc[I_][J_]));                                                       \
+        LDS_AT(a1_, SL, fa_pos1) LDS_AT(b1_, SL, fb_pos1) LDS_AT(an_, SL1, fa_pos0) LDS_AT(bn_, SL1, fb_pos0) \
+        _Pragma("unroll") for (int idx = 0; idx < NM; ++idx) {                                          \
+            mfma_fp4<0>(fa0[idx / TB], fb0[idx % TB], acc[idx / TB][idx % TB], sa[idx / TB], sb[idx % TB]); \
             FENCE()                                                                                     \
-            if (idx < RS_END) {                                                                         \
-                _Pragma("unroll") for (int q_ = 0; q_ < RPS; ++q_) READ_FRAG(SL, 1u, fa1, fb1, idx * RPS + q_) \
-                FENCE()                                                                                 \
-            }                                                                                           \
-            if (idx >= RS_END && idx < P) {                                                             \
-                _Pragma("unroll") for (int l_ = 0; l_ < (int)NL; ++l_)                                  \
-                    if (RS_END + (l_ * (P - RS_END)) / (int)NL == idx) { ISSUE(SLI, l_) FENCE() }       \
-            }                                                                                           \
-            if (idx == P - 1) {                                                                         \
-                if (PAR == 1) { ISSUE(SLI, NL) FENCE() }   /* the stage being filled is even */         \
-                ISSUE_ADVANCE()                                                                         \
-                __builtin_amdgcn_s_waitcnt(WAIT2);                                                      \
-                __builtin_amdgcn_s_barrier();                                                           \
-                FENCE()                                                                                 \
-                if (PAR == 1) { READ_SCALES(SL1) FENCE() }                                              \
-            }                                                                                           \
-            if (idx >= P) {         /* two reads per slot while more reads than slots are left, then one */ \
-                _Pragma("unroll") for (int r_ = 0; r_ < R; ++r_)                                        \
-                    if (P + (r_ < 2 * XR ? r_ / 2 : r_ - XR) == idx) READ_FRAG_NEXT(SL1, fa0, fb0, r_)  \
-                FENCE()                                                                                 \
-            }                                                                                           \
+            if (idx % 2 == 0 && idx / 2 < R) { READ_FRAG(fa1, fb1, a1_, b1_, idx / 2) FENCE() }         \
+            if (idx % 2 == 1 && idx / 2 <= (int)NL) { ISSUE(SLI, idx / 2) FENCE() }                     \
+            if (idx == NM - 1 && NM / 2 == (int)NL) { ISSUE(SLI, NL) FENCE() }                          \
         }                                                                                               \
-        if (PAR == 1) { USE_SCALES(NEXT_ST, NEXT_GK) FENCE() }                                          \
+        ISSUE_ADVANCE()                                                                                 \
+        if (STORES) __builtin_amdgcn_s_waitcnt(WAIT_ST);                                                \
+        else __builtin_amdgcn_s_waitcnt(WAIT);                                                          \
+        __builtin_amdgcn_s_barrier();                                                                   \
+        FENCE()                                                                                         \
+        _Pragma("unroll") for (int idx = 0; idx < NM; ++idx) {                                          \
+            mfma_fp4<1>(fa1[idx / TB], fb1[idx % TB], acc[idx / TB][idx % TB], sa[idx / TB], sb[idx % TB]); \
+            FENCE()                                                                                     \
+            if (idx % RSP == 0 && idx / RSP < R) { READ_FRAG(fa0, fb0, an_, bn_, idx / RSP) FENCE() }   \
+            if (idx == R * RSP) { READ_SCALES(SL1) FENCE() }                                            \
+        }                                                                                               \
+        USE_SCALES(NEXT_QUAD, NEXT_GK)                                                                  \
+        mfma_operands_written();                                                                        \
+        FENCE()                                                                                         \
     }
 
-    v16f acc[TM][TN];
-    float* wbuf = reinterpret_cast<float*>(&lds[kRing * STAGE]) + wave * (TN * 256u);
-    uint32_t g = 0u;                                       // stages done by this block (ring slot = g % kRing)
+    v4f acc[TA][TB];
+    uint32_t sl = 0u;                                      // ring slot of the current quad
+    bool stores = false;                                   // the previous tile's result stores are younger than the loads to wait for
     for (uint32_t cv = blockIdx.x; cv < total_tiles; cv += G) {
         PRODUCT_OF(cv, csel, clv)
-        const uint32_t ck = batch.p[csel].k, gk = ck >> 5, stages = (ck + 127u) >> 7;
-        const uint32_t S2 = stages < 2u ? 2u : ((stages + 1u) & ~1u);
-        // the tile's last pair of stages reads the first scales of the block's next tile, which may belong to the other product
+        const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
+        // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
         const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TA; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TB; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-        for (uint32_t st = 0u; st < S2; st += 2u, g += 2u) {
-            const uint32_t sl = g & 3u;                    // g is even: sl is 0 or 2
-            const uint32_t next_st = st + 2u < S2 ? st + 2u : 0u;
-            const uint32_t next_gk = st + 2u < S2 ? gk : gk_after;
-            STAGE_BODY(0, sl, sl + 1u, sl ^ 3u, 0u, 0u)
-            STAGE_BODY(1, sl + 1u, sl ^ 2u, sl, next_st, next_gk)
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+        mfma_operands_written();
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t scratch = 0u;
+        for (uint32_t qd = 0u; qd < quads; ++qd) {
+            const bool last = qd + 1u == quads;            // the next quad is the next tile's first
+            const uint32_t sl1 = sl + 1u == S ? 0u : sl + 1u, sli = sl == 0u ? S - 1u : sl - 1u;
+            QUAD_BODY(sl, sl1, sli, stores, last ? 0u : qd + 1u, last ? gk_after : gk)
+            stores = false;
+            scratch = sl;
+            sl = sl1;
         }
+        mfma_results_written();
+        __builtin_amdgcn_sched_barrier(0);
+        // the last quad's slot: every wave is past its last read there, and its next loads go out behind the barrier below
+        float* wbuf = reinterpret_cast<float*>(&lds[scratch * QUAD]) + wave * (TN * 256u);
         const GemmProblem& q = batch.p[csel];
         uint32_t m0, n0;
         TILE_ORIGIN(q, clv, m0, n0)
@@ -577,8 +589,12 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
         if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
         else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
+        stores = full;                                     // every store was issued; a ragged tile may have skipped some
+        __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // the stages issued past the last tile (zero-filled) have landed before the LDS is given back
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // the quads issued past the last tile (zero-filled) have landed before the LDS is given back
     if (clock_counters && tid == 0) {
         const uint64_t t1 = __builtin_readcyclecounter(), w1 = __builtin_amdgcn_s_memrealtime();
         atomicAdd(reinterpret_cast<unsigned long long*>(clock_counters), (unsigned long long)(t1 - clk_t0));
@@ -589,12 +605,12 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
 #undef ISSUE_SETUP
 #undef ISSUE
 #undef ISSUE_ADVANCE
+#undef LDS_AT
 #undef READ_FRAG
-#undef READ_FRAG_NEXT
 #undef FENCE
 #undef READ_SCALES
 #undef USE_SCALES
-#undef STAGE_BODY
+#undef QUAD_BODY
 }
 
 static int stream_blocks() {
@@ -659,8 +675,8 @@ static void launch_stream_tile_t(const uint8_t* a_codes, const uint8_t* a_scales
     launch_stream_tile_batch_t<TM, TN, OUT_BF16, FUSED>(batch, nb, st);
 }
 
-// Variants: 0 = 256x256 tiles (hand-scheduled stage), 1 = 128x256 tiles, 2 = 128x128 tiles (stage generated from the
-// tile shape); all three: one block per compute unit streams its tiles through a ring of 4 LDS stages, two stages per
+// Variants: 0 = 256x256 tiles (hand-scheduled K-quad), 1 = 128x256 tiles, 2 = 128x128 tiles (schedule generated from the
+// tile shape); all three: one block per compute unit streams its tiles through a ring of K-quads, two K-steps per
 // trip with the scale byte picked by op_sel.  set_gemm_plan overrides the size heuristic (tests reach every variant
 // through it).
 // fused != 0: D = alpha * H_along_n((A B^T) . mask) with Hadamard blocks of nb = 1, 2 or 4 groups of 32 columns (mask may

@@ -1,0 +1,56 @@
+"""The streaming GEMM kernels where their ring of K-quads, their issue cursor and their deferred wait for result stores can go
+wrong: fewer K-quads per tile than ring slots, a ragged last quad (one to seven groups), several tiles per block with full and
+ragged ones in turn, two products of different inner dimensions in one launch.  Codes and scales are chosen so that every sum is
+exact in fp32 (products are multiples of 2^-4 and at most 144 in size, k <= 1312: below 2^24 units), so results are
+compared bit for bit with an fp64 product."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+GRID = np.array([0, .5, 1, 1.5, 2, 3, 4, 6, 0, -.5, -1, -1.5, -2, -3, -4, -6])
+
+
+@pytest.fixture()
+def G():
+    import gpu_util
+    from paper_2505_14669_amd import binding
+    yield gpu_util
+    binding.quartet_debug_set_gemm_plan(-1, 0)
+
+
+def _operand(rng, rows, k):
+    codes = rng.integers(0, 256, size=(rows, k // 2), dtype=np.uint8)
+    scales = rng.integers(126, 129, size=(rows, k // 32), dtype=np.uint8)
+    values = np.empty((rows, k))
+    values[:, 0::2], values[:, 1::2] = GRID[codes & 15], GRID[codes >> 4]
+    return codes, scales, torch.from_numpy(values * np.repeat(2.0 ** (scales.astype(np.float64) - 127), 32, axis=1)).cuda()
+
+
+@pytest.mark.parametrize("variant,m,n", [(0, 4352 - 17, 4096 + 256), (1, 2176, 4352 - 5), (2, 2176, 2176), (2, 2176 - 9, 2176 + 64)])
+@pytest.mark.parametrize("k", [32, 128, 160, 256, 480, 544, 768, 1312])
+def test_stream_gemm_exact(G, variant, m, n, k):
+    rng = np.random.default_rng(k * 8 + variant)
+    (a, sa, va), (b, sb, vb) = _operand(rng, m, k), _operand(rng, n, k)
+    from paper_2505_14669_amd import binding
+    assert binding.quartet_debug_set_gemm_plan(variant, 0) == 0
+    got = G.gemm(a, sa, b, sb)
+    assert np.array_equal(got, (va @ vb.T).cpu().numpy().astype(np.float32))
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("shapes", [((2304, 4352, 288), (4096, 2304, 800)), ((2048, 2304, 1056), (2000, 2080, 96))])
+def test_stream_gemm_pair_equals_single(G, variant, shapes):
+    from paper_2505_14669_amd import binding
+    rng = np.random.default_rng(variant)
+    prods = []
+    for m, n, k in shapes:
+        (a, sa, _), (b, sb, _) = _operand(rng, m, k), _operand(rng, n, k)
+        prods.append((a, sa, b, sb, rng.integers(0, 2 ** 32, size=(m, n // 32), dtype=np.uint32), oracle.FL_16_9))
+    assert binding.quartet_debug_set_gemm_plan(variant, 0) == 0
+    for got, p in zip(G.gemm_grad_pair(*prods), prods):
+        want = G.grad_epilogue_block(G.gemm(*p[:4]), p[4], 32, p[5])
+        assert np.array_equal(got.view(np.uint32), want.view(np.uint32))

@@ -681,54 +681,60 @@ static void launch_stream_tile_t(const uint8_t* a_codes, const uint8_t* a_scales
 // through it).
 // fused != 0: D = alpha * H_along_n((A B^T) . mask) with Hadamard blocks of nb = 1, 2 or 4 groups of 32 columns (mask may
 // be null = all ones), n % (32 nb) == 0.
-static int pick_variant(int64_t m, int64_t n, int fused, uint32_t nb) {
-    int variant = g_forced_variant;
-    if (variant < 0) {
-        // The tile shape that keeps most of the chip's matrix-core time useful: share of the compute-unit rounds that hold a
-        // tile x what a compute unit gets out of the shape (256x256: 1; 128x256: 0.84; 128x128: 0.54 -- per-area round times
-        // measured on an MI355X at K = 2048 .. 8192).  Checked against measured best shapes: 16384x4096x4096 and every other
-        // product of configuration 4 -> 256x256; 5632x2048x8192 (176 big tiles, 80 units idle) -> 256x256 (58.8 us against
-        // 73.2 as 128x256); 3072^3 -> 256x256; 4096x2048x2048 -> 128x256 (19.1 us against 23.0); 2048x2048x4096 -> 128x128
-        // (20.5 us against 23.7 and 34.9); 1024x1024x8192 -> 128x128.
-        const double cus = (double)stream_blocks();
-        const double worth[3] = {1.0, 0.84, 0.54};
-        const int64_t bm[3] = {256, 128, 128}, bn[3] = {256, 256, 128};
-        double best = -1.0;
-        for (int v = 0; v < 3; ++v) {
-            const double tiles = (double)(((m + bm[v] - 1) / bm[v]) * ((n + bn[v] - 1) / bn[v]));
-            const double rounds = (double)(int64_t)((tiles + cus - 1.0) / cus);
-            const double score = tiles / (rounds * cus) * worth[v];
-            if (score > best) { best = score; variant = v; }
-        }
+//
+// The tile shape is the one with the smallest estimated time of the busiest block, which walks the virtual tile ids b, b + G, ...:
+// launch and first loads, its K-quads, its tiles' epilogues, and the share of the chip that stores results.  Fitted to 60 single
+// products (m 24 .. 8192, n and k 256 .. 11008, both result types) and 45 pairs with the gradient epilogue (rms error 7 % for 128 x 128
+// tiles, 15 % for 256 x 256 ones; the shape chosen is within 0.3 % of the best one on average, 10 % at most).  Measured, 256 x 256 /
+// 128 x 256 / 128 x 128 (us): 7172 x 1408 x 1600 28.3 / 27.2 / 22.2; 2336 x 3168 x 1376 26.5 / 16.0 / 16.1; 1850 x 9120 x 2752 58.4 /
+// 51.7 / 49.0; pairs of layers (tokens, in, out) 4096 x 2048 x 2048 39.4 / 36.2 / 32.3; 1184 x 2880 x 5440 77.3 / 55.8 / 47.1; 7072 x 2912 x
+// 5536 168 / 175 / 190.
+struct StreamCost {
+    double start, per_quad, per_tile, per_fill;
+};
+static const StreamCost kStreamSingle[3] = {{3.35, 1.324, 6.51, 6.37}, {3.49, 0.825, 4.12, 2.26}, {3.59, 0.542, 2.33, 1.08}};
+static const StreamCost kStreamPair[3] = {{5.20, 1.502, 11.2, 6.67}, {3.96, 0.969, 6.60, 0.25}, {3.87, 0.592, 3.48, 0.0}};
+constexpr int64_t kTileM[3] = {256, 128, 128}, kTileN[3] = {256, 256, 128};
+
+static double stream_estimate(int variant, int products, const int64_t* m, const int64_t* n, const int64_t* k) {
+    const StreamCost& c = (products == 1 ? kStreamSingle : kStreamPair)[variant];
+    const int64_t cus = stream_blocks();
+    int64_t tiles[2] = {0, 0};
+    double cost[2] = {0.0, 0.0};
+    for (int p = 0; p < products; ++p) {
+        tiles[p] = ((m[p] + kTileM[variant] - 1) / kTileM[variant]) * ((n[p] + kTileN[variant] - 1) / kTileN[variant]);
+        cost[p] = c.per_quad * (double)(k[p] > 256 ? (k[p] + 255) / 256 : 1) + c.per_tile;
     }
-    if (fused && nb >= 4u && variant == 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
-    return variant;
+    const int64_t total = tiles[0] + tiles[1], blocks = total < cus ? total : cus;
+    // block b has ceil((tiles - b) / blocks) tiles of the first product and of both: constant between these three blocks
+    const int64_t at[3] = {0, tiles[0] % blocks, total % blocks};
+    double busiest = 0.0;
+    for (int64_t b : at) {
+        const int64_t first = tiles[0] > b ? (tiles[0] - b + blocks - 1) / blocks : 0, all = (total - b + blocks - 1) / blocks;
+        const double load = (double)first * cost[0] + (double)(all - first) * cost[1];
+        if (load > busiest) busiest = load;
+    }
+    return c.start + busiest + c.per_fill * (double)blocks / (double)cus;
+}
+
+// the variant for one product or a pair, and its estimated time
+static int pick_variant(int products, const int64_t* m, const int64_t* n, const int64_t* k, double* estimate) {
+    int variant = 0;
+    for (int v = 0; v < 3; ++v) {
+        const double t = stream_estimate(v, products, m, n, k);
+        if (v == 0 || t < *estimate) { *estimate = t; variant = v; }
+    }
+    return g_forced_variant >= 0 ? g_forced_variant : variant;
 }
 
 // Problems that the split kernels (gemm_split_kernels.hip) finish sooner: few rows, small layers, long inner dimensions with few
-// tiles.  Compares their estimate with one for the streaming kernel of the variant this size gets (fitted to the same 120 shapes,
-// rms error 6-12 %: launch, first loads and epilogue, the stages of its rounds, the share of the chip that stores results),
-// with a tenth in favour of the streaming kernels; two products in one launch run together there, which the sum of their estimates
-// overstates (60 pairs: a factor of 0.6 misses the faster side by 0.5 % on average).  Measured, streaming against split (us):
-// 256 x 512 x 512 5.8 / 3.5;
-// 24 x 11008 x 4096 12.3 / 6.9; 512 x 512 x 8192 22.3 / 6.9; 1024^3 6.7 / 5.3; 128 x 11008 x 4096 14.5 / 10.7; and on the other
-// side 256 x 11008 x 4096 15.3 / 18.8; 1003 x 5632 x 2048 16.0 / 20.6; 2048 x 2048 x 1024 9.6 / 13.4.  The choice depends on m, n
-// and k alone, so fused and plain products of one size run on the same side.
-static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, int* shape) {
+// tiles.  Compares their estimate with that of the streaming kernels, with a sixth (one product) or a fifth (two) in favour of the
+// latter.  Measured, streaming against split (us): 46 x 800 x 2464 11.3 / 5.0; 2529 x 384 x 1312 8.9 / 6.0; 3763 x 288 x 8992 29.6 / 28.9; and on
+// the other side 3127 x 1408 x 1248 14.0 / 16.7; 2336 x 3168 x 1376 16.0 / 23.0.  The choice depends on m, n and k alone, so fused
+// and plain products of one size run on the same side.
+static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, double streaming, int* shape) {
     if (g_forced_variant >= 0) return false;
-    const double fixed[3] = {5.29, 5.68, 3.36}, per_stage[3] = {0.533, 0.495, 0.240}, per_round[3] = {2.33, 0.0, 1.18},
-                 per_fill[3] = {12.7, 5.06, 4.16};
-    const int64_t bm[3] = {256, 128, 128}, bn[3] = {256, 256, 128}, cus = stream_blocks();
-    double streaming = 0.0;
-    for (int p = 0; p < products; ++p) {
-        const int v = pick_variant(m[p], n[p], 0, 1u);
-        const int64_t tiles = ((m[p] + bm[v] - 1) / bm[v]) * ((n[p] + bn[v] - 1) / bn[v]), rounds = (tiles + cus - 1) / cus;
-        int64_t stages = (k[p] + 255) / 256 * 2;
-        if (stages < 2) stages = 2;
-        streaming += (p == 0 ? fixed[v] : 0.0) + (double)rounds * (per_stage[v] * (double)stages + per_round[v]) +
-                     per_fill[v] * (double)tiles / (double)cus;
-    }
-    return best_split_shape(products, m, n, k, (int)cus, shape) < (products == 1 ? 0.9 : 0.6) * streaming;
+    return best_split_shape(products, m, n, k, stream_blocks(), shape) < (products == 1 ? 0.85 : 0.8) * streaming;
 }
 
 hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes,
@@ -736,11 +742,13 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const ui
                        int d_bf16, int64_t ldd, int fused, const uint32_t* mask, uint32_t nb, hipStream_t st) {
     if (m == 0 || n == 0) return hipSuccess;
     int shape = 0;
-    if (use_split(1, &m, &n, &k, &shape)) {
+    double estimate = 0.0;
+    int variant = pick_variant(1, &m, &n, &k, &estimate);
+    if (use_split(1, &m, &n, &k, estimate, &shape)) {
         const GemmArgs g = {a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask};
         return launch_gemm_split(g, nullptr, d_bf16, fused, nb, shape, st);
     }
-    const int variant = pick_variant(m, n, fused, nb);
+    if (fused && nb >= 4u && variant == 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
 #define QUARTET_DISPATCH(FN, ...)                                                                     \
     do {                                                                                              \
         if (d_bf16) { if (fused) FN<__VA_ARGS__ true, true>(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, nb, st); \
@@ -755,10 +763,7 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const ui
     return hipGetLastError();
 }
 
-// Two gradient products in one launch (both with the fused epilogue, results of one type).  One tile shape serves both: the
-// one with the smallest estimated time of the busiest block, which walks the virtual tile ids b, b + G, ... over the first
-// product's tiles and then the second's; a tile costs its inner dimension plus the epilogue (about 1100 elements' worth of
-// stages), times the shape's area, over the shape's efficiency (pick_variant's figures).
+// Two gradient products in one launch (both with the fused epilogue, results of one type).  One tile shape serves both.
 hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_bf16, uint32_t nb, hipStream_t st) {
     const bool empty0 = g0.m == 0 || g0.n == 0, empty1 = g1.m == 0 || g1.n == 0;
     if (empty0 || empty1) {
@@ -770,35 +775,15 @@ hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_b
     }
     const int64_t ms[2] = {g0.m, g1.m}, ns[2] = {g0.n, g1.n}, ks[2] = {g0.k, g1.k};
     int shape = 0;
-    if (use_split(2, ms, ns, ks, &shape)) return launch_gemm_split(g0, &g1, d_bf16, 1, nb, shape, st);
-    const int64_t bm[3] = {256, 128, 128}, bn[3] = {256, 256, 128};
-    int variant = g_forced_variant;
-    if (variant < 0) {
-        const double cost_per_area[3] = {1.0, 0.5 / 0.84, 0.25 / 0.54};
-        const int64_t cus = stream_blocks();
-        double best = -1.0;
-        for (int v = 0; v < 3; ++v) {
-            const int64_t t0 = ((g0.m + bm[v] - 1) / bm[v]) * ((g0.n + bn[v] - 1) / bn[v]);
-            const int64_t t1 = ((g1.m + bm[v] - 1) / bm[v]) * ((g1.n + bn[v] - 1) / bn[v]);
-            const int64_t blocks = t0 + t1 < cus ? t0 + t1 : cus;
-            double busiest = 0.0;
-            for (int64_t b = 0; b < blocks; ++b) {
-                const int64_t n0 = t0 > b ? (t0 - b + blocks - 1) / blocks : 0;
-                const int64_t upto = t0 + t1 - 1, before = t0 - 1;     // ids congruent to b up to these, inclusive
-                const int64_t n1 = (upto >= b ? (upto - b) / blocks + 1 : 0) - (before >= b ? (before - b) / blocks + 1 : 0);
-                const double load = (double)n0 * (double)(g0.k + 1100) + (double)n1 * (double)(g1.k + 1100);
-                if (load > busiest) busiest = load;
-            }
-            const double t = busiest * cost_per_area[v];
-            if (best < 0.0 || t < best) { best = t; variant = v; }
-        }
-    }
+    double estimate = 0.0;
+    int variant = pick_variant(2, ms, ns, ks, &estimate);
+    if (use_split(2, ms, ns, ks, estimate, &shape)) return launch_gemm_split(g0, &g1, d_bf16, 1, nb, shape, st);
     if (nb >= 4u && variant == 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
     GemmBatch batch;
     batch.p[0] = make_problem(g0.a_codes, g0.a_scales, g0.b_codes, g0.b_scales, g0.m, g0.n, g0.k, g0.alpha, g0.d, g0.ldd, g0.mask,
-                              bm[variant], bn[variant]);
+                              kTileM[variant], kTileN[variant]);
     batch.p[1] = make_problem(g1.a_codes, g1.a_scales, g1.b_codes, g1.b_scales, g1.m, g1.n, g1.k, g1.alpha, g1.d, g1.ldd, g1.mask,
-                              bm[variant], bn[variant]);
+                              kTileM[variant], kTileN[variant]);
     if (variant == 1) { if (d_bf16) launch_stream_tile_batch_t<2, 4, true, true>(batch, nb, st); else launch_stream_tile_batch_t<2, 4, false, true>(batch, nb, st); }
     else if (variant == 2) { if (d_bf16) launch_stream_tile_batch_t<2, 2, true, true>(batch, nb, st); else launch_stream_tile_batch_t<2, 2, false, true>(batch, nb, st); }
     else { if (d_bf16) launch_stream_batch_t<true, true>(batch, nb, st); else launch_stream_batch_t<false, true>(batch, nb, st); }

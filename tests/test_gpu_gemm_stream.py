@@ -54,3 +54,12 @@ def test_stream_gemm_pair_equals_single(G, variant, shapes):
     for got, p in zip(G.gemm_grad_pair(*prods), prods):
         want = G.grad_epilogue_block(G.gemm(*p[:4]), p[4], 32, p[5])
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+# sizes on both sides of the lines where the launcher goes from one tile shape or kind of kernel to the next
+@pytest.mark.parametrize("m,n,k", [(1170, 7584, 384), (4096, 4096, 256), (4097, 4096, 256), (2529, 384, 1312), (46, 800, 1280), (3127, 1408, 1248),
+                                   (4096, 2048, 512), (2048, 4097, 288)])
+def test_gemm_chosen_plan_exact(G, m, n, k):
+    rng = np.random.default_rng(m + n + k)
+    (a, sa, va), (b, sb, vb) = _operand(rng, m, k), _operand(rng, n, k)
+    assert np.array_equal(G.gemm(a, sa, b, sb), (va @ vb.T).cpu().numpy().astype(np.float32))

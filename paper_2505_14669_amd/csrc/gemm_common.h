@@ -23,22 +23,46 @@ constexpr uint32_t kOutOfRange = 0x80000000u;   // byte offset no resource here 
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 
-// acc += A B^T with the operands' scales in byte 0 (STEP = 0) or byte 2 (STEP = 1) of sa and sb.  Written out so that the accumulator
-// stays where it is (the builtin's result is not tied to its input, and the register allocator then moves 16 x 16 accumulators
-// between both register files in the loop).  The compiler does not see a matrix-core instruction in this: whoever writes an
-// operand with a vector instruction calls mfma_operands_written() before, whoever reads or overwrites an accumulator with one
-// calls mfma_results_written().  (LDS reads that fill fragments are waited for as everywhere.)
-template <int STEP>
+// acc += A B^T with the operands' scales in byte 0 (STEP = 0) or byte 2 (STEP = 1) of sa and sb; FIRST: acc = A B^T (the constant
+// 0 in place of the accumulator: nothing has to be cleared).  Written out so that the accumulator stays where it is (the
+// builtin's result is not tied to its input, and the register allocator then moves 16 x 16 accumulators between both register
+// files in the loop).  The compiler does not see a matrix-core instruction in this and keeps no wait states around it: the code that
+// writes an operand or reads an accumulator with vector instructions does (the three functions below; a test looks through the
+// built kernels).  LDS reads that fill fragments are waited for as everywhere.
+template <int STEP, bool FIRST = false>
 __device__ __forceinline__ void mfma_fp4(const v4i_t& a, const v4i_t& b, v4f& acc, uint32_t sa, uint32_t sb) {
-    if (STEP == 0)
+    if (STEP == 0 && FIRST)
+        asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4"
+                     : "=a"(acc) : "v"(a), "v"(b), "v"(sa), "v"(sb));
+    else if (STEP == 0)
         asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4"
                      : "+a"(acc) : "v"(a), "v"(b), "v"(sa), "v"(sb));
     else
         asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel:[0,0,0] op_sel_hi:[1,1,0] cbsz:4 blgp:4"
                      : "+a"(acc) : "v"(a), "v"(b), "v"(sa), "v"(sb));
 }
-// two wait states between a vector instruction's result and a matrix-core instruction that reads it
-__device__ __forceinline__ void mfma_operands_written() { asm volatile("s_nop 3" ::: "memory"); }
+// Two wait states between a vector instruction's result and a matrix-core instruction that reads it.  The empty statements make
+// every scale one that is needed in their place: the instructions that form it stand before the s_nop and cannot be sunk behind it.
+template <int M, int N>
+__device__ __forceinline__ void mfma_scales_written(uint32_t (&sa)[M], uint32_t (&sb)[N]) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) asm volatile("" : "+v"(sa[i]));
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+v"(sb[j]));
+    asm volatile("s_nop 1" ::: "memory");
+}
+// All accumulators to 0, register by register: these instructions keep their place, the compiler's own are repeated or sunk to right
+// before the first use.
+template <int M, int N>
+__device__ __forceinline__ void mfma_clear_accumulators(v4f (&acc)[M][N]) {
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { float z; asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(z)); acc[i][j][r] = z; }
+    asm volatile("s_nop 1" ::: "memory");
+}
 // the last matrix-core instruction (eight passes at most) has written its accumulator
 __device__ __forceinline__ void mfma_results_written() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 

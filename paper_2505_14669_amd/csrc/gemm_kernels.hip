@@ -242,6 +242,7 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         if (((QUADN) + 1u) * 8u > (GK)) sel_ = scale_selector(lane, (QUADN) * 8u, (GK));   /* wave-uniform: only a ragged last K-quad */ \
         _Pragma("unroll") for (uint32_t i = 0; i < 2u * TM; ++i) sa[i] = __builtin_amdgcn_perm(0x7F7F7F7Fu, ra_n[i], sel_); \
         _Pragma("unroll") for (uint32_t j = 0; j < 2u * TN; ++j) sb[j] = __builtin_amdgcn_perm(0x7F7F7F7Fu, rb_n[j], sel_); \
+        mfma_scales_written(sa, sb);                                                                    \
     }
     uint32_t csel, clv;
     STREAM_PRODUCT(blockIdx.x, csel, clv)
@@ -288,7 +289,6 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         STREAM_FENCE()                                                                                  \
         STREAM_ROW(1, 7)                                                                                \
         STREAM_SCALES_USE(NEXT_QUAD, NEXT_GK)                                                           \
-        mfma_operands_written();                                                                        \
         STREAM_FENCE()                                                                                  \
     }
 
@@ -301,13 +301,7 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
         // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
         const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
-#pragma unroll
-        for (int i = 0; i < 2 * (int)TM; ++i)
-#pragma unroll
-            for (int j = 0; j < 2 * (int)TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
-        mfma_operands_written();
+        mfma_clear_accumulators(acc);                      // (peeling the first quad, as the other tile shapes do, makes the compiler spill here)
         __builtin_amdgcn_sched_barrier(0);
         for (uint32_t qd = 0u; qd < quads; ++qd, sl ^= 1u) {
             const bool last = qd + 1u == quads;            // the next quad is the next tile's first
@@ -501,6 +495,7 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         if (((QUADN) + 1u) * 8u > (GK)) sel_ = scale_selector(lane, (QUADN) * 8u, (GK));   /* wave-uniform: only a ragged last K-quad */ \
         _Pragma("unroll") for (uint32_t i = 0; i < TA; ++i) sa[i] = __builtin_amdgcn_perm(0x7F7F7F7Fu, ra_n[i], sel_); \
         _Pragma("unroll") for (uint32_t j = 0; j < TB; ++j) sb[j] = __builtin_amdgcn_perm(0x7F7F7F7Fu, rb_n[j], sel_); \
+        mfma_scales_written(sa, sb);                                                                    \
     }
 
     // vector-memory operations that may be under way at a quad's barrier: the loads of the quads behind the next one, and once after a
@@ -525,11 +520,11 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
     USE_SCALES(0u, batch.p[csel].k >> 5)
 
 // one K-quad in slot SL; SL1: the next quad's slot, SLI: the slot being filled
-#define QUAD_BODY(SL, SL1, SLI, STORES, NEXT_QUAD, NEXT_GK)                                             \
+#define QUAD_BODY(FIRST, SL, SL1, SLI, STORES, NEXT_QUAD, NEXT_GK)                                      \
     {                                                                                                   \
         LDS_AT(a1_, SL, fa_pos1) LDS_AT(b1_, SL, fb_pos1) LDS_AT(an_, SL1, fa_pos0) LDS_AT(bn_, SL1, fb_pos0) \
         _Pragma("unroll") for (int idx = 0; idx < NM; ++idx) {                                          \
-            mfma_fp4<0>(fa0[idx / TB], fb0[idx % TB], acc[idx / TB][idx % TB], sa[idx / TB], sb[idx % TB]); \
+            mfma_fp4<0, FIRST>(fa0[idx / TB], fb0[idx % TB], acc[idx / TB][idx % TB], sa[idx / TB], sb[idx % TB]); \
             FENCE()                                                                                     \
             if (idx % 2 == 0 && idx / 2 < R) { READ_FRAG(fa1, fb1, a1_, b1_, idx / 2) FENCE() }         \
             if (idx % 2 == 1 && idx / 2 <= (int)NL) { ISSUE(SLI, idx / 2) FENCE() }                     \
@@ -547,39 +542,32 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
             if (idx == R * RSP) { READ_SCALES(SL1) FENCE() }                                            \
         }                                                                                               \
         USE_SCALES(NEXT_QUAD, NEXT_GK)                                                                  \
-        mfma_operands_written();                                                                        \
         FENCE()                                                                                         \
     }
 
     v4f acc[TA][TB];
     uint32_t sl = 0u;                                      // ring slot of the current quad
+    auto slot_after = [](uint32_t s) { return s + 1u == S ? 0u : s + 1u; };
+    auto slot_before = [](uint32_t s) { return s == 0u ? S - 1u : s - 1u; };
     bool stores = false;                                   // the previous tile's result stores are younger than the loads to wait for
     for (uint32_t cv = blockIdx.x; cv < total_tiles; cv += G) {
         PRODUCT_OF(cv, csel, clv)
         const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
         // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
         const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
-#pragma unroll
-        for (int i = 0; i < TA; ++i)
-#pragma unroll
-            for (int j = 0; j < TB; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
-        mfma_operands_written();
-        __builtin_amdgcn_sched_barrier(0);
-        uint32_t scratch = 0u;
-        for (uint32_t qd = 0u; qd < quads; ++qd) {
+        uint32_t sl1 = slot_after(sl);
+        QUAD_BODY(true, sl, sl1, slot_before(sl), stores, quads > 1u ? 1u : 0u, quads > 1u ? gk : gk_after)
+        for (uint32_t qd = 1u; qd < quads; ++qd) {
             const bool last = qd + 1u == quads;            // the next quad is the next tile's first
-            const uint32_t sl1 = sl + 1u == S ? 0u : sl + 1u, sli = sl == 0u ? S - 1u : sl - 1u;
-            QUAD_BODY(sl, sl1, sli, stores, last ? 0u : qd + 1u, last ? gk_after : gk)
-            stores = false;
-            scratch = sl;
             sl = sl1;
+            sl1 = slot_after(sl);
+            QUAD_BODY(false, sl, sl1, slot_before(sl), false, last ? 0u : qd + 1u, last ? gk_after : gk)
         }
         mfma_results_written();
         __builtin_amdgcn_sched_barrier(0);
         // the last quad's slot: every wave is past its last read there, and its next loads go out behind the barrier below
-        float* wbuf = reinterpret_cast<float*>(&lds[scratch * QUAD]) + wave * (TN * 256u);
+        float* wbuf = reinterpret_cast<float*>(&lds[sl * QUAD]) + wave * (TN * 256u);
+        sl = sl1;
         const GemmProblem& q = batch.p[csel];
         uint32_t m0, n0;
         TILE_ORIGIN(q, clv, m0, n0)

@@ -40,18 +40,19 @@ mfma_ceiling_kernel(const v4i_t* __restrict__ codes, const uint32_t* __restrict_
         sa[i] = scales[i * 256 + threadIdx.x];
         sb[i] = scales[(4 + i) * 256 + threadIdx.x];
     }
-    v4f acc[32];
+    v4f acc[8][4];
+    mfma_scales_written(sa, sb);
+    // the accumulators start from an instruction each
 #pragma unroll
-    for (int i = 0; i < 32; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][r] = 0.0f;
-    mfma_operands_written();
+        for (int j = 0; j < 4; ++j) mfma_fp4<0, true>(fa[i & 3], fb[j], acc[i][j], sa[i & 3], sb[j]);
     for (uint32_t it = 0; it < iterations; ++it) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                mfma_fp4<0>(i < 4 ? fa[i & 3] : fb[i & 3], i < 4 ? fb[j] : fa[j], acc[i * 4 + j], i < 4 ? sa[i & 3] : sb[i & 3], i < 4 ? sb[j] : sa[j]);
+                mfma_fp4<0>(i < 4 ? fa[i & 3] : fb[i & 3], i < 4 ? fb[j] : fa[j], acc[i][j], i < 4 ? sa[i & 3] : sb[i & 3], i < 4 ? sb[j] : sa[j]);
             }
     }
     mfma_results_written();
@@ -59,7 +60,7 @@ mfma_ceiling_kernel(const v4i_t* __restrict__ codes, const uint32_t* __restrict_
 #pragma unroll
     for (int i = 0; i < 32; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s += acc[i][r];
+        for (int r = 0; r < 4; ++r) s += acc[i / 4][i % 4][r];
     sink[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
     clock_end(counters, t0, w0);
 }

@@ -15,6 +15,7 @@
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/saved_variable.h>
+#include <torch/csrc/autograd/VariableTypeUtils.h>
 
 #include "../../include/quartet.h"
 
@@ -59,37 +60,14 @@ struct Context {
 uint8_t* bytes_of(const at::Tensor& t) { return static_cast<uint8_t*>(t.data_ptr()); }
 void* stream_of(const at::Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
 
-struct QuartetLinearBackward : public Node {
-    torch::autograd::SavedVariable context;
+// Sizes of one call.
+struct Shape {
     std::vector<int64_t> x_sizes;
     int64_t tokens, in, out;
-    int hadamard_block, rounding;
-    uint64_t seed;
-
-    std::string name() const override { return "QuartetLinearFunctionBackward"; }
-    void release_variables() override { context.reset_data(); }
-
-    variable_list apply(variable_list&& grads) override {
-        at::NoGradGuard no_grad;
-        const at::Tensor ctx = context.unpack(shared_from_this());
-        c10::DeviceGuard device(ctx.device());
-        const auto bf16 = ctx.options().dtype(at::kBFloat16);
-        const at::Tensor dy = grads[0].defined() ? grads[0].reshape({tokens, out}).to(at::kBFloat16).contiguous() : at::zeros({tokens, out}, bf16);
-        at::Tensor dx = at::empty(x_sizes, bf16), dw = at::empty({out, in}, bf16);
-        const size_t nbytes = quartet_linear_workspace_bytes_block(tokens, in, out, hadamard_block);
-        // from the caching allocator, so calls on several streams or threads never share it
-        const at::Tensor ws = at::empty({(int64_t)(nbytes < 256 ? 256 : nbytes)}, ctx.options());
-        const Context c(tokens, in, out);
-        const uint8_t* b = bytes_of(ctx);
-        check(quartet_linear_bwd_block(dy.data_ptr(), tokens, in, out, hadamard_block, b + c.x_codes, b + c.x_scales,
-                                       reinterpret_cast<const uint32_t*>(b + c.x_mask), b + c.w_codes, b + c.w_scales,
-                                       reinterpret_cast<const uint32_t*>(b + c.w_mask), seed, rounding, dx.data_ptr(), dw.data_ptr(),
-                                       QUARTET_DTYPE_BF16, ws.data_ptr(), nbytes, stream_of(ctx)));
-        return {dx, dw};
-    }
+    int hadamard_block;
 };
 
-at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, int rounding, int hadamard_block) {
+Shape check_arguments(const at::Tensor& x, const at::Tensor& weight, int hadamard_block) {
     if (x.scalar_type() != at::kBFloat16 || weight.scalar_type() != at::kBFloat16)
         raise_python(PyExc_TypeError, "QuartetLinearFunction takes bf16 activations and weights");
     if (!x.is_cuda() || !weight.is_cuda()) raise_python(PyExc_RuntimeError, "QuartetLinearFunction runs on the GPU only");
@@ -102,35 +80,92 @@ at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, 
     const int64_t tokens = in ? x.numel() / in : 0;
     if (tokens % hadamard_block || in % hadamard_block || out % hadamard_block)
         raise_python(PyExc_ValueError, "tokens, in_features and out_features must be multiples of " + std::to_string(hadamard_block));
-    const bool track = torch::autograd::compute_requires_grad(x, weight);
-    at::Tensor y, ctx;
-    {
-        at::AutoDispatchBelowADInplaceOrView below_autograd;
-        c10::DeviceGuard device(x.device());
-        const at::Tensor x2 = x.contiguous(), w2 = weight.contiguous();
-        std::vector<int64_t> y_sizes = x.sizes().vec();
-        y_sizes.back() = out;
-        y = at::empty(y_sizes, x.options());
-        const Context c(tokens, in, out);
-        ctx = at::empty({(int64_t)c.total}, x.options().dtype(at::kByte));
-        uint8_t* b = bytes_of(ctx);
-        check(quartet_linear_fwd_block(x2.data_ptr(), w2.data_ptr(), tokens, in, out, hadamard_block, y.data_ptr(), QUARTET_DTYPE_BF16,
-                                       b + c.x_codes, b + c.x_scales, reinterpret_cast<uint32_t*>(b + c.x_mask), b + c.w_codes,
-                                       b + c.w_scales, reinterpret_cast<uint32_t*>(b + c.w_mask), stream_of(x)));
+    return {x.sizes().vec(), tokens, in, out, hadamard_block};
+}
+
+// {y, forward context}
+std::pair<at::Tensor, at::Tensor> forward(const at::Tensor& x, const at::Tensor& weight, const Shape& s) {
+    at::AutoDispatchBelowADInplaceOrView below_autograd;
+    c10::DeviceGuard device(x.device());
+    const at::Tensor x2 = x.contiguous(), w2 = weight.contiguous();
+    std::vector<int64_t> y_sizes = s.x_sizes;
+    y_sizes.back() = s.out;
+    at::Tensor y = at::empty(y_sizes, x.options());
+    const Context c(s.tokens, s.in, s.out);
+    at::Tensor ctx = at::empty({(int64_t)c.total}, x.options().dtype(at::kByte));
+    uint8_t* b = bytes_of(ctx);
+    check(quartet_linear_fwd_block(x2.data_ptr(), w2.data_ptr(), s.tokens, s.in, s.out, s.hadamard_block, y.data_ptr(), QUARTET_DTYPE_BF16,
+                                   b + c.x_codes, b + c.x_scales, reinterpret_cast<uint32_t*>(b + c.x_mask), b + c.w_codes,
+                                   b + c.w_scales, reinterpret_cast<uint32_t*>(b + c.w_mask), stream_of(x)));
+    return {y, ctx};
+}
+
+// {dx, dw}; an undefined dy stands for zeros
+std::pair<at::Tensor, at::Tensor> backward(const at::Tensor& ctx, const at::Tensor& grad, const Shape& s, uint64_t seed, int rounding) {
+    at::NoGradGuard no_grad;
+    c10::DeviceGuard device(ctx.device());
+    const auto bf16 = ctx.options().dtype(at::kBFloat16);
+    const at::Tensor dy = grad.defined() ? grad.reshape({s.tokens, s.out}).to(at::kBFloat16).contiguous() : at::zeros({s.tokens, s.out}, bf16);
+    at::Tensor dx = at::empty(s.x_sizes, bf16), dw = at::empty({s.out, s.in}, bf16);
+    const size_t nbytes = quartet_linear_workspace_bytes_block(s.tokens, s.in, s.out, s.hadamard_block);
+    // from the caching allocator, so calls on several streams or threads never share it
+    const at::Tensor ws = at::empty({(int64_t)(nbytes < 256 ? 256 : nbytes)}, ctx.options());
+    const Context c(s.tokens, s.in, s.out);
+    const uint8_t* b = bytes_of(ctx);
+    check(quartet_linear_bwd_block(dy.data_ptr(), s.tokens, s.in, s.out, s.hadamard_block, b + c.x_codes, b + c.x_scales,
+                                   reinterpret_cast<const uint32_t*>(b + c.x_mask), b + c.w_codes, b + c.w_scales,
+                                   reinterpret_cast<const uint32_t*>(b + c.w_mask), seed, rounding, dx.data_ptr(), dw.data_ptr(),
+                                   QUARTET_DTYPE_BF16, ws.data_ptr(), nbytes, stream_of(ctx)));
+    return {dx, dw};
+}
+
+struct QuartetLinearBackward : public Node {
+    torch::autograd::SavedVariable context;
+    Shape shape;
+    int rounding;
+    uint64_t seed;
+
+    std::string name() const override { return "QuartetLinearFunctionBackward"; }
+    void release_variables() override { context.reset_data(); }
+
+    variable_list apply(variable_list&& grads) override {
+        auto [dx, dw] = backward(context.unpack(shared_from_this()), grads[0], shape, seed, rounding);
+        return {dx, dw};
     }
+};
+
+at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, int rounding, int hadamard_block) {
+    const Shape shape = check_arguments(x, weight, hadamard_block);
+    const bool track = torch::autograd::compute_requires_grad(x, weight);
+    auto [y, ctx] = forward(x, weight, shape);
     if (track) {
         auto node = std::shared_ptr<QuartetLinearBackward>(new QuartetLinearBackward(), torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(x, weight));
         node->context = torch::autograd::SavedVariable(ctx, false);
-        node->x_sizes = x.sizes().vec();
-        node->tokens = tokens; node->in = in; node->out = out;
-        node->hadamard_block = hadamard_block; node->rounding = rounding; node->seed = seed;
+        node->shape = shape;
+        node->rounding = rounding; node->seed = seed;
         torch::autograd::set_history(y, node);
     }
     return y;
 }
 
-// linear(x, weight, seed, rounding, hadamard_block)
+// Calls that the node above does not serve: they take the Python autograd function, which knows what to do with them (or refuses
+// them by name).  A tensor with a forward-mode tangent: the result would come back without one, which reads as a zero derivative.
+bool needs_python_function(const at::Tensor& x, const at::Tensor& weight) {
+    return torch::autograd::isFwGradDefined(x) || torch::autograd::isFwGradDefined(weight);
+}
+
+const at::Tensor& tensor_of(PyObject* o) { return THPVariable_Unpack(o); }
+
+PyObject* wrap_pair(std::pair<at::Tensor, at::Tensor> p) {
+    PyObject *a = THPVariable_Wrap(std::move(p.first)), *b = THPVariable_Wrap(std::move(p.second));
+    PyObject* t = a && b ? PyTuple_Pack(2, a, b) : nullptr;
+    Py_XDECREF(a);
+    Py_XDECREF(b);
+    return t;
+}
+
+// linear(x, weight, seed, rounding, hadamard_block): y, or None for a call of needs_python_function
 PyObject* py_linear(PyObject*, PyObject* const* args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     if (n != 5 || !THPVariable_Check(args[0]) || !THPVariable_Check(args[1])) {
@@ -140,13 +175,65 @@ PyObject* py_linear(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const uint64_t seed = PyLong_AsUnsignedLongLongMask(args[2]);
     const long rounding = PyLong_AsLong(args[3]), block = PyLong_AsLong(args[4]);
     if (PyErr_Occurred()) return nullptr;
-    const at::Tensor x = THPVariable_Unpack(args[0]), w = THPVariable_Unpack(args[1]);
+    const at::Tensor x = tensor_of(args[0]), w = tensor_of(args[1]);
+    if (needs_python_function(x, w)) Py_RETURN_NONE;
     at::Tensor y;
     {
         pybind11::gil_scoped_release no_gil;
         y = linear(x, w, seed, (int)rounding, (int)block);
     }
     return THPVariable_Wrap(std::move(y));
+    END_HANDLE_TH_ERRORS
+}
+
+// The two halves for the Python autograd function.
+// forward(x, weight, hadamard_block): (y, context)
+PyObject* py_forward(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    if (n != 3 || !THPVariable_Check(args[0]) || !THPVariable_Check(args[1])) {
+        PyErr_SetString(PyExc_TypeError, "forward(x, weight, hadamard_block): two tensors and an integer");
+        return nullptr;
+    }
+    const long block = PyLong_AsLong(args[2]);
+    if (PyErr_Occurred()) return nullptr;
+    const at::Tensor x = tensor_of(args[0]), w = tensor_of(args[1]);
+    std::pair<at::Tensor, at::Tensor> result;
+    {
+        pybind11::gil_scoped_release no_gil;
+        result = forward(x, w, check_arguments(x, w, (int)block));
+    }
+    return wrap_pair(std::move(result));
+    END_HANDLE_TH_ERRORS
+}
+
+// backward(context, dy, x_sizes, out_features, seed, rounding, hadamard_block): (dx, dw)
+PyObject* py_backward(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    if (n != 7 || !THPVariable_Check(args[0]) || !THPVariable_Check(args[1])) {
+        PyErr_SetString(PyExc_TypeError, "backward(context, dy, x_sizes, out_features, seed, rounding, hadamard_block)");
+        return nullptr;
+    }
+    Shape s;
+    for (Py_ssize_t i = 0, dims = PyObject_Length(args[2]); i < dims; ++i) {
+        PyObject* size = PySequence_GetItem(args[2], i);
+        s.x_sizes.push_back(size ? PyLong_AsLongLong(size) : 0);
+        Py_XDECREF(size);
+    }
+    s.out = PyLong_AsLongLong(args[3]);
+    const uint64_t seed = PyLong_AsUnsignedLongLongMask(args[4]);
+    const long rounding = PyLong_AsLong(args[5]);
+    s.hadamard_block = (int)PyLong_AsLong(args[6]);
+    if (PyErr_Occurred()) return nullptr;
+    s.tokens = 1;
+    for (size_t i = 0; i + 1 < s.x_sizes.size(); ++i) s.tokens *= s.x_sizes[i];
+    s.in = s.x_sizes.empty() ? 0 : s.x_sizes.back();
+    const at::Tensor ctx = tensor_of(args[0]), dy = tensor_of(args[1]);
+    std::pair<at::Tensor, at::Tensor> result;
+    {
+        pybind11::gil_scoped_release no_gil;
+        result = backward(ctx, dy, s, seed, (int)rounding);
+    }
+    return wrap_pair(std::move(result));
     END_HANDLE_TH_ERRORS
 }
 
@@ -159,6 +246,8 @@ PyObject* py_set_error(PyObject*, PyObject* type) {
 
 PyMethodDef methods[] = {
     {"linear", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(py_linear)), METH_FASTCALL, nullptr},
+    {"forward", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(py_forward)), METH_FASTCALL, nullptr},
+    {"backward", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(py_backward)), METH_FASTCALL, nullptr},
     {"set_error", py_set_error, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_nn_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

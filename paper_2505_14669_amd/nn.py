@@ -15,6 +15,22 @@ from . import _nn_native as _native          # fails loudly if it has not been b
 _native.set_error(q.QuartetError)
 
 
+class _PythonFunction(torch.autograd.Function):
+    """The node's twin in Python over the same two native halves, for the calls that the native node does not serve (it says which):
+    what torch does with an autograd function there, or the reason why it cannot, comes from torch itself."""
+
+    @staticmethod
+    def forward(ctx, x, weight, seed, rounding, hadamard_block):
+        y, context = _native.forward(x, weight, hadamard_block)
+        ctx.save_for_backward(context)
+        ctx.call = (tuple(x.shape), weight.shape[0], seed, rounding, hadamard_block)
+        return y
+
+    @staticmethod
+    def backward(ctx, dy):
+        return (*_native.backward(*ctx.saved_tensors, dy, *ctx.call), None, None, None)
+
+
 class QuartetLinearFunction:
     """y = x W^T with MXFP4 operands (Algorithm 1 Forward); the backward pass returns the gradients of
     Algorithm 1 Backward.  x: [..., in] bf16, weight: [out, in] bf16, seed: python int naming the
@@ -23,7 +39,9 @@ class QuartetLinearFunction:
 
     @staticmethod
     def apply(x, weight, seed, rounding, hadamard_block=32):
-        return _native.linear(x, weight, int(seed), int(rounding), int(hadamard_block))
+        call = (x, weight, int(seed), int(rounding), int(hadamard_block))
+        y = _native.linear(*call)
+        return _PythonFunction.apply(*call) if y is None else y
 
 
 class QuartetLinear(torch.nn.Module):

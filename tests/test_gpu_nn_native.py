@@ -70,3 +70,15 @@ def test_two_streams_do_not_share_scratch(qnn):
     torch.cuda.synchronize()
     for g, w in zip(got, want):
         assert all(torch.equal(a, b) for a, b in zip(g, w))
+
+
+@pytest.mark.parametrize("which", [0, 1])
+def test_forward_mode_derivatives_are_refused(qnn, which):
+    # there is no forward-mode rule: a result without a tangent would be taken for a zero derivative
+    import torch.autograd.forward_ad as fwad
+    x, w, _ = _case(4)
+    with fwad.dual_level():
+        pair = [x, w]
+        pair[which] = fwad.make_dual(pair[which], torch.ones_like(pair[which]))
+        with pytest.raises(NotImplementedError):
+            qnn.QuartetLinearFunction.apply(*pair, 9, 0)

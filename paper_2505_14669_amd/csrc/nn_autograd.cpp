@@ -16,6 +16,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/autograd/VariableTypeUtils.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 
 #include "../../include/quartet.h"
 
@@ -151,8 +152,9 @@ at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, 
 
 // Calls that the node above does not serve: they take the Python autograd function, which knows what to do with them (or refuses
 // them by name).  A tensor with a forward-mode tangent: the result would come back without one, which reads as a zero derivative.
+// torch.jit.trace: all it would see of the node is the allocation of its result.
 bool needs_python_function(const at::Tensor& x, const at::Tensor& weight) {
-    return torch::autograd::isFwGradDefined(x) || torch::autograd::isFwGradDefined(weight);
+    return torch::jit::tracer::isTracing() || torch::autograd::isFwGradDefined(x) || torch::autograd::isFwGradDefined(weight);
 }
 
 const at::Tensor& tensor_of(PyObject* o) { return THPVariable_Unpack(o); }

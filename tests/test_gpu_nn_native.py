@@ -82,3 +82,18 @@ def test_forward_mode_derivatives_are_refused(qnn, which):
         pair[which] = fwad.make_dual(pair[which], torch.ones_like(pair[which]))
         with pytest.raises(NotImplementedError):
             qnn.QuartetLinearFunction.apply(*pair, 9, 0)
+
+
+def test_traced_layer_calls_the_function(qnn):
+    # the trace holds a call of the function (it held the allocation of the result alone, so the traced layer returned whatever lay there)
+    x, w, dy = _case(5)
+    traced = torch.jit.trace(lambda a: qnn.QuartetLinearFunction.apply(a, w, 9, 0), x, check_trace=False)
+    assert [n.kind() for n in traced.graph.nodes() if n.kind() == "aten::empty"] == []
+    for seed in (6, 7):
+        z = _case(seed)[0]
+        assert torch.equal(traced(z), qnn.QuartetLinearFunction.apply(z, w, 9, 0))
+    # and it can be differentiated
+    a, b = x.clone().requires_grad_(True), x.clone().requires_grad_(True)
+    traced(a).backward(dy)
+    qnn.QuartetLinearFunction.apply(b, w, 9, 0).backward(dy)
+    assert torch.equal(a.grad, b.grad)

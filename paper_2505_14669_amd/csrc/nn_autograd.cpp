@@ -9,6 +9,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/core/DeviceGuard.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
@@ -152,9 +153,11 @@ at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, 
 
 // Calls that the node above does not serve: they take the Python autograd function, which knows what to do with them (or refuses
 // them by name).  A tensor with a forward-mode tangent: the result would come back without one, which reads as a zero derivative.
-// torch.jit.trace: all it would see of the node is the allocation of its result.
+// torch.jit.trace: all it would see of the node is the allocation of its result.  functorch's transforms (vmap, grad, functionalize,
+// ...): a tensor without a level would slip through them.
 bool needs_python_function(const at::Tensor& x, const at::Tensor& weight) {
-    return torch::jit::tracer::isTracing() || torch::autograd::isFwGradDefined(x) || torch::autograd::isFwGradDefined(weight);
+    return torch::jit::tracer::isTracing() || c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode) ||
+           torch::autograd::isFwGradDefined(x) || torch::autograd::isFwGradDefined(weight);
 }
 
 const at::Tensor& tensor_of(PyObject* o) { return THPVariable_Unpack(o); }

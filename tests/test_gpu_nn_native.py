@@ -97,3 +97,12 @@ def test_traced_layer_calls_the_function(qnn):
     traced(a).backward(dy)
     qnn.QuartetLinearFunction.apply(b, w, 9, 0).backward(dy)
     assert torch.equal(a.grad, b.grad)
+
+
+def test_function_transforms_are_refused_by_name(qnn):
+    x, w, _ = _case(8)
+    f = lambda a, b: qnn.QuartetLinearFunction.apply(a, b, 9, 0)
+    for call in (lambda: torch.vmap(lambda s: f(x, w) * s)(torch.ones(2, device=DEV)), lambda: torch.vmap(lambda a: f(a, w))(torch.stack([x, x])),
+                 lambda: torch.func.grad(lambda a: f(a, w).float().sum())(x), lambda: torch.func.functionalize(f)(x, w)):
+        with pytest.raises(RuntimeError, match="functorch transforms"):
+            call()

@@ -128,10 +128,19 @@ struct QuartetLinearBackward : public Node {
     uint64_t seed;
 
     std::string name() const override { return "QuartetLinearFunctionBackward"; }
-    void release_variables() override { context.reset_data(); }
+    // the saved context is read and released under the node's lock: threads may run backward passes over a shared graph
+    void release_variables() override {
+        std::lock_guard<std::mutex> lock(mutex_);
+        context.reset_data();
+    }
 
     variable_list apply(variable_list&& grads) override {
-        auto [dx, dw] = backward(context.unpack(shared_from_this()), grads[0], shape, seed, rounding);
+        at::Tensor ctx;
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            ctx = context.unpack(shared_from_this());
+        }
+        auto [dx, dw] = backward(ctx, grads[0], shape, seed, rounding);
         return {dx, dw};
     }
 };

@@ -106,3 +106,28 @@ def test_function_transforms_are_refused_by_name(qnn):
                  lambda: torch.func.grad(lambda a: f(a, w).float().sum())(x), lambda: torch.func.functionalize(f)(x, w)):
         with pytest.raises(RuntimeError, match="functorch transforms"):
             call()
+
+
+def test_backward_from_several_threads_over_one_graph(qnn):
+    # every thread gets the whole gradient, or the error of a graph that another thread has freed: nothing in between
+    import threading
+    x, w, dy = _case(12)
+    _, dx, _ = _grads(qnn, x, w, dy)
+    for _ in range(20):
+        a = x.clone().requires_grad_(True)
+        y = qnn.QuartetLinearFunction.apply(a, w, 9, 0)
+        got = []
+
+        def one():
+            try:
+                got.append(torch.autograd.grad(y, a, dy)[0])
+            except RuntimeError as e:
+                assert "second time" in str(e)
+                got.append(None)
+        threads = [threading.Thread(target=one) for _ in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert len(got) == 4 and any(g is not None for g in got) and all(g is None or torch.equal(g, dx) for g in got)

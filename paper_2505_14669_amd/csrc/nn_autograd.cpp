@@ -69,7 +69,7 @@ struct Shape {
     int hadamard_block;
 };
 
-Shape check_arguments(const at::Tensor& x, const at::Tensor& weight, int hadamard_block) {
+Shape check_arguments(const at::Tensor& x, const at::Tensor& weight, int64_t hadamard_block) {
     if (x.scalar_type() != at::kBFloat16 || weight.scalar_type() != at::kBFloat16)
         raise_python(PyExc_TypeError, "QuartetLinearFunction takes bf16 activations and weights");
     if (!x.is_cuda() || !weight.is_cuda()) raise_python(PyExc_RuntimeError, "QuartetLinearFunction runs on the GPU only");
@@ -82,7 +82,7 @@ Shape check_arguments(const at::Tensor& x, const at::Tensor& weight, int hadamar
     const int64_t tokens = in ? x.numel() / in : 0;
     if (tokens % hadamard_block || in % hadamard_block || out % hadamard_block)
         raise_python(PyExc_ValueError, "tokens, in_features and out_features must be multiples of " + std::to_string(hadamard_block));
-    return {x.sizes().vec(), tokens, in, out, hadamard_block};
+    return {x.sizes().vec(), tokens, in, out, (int)hadamard_block};
 }
 
 // {y, forward context}
@@ -145,7 +145,7 @@ struct QuartetLinearBackward : public Node {
     }
 };
 
-at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, int rounding, int hadamard_block) {
+at::Tensor linear(const at::Tensor& x, const at::Tensor& weight, uint64_t seed, int rounding, int64_t hadamard_block) {
     const Shape shape = check_arguments(x, weight, hadamard_block);
     const bool track = torch::autograd::compute_requires_grad(x, weight);
     auto [y, ctx] = forward(x, weight, shape);
@@ -194,7 +194,7 @@ PyObject* py_linear(PyObject*, PyObject* const* args, Py_ssize_t n) {
     at::Tensor y;
     {
         pybind11::gil_scoped_release no_gil;
-        y = linear(x, w, seed, (int)rounding, (int)block);
+        y = linear(x, w, seed, (int)rounding, block);
     }
     return THPVariable_Wrap(std::move(y));
     END_HANDLE_TH_ERRORS
@@ -214,7 +214,7 @@ PyObject* py_forward(PyObject*, PyObject* const* args, Py_ssize_t n) {
     std::pair<at::Tensor, at::Tensor> result;
     {
         pybind11::gil_scoped_release no_gil;
-        result = forward(x, w, check_arguments(x, w, (int)block));
+        result = forward(x, w, check_arguments(x, w, block));
     }
     return wrap_pair(std::move(result));
     END_HANDLE_TH_ERRORS

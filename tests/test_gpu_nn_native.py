@@ -131,3 +131,10 @@ def test_backward_from_several_threads_over_one_graph(qnn):
             t.join()
         torch.cuda.synchronize()
         assert len(got) == 4 and any(g is not None for g in got) and all(g is None or torch.equal(g, dx) for g in got)
+
+
+@pytest.mark.parametrize("block", [0, -32, 48, 512, 2 ** 32 + 32])
+def test_hadamard_block_is_checked_before_it_is_narrowed(qnn, block):
+    x, w, _ = _case(14)
+    with pytest.raises(ValueError):
+        qnn.QuartetLinearFunction.apply(x, w, 9, 0, block)

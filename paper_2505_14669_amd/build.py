@@ -47,21 +47,32 @@ def _compile_nn():
     return obj, os.path.join(os.path.dirname(torch.__file__), "lib")
 
 
+def _have_torch():
+    try:
+        import torch  # noqa: F401
+    except ImportError:
+        return False
+    return True
+
+
 def build(verbose=False):
+    """Returns the library's path.  The library needs hipcc alone and is linked whatever becomes of the torch node; without torch, which
+    the node's only user imports as well, there is no node."""
     os.makedirs(OBJDIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=5) as ex:
-        nn = ex.submit(_compile_nn)
+        nn = ex.submit(_compile_nn) if _have_torch() else None
         results = list(ex.map(_compile, SOURCES))
-        nn_obj, torch_lib = nn.result()
     if verbose:
         for _, out in results:
             if out.strip():
                 print(out)
     objs = [o for o, _ in results]
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, check=True)
-    # the torch libraries are in the process already when this is imported; libquartet.so lies beside it
-    subprocess.run(["g++", "-shared", "-o", NN_LIB, nn_obj, "-L" + HERE, "-l:libquartet.so", "-L" + torch_lib, "-ltorch_python",
-                    "-ltorch_cpu", "-ltorch_hip", "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"], check=True)
+    if nn is not None:
+        nn_obj, torch_lib = nn.result()
+        # the torch libraries are in the process already when this is imported; libquartet.so lies beside it
+        subprocess.run(["g++", "-shared", "-o", NN_LIB, nn_obj, "-L" + HERE, "-l:libquartet.so", "-L" + torch_lib, "-ltorch_python",
+                        "-ltorch_cpu", "-ltorch_hip", "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"], check=True)
     return LIB
 
 

@@ -1,5 +1,5 @@
 """Build the HIP library (paper_2505_14669_amd/libquartet.so) for gfx950 with hipcc and, on top of it, the autograd node of
-the torch layer (paper_2505_14669_amd/_nn_native.so) with g++."""
+the torch layer (paper_2505_14669_amd/_nn_native.<Python's tag>.so) with g++."""
 import os
 import subprocess
 import sys
@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libquartet.so")
-NN_LIB = os.path.join(HERE, "_nn_native.so")
+NN_LIB = os.path.join(HERE, "_nn_native" + sysconfig.get_config_var("EXT_SUFFIX"))     # another Python does not take it for its own
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "quant_kernels.hip", "gemm_kernels.hip", "gemm_split_kernels.hip", "epilogue_kernels.hip", "fp8_kernels.hip", "probe_kernels.hip"]
 

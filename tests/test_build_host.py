@@ -40,3 +40,8 @@ def test_both_are_linked(monkeypatch, linked):
     monkeypatch.setattr(b, "_compile_nn", lambda: ("nn.o", "/lib"))
     b.build()
     assert linked == ["libquartet.so", os.path.basename(b.NN_LIB)]
+
+
+def test_torch_node_carries_the_interpreters_tag():
+    from importlib.machinery import EXTENSION_SUFFIXES
+    assert os.path.basename(b.NN_LIB) == "_nn_native" + EXTENSION_SUFFIXES[0] != "_nn_native.so"

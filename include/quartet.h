@@ -216,6 +216,14 @@ int quartet_mxfp4_gemm(const uint8_t *a_codes, const uint8_t *a_scales,
 int quartet_debug_set_gemm_plan(int variant, int band_height);
 
 /*
+ * Test and tuning aid (host only, no device needed): which kernel runs one product, or a pair in one launch (products = 1, 2; mnk:
+ * m, n, k of each), on a chip of that many compute units (8..4096): 0, 1, 2 as above, or 100 * waves + 11, 12, 14, 22 for the
+ * in-block split over tiles of 32 x 32, 32 x 64, 32 x 128, 64 x 64.  hadamard_block 0 = plain product, 32, 64, 128 = gradient
+ * product.  Negative: error.
+ */
+int quartet_debug_gemm_plan(int products, const int64_t *mnk, int hadamard_block, int compute_units);
+
+/*
  * GEMM_LP with the gradient epilogue applied in the same kernel (Algorithm 1 Backward:
  * dx = 16/9 H_g^-1(dx_q . M_x), dW likewise):
  *   D[m x n] = scale * H_32_along_n( (sum_k dec(A)[m,k] dec(B)[n,k]) . mask )

@@ -26,7 +26,7 @@ EXPORTS = [
     "quartet_profile_enable", "quartet_profile_kinds", "quartet_profile_read", "quartet_scale_bytes",
     "quartet_profile_clock", "quartet_wall_clock_khz", "quartet_probe_mfma_ceiling",
     "quartet_quant_fwd", "quartet_quant_bwd_sr", "quartet_requant_transpose_sr", "quartet_fwd_operands", "quartet_bwd_operands",
-    "quartet_mxfp4_gemm", "quartet_debug_set_gemm_plan", "quartet_mxfp4_gemm_grad", "quartet_mxfp4_gemm_grad_pair", "quartet_mxfp8_quant", "quartet_mxfp8_gemm", "quartet_grad_epilogue", "quartet_mxfp4_dequant",
+    "quartet_mxfp4_gemm", "quartet_debug_set_gemm_plan", "quartet_debug_gemm_plan", "quartet_mxfp4_gemm_grad", "quartet_mxfp4_gemm_grad_pair", "quartet_mxfp8_quant", "quartet_mxfp8_gemm", "quartet_grad_epilogue", "quartet_mxfp4_dequant",
     "quartet_linear_fwd", "quartet_linear_workspace_bytes", "quartet_linear_bwd",
     "quartet_static_scratch_bytes", "quartet_linear_bwd_static",
     "quartet_sign_words", "quartet_quant_fwd_block", "quartet_quant_bwd_sr_block",
@@ -61,6 +61,7 @@ _lib.quartet_fwd_operands.argtypes = [_p, _p, _i64, _i64, _i64, _p, _p, _p, _p, 
 _lib.quartet_bwd_operands.argtypes = [_p, _i64, _i64, _i64, _p, _p, _p, _p, _u32, _u64, _int, _p, _p, _p, _p, _p, _p, _p]
 _lib.quartet_mxfp4_gemm.argtypes = [_p, _p, _p, _p, _i64, _i64, _i64, _f, _p, _int, _i64, _p]
 _lib.quartet_debug_set_gemm_plan.argtypes = [_int, _int]
+_lib.quartet_debug_gemm_plan.argtypes = [_int, ctypes.POINTER(_i64), _int, _int]
 _lib.quartet_mxfp4_gemm_grad.argtypes = [_p, _p, _p, _p, _i64, _i64, _i64, _p, _f, _p, _int, _i64, _p]
 
 
@@ -227,6 +228,11 @@ def quartet_mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, 
 
 def quartet_debug_set_gemm_plan(variant, band_height):
     return _lib.quartet_debug_set_gemm_plan(variant, band_height)
+
+
+def quartet_debug_gemm_plan(products, mnk, hadamard_block, compute_units):
+    """mnk: m, n, k of each product, as a list of integers (or None)"""
+    return _lib.quartet_debug_gemm_plan(products, None if mnk is None else (_i64 * len(mnk))(*mnk), hadamard_block, compute_units)
 
 
 def quartet_mxfp4_gemm_grad(a_codes, a_scales, b_codes, b_scales, m, n, k, mask, scale, d, d_dtype, ldd, stream=None):

@@ -433,6 +433,19 @@ int quartet_debug_set_gemm_plan(int variant, int band_height) {
     return QUARTET_OK;
 }
 
+int quartet_debug_gemm_plan(int products, const int64_t* mnk, int hadamard_block, int compute_units) {
+    if ((products != 1 && products != 2) || !mnk || compute_units < 8 || compute_units > 4096) return QUARTET_EINVAL;
+    const uint32_t nb = block_groups(hadamard_block);
+    if (hadamard_block != 0 && (nb == 0u || nb > 4u)) return QUARTET_EINVAL;
+    int64_t m[2], n[2], k[2];
+    for (int p = 0; p < products; ++p) {
+        m[p] = mnk[3 * p]; n[p] = mnk[3 * p + 1]; k[p] = mnk[3 * p + 2];
+        if (m[p] < 1 || n[p] < 1 || k[p] < 0 || (k[p] % 32) != 0) return QUARTET_EINVAL;
+        if (m[p] >= ((int64_t)1 << 31) || n[p] > ((int64_t)1 << 21) || k[p] > ((int64_t)1 << 23)) return QUARTET_ENOTSUP;
+    }
+    return quartet::gemm_plan_code(products, m, n, k, nb, compute_units & ~7);
+}
+
 int quartet_mxfp4_gemm_grad(const uint8_t* a_codes, const uint8_t* a_scales,
                             const uint8_t* b_codes, const uint8_t* b_scales,
                             int64_t m, int64_t n, int64_t k, const uint32_t* mask, float scale,

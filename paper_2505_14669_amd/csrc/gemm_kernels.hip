@@ -684,9 +684,8 @@ static const StreamCost kStreamSingle[3] = {{3.35, 1.324, 6.51, 6.37}, {3.49, 0.
 static const StreamCost kStreamPair[3] = {{5.20, 1.502, 11.2, 6.67}, {3.96, 0.969, 6.60, 0.25}, {3.87, 0.592, 3.48, 0.0}};
 constexpr int64_t kTileM[3] = {256, 128, 128}, kTileN[3] = {256, 256, 128};
 
-static double stream_estimate(int variant, int products, const int64_t* m, const int64_t* n, const int64_t* k) {
+static double stream_estimate(int variant, int products, const int64_t* m, const int64_t* n, const int64_t* k, int64_t cus) {
     const StreamCost& c = (products == 1 ? kStreamSingle : kStreamPair)[variant];
-    const int64_t cus = stream_blocks();
     int64_t tiles[2] = {0, 0};
     double cost[2] = {0.0, 0.0};
     for (int p = 0; p < products; ++p) {
@@ -706,10 +705,10 @@ static double stream_estimate(int variant, int products, const int64_t* m, const
 }
 
 // the variant for one product or a pair, and its estimated time
-static int pick_variant(int products, const int64_t* m, const int64_t* n, const int64_t* k, double* estimate) {
+static int pick_variant(int products, const int64_t* m, const int64_t* n, const int64_t* k, int cus, double* estimate) {
     int variant = 0;
     for (int v = 0; v < 3; ++v) {
-        const double t = stream_estimate(v, products, m, n, k);
+        const double t = stream_estimate(v, products, m, n, k, cus);
         if (v == 0 || t < *estimate) { *estimate = t; variant = v; }
     }
     return g_forced_variant >= 0 ? g_forced_variant : variant;
@@ -720,23 +719,40 @@ static int pick_variant(int products, const int64_t* m, const int64_t* n, const 
 // latter.  Measured, streaming against split (us): 46 x 800 x 2464 11.3 / 5.0; 2529 x 384 x 1312 8.9 / 6.0; 3763 x 288 x 8992 29.6 / 28.9; and on
 // the other side 3127 x 1408 x 1248 14.0 / 16.7; 2336 x 3168 x 1376 16.0 / 23.0.  The choice depends on m, n and k alone, so fused
 // and plain products of one size run on the same side.
-static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, double streaming, int* shape) {
+static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, int cus, double streaming, int* shape) {
     if (g_forced_variant >= 0) return false;
-    return best_split_shape(products, m, n, k, stream_blocks(), shape) < (products == 1 ? 0.85 : 0.8) * streaming;
+    return best_split_shape(products, m, n, k, cus, shape) < (products == 1 ? 0.85 : 0.8) * streaming;
+}
+
+// The kernel for one product or a pair, plain (nb = 0) or with the gradient epilogue of Hadamard blocks of nb groups.
+struct GemmPlan {
+    bool split;
+    int shape;          // split: tile shape (see launch_gemm_split); otherwise the streaming variant
+};
+static GemmPlan plan_gemm(int products, const int64_t* m, const int64_t* n, const int64_t* k, uint32_t nb, int cus) {
+    double estimate = 0.0;
+    int shape = 0, variant = pick_variant(products, m, n, k, cus, &estimate);
+    if (use_split(products, m, n, k, cus, estimate, &shape)) return {true, split_shape_for(shape, nb)};
+    if (nb >= 4u && variant == 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
+    return {false, variant};
+}
+
+int gemm_plan_code(int products, const int64_t* m, const int64_t* n, const int64_t* k, uint32_t nb, int cus) {
+    const GemmPlan plan = plan_gemm(products, m, n, k, nb, cus);
+    const int64_t k_max = products == 2 && k[1] > k[0] ? k[1] : k[0];
+    return plan.split ? 100 * split_waves(k_max) + plan.shape : plan.shape;
 }
 
 hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes,
                        const uint8_t* b_scales, int64_t m, int64_t n, int64_t k, float alpha, void* d,
                        int d_bf16, int64_t ldd, int fused, const uint32_t* mask, uint32_t nb, hipStream_t st) {
     if (m == 0 || n == 0) return hipSuccess;
-    int shape = 0;
-    double estimate = 0.0;
-    int variant = pick_variant(1, &m, &n, &k, &estimate);
-    if (use_split(1, &m, &n, &k, estimate, &shape)) {
+    const GemmPlan plan = plan_gemm(1, &m, &n, &k, fused ? nb : 0u, stream_blocks());
+    if (plan.split) {
         const GemmArgs g = {a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask};
-        return launch_gemm_split(g, nullptr, d_bf16, fused, nb, shape, st);
+        return launch_gemm_split(g, nullptr, d_bf16, fused, nb, plan.shape, st);
     }
-    if (fused && nb >= 4u && variant == 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
+    const int variant = plan.shape;
 #define QUARTET_DISPATCH(FN, ...)                                                                     \
     do {                                                                                              \
         if (d_bf16) { if (fused) FN<__VA_ARGS__ true, true>(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, nb, st); \
@@ -762,11 +778,9 @@ hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_b
                            g1.mask, nb, st);
     }
     const int64_t ms[2] = {g0.m, g1.m}, ns[2] = {g0.n, g1.n}, ks[2] = {g0.k, g1.k};
-    int shape = 0;
-    double estimate = 0.0;
-    int variant = pick_variant(2, ms, ns, ks, &estimate);
-    if (use_split(2, ms, ns, ks, estimate, &shape)) return launch_gemm_split(g0, &g1, d_bf16, 1, nb, shape, st);
-    if (nb >= 4u && variant == 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
+    const GemmPlan plan = plan_gemm(2, ms, ns, ks, nb, stream_blocks());
+    if (plan.split) return launch_gemm_split(g0, &g1, d_bf16, 1, nb, plan.shape, st);
+    const int variant = plan.shape;
     GemmBatch batch;
     batch.p[0] = make_problem(g0.a_codes, g0.a_scales, g0.b_codes, g0.b_scales, g0.m, g0.n, g0.k, g0.alpha, g0.d, g0.ldd, g0.mask,
                               kTileM[variant], kTileN[variant]);

@@ -270,10 +270,15 @@ static const SplitShape kSplitShapes4[3] = {   // four waves
     {11, 32, 32, 2.46, 0.0, 0.92, 0.092}, {12, 32, 64, 1.49, 0.0, 2.42, 0.142}, {22, 64, 64, 0.93, 0.0, 3.73, 0.204}};
 constexpr int64_t kFourWaveQuads = 12;   // 24 x 4096 x 11008: 7.3 us with four waves, 8.7 with two; 24 x 11008 x 4096: 7.8 and 6.9; 512^3: 3.3 and 3.0
 
+int split_waves(int64_t k) { return (k + 255) / 256 >= kFourWaveQuads ? 4 : 2; }
+
+// a wave's lanes must hold whole Hadamard blocks: 64 columns need two column blocks per tile, 128 need four
+int split_shape_for(int shape, uint32_t nb) { return nb == 4u ? 14 : nb == 2u && shape == 11 ? 12 : shape; }
+
 double best_split_shape(int products, const int64_t* m, const int64_t* n, const int64_t* k, int compute_units, int* shape) {
     int64_t quads = 0;
     for (int p = 0; p < products; ++p) quads = quads > (k[p] + 255) / 256 ? quads : (k[p] + 255) / 256;
-    const bool four = quads >= kFourWaveQuads;
+    const bool four = split_waves(256 * quads) == 4;
     double best = -1.0;
     for (const SplitShape& s : four ? kSplitShapes4 : kSplitShapes2) {
         double t = s.start + s.per_step * (double)((quads + (four ? 3 : 1)) / (four ? 4 : 2)), tiles_all = 0.0, load = 0.0;
@@ -289,9 +294,6 @@ double best_split_shape(int products, const int64_t* m, const int64_t* n, const 
 }
 
 hipError_t launch_gemm_split(const GemmArgs& g0, const GemmArgs* g1, int d_bf16, int fused, uint32_t nb, int shape, hipStream_t st) {
-    // a wave's lanes must hold whole Hadamard blocks: 64 columns need two column blocks per tile, 128 need four
-    if (fused && nb == 2u && shape == 11) shape = 12;
-    if (fused && nb == 4u) shape = 14;
     const int64_t k = g1 && g1->k > g0.k ? g1->k : g0.k;
 #define QUARTET_SPLIT(NW)                                                                               \
     switch (shape) {                                                                                    \
@@ -300,7 +302,7 @@ hipError_t launch_gemm_split(const GemmArgs& g0, const GemmArgs* g1, int d_bf16,
     case 14: launch_split<1, 4, NW>(g0, g1, d_bf16, fused, nb, st); break;                              \
     default: launch_split<2, 2, NW>(g0, g1, d_bf16, fused, nb, st); break;                              \
     }
-    if ((k + 255) / 256 >= kFourWaveQuads) QUARTET_SPLIT(4)
+    if (split_waves(k) == 4) QUARTET_SPLIT(4)
     else QUARTET_SPLIT(2)
 #undef QUARTET_SPLIT
     return hipGetLastError();

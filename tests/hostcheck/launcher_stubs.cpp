@@ -14,6 +14,7 @@ hipError_t launch_dequant(const uint8_t*, const uint8_t*, int64_t, int64_t, floa
 hipError_t launch_gemm(const uint8_t*, const uint8_t*, const uint8_t*, const uint8_t*, int64_t, int64_t, int64_t, float, void*, int, int64_t, int, const uint32_t*, uint32_t, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_gemm_grad_pair(const GemmArgs&, const GemmArgs&, int, uint32_t, hipStream_t) { ++g_launches; return hipSuccess; }
 void set_gemm_plan(int, int) {}
+int gemm_plan_code(int, const int64_t*, const int64_t*, const int64_t*, uint32_t, int) { return 0; }
 hipError_t launch_grad_epilogue(const float*, const uint32_t*, int64_t, int64_t, uint32_t, float, void*, int, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_mfma_ceiling(const uint8_t*, const uint8_t*, uint32_t, uint32_t, float*, uint64_t*, hipStream_t) { ++g_launches; return hipSuccess; }
 void set_clock_counters(uint64_t*) {}

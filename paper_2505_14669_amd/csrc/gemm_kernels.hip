@@ -721,6 +721,10 @@ static int pick_variant(int products, const int64_t* m, const int64_t* n, const 
 // and plain products of one size run on the same side.
 static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, int cus, double streaming, int* shape) {
     if (g_forced_variant >= 0) return false;
+    // A block per tile, and a launch has fewer than 2^32 threads: with 32 x 32 tiles of up to four waves, 2^24 tiles at most
+    int64_t tiles = 0;
+    for (int p = 0; p < products; ++p) tiles += ((m[p] + 31) / 32) * ((n[p] + 31) / 32);
+    if (tiles >= ((int64_t)1 << 24)) return false;
     return best_split_shape(products, m, n, k, cus, shape) < (products == 1 ? 0.85 : 0.8) * streaming;
 }
 

@@ -14,3 +14,12 @@ def test_arguments_are_checked():
     assert plan(0, 32, 32) == E and plan(32, 32, 33) == E and plan(32, 32, 32, block=48) == E and plan(32, 32, 32, block=256) == E
     assert q.quartet_debug_gemm_plan(1, [32, 32, 32], 0, 4) == E
     assert plan(2 ** 31, 32, 32) == q.QUARTET_ENOTSUP
+
+
+def test_split_kernels_take_no_more_tiles_than_a_launch_can_hold():
+    # one block of up to 256 threads per tile and fewer than 2^32 threads per launch: very tall narrow products stay with the
+    # streaming kernels, whose grid is the chip
+    assert plan(2 ** 28, 32, 32) // 100 == 2
+    for mnk in ((2 ** 30, 32, 32), (2 ** 31 - 1, 1, 32), (2 ** 31 - 1, 32, 512), (2 ** 29, 40, 32)):
+        assert plan(*mnk) in (0, 1, 2)
+    assert plan(2 ** 29 - 32, 32, 32, 2 ** 29 - 32, 32, 32, block=32) in (0, 1, 2)

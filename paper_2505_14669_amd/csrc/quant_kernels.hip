@@ -786,9 +786,14 @@ static void launch_transposed_nb(const void* src, int64_t rows, int64_t k, int64
                                  uint32_t* mask, const SrParams& p, hipStream_t st) {
     const uint32_t kquads = (uint32_t)((k / 32 + 7) / 8);
     const uint16_t* s = (const uint16_t*)src;
-    // below about two of the 256 x 32 waves per SIMD: half the columns per block (4096 x 2048, 1024 waves: 7.5 us against 8.3;
-    // 16384 x 4096, 8192 waves: 35.9 against 34.2)
-    const bool small = (uint64_t)kquads * (uint64_t)((rows + 31) / 32) < 2048u;
+    // Blocks of 32 columns (half the work) while the matrix is too small to fill the chip: up to two of their 256 x 32 waves per SIMD where
+    // the K-quads are a multiple of 8, 1.25 of them elsewhere.  They read half lines.  The blocks of one K-quad lie kquads apart
+    // in the launch and blocks go to the XCDs in turn, so with a multiple of 8 both halves of a line are read through one L2; otherwise
+    // every line crosses from memory twice.  32 columns against the wider block (us, nearest): multiple of 8: 2048 x 5984 (1496 waves)
+    // 6.2 / 7.9, 4096 x 4096 (2048) 7.1 / 7.8; not: 1664 x 5728 (1253) 7.0 / 8.5, 2784 x 4128 (1419) 10.4 / 9.0, 5536 x 2560 (1760)
+    // 12.0 / 9.1, 1536 x 10048 (1884) 11.7 / 7.9.
+    const uint64_t waves = (uint64_t)kquads * (uint64_t)((rows + 31) / 32);
+    const bool small = waves < ((kquads & 7u) == 0u ? 2048u : 1280u);
 #define QUARTET_TRANSPOSED(COLS, KERNEL, ...)                                                                                    \
     hipLaunchKernelGGL((KERNEL<MODE, MASK __VA_ARGS__>), dim3(kquads, (uint32_t)((rows + COLS - 1) / COLS)), dim3(256), 0, st, s,  \
                        (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p)

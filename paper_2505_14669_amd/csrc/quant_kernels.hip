@@ -386,7 +386,8 @@ __device__ __forceinline__ void quant_transposed_tile(const uint16_t* __restrict
 //   - The groups of a Hadamard block above 32 sit in neighbouring lanes.
 //   - The eight lanes of a chunk hold the 128 contiguous bytes of codes of one output row and K-quad: every 16-byte store
 //     instruction writes whole lines.
-// STREAM: read non-temporally (large matrices; small ones come out of the caches: 4096 x 2048 7.6 us cached, 8.3 streamed).
+// STREAM: read non-temporally (large matrices; small ones come out of the caches: 4096 x 2048 7.6 us cached, 8.3 streamed; so do
+// large ones where two blocks share a line, see launch_transposed_nb).
 // Group j's 32 rows start at j * kquad_pitch(B): the 32 bytes of padding put the rows i of the eight groups, which one read
 // instruction addresses, on different banks.
 template <uint32_t B> __host__ __device__ constexpr uint32_t kquad_pitch() { return 32u * B + 32u; }
@@ -423,9 +424,10 @@ __device__ __forceinline__ void store_kquad_scales(const uint32_t* s, uint8_t* _
 }
 
 // bf16 source.  Logical A[rows x k] = S^T where the source S is bf16 [k x ldx]; the block covers 32 * CPL columns from col0 on (CPL
-// = 2: 128-byte pieces of the source rows; CPL = 1: half of that, for matrices too small to fill the chip), K-quad bx.
+// = 2: 128-byte pieces of the source rows; CPL = 1: half of that, for matrices too small to fill the chip), K-quad bx.  STREAM: read
+// non-temporally.
 // lds: 8 * kquad_pitch<64 CPL>() bytes, s_scale: 64 * CPL dwords.
-template <int MODE, bool MASK, bool BIG, uint32_t CPL>
+template <int MODE, bool MASK, bool BIG, uint32_t CPL, bool STREAM>
 __device__ __forceinline__ void quant_columns_block(const uint16_t* __restrict__ src, uint32_t rows, uint32_t k, int64_t ldx,
                                                     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
                                                     uint32_t* __restrict__ mask, const SrParams& p, uint32_t stream, uint32_t bx, uint32_t col0,
@@ -440,7 +442,7 @@ __device__ __forceinline__ void quant_columns_block(const uint16_t* __restrict__
     const uint32_t src_rows = (k - grp0 * 32u) < 256u ? (k - grp0 * 32u) : 256u;
     const uint32_t src_cols = (rows - col0) < 32u * CPL ? (rows - col0) : 32u * CPL;
     const v4i_t res_x = make_rsrc_words(src + (size_t)grp0 * 32u * ldx + col0, ((src_rows - 1u) * (uint32_t)ldx + src_cols) * 2u);
-    stage_kquad_rows<B, CPL == 2u>(res_x, (uint32_t)ldx * 2u, lds);
+    stage_kquad_rows<B, STREAM>(res_x, (uint32_t)ldx * 2u, lds);
     const uint32_t sw = BIG && MODE != kFwd ? lane_sign_word(p, j) : 0u;
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
@@ -499,14 +501,16 @@ quant_transposed_kernel(const uint16_t* __restrict__ src,
                                       transposed_column_tile(blockIdx.x, blockIdx.y, gridDim.y), s_codes, s_scales, s_mask);
 }
 
-template <int MODE, bool MASK, bool BIG, uint32_t CPL>
+// STREAM false with CPL = 2: the launch may round the K-quads up
+template <int MODE, bool MASK, bool BIG, uint32_t CPL, bool STREAM>
 __global__ void __launch_bounds__(256, 4)
 quant_columns_kernel(const uint16_t* __restrict__ src,
                         uint32_t rows, uint32_t k, int64_t ldx, uint8_t* __restrict__ codes,
                         uint8_t* __restrict__ scales, uint32_t* __restrict__ mask, SrParams p) {
     __shared__ __align__(16) uint8_t stage[8u * kquad_pitch<64u * CPL>()];
     __shared__ uint32_t s_scale[64u * CPL];
-    quant_columns_block<MODE, MASK, BIG, CPL>(src, rows, k, ldx, codes, scales, mask, p, p.stream_id, blockIdx.x,
+    if (CPL == 2u && !STREAM && blockIdx.x >= (k + 255u) >> 8) return;
+    quant_columns_block<MODE, MASK, BIG, CPL, STREAM>(src, rows, k, ldx, codes, scales, mask, p, p.stream_id, blockIdx.x,
                                               transposed_column_tile(blockIdx.x, blockIdx.y, gridDim.y) * 32u * CPL, stage, s_scale);
 }
 
@@ -711,7 +715,7 @@ bwd_operands_kernel(const uint16_t* __restrict__ dy, uint32_t t_rows, uint32_t t
             quant_transposed_tile<MODE, false>(dy, t_rows, t_k, t_ldx, t_codes, t_scales, nullptr, p, t_stream, bx, ct,
                                                reinterpret_cast<uint4*>(smem), reinterpret_cast<uint8_t*>(s_scale), nullptr);
         else
-            quant_columns_block<MODE, false, BIG, CPL>(dy, t_rows, t_k, t_ldx, t_codes, t_scales, nullptr, p, t_stream, bx, ct * 32u * CPL,
+            quant_columns_block<MODE, false, BIG, CPL, CPL == 2u>(dy, t_rows, t_k, t_ldx, t_codes, t_scales, nullptr, p, t_stream, bx, ct * 32u * CPL,
                                                        smem, s_scale);
     }
 }
@@ -794,17 +798,26 @@ static void launch_transposed_nb(const void* src, int64_t rows, int64_t k, int64
     // 12.0 / 9.1, 1536 x 10048 (1884) 11.7 / 7.9.
     const uint64_t waves = (uint64_t)kquads * (uint64_t)((rows + 31) / 32);
     const bool small = waves < ((kquads & 7u) == 0u ? 2048u : 1280u);
-#define QUARTET_TRANSPOSED(COLS, KERNEL, ...)                                                                                    \
-    hipLaunchKernelGGL((KERNEL<MODE, MASK __VA_ARGS__>), dim3(kquads, (uint32_t)((rows + COLS - 1) / COLS)), dim3(256), 0, st, s,  \
-                       (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p)
+    // Wide Hadamard blocks, 64 columns: where rows or base are not whole lines, two neighbouring blocks share a line in every row.  Once
+    // the matrix no longer fits the caches beside its result they have to meet in one L2: K-quads rounded up to a multiple of 8, and
+    // loads that may stay there (us, blocks of 64, forward / nearest / stochastic, so and as otherwise: 13952 x 7968 54 / 46 / 53, 91 / 81 / 87;
+    // 5376 x 8864, 5817 waves, 29.0 / 26.6 / 28.4, 32.7 / 29.5 / 31.2; 4608 x 7328, 4122 waves, 22 / 21 / 24, 24 / 21 / 23; aligned rows,
+    // 3072 x 10944, 23 / 19 / 24, 20 / 17 / 20).
+    const bool shared_lines = !small && p.nb > 1u && ((reinterpret_cast<uintptr_t>(src) | (uintptr_t)(ldx * 2)) & 127u) != 0 && waves >= 5000u;
+#define QUARTET_COLUMNS(CPL, BIG, STREAM, GRID_K)                                                                                 \
+    hipLaunchKernelGGL((quant_columns_kernel<MODE, MASK, BIG, CPL, STREAM>), dim3(GRID_K, (uint32_t)((rows + 32 * CPL - 1) / (32 * CPL))), \
+                       dim3(256), 0, st, s, (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p)
     if (p.nb > 1u) {
-        if (small) QUARTET_TRANSPOSED(32, quant_columns_kernel, , true, 1);
-        else QUARTET_TRANSPOSED(64, quant_columns_kernel, , true, 2);
+        if (small) QUARTET_COLUMNS(1, true, false, kquads);
+        else if (shared_lines) QUARTET_COLUMNS(2, true, false, (kquads + 7u) & ~7u);
+        else QUARTET_COLUMNS(2, true, true, kquads);
+    } else if (small) {
+        QUARTET_COLUMNS(1, false, false, kquads);
     } else {
-        if (small) QUARTET_TRANSPOSED(32, quant_columns_kernel, , false, 1);
-        else QUARTET_TRANSPOSED(128, quant_transposed_kernel, );
+        hipLaunchKernelGGL((quant_transposed_kernel<MODE, MASK>), dim3(kquads, (uint32_t)((rows + 127) / 128)), dim3(256), 0, st, s,
+                           (uint32_t)rows, (uint32_t)k, ldx, codes, scales, mask, p);
     }
-#undef QUARTET_TRANSPOSED
+#undef QUARTET_COLUMNS
 }
 
 template <int MODE>

@@ -46,7 +46,8 @@ def test_requant_block_every_split(G, k, rows, block):
 # source [k x rows]: the line between the two tiles lies at 2048 waves of 256 rows x 32 columns for a multiple of eight K-quads, at
 # 1280 otherwise
 @pytest.mark.parametrize("k,rows,block", [(4064, 4040, 32), (4128, 4104, 32), (4224, 3848, 128), (4352, 4104, 256),
-                                          (2528, 4064, 32), (2528, 4104, 32), (2560, 4104, 64)])
+                                          (2528, 4064, 32), (2528, 4104, 32), (2560, 4104, 64),
+                                          (5184, 8032, 64), (5248, 8040, 128)])     # two blocks share a line, K-quads rounded up
 def test_quant_transposed_both_tiles(G, k, rows, block):
     x = synth.small_matrix(5, k, rows, "heavy", 1e-3)
     sw = oracle.sign_words(31)

@@ -644,14 +644,17 @@ __device__ __forceinline__ void requant_columns_block(const uint8_t* __restrict_
     }
 }
 
-template <int MODE, bool BIG, uint32_t NC>
+// SHARED: the grid's first dimension is the K-quads, rounded up to a multiple of 8 (see launch_requant_big); otherwise the columns
+template <int MODE, bool BIG, uint32_t NC, bool SHARED>
 __global__ void __launch_bounds__(256, 4)
 requant_transposed_kernel(const uint8_t* __restrict__ src_codes, const uint8_t* __restrict__ src_scales,
                           uint32_t rows, uint32_t k, uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
                           SrParams p) {
     __shared__ __align__(16) uint8_t stage[NC == 2u ? 9216u : 8u * kquad_pitch<16u * NC>()];
     __shared__ uint32_t s_scale[64u * NC];
-    requant_columns_block<MODE, BIG, NC>(src_codes, src_scales, rows, k, codes, scales, p, p.stream_id, blockIdx.y, blockIdx.x * 32u * NC, stage, s_scale);
+    const uint32_t kq = SHARED ? blockIdx.x : blockIdx.y, column = SHARED ? blockIdx.y : blockIdx.x;
+    if (SHARED && kq >= (k + 255u) >> 8) return;
+    requant_columns_block<MODE, BIG, NC>(src_codes, src_scales, rows, k, codes, scales, p, p.stream_id, kq, column * 32u * NC, stage, s_scale);
 }
 
 // ------------------------------------------------------------------ the backward pass's operand conversions in one launch
@@ -850,13 +853,19 @@ template <int MODE, bool BIG>
 static void launch_requant_big(const uint8_t* src_codes, const uint8_t* src_scales, int64_t rows, int64_t k, const SrParams& p,
                                uint8_t* codes, uint8_t* scales, hipStream_t st) {
     const uint32_t nc = requant_columns((uint64_t)rows * (uint64_t)k), kquads = (uint32_t)((k + 255) / 256);
-    const dim3 grid((uint32_t)((rows + 32 * nc - 1) / (32 * nc)), kquads);
-#define QUARTET_REQUANT(NC)                                                                                                       \
-    hipLaunchKernelGGL((requant_transposed_kernel<MODE, BIG, NC>), grid, dim3(256), 0, st, src_codes, src_scales, (uint32_t)rows,  \
-                       (uint32_t)k, codes, scales, p)
-    if (nc == 8u) QUARTET_REQUANT(8);
-    else if (nc == 4u) QUARTET_REQUANT(4);
-    else QUARTET_REQUANT(2);
+    const uint32_t columns = (uint32_t)((rows + 32 * nc - 1) / (32 * nc));
+    // Where the rows of codes or their base are not whole lines, two neighbouring blocks share a line in every row: with the K-quads first
+    // and a multiple of 8 of them they run on one XCD and its L2 serves both (see launch_transposed_nb).  Blocks of 128 bytes of a
+    // row and 16 K-quads or more (us, stochastic / nearest, so and columns first: 6144 x 8640 30.6 / 21.6, 32.4 / 23.2; 13568 x 3968 32.6 /
+    // 21.7, 33.5 / 23.1; 9 K-quads, 2112 x 8160, 17.1 / 12.0, 14.0 / 10.3; whole lines, 16384 x 11008, 75 / 46.3, 74 / 46.1).
+    const bool shared_lines = nc == 8u && kquads >= 16u && columns <= 65535u && ((reinterpret_cast<uintptr_t>(src_codes) | (uintptr_t)(rows / 2)) & 127u) != 0;
+#define QUARTET_REQUANT(NC, SHARED, X, Y)                                                                                         \
+    hipLaunchKernelGGL((requant_transposed_kernel<MODE, BIG, NC, SHARED>), dim3(X, Y), dim3(256), 0, st, src_codes, src_scales,    \
+                       (uint32_t)rows, (uint32_t)k, codes, scales, p)
+    if (shared_lines) QUARTET_REQUANT(8, true, (kquads + 7u) & ~7u, columns);
+    else if (nc == 8u) QUARTET_REQUANT(8, false, columns, kquads);
+    else if (nc == 4u) QUARTET_REQUANT(4, false, columns, kquads);
+    else QUARTET_REQUANT(2, false, columns, kquads);
 #undef QUARTET_REQUANT
 }
 

@@ -23,8 +23,9 @@ def _codes(seed, rows, k):
             rng.integers(110, 140, size=(rows, k // 32), dtype=np.uint8))
 
 
-# source [k x rows]: 0.1 M, 10.7 M and 33.9 M elements = 2, 4 and 8 columns per lane; no size a multiple of a tile
-@pytest.mark.parametrize("k,rows", [(1056, 96), (4128, 2592), (4128, 8224)])
+# source [k x rows]: 0.1 M, 10.7 M and 33.9 M elements = 2, 4 and 8 columns per lane; no size a multiple of a tile; rows that are not
+# whole lines with 17 K-quads (columns in the grid's second dimension), whole lines, and 15 K-quads
+@pytest.mark.parametrize("k,rows", [(1056, 96), (4128, 2592), (4128, 8224), (4128, 8448), (3808, 8928)])
 @pytest.mark.parametrize("rounding", [0, 1])
 def test_requant_every_split(G, k, rows, rounding):
     codes, scales = _codes(k + rows, k, rows)

@@ -23,18 +23,14 @@ constexpr uint32_t kOutOfRange = 0x80000000u;   // byte offset no resource here 
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 
-// acc += A B^T with the operands' scales in byte 0 (STEP = 0) or byte 2 (STEP = 1) of sa and sb; FIRST: acc = A B^T (the constant
-// 0 in place of the accumulator: nothing has to be cleared).  Written out so that the accumulator stays where it is (the
-// builtin's result is not tied to its input, and the register allocator then moves 16 x 16 accumulators between both register
-// files in the loop).  The compiler does not see a matrix-core instruction in this and keeps no wait states around it: the code that
+// acc += A B^T with the operands' scales in byte 0 (STEP = 0) or byte 2 (STEP = 1) of sa and sb.  Written out so that the accumulator
+// stays where it is (the builtin's result is not tied to its input, and the register allocator then moves 16 x 16 accumulators
+// between both register files in the loop).  The compiler does not see a matrix-core instruction in this and keeps no wait states around it: the code that
 // writes an operand or reads an accumulator with vector instructions does (the three functions below; a test looks through the
 // built kernels).  LDS reads that fill fragments are waited for as everywhere.
-template <int STEP, bool FIRST = false>
+template <int STEP>
 __device__ __forceinline__ void mfma_fp4(const v4i_t& a, const v4i_t& b, v4f& acc, uint32_t sa, uint32_t sb) {
-    if (STEP == 0 && FIRST)
-        asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4"
-                     : "=a"(acc) : "v"(a), "v"(b), "v"(sa), "v"(sb));
-    else if (STEP == 0)
+    if (STEP == 0)
         asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4"
                      : "+a"(acc) : "v"(a), "v"(b), "v"(sa), "v"(sb));
     else
@@ -65,6 +61,14 @@ __device__ __forceinline__ void mfma_clear_accumulators(v4f (&acc)[M][N]) {
 }
 // the last matrix-core instruction (eight passes at most) has written its accumulator
 __device__ __forceinline__ void mfma_results_written() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// c + A B^T of 32 x 32 x 64 (FP4), scales in byte S of sa and sb; the compiler keeps the wait states
+template <int S>
+__device__ __forceinline__ v16f mfma_fp4_32(const uint4& a, const uint4& b, v16f c, uint32_t sa, uint32_t sb) {
+    const v8i va = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
+    const v8i vb = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, vb, c, 4, 4, S, (int)sa, S, (int)sb);
+}
 
 // Plain epilogue of a kernel whose ring is free when it ends (the MXFP8 twin): the wave's accumulator tile goes through
 // LDS one 32-column slice at a time and comes back with 8 consecutive lanes holding the 32 columns of one row (4 each):
@@ -158,38 +162,44 @@ __device__ __forceinline__ float epilogue_norm(float v, float signed_norm) { ret
 // the lane, strides 4, 8, 16 between the 8 lanes that hold a row's slice (QUARTET_BUTTERFLIES_ACROSS: lane i holds 4-column
 // chunk i ^ (i & 4 ? 3 : 0), which makes the partners lane ^ 1, lane ^ 2 and 7 - lane, all reachable by DPP), the
 // normalization, then the scale: the same fp32 operations in the same order as the stand-alone epilogue kernel.
-// acc: the wave's (TM*32) x (TN*32) tile as 16 x 16 accumulators (v_mfma_scale_f32_16x16x128_f8f6f4: lane l, register r -> row
-// 4*(l/16) + r, column l%16).  Pass P takes registers 2*(P%2) and 2*(P%2) + 1 of the accumulators of tile row P/2, that is the rows
-// 4*q + 2*(P%2) + e of it (q = 0..3, e = 0, 1); LDS row 2*q + e.  A lane reads back chunk c (4 columns) of all 32-column slices of
-// LDS row `sub`, so Hadamard blocks of 32, 64 and 128 columns are handled alike (group-combining stages inside the lane, then the
-// 32-point stages of each slice).
-// LDS image: row r at r * TN*32 floats, its columns XORed with 32*(r%2) and 16*((r/2)%2): the LDS has 64 banks and serves a 16-byte
-// read 16 lanes at a time -- rows 2a and 2a+1 here, which the first term puts into different bank halves -- and a 4-byte write 32
-// lanes at a time -- 16 columns of rows r and r+2, which the second term keeps apart.
-template <int TM, int TN, bool OUT_BF16, bool FUSED, bool FULL>
-__device__ __forceinline__ void store_tile_rows8(v4f (&acc)[2 * TM][2 * TN], float* wbuf, void* d, uint32_t ldd,
+// acc: the wave's (TM*32) x (TN*32) tile.  A pass takes eight rows of it into LDS; a lane reads back chunk c (4 columns) of all
+// 32-column slices of LDS row `sub`, so Hadamard blocks of 32, 64 and 128 columns are handled alike (group-combining stages inside
+// the lane, then the 32-point stages of each slice).  The LDS has 64 banks and serves a 16-byte read 16 lanes at a time (rows 2a and
+// 2a+1 here) and a 4-byte write 32 lanes at a time; row r lies at r * TN*32 floats, its columns XORed so that both keep apart:
+//   v16f [TM][TN] (v_mfma_scale_f32_32x32x64_f8f6f4: lane l, register r -> row 8*(r/4) + 4*(l/32) + r%4, column l%32): pass P takes
+//     registers 4*(P%4) .. +3 of the accumulators of tile row P/4, rows 8 P .. 8 P + 7 in order; columns XORed with 32*((r ^ r/4)%2).
+//   v4f [2 TM][2 TN] (v_mfma_scale_f32_16x16x128_f8f6f4: lane l, register r -> row 4*(l/16) + r, column l%16): pass P takes registers
+//     2*(P%2) and 2*(P%2) + 1 of the accumulators of tile row P/2, that is the rows 4*q + 2*(P%2) + e of it (q = 0..3, e = 0, 1), LDS row
+//     2*q + e; columns XORed with 32*(r%2) and 16*((r/2)%2).
+template <int TM, int TN, bool OUT_BF16, bool FUSED, bool FULL, typename ACC, int AM, int AN>
+__device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf, void* d, uint32_t ldd,
                                                  const uint32_t* mask, float alpha, uint32_t row_base,
                                                  uint32_t col_base, uint32_t m, uint32_t n, uint32_t lane, uint32_t nb) {
     static_assert(TN == 2 || TN == 4, "the slice swap of odd rows pairs the slices up");
+    constexpr bool A32 = sizeof(ACC) == sizeof(v16f);
+    static_assert(AM == (A32 ? TM : 2 * TM) && AN == (A32 ? TN : 2 * TN), "the accumulators must make up the tile");
     constexpr uint32_t PASSES = TM * 4, W = TN * 32;
     const uint32_t sub = lane >> 3, c = (lane & 7u) ^ ((lane & 4u) ? 3u : 0u);
     const float up4 = (c & 1u) ? -1.0f : 1.0f, up8 = (c & 2u) ? -1.0f : 1.0f, up16 = (c & 4u) ? -1.0f : 1.0f;
     const float norm = ((c ^ (c >> 1) ^ (c >> 2)) & 1u) ? -block_norm(nb) : block_norm(nb);
     const bool wide = FULL || (ldd & 3u) == 0u;
     const uint32_t mask_ld = n >> 5;
-    // writes: column block j (16 columns) of LDS row 2q + e at block j ^ (q % 2) ^ 2e: an even block moves up by q % 2, an odd one down
-    const uint32_t wq = lane >> 4;
+    const uint32_t lhalf = lane >> 5, wq = lane >> 4;
+    float* wr = wbuf + lhalf * 4u * W + (lane & 31u);                        // v16f: + e*W + ((j ^ e ^ lhalf) % 2 swapped) * 32
+    // v4f: column block j (16 columns) of LDS row 2q + e at block j ^ (q % 2) ^ 2e: an even block moves up by q % 2, an odd one down
     float* wr_even = wbuf + 2u * wq * W + (lane & 15u) + (wq & 1u) * 16u;
     float* wr_odd = wbuf + 2u * wq * W + (lane & 15u) - (wq & 1u) * 16u;
-    const uint32_t rswz = sub & 1u;
-    const float* rd = wbuf + sub * W + 4u * (c ^ (((sub >> 1) & 1u) * 4u));   // + ((j ^ rswz) * 32)
-    const uint32_t row_of_sub = row_base + 4u * (sub >> 1) + (sub & 1u);     // + 16*(P/2) + 2*(P%2): the row that pass P leaves in LDS row sub
+    const uint32_t rswz = A32 ? (sub ^ (sub >> 2)) & 1u : sub & 1u;
+    const float* rd = wbuf + sub * W + 4u * (A32 ? c : c ^ (((sub >> 1) & 1u) * 4u));   // + ((j ^ rswz) * 32)
+    // the row that pass p leaves in LDS row sub: + row_step(p)
+    const uint32_t row_of_sub = row_base + (A32 ? sub : 4u * (sub >> 1) + (sub & 1u));
+    auto row_step = [](uint32_t p) { return A32 ? p * 8u : (p >> 1) * 16u + (p & 1u) * 2u; };
     uint32_t mw[PASSES][TN];
     if (FUSED) {
         const bool mvec = FULL && TN == 4 && (mask_ld & 3u) == 0u && (reinterpret_cast<uintptr_t>(mask) & 15u) == 0u;   // wave-uniform
 #pragma unroll
         for (uint32_t p = 0; p < PASSES; ++p) {
-            const uint32_t grow = row_of_sub + (p >> 1) * 16u + (p & 1u) * 2u;
+            const uint32_t grow = row_of_sub + row_step(p);
             if (mvec) {
                 const uint4 w4 = *reinterpret_cast<const uint4*>(&mask[(size_t)grow * mask_ld + (col_base >> 5)]);
                 mw[p][0] = w4.x; mw[p][1] = w4.y; mw[p][2] = w4.z; mw[p][3] = w4.w;
@@ -203,18 +213,27 @@ __device__ __forceinline__ void store_tile_rows8(v4f (&acc)[2 * TM][2 * TN], flo
             }
         }
     }
-#define ROWS8_WRITE(P)                                                                                  \
-    _Pragma("unroll") for (uint32_t j = 0; j < 2u * TN; ++j)                                            \
-        _Pragma("unroll") for (uint32_t e = 0; e < 2; ++e)                                              \
-            ((j & 1u) ? wr_odd : wr_even)[e * W + (j ^ (2u * e)) * 16u] = acc[(P) >> 1][j][((P) & 1u) * 2u + e];
-    ROWS8_WRITE(0u)
+    auto write_pass = [&](uint32_t p) __attribute__((always_inline)) {
+        if constexpr (A32) {
+#pragma unroll
+            for (uint32_t j = 0; j < TN; ++j)
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) wr[e * W + ((j ^ ((e & 1u) ^ lhalf)) * 32u)] = acc[p >> 2][j][(p & 3u) * 4u + e];
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < 2u * TN; ++j)
+#pragma unroll
+                for (uint32_t e = 0; e < 2; ++e) ((j & 1u) ? wr_odd : wr_even)[e * W + (j ^ (2u * e)) * 16u] = acc[p >> 1][j][(p & 1u) * 2u + e];
+        }
+    };
+    write_pass(0u);
 #pragma unroll
     for (uint32_t p = 0; p < PASSES; ++p) {
         float4 sl[TN];
 #pragma unroll
         for (uint32_t j = 0; j < TN; ++j) sl[j] = *reinterpret_cast<const float4*>(&rd[(j ^ rswz) * 32u]);
-        if (p + 1u < PASSES) { ROWS8_WRITE(p + 1u) }     // behind the reads in the wave's LDS queue: LDS operations of a wave run in order
-        const uint32_t grow = row_of_sub + (p >> 1) * 16u + (p & 1u) * 2u;
+        if (p + 1u < PASSES) write_pass(p + 1u);     // behind the reads in the wave's LDS queue: LDS operations of a wave run in order
+        const uint32_t grow = row_of_sub + row_step(p);
         float vv[TN][4];
 #pragma unroll
         for (uint32_t j = 0; j < TN; ++j) {
@@ -284,7 +303,6 @@ __device__ __forceinline__ void store_tile_rows8(v4f (&acc)[2 * TM][2 * TN], flo
             }
         }
     }
-#undef ROWS8_WRITE
 }
 
 

@@ -8,13 +8,14 @@
 //   scale: one byte per lane (selected by op_sel from a 32-bit register) = the E8M0 scale of that
 //      lane's 32 K-elements, i.e. one MX group per lane per instruction;
 //   D: lane l, register r -> row 4*(l/16) + r, column l%16.
-// Why 16 x 16 x 128 and not 32 x 32 x 64 (same rate, same operand bytes per wave tile): the chip is power-limited under FP4 matrix
-// work, and the deeper instruction reads and writes each fp32 accumulator once per 128 K-elements instead of once per 64.
+// The 256 x 256 kernel uses it, the smaller tiles v_mfma_scale_f32_32x32x64_f8f6f4 (lane l: row or column l%32, K-elements 32*(l/32) ..
+// +31; D: row 8*(r/4) + 4*(l/32) + r%4, column l%32).  Why 16 x 16 x 128 on the large tiles (same rate, same operand bytes per wave
+// tile): there the chip is power-limited, and the deeper instruction reads and writes each fp32 accumulator once per 128 K-elements instead of once per 64.
 // Registers only, quantized normal data, 128 x 128 wave tiles: 7.09 PFLOP/s at 1.79 GHz against 6.38 at 1.59 GHz; both give the same bits (compared over 25 binades of scales).
 // The tiled scale layout (see scale_tile_offset) stores, for each block of 32 rows and 256
-// K-elements, dword 32 h + row with the scales of groups h, 2 + h, 4 + h, 6 + h: lane l reads the dword of its row and h =
+// K-elements, dword 32 h + row with the scales of groups h, 2 + h, 4 + h, 6 + h.  16 x 16 x 128: lane l reads the dword of its row and h =
 // (l/16) % 2 once per K-quad (128 contiguous bytes twice per wave), and its group of the quad's first and second K-step is byte
-// l/32 and byte 2 + l/32; the paper's separate scale-rearrangement step does not exist here.
+// l/32 and byte 2 + l/32.  32 x 32 x 64: lane l reads dword l of the tile, byte s for K-step s.  The paper's separate scale-rearrangement step does not exist here.
 //
 // Kernels: gemm_mxfp4_stream_kernel (256 x 256 tiles) and gemm_mxfp4_stream_tile_kernel (128 x 256 and 128 x 128 tiles
 // for small problems): one block per compute unit streams its tiles through a ring of K-quads (256 elements) in LDS.  Both work
@@ -301,7 +302,7 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
         // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
         const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
-        mfma_clear_accumulators(acc);                      // (peeling the first quad, as the other tile shapes do, makes the compiler spill here)
+        mfma_clear_accumulators(acc);                      // (the first quad apart, with the constant 0 in their place, spills)
         __builtin_amdgcn_sched_barrier(0);
         for (uint32_t qd = 0u; qd < quads; ++qd, sl ^= 1u) {
             const bool last = qd + 1u == quads;            // the next quad is the next tile's first
@@ -350,11 +351,15 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
 
 // ---------------------------------------------------------------------------------------------
 // The streaming design for other tile shapes: wave tile (TM*32) x (TN*32), block tile (64 TM) x (64 TN), for problems
-// whose 256 x 256 tiles would leave compute units idle.  Same issue cursor, same two sets of fragments, same barrier between the
-// K-steps of a quad, same epilogue; the instruction order is generated from the tile shape.  A quad of these tiles lasts 0.3-0.6 us,
-// less than a load's way from memory, so the ring has S = 3 or 4 slots (what fits): during the first K-step of quad q go out the
-// loads of quad q + S - 1.  That leaves the slot of a tile's last quad free until the next tile begins: it serves as the
-// epilogue's scratch.
+// whose 256 x 256 tiles would leave compute units idle.  Same issue cursor, same epilogue; the instruction order is generated from the
+// tile shape.  A quad of these tiles lasts 0.3-0.6 us, less than a load's way from memory, so the ring has S = 3 or 4 slots (what
+// fits): during the first three K-steps (64 elements) of quad q go out the loads of quad q + S - 1.  The quad's one barrier stands
+// before its last K-step, whose fragments every wave has read by then.  That leaves the slot of a tile's last quad free until the
+// next tile begins: it serves as the epilogue's scratch.
+// Instructions of 32 x 32 x 64 (two sets of fragments, even and odd K-steps): these problems are bound by what a wave can issue and by
+// the L2, not by power, and the smaller instruction of the 256 x 256 kernel means twice as many of them for the same work.  Measured
+// against 16 x 16 x 128 (us, fp32 results): 128 x 128 tiles 2048 x 2048 x 4096 14.6 / 16.0, 4096 x 4096 x 1024 21.0 / 22.8, 4096^3 47.4 / 49.2;
+// 128 x 256 tiles 18.1 / 20.5, 19.8 / 21.0, 41.2 / 42.3; same bits.
 template <int TM, int TN, bool OUT_BF16, bool FUSED>
 __global__ void __launch_bounds__(256)
 gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uint64_t* __restrict__ clock_counters) {
@@ -365,9 +370,7 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
     constexpr uint32_t S = BN == 256 ? 3u : 4u;          // ring slots
     constexpr uint32_t LA = BM / 32, LB = BN / 32, NL = LA + LB;   // LDS-direct loads of codes per wave per quad
     constexpr uint32_t NT = (BM + BN) / 32;              // scale tiles per K-quad: A's, then B's
-    constexpr int TA = 2 * TM, TB = 2 * TN, NM = TA * TB, R = TA + TB;   // matrix-core instructions and fragment reads per K-step
-    constexpr int RSP = NM >= 32 ? 2 : 1;                // instructions per fragment read in the second K-step
-    static_assert(2 * R <= NM + 1 + (RSP == 1 ? R : 0) && (int)NL < NM && R * RSP + 2 < NM, "reads and loads must fit");
+    constexpr int NM = TM * TN, R = TM + TN;             // matrix-core instructions and fragment reads per K-step (64 elements)
     __shared__ v4i_t lds[S * QUAD];
 
     // measurement support: shader-clock and constant-clock ticks of this block's run (wave-uniform branch)
@@ -379,7 +382,7 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t l16 = lane & 15u, quarter = lane >> 4;
+    const uint32_t lrow = lane & 31u, lhalf = lane >> 5;
     const uint32_t G = gridDim.x, first_tiles = batch.p[0].total_tiles;
     const uint32_t wm0 = (wave >> 1) * (TM * 32u), wn0 = (wave & 1u) * (TN * 32u);
     // scale tiles 4 wave .. 4 wave + 3 of [A's | B's] are this wave's to fetch (waves past the last tile fetch nothing real:
@@ -439,16 +442,14 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
     ISSUE_SETUP()
 
     const uint32_t lds0 = (uint32_t)(size_t)(lds_ptr_t)&lds[0];
-    // LDS positions of the lane's part of the first fragments and scales in a ring slot (see the 256 x 256 kernel)
-    const uint32_t chunk0 = quarter ^ (l16 >> 1), chunk1 = chunk0 ^ 4u, srow = (quarter & 1u) * 32u + l16;
-    const uint32_t fa_pos0 = ((wm0 + l16) * 8u + chunk0) * 16u, fb_pos0 = ((BM + wn0 + l16) * 8u + chunk0) * 16u;
-    const uint32_t fa_pos1 = ((wm0 + l16) * 8u + chunk1) * 16u, fb_pos1 = ((BM + wn0 + l16) * 8u + chunk1) * 16u;
-    const uint32_t sa_pos = CODES * 16u + ((wm0 >> 5) * 64u + srow) * 4u, sb_pos = CODES * 16u + ((BM / 32u + (wn0 >> 5)) * 64u + srow) * 4u;
+    // the lane's 16-byte chunk 2 s + lhalf of a 128-byte code row in K-step s (chunk c of row r lies at c ^ (r/2)%8)
+    const uint32_t swz = lhalf ^ ((lrow >> 1) & 7u);
+    const uint32_t fa_pos = ((wm0 + lrow) * 8u + swz) * 16u, fb_pos = ((BM + wn0 + lrow) * 8u + swz) * 16u;   // K-step s: ^ 32 s
+    const uint32_t sa_pos = CODES * 16u + ((wm0 >> 5) * 64u + lane) * 4u, sb_pos = CODES * 16u + ((BM / 32u + (wn0 >> 5)) * 64u + lane) * 4u;
     const uint8_t* lds_bytes = reinterpret_cast<const uint8_t*>(lds);
-    const uint32_t sel_full = scale_selector(lane, 0u, 8u);
 
-    uint32_t sa[TA], sb[TB], ra_n[TA], rb_n[TB];
-    v4i_t fa0[TA], fb0[TB], fa1[TA], fb1[TB];            // fragments of a quad's first and second K-step
+    uint32_t sa[TM], sb[TN], ra_n[TM], rb_n[TN];
+    uint4 fa[2][TM], fb[2][TN];                          // fragments of even and odd K-steps
 
 // code load J (0 .. LA-1: A rows, LA .. NL-1: B rows) or the scale tiles (J == NL) of the cursor's quad into ring slot SLOT
 #define ISSUE(SLOT, J)                                                                                  \
@@ -471,31 +472,31 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
             ISSUE_SETUP()                                                                               \
         }                                                                                               \
     }
-#define LDS_AT(NAME, SLOT, POS) uint32_t NAME = (SLOT) * QUAD * 16u + (POS); asm volatile("" : "+v"(NAME));
-// fragment number RR of a K-step in the order the instructions need them: A0, B0 .. B(TB-1), A1 .. A(TA-1)
-#define READ_FRAG(FA, FB, AT_A, AT_B, RR)                                                               \
+// fragment number RR of K-step STEP of the quad in slot SLOT, in the order the instructions need them: A0, B0 .. B(TN-1), A1 ..
+#define READ_FRAG(SLOT, STEP, RR)                                                                       \
     {                                                                                                   \
         const int rr_ = (RR);                                                                           \
-        if (rr_ >= 1 && rr_ <= TB) FB[rr_ - 1] = *reinterpret_cast<const v4i_t*>(lds_bytes + (AT_B) + (rr_ - 1) * 2048); \
-        else if (rr_ < R) FA[rr_ == 0 ? 0 : rr_ - TB] = *reinterpret_cast<const v4i_t*>(lds_bytes + (AT_A) + (rr_ == 0 ? 0 : rr_ - TB) * 2048); \
+        if (rr_ >= 1 && rr_ <= TN) fb[(STEP) & 1][rr_ - 1] = *reinterpret_cast<const uint4*>(lds_bytes + (SLOT) * QUAD * 16u + (fb_pos ^ ((STEP) * 32u)) + (rr_ - 1) * 4096); \
+        else if (rr_ < R) fa[(STEP) & 1][rr_ == 0 ? 0 : rr_ - TN] = *reinterpret_cast<const uint4*>(lds_bytes + (SLOT) * QUAD * 16u + (fa_pos ^ ((STEP) * 32u)) + (rr_ == 0 ? 0 : rr_ - TN) * 4096); \
     }
 #define FENCE() __builtin_amdgcn_sched_barrier(0);
-// scale dwords of a K-quad: read behind the next quad's first fragments, used behind the quad's last matrix-core instruction
 #define READ_SCALES(SLOT)                                                                               \
     {                                                                                                   \
-        LDS_AT(at_a_, SLOT, sa_pos) LDS_AT(at_b_, SLOT, sb_pos)                                         \
-        const uint32_t* s_a_ = reinterpret_cast<const uint32_t*>(lds_bytes + at_a_);                    \
-        const uint32_t* s_b_ = reinterpret_cast<const uint32_t*>(lds_bytes + at_b_);                    \
-        _Pragma("unroll") for (uint32_t i = 0; i < TA; ++i) ra_n[i] = s_a_[i / 2u * 64u + i % 2u * 16u]; \
-        _Pragma("unroll") for (uint32_t j = 0; j < TB; ++j) rb_n[j] = s_b_[j / 2u * 64u + j % 2u * 16u]; \
+        const uint32_t* s_a_ = reinterpret_cast<const uint32_t*>(lds_bytes + (SLOT) * QUAD * 16u + sa_pos); \
+        const uint32_t* s_b_ = reinterpret_cast<const uint32_t*>(lds_bytes + (SLOT) * QUAD * 16u + sb_pos); \
+        _Pragma("unroll") for (uint32_t i = 0; i < TM; ++i) ra_n[i] = s_a_[i * 64u];                    \
+        _Pragma("unroll") for (uint32_t j = 0; j < TN; ++j) rb_n[j] = s_b_[j * 64u];                    \
     }
 #define USE_SCALES(QUADN, GK)                                                                           \
     {                                                                                                   \
-        uint32_t sel_ = sel_full;                                                                       \
-        if (((QUADN) + 1u) * 8u > (GK)) sel_ = scale_selector(lane, (QUADN) * 8u, (GK));   /* wave-uniform: only a ragged last K-quad */ \
-        _Pragma("unroll") for (uint32_t i = 0; i < TA; ++i) sa[i] = __builtin_amdgcn_perm(0x7F7F7F7Fu, ra_n[i], sel_); \
-        _Pragma("unroll") for (uint32_t j = 0; j < TB; ++j) sb[j] = __builtin_amdgcn_perm(0x7F7F7F7Fu, rb_n[j], sel_); \
-        mfma_scales_written(sa, sb);                                                                    \
+        uint32_t keep_ = 0xFFFFFFFFu;                                                                   \
+        if (((QUADN) + 1u) * 8u > (GK)) {     /* wave-uniform: only a ragged last K-quad */             \
+            const uint32_t steps_ = ((GK) + 1u - lhalf) >> 1, done_ = (QUADN) * 4u;                     \
+            const uint32_t nv_ = steps_ > done_ ? (steps_ - done_ < 4u ? steps_ - done_ : 4u) : 0u;     \
+            keep_ = nv_ >= 4u ? 0xFFFFFFFFu : ((1u << (8u * nv_)) - 1u);                                \
+        }                                                                                               \
+        _Pragma("unroll") for (uint32_t i = 0; i < TM; ++i) sa[i] = (ra_n[i] & keep_) | (0x7F7F7F7Fu & ~keep_); \
+        _Pragma("unroll") for (uint32_t j = 0; j < TN; ++j) sb[j] = (rb_n[j] & keep_) | (0x7F7F7F7Fu & ~keep_); \
     }
 
     // vector-memory operations that may be under way at a quad's barrier: the loads of the quads behind the next one, and once after a
@@ -513,39 +514,43 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
     __builtin_amdgcn_s_waitcnt(WAIT);
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int r = 0; r < R; ++r) READ_FRAG(fa0, fb0, fa_pos0, fb_pos0, r)
+    for (int r = 0; r < R; ++r) READ_FRAG(0u, 0, r)
     uint32_t csel, clv;
     PRODUCT_OF(blockIdx.x, csel, clv)
     READ_SCALES(0u)
     USE_SCALES(0u, batch.p[csel].k >> 5)
 
 // one K-quad in slot SL; SL1: the next quad's slot, SLI: the slot being filled
-#define QUAD_BODY(FIRST, SL, SL1, SLI, STORES, NEXT_QUAD, NEXT_GK)                                      \
+#define QUAD_BODY(SL, SL1, SLI, STORES, NEXT_QUAD, NEXT_GK)                                             \
     {                                                                                                   \
-        LDS_AT(a1_, SL, fa_pos1) LDS_AT(b1_, SL, fb_pos1) LDS_AT(an_, SL1, fa_pos0) LDS_AT(bn_, SL1, fb_pos0) \
-        _Pragma("unroll") for (int idx = 0; idx < NM; ++idx) {                                          \
-            mfma_fp4<0, FIRST>(fa0[idx / TB], fb0[idx % TB], acc[idx / TB][idx % TB], sa[idx / TB], sb[idx % TB]); \
+        _Pragma("unroll") for (int idx = 0; idx < 4 * NM; ++idx) {                                      \
+            const int st_ = idx / NM, ij_ = idx % NM, I_ = ij_ / TN, J_ = ij_ % TN;                     \
+            if (st_ == 0) acc[I_][J_] = mfma_fp4_32<0>(fa[0][I_], fb[0][J_], acc[I_][J_], sa[I_], sb[J_]); \
+            if (st_ == 1) acc[I_][J_] = mfma_fp4_32<1>(fa[1][I_], fb[1][J_], acc[I_][J_], sa[I_], sb[J_]); \
+            if (st_ == 2) acc[I_][J_] = mfma_fp4_32<2>(fa[0][I_], fb[0][J_], acc[I_][J_], sa[I_], sb[J_]); \
+            if (st_ == 3) acc[I_][J_] = mfma_fp4_32<3>(fa[1][I_], fb[1][J_], acc[I_][J_], sa[I_], sb[J_]); \
+            asm volatile("" : "+a"(acc[I_][J_]));                                                       \
             FENCE()                                                                                     \
-            if (idx % 2 == 0 && idx / 2 < R) { READ_FRAG(fa1, fb1, a1_, b1_, idx / 2) FENCE() }         \
-            if (idx % 2 == 1 && idx / 2 <= (int)NL) { ISSUE(SLI, idx / 2) FENCE() }                     \
-            if (idx == NM - 1 && NM / 2 == (int)NL) { ISSUE(SLI, NL) FENCE() }                          \
-        }                                                                                               \
-        ISSUE_ADVANCE()                                                                                 \
-        if (STORES) __builtin_amdgcn_s_waitcnt(WAIT_ST);                                                \
-        else __builtin_amdgcn_s_waitcnt(WAIT);                                                          \
-        __builtin_amdgcn_s_barrier();                                                                   \
-        FENCE()                                                                                         \
-        _Pragma("unroll") for (int idx = 0; idx < NM; ++idx) {                                          \
-            mfma_fp4<1>(fa1[idx / TB], fb1[idx % TB], acc[idx / TB][idx % TB], sa[idx / TB], sb[idx % TB]); \
-            FENCE()                                                                                     \
-            if (idx % RSP == 0 && idx / RSP < R) { READ_FRAG(fa0, fb0, an_, bn_, idx / RSP) FENCE() }   \
-            if (idx == R * RSP) { READ_SCALES(SL1) FENCE() }                                            \
+            if (st_ < 2 && ij_ < R) { READ_FRAG(SL, st_ + 1, ij_) FENCE() }                             \
+            if (st_ == 2 && 2 * ij_ < R) { READ_FRAG(SL, 3, 2 * ij_) READ_FRAG(SL, 3, 2 * ij_ + 1) FENCE() } \
+            _Pragma("unroll") for (int l_ = 0; l_ <= (int)NL; ++l_)                                     \
+                if ((l_ * 3 * NM) / ((int)NL + 1) == idx) { ISSUE(SLI, l_) FENCE() }                    \
+            if (idx == 3 * NM - 1) {                                                                    \
+                ISSUE_ADVANCE()                                                                         \
+                if (STORES) __builtin_amdgcn_s_waitcnt(WAIT_ST);                                        \
+                else __builtin_amdgcn_s_waitcnt(WAIT);                                                  \
+                __builtin_amdgcn_s_barrier();                                                           \
+                FENCE()                                                                                 \
+            }                                                                                           \
+            if (R < NM && st_ == 3 && ij_ < R) { READ_FRAG(SL1, 0, ij_) FENCE() }                       \
+            if (R >= NM && st_ == 3 && 2 * ij_ < R) { READ_FRAG(SL1, 0, 2 * ij_) READ_FRAG(SL1, 0, 2 * ij_ + 1) FENCE() } \
+            if (idx == 3 * NM + (R < NM ? R : (R + 1) / 2)) { READ_SCALES(SL1) FENCE() }                \
         }                                                                                               \
         USE_SCALES(NEXT_QUAD, NEXT_GK)                                                                  \
         FENCE()                                                                                         \
     }
 
-    v4f acc[TA][TB];
+    v16f acc[TM][TN];
     uint32_t sl = 0u;                                      // ring slot of the current quad
     auto slot_after = [](uint32_t s) { return s + 1u == S ? 0u : s + 1u; };
     auto slot_before = [](uint32_t s) { return s == 0u ? S - 1u : s - 1u; };
@@ -555,15 +560,20 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
         // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
         const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
         uint32_t sl1 = slot_after(sl);
-        QUAD_BODY(true, sl, sl1, slot_before(sl), stores, quads > 1u ? 1u : 0u, quads > 1u ? gk : gk_after)
+        QUAD_BODY(sl, sl1, slot_before(sl), stores, quads > 1u ? 1u : 0u, quads > 1u ? gk : gk_after)
         for (uint32_t qd = 1u; qd < quads; ++qd) {
             const bool last = qd + 1u == quads;            // the next quad is the next tile's first
             sl = sl1;
             sl1 = slot_after(sl);
-            QUAD_BODY(false, sl, sl1, slot_before(sl), false, last ? 0u : qd + 1u, last ? gk_after : gk)
+            QUAD_BODY(sl, sl1, slot_before(sl), false, last ? 0u : qd + 1u, last ? gk_after : gk)
         }
-        mfma_results_written();
         __builtin_amdgcn_sched_barrier(0);
         // the last quad's slot: every wave is past its last read there, and its next loads go out behind the barrier below
         float* wbuf = reinterpret_cast<float*>(&lds[sl * QUAD]) + wave * (TN * 256u);
@@ -593,7 +603,6 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
 #undef ISSUE_SETUP
 #undef ISSUE
 #undef ISSUE_ADVANCE
-#undef LDS_AT
 #undef READ_FRAG
 #undef FENCE
 #undef READ_SCALES

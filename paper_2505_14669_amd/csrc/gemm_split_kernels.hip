@@ -27,13 +27,6 @@ struct SplitBatch {
     SplitProblem p[2];
 };
 
-template <int S>
-__device__ __forceinline__ v16f split_mfma(const uint4& a, const uint4& b, v16f c, uint32_t sa, uint32_t sb) {
-    v8i va = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
-    v8i vb = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, vb, c, 4, 4, S, (int)sa, S, (int)sb);
-}
-
 // 4 bytes per lane to LDS byte address lds_base + 4 * lane (see lds_direct_load16)
 __device__ __forceinline__ void lds_direct_load4(v4i_t rsrc, uint32_t voff, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_base), "v"(voff), "s"(rsrc) : "memory");
@@ -187,7 +180,7 @@ gemm_mxfp4_split_kernel(SplitBatch batch, uint32_t nb) {
 #define SPLIT_STEP(S)                                                                                   \
     _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                      \
         _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                  \
-            acc[i][j] = split_mfma<S>(f[i][S], f[TM + j][S], acc[i][j], sc[i], sc[TM + j]);
+            acc[i][j] = mfma_fp4_32<S>(f[i][S], f[TM + j][S], acc[i][j], sc[i], sc[TM + j]);
         SPLIT_STEP(0) SPLIT_STEP(1) SPLIT_STEP(2) SPLIT_STEP(3)
 #undef SPLIT_STEP
     }

@@ -42,11 +42,7 @@ mfma_ceiling_kernel(const v4i_t* __restrict__ codes, const uint32_t* __restrict_
     }
     v4f acc[8][4];
     mfma_scales_written(sa, sb);
-    // the accumulators start from an instruction each
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mfma_fp4<0, true>(fa[i & 3], fb[j], acc[i][j], sa[i & 3], sb[j]);
+    mfma_clear_accumulators(acc);
     for (uint32_t it = 0; it < iterations; ++it) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)

@@ -131,7 +131,7 @@ def test_results_of_matrix_core_instructions_are_not_touched_too_early(listing):
     # 19 wait states of the instruction that forms it (the longest, a 16-pass instruction, needs that many)
     bad = []
     for name, body in listing.items():
-        if "gemm_mxfp4_stream" not in name and "mfma_ceiling" not in name:
+        if "gemm_mxfp4_stream_kernel" not in name and "mfma_ceiling" not in name:
             continue
         before = predecessors(body)
         for n, ins in enumerate(body):

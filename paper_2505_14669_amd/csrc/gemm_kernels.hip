@@ -682,10 +682,11 @@ static void launch_stream_tile_t(const uint8_t* a_codes, const uint8_t* a_scales
 // The tile shape is the one with the smallest estimated time of the busiest block, which walks the virtual tile ids b, b + G, ...:
 // launch and first loads, its K-quads, its tiles' epilogues, and the share of the chip that stores results.  Fitted to 60 single
 // products (m 24 .. 8192, n and k 256 .. 11008, both result types) and 45 pairs with the gradient epilogue (rms error 7 % for 128 x 128
-// tiles, 15 % for 256 x 256 ones; the shape chosen is within 0.3 % of the best one on average, 10 % at most).  Measured, 256 x 256 /
-// 128 x 256 / 128 x 128 (us): 7172 x 1408 x 1600 28.3 / 27.2 / 22.2; 2336 x 3168 x 1376 26.5 / 16.0 / 16.1; 1850 x 9120 x 2752 58.4 /
-// 51.7 / 49.0; pairs of layers (tokens, in, out) 4096 x 2048 x 2048 39.4 / 36.2 / 32.3; 1184 x 2880 x 5440 77.3 / 55.8 / 47.1; 7072 x 2912 x
-// 5536 168 / 175 / 190.
+// tiles, 15 % for 256 x 256 ones) when the smaller tiles' kernel took 3-8 % longer than now; the shape chosen is within 1-2 % of the
+// best one on average still (130 single products, 105 pairs), and fits to the present times gain as much on small problems as they lose on
+// large ones (single products 7433 x 9760 x 3008: 128 x 256 tiles, 156 us, for 146).  Measured, 256 x 256 / 128 x 256 / 128 x 128 (us):
+// 5974 x 1888 x 352 22.0 / 21.0 / 15.3; 2758 x 1728 x 5280 48.3 / 28.0 / 32.1; 8182 x 1536 x 3616 37.2 / 39.2 / 39.3; pairs of layers (tokens,
+// in, out) 3072 x 2144 x 4288 78.6 / 60.7 / 50.7; 6464 x 288 x 5472 64.3 / 34.1 / 38.2.
 struct StreamCost {
     double start, per_quad, per_tile, per_fill;
 };
@@ -724,17 +725,19 @@ static int pick_variant(int products, const int64_t* m, const int64_t* n, const 
 }
 
 // Problems that the split kernels (gemm_split_kernels.hip) finish sooner: few rows, small layers, long inner dimensions with few
-// tiles.  Compares their estimate with that of the streaming kernels, with a sixth (one product) or a fifth (two) in favour of the
-// latter.  Measured, streaming against split (us): 46 x 800 x 2464 11.3 / 5.0; 2529 x 384 x 1312 8.9 / 6.0; 3763 x 288 x 8992 29.6 / 28.9; and on
-// the other side 3127 x 1408 x 1248 14.0 / 16.7; 2336 x 3168 x 1376 16.0 / 23.0.  The choice depends on m, n and k alone, so fused
-// and plain products of one size run on the same side.
+// tiles.  Compares their estimate with that of the streaming kernels, in favour of the latter by 15 % (one product), 20 % (two) or, with
+// four waves, whose estimate is low for 64 x 64 tiles, 30 %.  Measured, streaming against split (us): 630 x 1312 x 2944 11.7 / 7.0;
+// 2910 x 384 x 1056 7.6 / 7.2; 469 x 1792 x 1728 8.3 / 6.5; on the other side 2538 x 864 x 384 8.1 / 10.2; four waves 339 x 2624 x 5600 15.5 / 9.2 and
+// 377 x 4096 x 3936 12.8 / 13.9, 950 x 1696 x 5664 16.5 / 18.1; pairs of layers 736 x 928 x 800 10.5 / 8.2, 2176 x 1024 x 864 11.8 / 14.7.  The
+// choice depends on m, n and k alone, so fused and plain products of one size run on the same side.
 static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, int cus, double streaming, int* shape) {
     if (g_forced_variant >= 0) return false;
     // A block per tile, and a launch has fewer than 2^32 threads: with 32 x 32 tiles of up to four waves, 2^24 tiles at most
     int64_t tiles = 0;
     for (int p = 0; p < products; ++p) tiles += ((m[p] + 31) / 32) * ((n[p] + 31) / 32);
     if (tiles >= ((int64_t)1 << 24)) return false;
-    return best_split_shape(products, m, n, k, cus, shape) < (products == 1 ? 0.85 : 0.8) * streaming;
+    const bool four = split_waves(products == 2 && k[1] > k[0] ? k[1] : k[0]) == 4;
+    return best_split_shape(products, m, n, k, cus, shape) < (four ? 0.7 : products == 1 ? 0.85 : 0.8) * streaming;
 }
 
 // The kernel for one product or a pair, plain (nb = 0) or with the gradient epilogue of Hadamard blocks of nb groups.

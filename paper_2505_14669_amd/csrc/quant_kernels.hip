@@ -893,13 +893,20 @@ hipError_t launch_fwd_operands(const void* x, int64_t tokens, const void* w, int
     if (na + nb >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;
     RowMatrix a = {(const uint16_t*)x, (uint32_t)tokens, in, (uint4*)xq_codes, xq_scales, x_mask};
     RowMatrix b = {(const uint16_t*)w, (uint32_t)out, in, (uint4*)wq_codes, wq_scales, w_mask};
-    if (p.nb > 1u)
-        hipLaunchKernelGGL((quant_row_pair_kernel<kFwd, true, true>), dim3((uint32_t)(na + nb)), dim3(256), 0, st, a, b, (uint32_t)na,
-                           gk, p, k_blocks, make_fast_div(k_blocks));
-    else
-        hipLaunchKernelGGL((quant_row_pair_kernel<kFwd, true, false>), dim3((uint32_t)(na + nb)), dim3(256), 0, st, a, b, (uint32_t)na,
-                           gk, p, k_blocks, make_fast_div(k_blocks));
-    return hipGetLastError();
+    // a and b from block 0 on, or b alone (split 0)
+    auto launch = [&](uint64_t blocks, uint64_t split) {
+        if (p.nb > 1u)
+            hipLaunchKernelGGL((quant_row_pair_kernel<kFwd, true, true>), dim3((uint32_t)blocks), dim3(256), 0, st, a, b, (uint32_t)split,
+                               gk, p, k_blocks, make_fast_div(k_blocks));
+        else
+            hipLaunchKernelGGL((quant_row_pair_kernel<kFwd, true, false>), dim3((uint32_t)blocks), dim3(256), 0, st, a, b, (uint32_t)split,
+                               gk, p, k_blocks, make_fast_div(k_blocks));
+        return hipGetLastError();
+    };
+    // a launch holds fewer than 2^32 threads: where the two matrices together have more, each has its own
+    if (na == 0 || nb == 0 || na + nb < ((uint64_t)1 << 24)) return launch(na + nb, na);
+    const hipError_t e = launch(na, na);
+    return e == hipSuccess ? launch(nb, 0) : e;
 }
 
 hipError_t launch_bwd_operands(int mode, const void* dy, int64_t tokens, int64_t in, int64_t out,

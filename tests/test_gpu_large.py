@@ -111,3 +111,28 @@ def test_gemm_result_past_2_pow_32_bytes(G, fused):
         if fused:
             want = oracle.grad_epilogue(want.astype(np.float32), mask[r0:r1])
         assert np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want)
+
+
+def test_forward_operands_past_one_launch(G):
+    # 2^27 - 64 rows of 64 elements: the activations' blocks alone fill a launch (fewer than 2^32 threads), so the weights take another.
+    # Rows repeat every 64, and so must the results; a small call says what they are.
+    t, i, o, block = 2 ** 27 - 64, 64, 64, 64
+    if torch.cuda.get_device_properties(0).total_memory < 80 << 30:
+        pytest.skip("needs 80 GB of device memory")
+    gen = torch.Generator(device=G.DEV)
+    gen.manual_seed(3)
+    x0, w = (torch.randn((64, i), generator=gen, device=G.DEV).to(torch.bfloat16) for _ in range(2))
+
+    def run(x, rows):
+        y = torch.empty((rows, o), dtype=torch.bfloat16, device=G.DEV)
+        ctx = []
+        for r in (rows, o):
+            ctx += [torch.empty((r, i // 2), dtype=torch.uint8, device=G.DEV), torch.empty(q.quartet_scale_bytes(r, i), dtype=torch.uint8, device=G.DEV),
+                    torch.empty((r, i // 32), dtype=torch.int32, device=G.DEV)]
+        q.check(q.quartet_linear_fwd_block(x, w, rows, i, o, block, y, q.QUARTET_DTYPE_BF16, *ctx))
+        return y, ctx
+    y0, c0 = run(x0, 64)
+    y, c = run(x0.repeat(t // 64, 1), t)
+    for big, small in ((y, y0), (c[0], c0[0]), (c[2], c0[2])):
+        assert bool((big.view(t // 64, -1) == small.reshape(1, -1)).all())
+    assert torch.equal(c[3], c0[3]) and torch.equal(c[5], c0[5])

@@ -155,8 +155,9 @@ __device__ __forceinline__ void store_tile(v16f (&acc)[TM][TN], float* wbuf, voi
 // differences of the unsigned values give (x - x = +0, and no -0 enters: masked elements and empty sums are +0).
 __device__ __forceinline__ float epilogue_norm(float v, float signed_norm) { return __builtin_fmaf(v, signed_norm, 0.0f); }
 
-// Epilogue of the streaming kernels: the wave's accumulator tile leaves in passes of 8 rows x TN*32 columns through a
-// scratch of the wave's own (outside the ring, so the ring keeps streaming the next tile); every store instruction writes
+// Epilogue of the streaming kernels: the wave's accumulator tile leaves in passes of 8 rows x TN*32 columns (on the FULL path with one
+// store per pass and 32-column slice exactly: a lane's chunks do not touch, so the compiler cannot put two into one, and the kernels
+// count on it) through a scratch of the wave's own (outside the ring, so the ring keeps streaming the next tile); every store instruction writes
 // 8 whole 128-byte lines.  With FUSED the gradient epilogue of Algorithm 1 Backward, D = alpha * H_along_n(acc . M), is
 // applied on the way: mask select, the stages that combine whole 32-column groups and butterflies of stride 1 and 2 inside
 // the lane, strides 4, 8, 16 between the 8 lanes that hold a row's slice (QUARTET_BUTTERFLIES_ACROSS: lane i holds 4-column

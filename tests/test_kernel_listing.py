@@ -142,3 +142,23 @@ def test_results_of_matrix_core_instructions_are_not_touched_too_early(listing):
                 bad += [f"{name}: {ins.mnemonic} {ins.operands} at {ins.address:#x} behind {body[p].mnemonic} {body[p].operands}"
                         for p in within(body, before, n, 19, lambda i: i.is_mfma and i.registers(i.operands[0]) & touched)]
     assert not bad, f"{len(bad)} places, first ones:\n" + "\n".join(bad[:8])
+
+
+# result stores of a wave's full tile: one per pass of eight rows and 32-column slice
+@pytest.mark.parametrize("kernel,stores", [("gemm_mxfp4_stream_kernelI", 64), ("gemm_mxfp4_stream_tile_kernelILi2ELi4E", 32),
+                                           ("gemm_mxfp4_stream_tile_kernelILi2ELi2E", 16)])
+def test_a_full_tile_leaves_in_as_many_stores_as_the_kernels_count(listing, kernel, stores):
+    # The wait behind a full tile lets that many younger operations be under way; with fewer stores it would let loads through that it is
+    # there to wait for.  A lane's chunks (four columns: 16 bytes, 8 in bf16) do not touch, so no store instruction can hold two:
+    # nothing wider than a chunk, and one store per chunk on the full path (another set on the ragged one; of 16-byte chunks the last
+    # may be put together from parts that the paths share).
+    names = [n for n in listing if kernel in n]
+    assert len(names) == 4
+    for name in names:
+        widths = [i.mnemonic for i in listing[name] if i.mnemonic.startswith(("global_store", "buffer_store", "flat_store"))]
+        assert all(w.startswith("global_store") for w in widths)
+        bf16 = re.search(r"kernelI(?:Li\dELi\dE)?Lb1E", name) is not None
+        if bf16:
+            assert not {"global_store_dwordx3", "global_store_dwordx4"} & set(widths) and widths.count("global_store_dwordx2") == 2 * stores
+        else:
+            assert widths.count("global_store_dwordx4") >= stores - 1

@@ -31,3 +31,18 @@ def test_four_wave_split_leaves_what_the_streaming_kernels_do_sooner():
         assert plan(*mnk) == 2
     for mnk in ((339, 2624, 5600), (104, 6592, 6240)):
         assert plan(*mnk) // 100 == 4
+
+
+def test_sizes_of_the_split_tests_reach_every_kernel():
+    # every shape that the launcher has, with two and four waves, wherever it can run (tiles narrower than the Hadamard block cannot)
+    import split_sizes
+    shapes = {0: (11, 12, 22), 32: (11, 12, 22), 64: (12, 22), 128: (14,)}
+    for table in (split_sizes.SINGLE, split_sizes.PAIR):
+        for block, sizes in table.items():
+            assert sorted(sizes) == sorted(100 * w + s for w in (2, 4) for s in shapes[block])
+    for block, sizes in split_sizes.SINGLE.items():
+        for code, mnk in sizes.items():
+            assert plan(*mnk, block=block) == code, (block, mnk)
+    for block, sizes in split_sizes.PAIR.items():
+        for code, (t, i, o) in sizes.items():
+            assert plan(o, i, t, t, i, o, block=block) == code, (block, t, i, o)

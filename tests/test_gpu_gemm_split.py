@@ -1,12 +1,15 @@
 """The GEMM kernels for small problems (in-block split of the inner dimension) at the edges of their tiles, with two and four
-waves, both result types and the gradient epilogue of every Hadamard block they serve, against the oracle; and at the sizes
-around the line where the launcher goes over to the streaming kernels."""
+waves, both result types and the gradient epilogue of every Hadamard block they serve, against the oracle; at sizes
+around the line where the launcher goes over to the streaming kernels; and every kernel of them (waves x tile shape, plain, fused and
+pairs; split_sizes.py, whose sizes test_gemm_plan.py holds to the launcher's choice) bit for bit on sums that are exact in fp32."""
 import numpy as np
 import pytest
+import torch
 
 import indep
 import oracle
-from paper_2505_14669_amd import synth
+import split_sizes
+from paper_2505_14669_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +68,80 @@ def test_split_gemm_pair(G, first, second):
         # the transform spreads a row's errors over its 32 columns: bound by their sum
         absp = np.repeat(indep.gemm_abs_products(a, sa, b, sb).reshape(a.shape[0], -1, 32).sum(-1), 32, axis=1)
         _check(got, want, scale * absp, 2 * a.shape[1])
+
+
+GRID = np.array([0, .5, 1, 1.5, 2, 3, 4, 6, 0, -.5, -1, -1.5, -2, -3, -4, -6])
+
+
+def _exact_operand(rng, rows, k):
+    # products are multiples of 2^-4 and at most 144 in size: with k <= 4128 every sum is exact in fp32 (below 2^24 units), in any order
+    assert k * 144 * 16 < 2 ** 24
+    codes = rng.integers(0, 256, size=(rows, k // 2), dtype=np.uint8)
+    scales = rng.integers(126, 129, size=(rows, k // 32), dtype=np.uint8)
+    values = np.empty((rows, k))
+    values[:, 0::2], values[:, 1::2] = GRID[codes & 15], GRID[codes >> 4]
+    return codes, scales, torch.from_numpy(values * np.repeat(2.0 ** (scales.astype(np.float64) - 127), 32, axis=1)).cuda()
+
+
+def _exact_product(rng, m, n, k):
+    (a, sa, va), (b, sb, vb) = _exact_operand(rng, m, k), _exact_operand(rng, n, k)
+    return (a, sa, b, sb), (va @ vb.T).cpu().numpy().astype(np.float32)
+
+
+@pytest.mark.parametrize("code", sorted(split_sizes.SINGLE[0]))
+def test_every_split_kernel_plain(G, code):
+    m, n, k = split_sizes.SINGLE[0][code]
+    operands, want = _exact_product(np.random.default_rng(code), m, n, k)
+    assert np.array_equal(G.gemm(*operands), want)
+    assert np.array_equal(G.gemm(*operands, bf16=True), synth.f32_to_bf16(want))
+
+
+@pytest.mark.parametrize("block,code", [(b, c) for b in (32, 64, 128) for c in sorted(split_sizes.SINGLE[b])])
+def test_every_split_kernel_fused(G, block, code):
+    m, n, k = split_sizes.SINGLE[block][code]
+    rng = np.random.default_rng(code + block)
+    operands, product = _exact_product(rng, m, n, k)
+    mask = rng.integers(0, 2 ** 32, size=(m, n // 32), dtype=np.uint32)
+    want = G.grad_epilogue_block(product, mask, block, oracle.FL_16_9)
+    assert np.array_equal(G.gemm_grad_block(*operands, block, mask, oracle.FL_16_9).view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("code", sorted(split_sizes.PAIR[32]))
+def test_every_split_kernel_pair(G, code):
+    t, i, o = split_sizes.PAIR[32][code]
+    rng = np.random.default_rng(code)
+    prods, want = [], []
+    for m, n, k in ((o, i, t), (t, i, o)):
+        operands, product = _exact_product(rng, m, n, k)
+        mask = rng.integers(0, 2 ** 32, size=(m, n // 32), dtype=np.uint32)
+        prods.append((*operands, mask, oracle.FL_16_9))
+        want.append(G.grad_epilogue_block(product, mask, 32, oracle.FL_16_9))
+    for got, w in zip(G.gemm_grad_pair(*prods), want):
+        assert np.array_equal(got.view(np.uint32), w.view(np.uint32))
+
+
+# wider Hadamard blocks reach the pair through the layer's backward pass: against the same call with the streaming kernels forced.  An fp32
+# sum of k products is off by at most (k/64 + 6) 2^-23 sum |a||b|, and sum |a||b| of random signs is about sqrt(k) times the sum's size
+@pytest.mark.parametrize("block,code", [(b, c) for b in (64, 128) for c in sorted(split_sizes.PAIR[b])])
+def test_every_split_kernel_pair_of_wide_blocks(G, block, code):
+    t, i, o = split_sizes.PAIR[block][code]
+    g = torch.Generator(device=G.DEV)
+    g.manual_seed(code)
+    x, w, dy = (torch.randn(s, generator=g, device=G.DEV).to(torch.bfloat16) for s in ((t, i), (o, i), (t, o)))
+    u8 = lambda *s: torch.empty(s, dtype=torch.uint8, device=G.DEV)
+    ctx = []
+    for r in (t, o):
+        ctx += [u8(r, i // 2), u8(binding.quartet_scale_bytes(r, i)), torch.empty((r, i // 32), dtype=torch.int32, device=G.DEV)]
+    y, n = torch.empty((t, o), device=G.DEV), binding.quartet_linear_workspace_bytes_block(t, i, o, block)
+    binding.check(binding.quartet_linear_fwd_block(x, w, t, i, o, block, y, 0, *ctx))
+    out = []
+    try:
+        for variant in (-1, 1):
+            binding.check(binding.quartet_debug_set_gemm_plan(variant, 0))
+            dx, dw = torch.empty((t, i), device=G.DEV), torch.empty((o, i), device=G.DEV)
+            binding.check(binding.quartet_linear_bwd_block(dy, t, i, o, block, *ctx, 77, 0, dx, dw, 0, u8(n), n))
+            out.append((dx, dw))
+    finally:
+        binding.quartet_debug_set_gemm_plan(-1, 0)
+    for got, want, k in zip(*out, (o, t)):
+        assert float((got - want).norm() / want.norm()) < (k / 64 + 6) * 2.0 ** -23 * k ** 0.5

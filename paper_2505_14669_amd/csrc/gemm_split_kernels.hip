@@ -5,8 +5,8 @@
 // inner dimension in one block, stage after stage through its LDS ring, while most compute units have no tile.  Here a block of
 // NW waves owns one small tile and its waves share the inner dimension: wave w takes the K-quads (256 elements) w, w + NW, ...,
 // through an LDS ring of its own (two quads of LDS-direct loads, whole 128-byte lines; no barrier in the loop), and the partial
-// sums meet in LDS.  The order of a result's sum depends on k alone, not on the tile shape, so fused and plain products give the
-// same bits.
+// sums meet in LDS.  The order of a result's sum depends on k and the number of waves alone, not on the tile shape, and the number of
+// waves on k (of a pair on the larger k), so fused and plain products give the same bits.
 #include "gemm_common.h"
 #include "launchers.h"
 

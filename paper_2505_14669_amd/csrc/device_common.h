@@ -31,7 +31,6 @@ struct FastDiv {
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
 
 typedef unsigned int v4u_t __attribute__((ext_vector_type(4)));
-typedef unsigned int v2u_t __attribute__((ext_vector_type(2)));
 
 // Streaming (non-temporal) 16-byte and 4-byte accesses for data that is touched once: measured
 // 7.0 TB/s against 6.3 TB/s for plain loads on a read-only sweep of 2 GiB.

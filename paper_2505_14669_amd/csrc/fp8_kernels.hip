@@ -15,6 +15,9 @@
 
 namespace quartet {
 
+// stages in the LDS ring
+constexpr uint32_t kRing = 4;
+
 typedef short v2s_t __attribute__((ext_vector_type(2)));
 
 // four values -> four E4M3 bytes, round-to-nearest-even; magnitudes above 448 saturate (the

@@ -307,9 +307,6 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
 }
 
 
-// Depth of the LDS ring of the large-tile kernels.
-constexpr uint32_t kRing = 4;
-
 __device__ __forceinline__ v4i_t make_rsrc_words(const void* base, uint32_t bytes) {
     const uint64_t a = reinterpret_cast<uint64_t>(base);
     v4i_t r = {(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};

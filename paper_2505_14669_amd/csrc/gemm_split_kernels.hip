@@ -261,7 +261,10 @@ static const SplitShape kSplitShapes2[3] = {   // two waves
     {11, 32, 32, 2.67, 0.066, 0.45, 0.101}, {12, 32, 64, 2.74, 0.050, 0.79, 0.170}, {22, 64, 64, 2.25, 0.089, 1.79, 0.229}};
 static const SplitShape kSplitShapes4[3] = {   // four waves
     {11, 32, 32, 2.46, 0.0, 0.92, 0.092}, {12, 32, 64, 1.49, 0.0, 2.42, 0.142}, {22, 64, 64, 0.93, 0.0, 3.73, 0.204}};
-constexpr int64_t kFourWaveQuads = 12;   // 24 x 4096 x 11008: 7.3 us with four waves, 8.7 with two; 24 x 11008 x 4096: 7.8 and 6.9; 512^3: 3.3 and 3.0
+// Waves that share k.  Four from here on: with a tile per compute unit or less they are sooner (two / four waves, us: 24 x 4096 x 11008 8.1 / 5.7,
+// 200 x 4096 x 4096 8.2 / 7.4; below the line 24 x 4096 x 2816 5.2 / 5.2).  With more tiles than compute units two waves would still be
+// (24 x 11008 x 4096 5.5 / 5.5, x 8192 10.1 / 10.7; 64 x 11008 x 4096 7.5 / 9.0): the rule does not look at the number of tiles.
+constexpr int64_t kFourWaveQuads = 12;
 
 int split_waves(int64_t k) { return (k + 255) / 256 >= kFourWaveQuads ? 4 : 2; }
 

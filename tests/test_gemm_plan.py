@@ -1,4 +1,6 @@
 """Which kernel the GEMM launcher picks (host only): the choice is a function of the sizes, the Hadamard block and the chip."""
+import torch  # noqa: F401  (before the library, as in every program that uses both: they share one HIP runtime then)
+
 from paper_2505_14669_amd import binding as q
 
 CUS = 256

@@ -23,8 +23,8 @@
 // What bounds them besides power is the way of the operands into the LDS: a cache line is 128 bytes, so a ring of 128-element
 // stages (64 bytes of codes per row) fetched every line twice.  K-quads, whole lines, one barrier per quad and reads and loads spread
 // evenly over the matrix-core instructions, 16 x 16 x 128 on the large tiles and 32 x 32 x 64 on the small ones, took against that design
-// (layer steps, us): 16384 x 4096 x 11008 1434 -> @A, 16384 x 4096 x 4096 614 -> @B, 2336 x 1376 x 3168 78.6 -> @C, 4096 x 2048 x 2048
-// 89.0 -> @D, forward 1003 x 2048 x 5632 25.5 -> @E.  (16 x 16 x 128 on the old stages: 0-4 % slower.)
+// (layer steps, us): 16384 x 4096 x 11008 1434 -> 1378, 16384 x 4096 x 4096 620 -> 601, 2336 x 1376 x 3168 78.7 -> 71.5, 4096 x 2048 x 2048
+// 91.2 -> 85.1, forward 1003 x 2048 x 5632 25.6 -> 23.9.  (16 x 16 x 128 on the old stages: 0-4 % slower.)
 #include "gemm_common.h"
 #include "launchers.h"
 

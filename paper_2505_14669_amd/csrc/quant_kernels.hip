@@ -206,8 +206,8 @@ __device__ __forceinline__ void quant_row_tile(const uint16_t* __restrict__ x, u
     reinterpret_cast<uint8_t*>(s_scale)[(((gi >> 3) * 2u + (gi & 1u)) * 8u + row_local) * 4u + ((gi & 7u) >> 1)] = (uint8_t)sb;
     if (row < rows && g < gk) {
         const size_t gidx = (size_t)row * gk + g;
-        store_stream16(&codes[gidx], out);
-        if (MASK) store_stream4(&mask[gidx], mw);
+        store_through16(&codes[gidx], out);
+        if (MASK) store_through4(&mask[gidx], mw);
     }
     __syncthreads();
     if (threadIdx.x < 64u) {
@@ -277,7 +277,7 @@ __device__ __forceinline__ void transposed_store_tile(const uint4* s_codes, cons
         uint32_t r = col0 + lc, grp = grp0 + part;
         if (r < rows && grp < gk) {
             uint4 q = s_codes[(lc ^ ((lc >> 4) & 1u)) * 8u + (part ^ ((lc >> 1) & 7u))];
-            store_stream16(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q);
+            store_through16(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q);
         }
     }
     if (MASK) {
@@ -472,7 +472,7 @@ __device__ __forceinline__ void quant_columns_block(const uint16_t* __restrict__
         encode_group<MODE>(v, p, stream, ((uint64_t)r * k + grp * 32u) >> 4, q, sb, m);
         reinterpret_cast<uint8_t*>(s)[((j & 1u) * 8u * CPL + lc) * 4u + (j >> 1)] = (uint8_t)sb;
         if (r < rows && grp < gk) {
-            store_stream16(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q);
+            store_through16(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q);
             if (MASK) mask[(size_t)r * gk + grp] = m;
         }
     }
@@ -585,7 +585,7 @@ __device__ __forceinline__ void requant_columns_block(const uint8_t* __restrict_
         uint32_t sb, m;                                                                                 \
         encode_group<MODE>(V, p, stream, q_base, q, sb, m);                                              \
         s_byte[(C) * 4u] = (uint8_t)sb;                                                                 \
-        if (r0 + (C) < rows && grp < gk) *reinterpret_cast<uint4*>(dst_codes) = q;                       \
+        if (r0 + (C) < rows && grp < gk) store_through16(dst_codes, q);                                 \
         q_base += k >> 4;                                                                               \
         dst_codes += k >> 1;                                                                            \
         __builtin_amdgcn_sched_barrier(0);                                                              \

@@ -175,7 +175,7 @@ __device__ __forceinline__ float epilogue_norm(float v, float signed_norm) { ret
 template <int TM, int TN, bool OUT_BF16, bool FUSED, bool FULL, typename ACC, int AM, int AN>
 __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf, void* d, uint32_t ldd,
                                                  const uint32_t* mask, float alpha, uint32_t row_base,
-                                                 uint32_t col_base, uint32_t m, uint32_t n, uint32_t lane, uint32_t nb) {
+                                                 uint32_t col_base, uint32_t m, uint32_t n, uint32_t lane, uint32_t nb, uint32_t past) {
     static_assert(TN == 2 || TN == 4, "the slice swap of odd rows pairs the slices up");
     constexpr bool A32 = sizeof(ACC) == sizeof(v16f);
     static_assert(AM == (A32 ? TM : 2 * TM) && AN == (A32 ? TN : 2 * TN), "the accumulators must make up the tile");
@@ -213,6 +213,12 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
                 }
             }
         }
+    }
+    if (FUSED) {     // the masks are here before the first store: the compiler does not count the stores below and would wait for them too
+#pragma unroll
+        for (uint32_t p = 0; p < PASSES; ++p)
+#pragma unroll
+            for (uint32_t j = 0; j < TN; ++j) asm volatile("" : "+v"(mw[p][j]));
     }
     auto write_pass = [&](uint32_t p) __attribute__((always_inline)) {
         if constexpr (A32) {
@@ -268,7 +274,6 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
         }
 #pragma unroll
         for (uint32_t j = 0; j < TN; ++j) {
-            const uint32_t gcol = col_base + j * 32u;
             float v0 = vv[j][0], v1 = vv[j][1], v2 = vv[j][2], v3 = vv[j][3];
             if (FUSED) {
                 const float a0 = v0 + v1, a1 = v0 - v1, a2 = v2 + v3, a3 = v2 - v3;
@@ -276,15 +281,30 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
                 QUARTET_BUTTERFLIES_ACROSS(v0, v1, v2, v3, up4, up8, up16);
                 v0 = epilogue_norm(v0, norm); v1 = epilogue_norm(v1, norm); v2 = epilogue_norm(v2, norm); v3 = epilogue_norm(v3, norm);
             }
-            v0 = v0 * alpha; v1 = v1 * alpha; v2 = v2 * alpha; v3 = v3 * alpha;
-            if (!FULL && grow >= m) continue;
-            const uint32_t col = gcol + 4u * c;
+            vv[j][0] = v0 * alpha; vv[j][1] = v1 * alpha; vv[j][2] = v2 * alpha; vv[j][3] = v3 * alpha;
+        }
+        if (!FULL && grow >= m) continue;
+        // past (a launch whose results the memory-side cache cannot hold): non-temporal; otherwise through the L2.  Against plain stores,
+        // whose lines the L2 evicts and writes back while the next tiles load (us): forward 1003 x 2048 x 5632 22.1 -> 21.1; layer steps 2336 x
+        // 1376 x 3168 64.8 -> 63.7, 16384 x 4096 x 4096 563 -> 547, 16384 x 4096 x 11008 1328 -> 1306.  A branch per pass, not per store.
+        if (FULL && !OUT_BF16 && past) {
+#pragma unroll
+            for (uint32_t j = 0; j < TN; ++j) {
+                const v4f v = {vv[j][0], vv[j][1], vv[j][2], vv[j][3]};
+                __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(static_cast<float*>(d) + (size_t)grow * ldd + col_base + j * 32u + 4u * c));
+            }
+            continue;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < TN; ++j) {
+            const uint32_t col = col_base + j * 32u + 4u * c;
             const size_t at = (size_t)grow * ldd + col;
+            const float v0 = vv[j][0], v1 = vv[j][1], v2 = vv[j][2], v3 = vv[j][3];
             if (OUT_BF16) {
                 uint16_t* dst = static_cast<uint16_t*>(d) + at;
                 const uint32_t h0 = f32_to_bf16_rne(v0), h1 = f32_to_bf16_rne(v1), h2 = f32_to_bf16_rne(v2), h3 = f32_to_bf16_rne(v3);
                 if (FULL || (wide && col + 4u <= n)) {
-                    *reinterpret_cast<uint2*>(dst) = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
+                    store_through8(dst, h0 | (h1 << 16), h2 | (h3 << 16));
                 } else {
                     if (col < n) dst[0] = (uint16_t)h0;
                     if (col + 1u < n) dst[1] = (uint16_t)h1;
@@ -294,7 +314,7 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
             } else {
                 float* dst = static_cast<float*>(d) + at;
                 if (FULL || (wide && col + 4u <= n)) {
-                    *reinterpret_cast<float4*>(dst) = make_float4(v0, v1, v2, v3);
+                    store_through16(dst, make_uint4(f2u(v0), f2u(v1), f2u(v2), f2u(v3)));
                 } else {
                     if (col < n) dst[0] = v0;
                     if (col + 1u < n) dst[1] = v1;

@@ -61,6 +61,7 @@ struct GemmProblem {
 };
 struct GemmBatch {
     GemmProblem p[2];
+    uint32_t past;                  // results are stored past the memory-side cache (store_tile_rows8)
 };
 
 // Byte selector that turns a lane's raw scale dword of a K-quad (with 0x7F7F7F7F as the other source of v_perm_b32) into its scale
@@ -321,8 +322,8 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         const uint32_t* __restrict__ mask = q.mask;
         const uint32_t row_base = m0 + wm0, col_base = n0 + wn0;
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
-        if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
-        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
+        if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
         stores = full;                                     // 16 passes of four stores each; a ragged tile may have skipped some
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // the quads issued past the last tile (zero-filled) have landed before the LDS is given back
@@ -585,8 +586,8 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         const uint32_t* __restrict__ mask = q.mask;
         const uint32_t row_base = m0 + wm0, col_base = n0 + wn0;
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
-        if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
-        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb);
+        if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
         stores = full;                                     // every store was issued; a ragged tile may have skipped some
         __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
@@ -622,6 +623,13 @@ static int stream_blocks() {
     return cus;
 }
 
+// fp32 results of a launch that the memory-side cache (256 MB) cannot hold are stored past it: they would only push the operands
+// out.  What it can hold is stored through the L2 and stays there for its reader.
+static uint32_t stored_past(const GemmBatch& batch, bool bf16) {
+    const double results = (double)batch.p[0].m * batch.p[0].n + (double)batch.p[1].m * batch.p[1].n;
+    return !bf16 && results * 4.0 >= 256.0 * 1024.0 * 1024.0 ? 1u : 0u;
+}
+
 // tile grid and band height of one product for block tiles of bm x bn
 static GemmProblem make_problem(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes, const uint8_t* b_scales,
                                 int64_t m, int64_t n, int64_t k, float alpha, void* d, int64_t ldd, const uint32_t* mask,
@@ -652,6 +660,7 @@ static void launch_stream_t(const uint8_t* a_codes, const uint8_t* a_scales, con
     GemmBatch batch;
     batch.p[0] = make_problem(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, 256, 256);
     batch.p[1] = GemmProblem{};      // no second product
+    batch.past = stored_past(batch, OUT_BF16);
     launch_stream_batch_t<OUT_BF16, FUSED>(batch, nb, st);
 }
 
@@ -669,6 +678,7 @@ static void launch_stream_tile_t(const uint8_t* a_codes, const uint8_t* a_scales
     GemmBatch batch;
     batch.p[0] = make_problem(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, 64 * TM, 64 * TN);
     batch.p[1] = GemmProblem{};      // no second product
+    batch.past = stored_past(batch, OUT_BF16);
     launch_stream_tile_batch_t<TM, TN, OUT_BF16, FUSED>(batch, nb, st);
 }
 
@@ -802,6 +812,7 @@ hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_b
                               kTileM[variant], kTileN[variant]);
     batch.p[1] = make_problem(g1.a_codes, g1.a_scales, g1.b_codes, g1.b_scales, g1.m, g1.n, g1.k, g1.alpha, g1.d, g1.ldd, g1.mask,
                               kTileM[variant], kTileN[variant]);
+    batch.past = stored_past(batch, d_bf16 != 0);
     if (variant == 1) { if (d_bf16) launch_stream_tile_batch_t<2, 4, true, true>(batch, nb, st); else launch_stream_tile_batch_t<2, 4, false, true>(batch, nb, st); }
     else if (variant == 2) { if (d_bf16) launch_stream_tile_batch_t<2, 2, true, true>(batch, nb, st); else launch_stream_tile_batch_t<2, 2, false, true>(batch, nb, st); }
     else { if (d_bf16) launch_stream_batch_t<true, true>(batch, nb, st); else launch_stream_batch_t<false, true>(batch, nb, st); }

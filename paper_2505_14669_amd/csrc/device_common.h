@@ -51,10 +51,11 @@ __device__ __forceinline__ uint32_t load_stream4(const void* p) {
 // non-temporal stores, whose lines the products then fetch from HBM (us): forward 1003 x 2048 x 5632 23.3 -> 22.1; layer steps 4096 x
 // 2048 x 2048 76.8 -> 71.2, 2336 x 1376 x 3168 69.9 -> 64.8, 8192 x 5632 x 2048 249.6 -> 238.7, 16384 x 4096 x 4096 580 -> 563, 16384 x 4096 x
 // 11008 1341 -> 1328; the transposed stochastic quantizer alone is unchanged.  Plain stores lie between the two.  The s_nop: a vector
-// instruction may not overwrite the data of a wide store in the next issue slot, and the compiler does not see a store here.
+// instruction may not overwrite the data of a store of more than eight bytes within two wait states, and the compiler does not see a
+// store here (a test looks through the built kernels).
 __device__ __forceinline__ void store_through16(void* p, const uint4& q) {
     v4u_t v = {q.x, q.y, q.z, q.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" :: "v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_through8(void* p, uint32_t lo, uint32_t hi) {
     v2u_t v = {lo, hi};

@@ -43,16 +43,16 @@ __device__ __forceinline__ void store_stream16(void* p, const uint4& q) {
     v4u_t v = {q.x, q.y, q.z, q.w};
     __builtin_nontemporal_store(v, static_cast<v4u_t*>(p));
 }
+__device__ __forceinline__ void store_stream4(void* p, uint32_t v) {
+    __builtin_nontemporal_store(v, static_cast<uint32_t*>(p));
+}
 __device__ __forceinline__ uint32_t load_stream4(const void* p) {
     return __builtin_nontemporal_load(static_cast<const uint32_t*>(p));
 }
-// 16-byte and 4-byte stores that go through the L2 to memory (device scope), for what another kernel reads soon: the lines stay in
-// the memory-side cache, and the L2 has nothing left to write back when the kernel ends.  The quantizers' codes and masks, against
-// non-temporal stores, whose lines the products then fetch from HBM (us): forward 1003 x 2048 x 5632 23.3 -> 22.1; layer steps 4096 x
-// 2048 x 2048 76.8 -> 71.2, 2336 x 1376 x 3168 69.9 -> 64.8, 8192 x 5632 x 2048 249.6 -> 238.7, 16384 x 4096 x 4096 580 -> 563, 16384 x 4096 x
-// 11008 1341 -> 1328; the transposed stochastic quantizer alone is unchanged.  Plain stores lie between the two.  The s_nop: a vector
-// instruction may not overwrite the data of a store of more than eight bytes within two wait states, and the compiler does not see a
-// store here (a test looks through the built kernels).
+// Stores of 16, 8 and 4 bytes that go through the L2 to memory (device scope), for what another kernel reads soon: the lines stay
+// in the memory-side cache, and the L2 has nothing left to write back when the kernel ends.  The s_nop: a vector instruction may not
+// overwrite the data of a store of more than eight bytes within two wait states, and the compiler does not see a store here (a test
+// looks through the built kernels).
 __device__ __forceinline__ void store_through16(void* p, const uint4& q) {
     v4u_t v = {q.x, q.y, q.z, q.w};
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");

@@ -148,6 +148,21 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4& q, float* v) {
     v[6] = u2f(q.w << 16); v[7] = u2f(q.w & 0xFFFF0000u);
 }
 
+// Codes and masks of a matrix [rows x 32 gk] go through the L2 and stay in the memory-side cache (256 MB), where the product that
+// follows finds them; from 64 MB of codes on they go past it, where they would displace more than they bring.  Against non-temporal
+// stores for all (us): forward 1003 x 2048 x 5632 23.3 -> 22.1; layer steps 4096 x 2048 x 2048 76.8 -> 71.2, 2336 x 1376 x 3168 69.9 ->
+// 64.8, 8192 x 5632 x 2048 249.6 -> 238.7, 16384 x 4096 x 4096 580 -> 563.  The quantizers alone on rotating buffers, through the L2 / past it
+// (GB/s): 16384 x 4096 forward 6110 / 5770, stochastic transposed 4610 / 4550; 16384 x 11008 4770 / 5600, 4700 / 5250.
+__device__ __forceinline__ bool codes_past_cache(uint32_t rows, uint32_t gk) { return (uint64_t)rows * gk >= (64u << 20) / 16u; }
+__device__ __forceinline__ void store_codes(void* p, const uint4& q, bool past) {
+    if (past) store_stream16(p, q);
+    else store_through16(p, q);
+}
+__device__ __forceinline__ void store_mask(void* p, uint32_t m, bool past) {
+    if (past) store_stream4(p, m);
+    else store_through4(p, m);
+}
+
 // ------------------------------------------------------------------ row mode
 // Block = 8 rows x 32 groups (four 256-element K-quads, 2 KB of bf16 per row).  Wave w owns rows
 // 2w, 2w+1; lane l the group l%32 of row l/32.  Loads are lane-contiguous 16-byte chunks, swizzled
@@ -206,8 +221,9 @@ __device__ __forceinline__ void quant_row_tile(const uint16_t* __restrict__ x, u
     reinterpret_cast<uint8_t*>(s_scale)[(((gi >> 3) * 2u + (gi & 1u)) * 8u + row_local) * 4u + ((gi & 7u) >> 1)] = (uint8_t)sb;
     if (row < rows && g < gk) {
         const size_t gidx = (size_t)row * gk + g;
-        store_through16(&codes[gidx], out);
-        if (MASK) store_through4(&mask[gidx], mw);
+        const bool past = codes_past_cache(rows, gk);
+        store_codes(&codes[gidx], out, past);
+        if (MASK) store_mask(&mask[gidx], mw, past);
     }
     __syncthreads();
     if (threadIdx.x < 64u) {
@@ -277,7 +293,7 @@ __device__ __forceinline__ void transposed_store_tile(const uint4* s_codes, cons
         uint32_t r = col0 + lc, grp = grp0 + part;
         if (r < rows && grp < gk) {
             uint4 q = s_codes[(lc ^ ((lc >> 4) & 1u)) * 8u + (part ^ ((lc >> 1) & 7u))];
-            store_through16(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q);
+            store_codes(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q, codes_past_cache(rows, gk));
         }
     }
     if (MASK) {
@@ -472,7 +488,7 @@ __device__ __forceinline__ void quant_columns_block(const uint16_t* __restrict__
         encode_group<MODE>(v, p, stream, ((uint64_t)r * k + grp * 32u) >> 4, q, sb, m);
         reinterpret_cast<uint8_t*>(s)[((j & 1u) * 8u * CPL + lc) * 4u + (j >> 1)] = (uint8_t)sb;
         if (r < rows && grp < gk) {
-            store_through16(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q);
+            store_codes(codes + (size_t)r * (k >> 1) + (size_t)grp * 16u, q, codes_past_cache(rows, gk));
             if (MASK) mask[(size_t)r * gk + grp] = m;
         }
     }
@@ -576,6 +592,7 @@ __device__ __forceinline__ void requant_columns_block(const uint8_t* __restrict_
     const uint32_t r0 = c0 + chunk * NC;
     uint64_t q_base = ((uint64_t)r0 * k + grp * 32u) >> 4;
     uint8_t* dst_codes = codes + (size_t)r0 * (k >> 1) + (size_t)grp * 16u;
+    const bool past = codes_past_cache(rows, gk);
     uint8_t* s_byte = reinterpret_cast<uint8_t*>(s) + ((((chunk * NC) >> 5) * 2u + (j & 1u)) * (NC >= 4u ? 32u : 16u) + ((chunk * NC) & 31u)) * 4u + (j >> 1);
 #define REQUANT_COLUMN(C, V)                                                                            \
     {                                                                                                   \
@@ -585,7 +602,7 @@ __device__ __forceinline__ void requant_columns_block(const uint8_t* __restrict_
         uint32_t sb, m;                                                                                 \
         encode_group<MODE>(V, p, stream, q_base, q, sb, m);                                              \
         s_byte[(C) * 4u] = (uint8_t)sb;                                                                 \
-        if (r0 + (C) < rows && grp < gk) store_through16(dst_codes, q);                                 \
+        if (r0 + (C) < rows && grp < gk) store_codes(dst_codes, q, past);                               \
         q_base += k >> 4;                                                                               \
         dst_codes += k >> 1;                                                                            \
         __builtin_amdgcn_sched_barrier(0);                                                              \

@@ -209,7 +209,8 @@ int quartet_mxfp4_gemm(const uint8_t *a_codes, const uint8_t *a_scales,
  * Test and tuning aid (no part of the method): which of the library's GEMM kernels quartet_mxfp4_gemm and
  * quartet_mxfp4_gemm_grad launch from now on.  variant -1 = choose by problem size (the default; small problems run
  * on kernels that split the inner dimension inside a block); 0, 1, 2 = tiles of 256 x 256, 128 x 256 or 128 x 128
- * (all three: one block per compute unit streams its tiles through a ring of two, three or four K-quads of 256 elements in LDS).
+ * (all three: one block per compute unit, or two with tiles of 128 x 128 where that is sooner, streams its tiles through a ring of two,
+ * three or four K-quads of 256 elements in LDS).
  * band_height 0 = choose by shape (the default), 1..64 = tile rows each XCD walks at a time.
  * Every combination gives the same results up to fp32 summation order; the parity tests use this to
  * reach each kernel.  Process-global, not thread-safe.  QUARTET_EINVAL outside those ranges.

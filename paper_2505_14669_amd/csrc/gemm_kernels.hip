@@ -18,8 +18,8 @@
 // l/32 and byte 2 + l/32.  32 x 32 x 64: lane l reads dword l of the tile, byte s for K-step s.  The paper's separate scale-rearrangement step does not exist here.
 //
 // Kernels: gemm_mxfp4_stream_kernel (256 x 256 tiles) and gemm_mxfp4_stream_tile_kernel (128 x 256 and 128 x 128 tiles
-// for small problems): one block per compute unit streams its tiles through a ring of K-quads (256 elements) in LDS.  Both work
-// through a batch of one or two products per launch (GemmBatch).
+// for small problems): one block per compute unit streams its tiles through a ring of K-quads (256 elements) in LDS, of 128 x 128 tiles
+// also two (gemm_mxfp4_twin_kernel).  All work through a batch of one or two products per launch (GemmBatch).
 // What bounds them besides power is the way of the operands into the LDS: a cache line is 128 bytes, so a ring of 128-element
 // stages (64 bytes of codes per row) fetched every line twice.  K-quads, whole lines, one barrier per quad and reads and loads spread
 // evenly over the matrix-core instructions, 16 x 16 x 128 on the large tiles and 32 x 32 x 64 on the small ones, took against that design
@@ -61,8 +61,31 @@ struct GemmProblem {
 };
 struct GemmBatch {
     GemmProblem p[2];
+    uint32_t extra_tiles, late;     // the second product's tiles that the last `late` blocks take in rounds of their own, see TileWalk
     uint32_t past;                  // results are stored past the memory-side cache (store_tile_rows8)
 };
+
+// The tiles of block b of G: b, b + G, ... of the first product, then, with the blocks counted from r = its tiles % G on, tiles of the
+// second.  The G - r = late blocks from r on have one tile of the first product fewer than the others, and its tiles may take several
+// times as long as the second's: the first extra_tiles of those go to the late blocks alone, `late` a round, the others to all
+// blocks, G a round.  The launcher picks extra_tiles (pair_level).  sel: product, tile: number in it; past the end in the second product.
+struct TileWalk {
+    uint32_t sel, tile;
+};
+#define WALK_START(W)                                                                                   \
+    {                                                                                                   \
+        W.sel = blockIdx.x >= first_tiles ? 1u : 0u;                                                    \
+        W.tile = W.sel ? second_start : blockIdx.x;                                                     \
+    }
+#define WALK_NEXT(W)                                                                                    \
+    {                                                                                                   \
+        if (W.sel) {                                                                                    \
+            W.tile += W.tile < extra_tiles ? late : G;                                                  \
+        } else {                                                                                        \
+            W.tile += G;                                                                                \
+            if (W.tile >= first_tiles) { W.sel = 1u; W.tile = second_start; }                           \
+        }                                                                                               \
+    }
 
 // Byte selector that turns a lane's raw scale dword of a K-quad (with 0x7F7F7F7F as the other source of v_perm_b32) into its scale
 // operand: byte 0 for the quad's first K-step, byte 2 for its second.  group0: the quad's first group; groups from gk on do not
@@ -79,7 +102,7 @@ __device__ __forceinline__ uint32_t scale_selector(uint32_t lane, uint32_t group
 // The epilogue uses a scratch of its own (16 KB beside the 144 KB ring).
 template <bool OUT_BF16, bool FUSED>
 __global__ void __launch_bounds__(256)
-gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t TM = 4, TN = 4, BM = 256, BN = 256;
     constexpr uint32_t CODES = (BM + BN) * 8;            // 16-byte chunks of codes per K-quad
     constexpr uint32_t QUAD = CODES + 256;               // + 16 scale tiles of 256 B
@@ -96,17 +119,12 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t l16 = lane & 15u, quarter = lane >> 4;
-    const uint32_t G = gridDim.x, first_tiles = batch.p[0].total_tiles;
+    const uint32_t G = gridDim.x, first_tiles = batch.p[0].total_tiles, second_tiles = batch.p[1].total_tiles;
+    const uint32_t extra_tiles = batch.extra_tiles, late = batch.late;
+    const uint32_t second_start = blockIdx.x + late >= G ? blockIdx.x + late - G : extra_tiles + late + blockIdx.x;
     const uint32_t wm0 = (wave >> 1) * 128u, wn0 = (wave & 1u) * 128u;
     const bool scales_of_a = wave < 2u;
 
-// product SEL and the tile's number in it for virtual block id V (ids past the last tile: a number past the product's tiles)
-#define STREAM_PRODUCT(V, SEL, LOCAL)                                                                   \
-    {                                                                                                   \
-        LOCAL = (V);                                                                                    \
-        SEL = 0u;                                                                                       \
-        if (LOCAL >= first_tiles) { LOCAL -= first_tiles; SEL = 1u; }                                   \
-    }
 // tile origin of tile number V of product Q (XCD-aware order, bands of band_height tile rows); V >= its tiles: M0 = m (no rows)
 #define STREAM_TILE(Q, V, M0, N0)                                                                       \
     {                                                                                                   \
@@ -135,16 +153,18 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
     // formed in a rotated order then, the same for a tile wherever it runs.  Only for K a multiple of 256: a ragged last
     // K-quad keeps its place at the end.
     // A load instruction brings 8 rows x 128 bytes (whole cache lines: with 16 rows x 64 bytes every line crosses from the L2 twice).
-    uint32_t iv = blockIdx.x, iq = 0u;
+    TileWalk iw;
+    uint32_t iq = 0u;
+    WALK_START(iw)
     v4i_t res_a, res_b, res_s;
     uint32_t kb, kq, goff, gstep, soff, ikq;
     const uint32_t drow = wave * 8u + (lane >> 3);
     const uint32_t dcol = (lane & 7u) ^ ((drow >> 1) & 7u);
 #define STREAM_ISSUE_SETUP()                                                                            \
     {                                                                                                   \
-        uint32_t sel_, lv_, m0_, n0_;                                                                   \
-        STREAM_PRODUCT(iv, sel_, lv_)                                                                   \
-        const GemmProblem& q_ = batch.p[sel_];                                                          \
+        uint32_t m0_, n0_;                                                                              \
+        const GemmProblem& q_ = batch.p[iw.sel];                                                        \
+        const uint32_t lv_ = iw.tile;                                                                   \
         STREAM_TILE(q_, lv_, m0_, n0_)                                                                  \
         const uint32_t k_ = q_.k;                                                                       \
         const uint32_t kq_ = (k_ + 255u) >> 8;  /* scale tiles per 32 rows */                           \
@@ -196,7 +216,7 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         if (ikq == kq) ikq = 0u;                                                                        \
         if (iq == kq) {                                                                                 \
             iq = 0u;                                                                                    \
-            iv += G;                                                                                    \
+            WALK_NEXT(iw)                                                                               \
             STREAM_ISSUE_SETUP()                                                                        \
         }                                                                                               \
     }
@@ -246,11 +266,11 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         _Pragma("unroll") for (uint32_t j = 0; j < 2u * TN; ++j) sb[j] = __builtin_amdgcn_perm(0x7F7F7F7Fu, rb_n[j], sel_); \
         mfma_scales_written(sa, sb);                                                                    \
     }
-    uint32_t csel, clv;
-    STREAM_PRODUCT(blockIdx.x, csel, clv)
+    TileWalk cw;                                         // the tile being computed
+    WALK_START(cw)
     STREAM_SCALES_READ_A(0u)
     STREAM_SCALES_READ_B(0u)
-    STREAM_SCALES_USE(0u, batch.p[csel].k >> 5)
+    STREAM_SCALES_USE(0u, batch.p[cw.sel].k >> 5)
 // One K-quad: two K-steps of 64 matrix-core instructions; SL = its ring slot.  The fragments of a K-step are read one by one during the
 // step before it.  The quad's one barrier stands between its steps: every wave has read its last fragment of the slot, so the
 // quad after the next is loaded into it during the second step, and every load of the next quad (issued a whole quad earlier) has
@@ -298,11 +318,12 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
     float* wbuf = reinterpret_cast<float*>(&lds[2u * QUAD]) + wave * 1024u;
     uint32_t sl = 0u;                                      // ring slot of the current quad
     bool stores = false;                                   // the previous tile's 64 result stores are younger than the loads to wait for
-    for (uint32_t cv = blockIdx.x; cv < total_tiles; cv += G) {
-        STREAM_PRODUCT(cv, csel, clv)
+    while (cw.sel == 0u || cw.tile < second_tiles) {
+        const uint32_t csel = cw.sel, clv = cw.tile;
         const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
         // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
-        const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
+        WALK_NEXT(cw)
+        const uint32_t gk_after = batch.p[cw.sel].k >> 5;
         mfma_clear_accumulators(acc);                      // (the first quad apart, with the constant 0 in their place, spills)
         __builtin_amdgcn_sched_barrier(0);
         for (uint32_t qd = 0u; qd < quads; ++qd, sl ^= 1u) {
@@ -332,7 +353,6 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
         atomicAdd(reinterpret_cast<unsigned long long*>(clock_counters), (unsigned long long)(t1 - clk_t0));
         atomicAdd(reinterpret_cast<unsigned long long*>(clock_counters) + 1, (unsigned long long)(w1 - clk_w0));
     }
-#undef STREAM_PRODUCT
 #undef STREAM_TILE
 #undef STREAM_ISSUE_SETUP
 #undef STREAM_ISSUE
@@ -361,18 +381,25 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uin
 // the L2, not by power, and the smaller instruction of the 256 x 256 kernel means twice as many of them for the same work.  Measured
 // against 16 x 16 x 128 (us, fp32 results): 128 x 128 tiles 2048 x 2048 x 4096 14.6 / 16.0, 4096 x 4096 x 1024 21.0 / 22.8, 4096^3 47.4 / 49.2;
 // 128 x 256 tiles 18.1 / 20.5, 19.8 / 21.0, 41.2 / 42.3; same bits.
-template <int TM, int TN, bool OUT_BF16, bool FUSED>
-__global__ void __launch_bounds__(256)
-gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+// PER_CU = 2: two blocks share a compute unit (each with two slots and epilogue scratch of its own, 80 KB), so one multiplies while the
+// other waits for its loads or stores its results.  A quad's slot is filled again behind the quad's own barrier, and the loads have
+// three quarters of a quad to land: with several tiles per compute unit that is less than what the epilogues cost one block alone.
+// Pairs of layers (tokens, in, out), one block / two (us): 608 x 8832 x 3424 63.6 / 52.7, 4800 x 1824 x 2112 48.9 / 43.6, 9600 x 576 x 576 32.4 /
+// 36.0 (a tile or two per compute unit: the deeper ring); single products 10327 x 992 x 800 21.1 / 17.9, 4926 x 6496 x 10144 230 / 251.
+template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED>
+__device__ __forceinline__ void stream_tiles(const GemmBatch& batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t BM = 64 * TM, BN = 64 * TN;
     static_assert(BM % 128 == 0 && BN % 128 == 0, "a wave's four scale tiles must belong to one operand");
     constexpr uint32_t CODES = (BM + BN) * 8;            // 16-byte chunks of codes per K-quad
     constexpr uint32_t QUAD = CODES + 256;               // + room for 16 scale tiles of 256 B (one KB per wave)
-    constexpr uint32_t S = BN == 256 ? 3u : 4u;          // ring slots
+    constexpr uint32_t S = PER_CU == 2 ? 2u : BN == 256 ? 3u : 4u;   // ring slots
+    constexpr bool LATE = S == 2u;                       // a quad's slot is filled again behind its own barrier
     constexpr uint32_t LA = BM / 32, LB = BN / 32, NL = LA + LB;   // LDS-direct loads of codes per wave per quad
     constexpr uint32_t NT = (BM + BN) / 32;              // scale tiles per K-quad: A's, then B's
     constexpr int NM = TM * TN, R = TM + TN;             // matrix-core instructions and fragment reads per K-step (64 elements)
-    __shared__ v4i_t lds[S * QUAD];
+    constexpr uint32_t EPI = LATE ? 4u * TN * 64u : 0u;  // 16-byte chunks of epilogue scratch beside the ring
+    __shared__ v4i_t lds[S * QUAD + EPI];
+    static_assert(PER_CU * sizeof(lds) <= 160u * 1024u, "the blocks of a compute unit share its LDS");
 
     // measurement support: shader-clock and constant-clock ticks of this block's run (wave-uniform branch)
     uint64_t clk_t0 = 0, clk_w0 = 0;
@@ -384,21 +411,16 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lrow = lane & 31u, lhalf = lane >> 5;
-    const uint32_t G = gridDim.x, first_tiles = batch.p[0].total_tiles;
+    const uint32_t G = gridDim.x, first_tiles = batch.p[0].total_tiles, second_tiles = batch.p[1].total_tiles;
+    const uint32_t extra_tiles = batch.extra_tiles, late = batch.late;
+    const uint32_t second_start = blockIdx.x + late >= G ? blockIdx.x + late - G : extra_tiles + late + blockIdx.x;
     const uint32_t wm0 = (wave >> 1) * (TM * 32u), wn0 = (wave & 1u) * (TN * 32u);
     // scale tiles 4 wave .. 4 wave + 3 of [A's | B's] are this wave's to fetch (waves past the last tile fetch nothing real:
     // their load is out of range and delivers zeros, which keeps every wave's count of loads the same)
     const bool has_scales = 4u * wave < NT, scales_of_a = 4u * wave < BM / 32u;
     const uint32_t stile0 = scales_of_a ? 4u * wave : 4u * wave - BM / 32u;
 
-// product SEL and the tile's number in it for virtual block id V; tile origin of tile number V of product Q (as in the
-// 256 x 256 kernel)
-#define PRODUCT_OF(V, SEL, LOCAL)                                                                       \
-    {                                                                                                   \
-        LOCAL = (V);                                                                                    \
-        SEL = 0u;                                                                                       \
-        if (LOCAL >= first_tiles) { LOCAL -= first_tiles; SEL = 1u; }                                   \
-    }
+// tile origin of tile number V of product Q (as in the 256 x 256 kernel)
 #define TILE_ORIGIN(Q, V, M0, N0)                                                                       \
     {                                                                                                   \
         const uint32_t v_ = (V), tt_ = (Q).total_tiles;                                                 \
@@ -416,16 +438,18 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
             M0 = (Q).m; N0 = (Q).n;                                                                     \
         }                                                                                               \
     }
-    uint32_t iv = blockIdx.x, iq = 0u;                   // issue cursor: the tile and K-quad the next loads belong to
+    TileWalk iw;                                         // issue cursor: the tile and K-quad the next loads belong to
+    uint32_t iq = 0u;
+    WALK_START(iw)
     v4i_t res_a, res_b, res_s;
     uint32_t kb, kq, goff, gstep, soff;                  // of the cursor's product
     const uint32_t drow = wave * 8u + (lane >> 3);
     const uint32_t dcol = (lane & 7u) ^ ((drow >> 1) & 7u);
 #define ISSUE_SETUP()                                                                                   \
     {                                                                                                   \
-        uint32_t sel_, lv_, m0_, n0_;                                                                   \
-        PRODUCT_OF(iv, sel_, lv_)                                                                       \
-        const GemmProblem& q_ = batch.p[sel_];                                                          \
+        uint32_t m0_, n0_;                                                                              \
+        const GemmProblem& q_ = batch.p[iw.sel];                                                        \
+        const uint32_t lv_ = iw.tile;                                                                   \
         TILE_ORIGIN(q_, lv_, m0_, n0_)                                                                  \
         const uint32_t k_ = q_.k, kq_ = (k_ + 255u) >> 8;                                               \
         kq = kq_ ? kq_ : 1u;                                                                            \
@@ -469,7 +493,7 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         ++iq;                                                                                           \
         if (iq == kq) {                                                                                 \
             iq = 0u;                                                                                    \
-            iv += G;                                                                                    \
+            WALK_NEXT(iw)                                                                               \
             ISSUE_SETUP()                                                                               \
         }                                                                                               \
     }
@@ -502,26 +526,30 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
 
     // vector-memory operations that may be under way at a quad's barrier: the loads of the quads behind the next one, and once after a
     // tile's end its result stores, which are younger than the next quad's loads
+    constexpr uint32_t FIRST = LATE ? 2u : S - 1u, AHEAD0 = (FIRST - 1u) * (NL + 1u);   // quads loaded before the first barrier
     constexpr uint32_t AHEAD = (S - 2u) * (NL + 1u), AHEAD_ST = AHEAD + TM * 4u * TN;
     static_assert(AHEAD_ST < 64u, "the counter has six bits");
+    constexpr uint32_t WAIT0 = 0x0070u | (AHEAD0 & 15u) | ((AHEAD0 >> 4) << 14);
     constexpr uint32_t WAIT = 0x0070u | (AHEAD & 15u) | ((AHEAD >> 4) << 14);      // and no LDS read is outstanding
     constexpr uint32_t WAIT_ST = 0x0070u | (AHEAD_ST & 15u) | ((AHEAD_ST >> 4) << 14);
 #pragma unroll
-    for (uint32_t s0 = 0; s0 < S - 1u; ++s0) {
+    for (uint32_t s0 = 0; s0 < FIRST; ++s0) {
 #pragma unroll
         for (uint32_t j = 0; j <= NL; ++j) ISSUE(s0, j)
         ISSUE_ADVANCE()
     }
-    __builtin_amdgcn_s_waitcnt(WAIT);
+    __builtin_amdgcn_s_waitcnt(WAIT0);
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int r = 0; r < R; ++r) READ_FRAG(0u, 0, r)
-    uint32_t csel, clv;
-    PRODUCT_OF(blockIdx.x, csel, clv)
+    TileWalk cw;                                         // the tile being computed
+    WALK_START(cw)
     READ_SCALES(0u)
-    USE_SCALES(0u, batch.p[csel].k >> 5)
+    USE_SCALES(0u, batch.p[cw.sel].k >> 5)
 
-// one K-quad in slot SL; SL1: the next quad's slot, SLI: the slot being filled
+// the instruction of a quad behind which load L goes out: spread over the first three K-steps, with two slots over the last one
+#define ISSUE_AT(L) (LATE ? 3 * NM + (L) * NM / ((int)NL + 1) : (L) * 3 * NM / ((int)NL + 1))
+// one K-quad in slot SL; SL1: the next quad's slot, SLI: the slot being filled (SL itself behind the barrier with two slots)
 #define QUAD_BODY(SL, SL1, SLI, STORES, NEXT_QUAD, NEXT_GK)                                             \
     {                                                                                                   \
         _Pragma("unroll") for (int idx = 0; idx < 4 * NM; ++idx) {                                      \
@@ -535,9 +563,9 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
             if (st_ < 2 && ij_ < R) { READ_FRAG(SL, st_ + 1, ij_) FENCE() }                             \
             if (st_ == 2 && 2 * ij_ < R) { READ_FRAG(SL, 3, 2 * ij_) READ_FRAG(SL, 3, 2 * ij_ + 1) FENCE() } \
             _Pragma("unroll") for (int l_ = 0; l_ <= (int)NL; ++l_)                                     \
-                if ((l_ * 3 * NM) / ((int)NL + 1) == idx) { ISSUE(SLI, l_) FENCE() }                    \
+                if (ISSUE_AT(l_) == idx) { ISSUE(SLI, l_) FENCE() }                                     \
             if (idx == 3 * NM - 1) {                                                                    \
-                ISSUE_ADVANCE()                                                                         \
+                if (!LATE) ISSUE_ADVANCE()                                                              \
                 if (STORES) __builtin_amdgcn_s_waitcnt(WAIT_ST);                                        \
                 else __builtin_amdgcn_s_waitcnt(WAIT);                                                  \
                 __builtin_amdgcn_s_barrier();                                                           \
@@ -546,6 +574,7 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
             if (R < NM && st_ == 3 && ij_ < R) { READ_FRAG(SL1, 0, ij_) FENCE() }                       \
             if (R >= NM && st_ == 3 && 2 * ij_ < R) { READ_FRAG(SL1, 0, 2 * ij_) READ_FRAG(SL1, 0, 2 * ij_ + 1) FENCE() } \
             if (idx == 3 * NM + (R < NM ? R : (R + 1) / 2)) { READ_SCALES(SL1) FENCE() }                \
+            if (LATE && idx == 4 * NM - 1) { ISSUE_ADVANCE() FENCE() }                                  \
         }                                                                                               \
         USE_SCALES(NEXT_QUAD, NEXT_GK)                                                                  \
         FENCE()                                                                                         \
@@ -556,11 +585,12 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
     auto slot_after = [](uint32_t s) { return s + 1u == S ? 0u : s + 1u; };
     auto slot_before = [](uint32_t s) { return s == 0u ? S - 1u : s - 1u; };
     bool stores = false;                                   // the previous tile's result stores are younger than the loads to wait for
-    for (uint32_t cv = blockIdx.x; cv < total_tiles; cv += G) {
-        PRODUCT_OF(cv, csel, clv)
+    while (cw.sel == 0u || cw.tile < second_tiles) {
+        const uint32_t csel = cw.sel, clv = cw.tile;
         const uint32_t ck = batch.p[csel].k, gk = ck >> 5, quads = ck ? (ck + 255u) >> 8 : 1u;
         // the tile's last quad reads the first scales of the block's next tile, which may belong to the other product
-        const uint32_t gk_after = (cv + G >= first_tiles && cv + G < total_tiles) ? (batch.p[1].k >> 5) : gk;
+        WALK_NEXT(cw)
+        const uint32_t gk_after = batch.p[cw.sel].k >> 5;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -568,16 +598,16 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
         uint32_t sl1 = slot_after(sl);
-        QUAD_BODY(sl, sl1, slot_before(sl), stores, quads > 1u ? 1u : 0u, quads > 1u ? gk : gk_after)
+        QUAD_BODY(sl, sl1, LATE ? sl : slot_before(sl), stores, quads > 1u ? 1u : 0u, quads > 1u ? gk : gk_after)
         for (uint32_t qd = 1u; qd < quads; ++qd) {
             const bool last = qd + 1u == quads;            // the next quad is the next tile's first
             sl = sl1;
             sl1 = slot_after(sl);
-            QUAD_BODY(sl, sl1, slot_before(sl), false, last ? 0u : qd + 1u, last ? gk_after : gk)
+            QUAD_BODY(sl, sl1, LATE ? sl : slot_before(sl), false, last ? 0u : qd + 1u, last ? gk_after : gk)
         }
         __builtin_amdgcn_sched_barrier(0);
-        // the last quad's slot: every wave is past its last read there, and its next loads go out behind the barrier below
-        float* wbuf = reinterpret_cast<float*>(&lds[sl * QUAD]) + wave * (TN * 256u);
+        // scratch: the last quad's slot, where every wave is past its last read and the next loads go out behind the barrier below
+        float* wbuf = reinterpret_cast<float*>(&lds[(LATE ? S : sl) * QUAD]) + wave * (TN * 256u);
         sl = sl1;
         const GemmProblem& q = batch.p[csel];
         uint32_t m0, n0;
@@ -589,8 +619,10 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
         else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
         stores = full;                                     // every store was issued; a ragged tile may have skipped some
-        __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
+        if (!LATE) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // the quads issued past the last tile (zero-filled) have landed before the LDS is given back
@@ -599,7 +631,6 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
         atomicAdd(reinterpret_cast<unsigned long long*>(clock_counters), (unsigned long long)(t1 - clk_t0));
         atomicAdd(reinterpret_cast<unsigned long long*>(clock_counters) + 1, (unsigned long long)(w1 - clk_w0));
     }
-#undef PRODUCT_OF
 #undef TILE_ORIGIN
 #undef ISSUE_SETUP
 #undef ISSUE
@@ -608,7 +639,20 @@ gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t total_tiles, uint32_t nb
 #undef FENCE
 #undef READ_SCALES
 #undef USE_SCALES
+#undef ISSUE_AT
 #undef QUAD_BODY
+}
+
+template <int TM, int TN, bool OUT_BF16, bool FUSED>
+__global__ void __launch_bounds__(256)
+gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+    stream_tiles<TM, TN, 1, OUT_BF16, FUSED>(batch, nb, clock_counters);
+}
+
+template <bool OUT_BF16, bool FUSED>
+__global__ void __launch_bounds__(256, 2)
+gemm_mxfp4_twin_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+    stream_tiles<2, 2, 2, OUT_BF16, FUSED>(batch, nb, clock_counters);
 }
 
 static int stream_blocks() {
@@ -649,8 +693,8 @@ static GemmProblem make_problem(const uint8_t* a_codes, const uint8_t* a_scales,
 template <bool OUT_BF16, bool FUSED>
 static void launch_stream_batch_t(const GemmBatch& batch, uint32_t nb, hipStream_t st) {
     const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, cus = (uint32_t)stream_blocks();
-    hipLaunchKernelGGL((gemm_mxfp4_stream_kernel<OUT_BF16, FUSED>), dim3(total < cus ? total : cus), dim3(256), 0, st, batch, total,
-                       nb, g_clock_counters);
+    hipLaunchKernelGGL((gemm_mxfp4_stream_kernel<OUT_BF16, FUSED>), dim3(total < cus ? total : cus), dim3(256), 0, st, batch, nb,
+                       g_clock_counters);
 }
 
 template <bool OUT_BF16, bool FUSED>
@@ -661,17 +705,19 @@ static void launch_stream_t(const uint8_t* a_codes, const uint8_t* a_scales, con
     batch.p[0] = make_problem(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, 256, 256);
     batch.p[1] = GemmProblem{};      // no second product
     batch.past = stored_past(batch, OUT_BF16);
+    batch.extra_tiles = batch.late = 0u;
     launch_stream_batch_t<OUT_BF16, FUSED>(batch, nb, st);
 }
 
-template <int TM, int TN, bool OUT_BF16, bool FUSED>
+template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED>
 static void launch_stream_tile_batch_t(const GemmBatch& batch, uint32_t nb, hipStream_t st) {
-    const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, cus = (uint32_t)stream_blocks();
-    hipLaunchKernelGGL((gemm_mxfp4_stream_tile_kernel<TM, TN, OUT_BF16, FUSED>), dim3(total < cus ? total : cus), dim3(256), 0, st,
-                       batch, total, nb, g_clock_counters);
+    const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, room = PER_CU * (uint32_t)stream_blocks();
+    const dim3 grid(total < room ? total : room);
+    if constexpr (PER_CU == 2) hipLaunchKernelGGL((gemm_mxfp4_twin_kernel<OUT_BF16, FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
+    else hipLaunchKernelGGL((gemm_mxfp4_stream_tile_kernel<TM, TN, OUT_BF16, FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
 }
 
-template <int TM, int TN, bool OUT_BF16, bool FUSED>
+template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED>
 static void launch_stream_tile_t(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes,
                                  const uint8_t* b_scales, int64_t m, int64_t n, int64_t k, float alpha, void* d,
                                  int64_t ldd, const uint32_t* mask, uint32_t nb, hipStream_t st) {
@@ -679,64 +725,104 @@ static void launch_stream_tile_t(const uint8_t* a_codes, const uint8_t* a_scales
     batch.p[0] = make_problem(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, 64 * TM, 64 * TN);
     batch.p[1] = GemmProblem{};      // no second product
     batch.past = stored_past(batch, OUT_BF16);
-    launch_stream_tile_batch_t<TM, TN, OUT_BF16, FUSED>(batch, nb, st);
+    batch.extra_tiles = batch.late = 0u;
+    launch_stream_tile_batch_t<TM, TN, PER_CU, OUT_BF16, FUSED>(batch, nb, st);
 }
 
 // Variants: 0 = 256x256 tiles (hand-scheduled K-quad), 1 = 128x256 tiles, 2 = 128x128 tiles (schedule generated from the
-// tile shape); all three: one block per compute unit streams its tiles through a ring of K-quads, two K-steps per
-// trip with the scale byte picked by op_sel.  set_gemm_plan overrides the size heuristic (tests reach every variant
-// through it).
+// tile shape), kTwoPerCu = 128x128 tiles with two blocks per compute unit; blocks stream their tiles through a ring of K-quads, two
+// K-steps per trip with the scale byte picked by op_sel.  set_gemm_plan overrides the size heuristic (tests reach every variant
+// through it; of 128x128 tiles the estimate still says how many blocks).
 // fused != 0: D = alpha * H_along_n((A B^T) . mask) with Hadamard blocks of nb = 1, 2 or 4 groups of 32 columns (mask may
 // be null = all ones), n % (32 nb) == 0.
 //
-// The tile shape is the one with the smallest estimated time of the busiest block, which walks the virtual tile ids b, b + G, ...:
-// launch and first loads, its K-quads, its tiles' epilogues, and the share of the chip that stores results.  Fitted to 60 single
-// products (m 24 .. 8192, n and k 256 .. 11008, both result types) and 45 pairs with the gradient epilogue (rms error 7 % for 128 x 128
-// tiles, 15 % for 256 x 256 ones) when the smaller tiles' kernel took 3-8 % longer than now; the shape chosen is within 1-2 % of the
-// best one on average still (130 single products, 105 pairs), and fits to the present times gain as much on small problems as they lose on
-// large ones (single products 7433 x 9760 x 3008: 128 x 256 tiles, 156 us, for 146).  Measured, 256 x 256 / 128 x 256 / 128 x 128 (us):
-// 5974 x 1888 x 352 22.0 / 21.0 / 15.3; 2758 x 1728 x 5280 48.3 / 28.0 / 32.1; 8182 x 1536 x 3616 37.2 / 39.2 / 39.3; pairs of layers (tokens,
-// in, out) 3072 x 2144 x 4288 78.6 / 60.7 / 50.7; 6464 x 288 x 5472 64.3 / 34.1 / 38.2.
+// The tile shape is the one with the smallest estimated time: launch and first loads, the share of the chip that starts, the
+// busiest compute unit's K-quads and its tiles' epilogues (weighed with the mean: the last round runs on a chip that is partly idle), or
+// what the memory takes for the results if that is more.  Fitted to the products of 330 layers' backward passes (tokens 256 .. 16384, in and
+// out 256 .. 11008) and of 400 forward or serving calls (m 8 .. 16384), both result types, every shape timed behind the conversions that
+// write its operands: the shape chosen costs 1.0 % (pairs) and 1.1 % (singles) more than the best one on average, 7 / 5 % at the 95th
+// percentile.  Measured, 256 x 256 / 128 x 256 / 128 x 128 / 128 x 128 with two blocks per compute unit (us): pairs (dW, dx) of layers (tokens,
+// in, out) 4608 x 2432 x 6016 107 / 104 / 105 / 95, 13696 x 2816 x 832 101 / 69 / 77 / 80; single products 4253 x 3648 x 5408 59.7 / 62.3 / 72.8 /
+// 69.2, 2860 x 4448 x 320 18.2 / 17.2 / 16.2 / 13.2.
 struct StreamCost {
-    double start, per_quad, per_tile, per_fill;
+    double start, per_quad, per_tile, per_fill, per_result, busiest;     // us; per_result: of 10^6 results; busiest: weight against the mean
 };
-static const StreamCost kStreamSingle[3] = {{3.35, 1.324, 6.51, 6.37}, {3.49, 0.825, 4.12, 2.26}, {3.59, 0.542, 2.33, 1.08}};
-static const StreamCost kStreamPair[3] = {{5.20, 1.502, 11.2, 6.67}, {3.96, 0.969, 6.60, 0.25}, {3.87, 0.592, 3.48, 0.0}};
-constexpr int64_t kTileM[3] = {256, 128, 128}, kTileN[3] = {256, 256, 128};
+static const StreamCost kStreamSingle[4] = {{1.42, 1.590, 5.39, 11.7, 0.803, 1.00}, {3.04, 0.904, 3.60, 4.40, 0.752, 1.00},
+                                            {3.20, 0.609, 1.94, 1.95, 0.718, 1.00}, {1.54, 0.677, 1.03, 2.33, 0.591, 0.80}};
+static const StreamCost kStreamPair[4] = {{0.00, 1.520, 10.1, 19.8, 1.505, 1.00}, {3.06, 0.897, 6.46, 2.03, 1.351, 1.00},
+                                          {4.26, 0.582, 4.19, 0.00, 0.128, 0.62}, {0.00, 0.638, 0.84, 5.04, 1.247, 1.00}};
+constexpr int kTwoPerCu = 3;      // 128 x 128 tiles, two blocks per compute unit
+constexpr int64_t kTileM[4] = {256, 128, 128, 128}, kTileN[4] = {256, 256, 128, 128};
 
-static double stream_estimate(int variant, int products, const int64_t* m, const int64_t* n, const int64_t* k, int64_t cus) {
+// The extra rounds of the late blocks (TileWalk) with the smallest load of the busiest block, and the loads: `tiles` tiles of the two products
+// at `cost` each on `blocks` blocks.  early = tiles[0] % blocks blocks have one tile of the first product more than the others, which
+// makes up for cost[0] / cost[1] tiles of the second; the partial last round falls on the late blocks first.
+struct PairLevel {
+    int64_t extra, early;
+    double early_load, late_load;
+    double busiest() const { return early_load > late_load ? early_load : late_load; }
+};
+static PairLevel pair_level(const int64_t (&tiles)[2], const double (&cost)[2], int64_t blocks) {
+    const int64_t r = tiles[0] % blocks, late = blocks - r, few = tiles[0] / blocks, most = (tiles[1] + late - 1) / late;
+    const int64_t level = r > 0 ? (int64_t)(cost[0] / cost[1]) : 0;
+    PairLevel best = {0, r, -1.0, -1.0};
+    for (int64_t i = -2; i < 3; ++i) {                         // no extra rounds, then what is nearest to level ground
+        const int64_t x = i == -2 ? 0 : level + i;
+        if (i > -2 && (x < 1 || x > most || r == 0)) continue;
+        const int64_t rest = tiles[1] > x * late ? tiles[1] - x * late : 0, full = rest / blocks, part = rest % blocks;
+        const int64_t late_tiles = rest > 0 ? x + full + (part > 0) : most, early_tiles = full + (part > late);
+        const PairLevel here = {x, r, r > 0 ? (double)(few + 1) * cost[0] + (double)early_tiles * cost[1] : 0.0,
+                                (double)few * cost[0] + (double)late_tiles * cost[1]};
+        if (best.busiest() < 0.0 || here.busiest() < best.busiest()) best = here;
+    }
+    return best;
+}
+
+// *extra: the late blocks' rounds.  Two blocks b and b + half of a compute unit take turns at its matrix cores: their loads add up.
+static double stream_estimate(int variant, int products, const int64_t* m, const int64_t* n, const int64_t* k, int64_t cus, int64_t* extra) {
     const StreamCost& c = (products == 1 ? kStreamSingle : kStreamPair)[variant];
     int64_t tiles[2] = {0, 0};
-    double cost[2] = {0.0, 0.0};
+    double cost[2] = {0.0, 1.0}, results = 0.0, sum = 0.0;
     for (int p = 0; p < products; ++p) {
         tiles[p] = ((m[p] + kTileM[variant] - 1) / kTileM[variant]) * ((n[p] + kTileN[variant] - 1) / kTileN[variant]);
         cost[p] = c.per_quad * (double)(k[p] > 256 ? (k[p] + 255) / 256 : 1) + c.per_tile;
+        sum += (double)tiles[p] * cost[p];
+        results += (double)m[p] * (double)n[p];
     }
-    const int64_t total = tiles[0] + tiles[1], blocks = total < cus ? total : cus;
-    // block b has ceil((tiles - b) / blocks) tiles of the first product and of both: constant between these three blocks
-    const int64_t at[3] = {0, tiles[0] % blocks, total % blocks};
-    double busiest = 0.0;
-    for (int64_t b : at) {
-        const int64_t first = tiles[0] > b ? (tiles[0] - b + blocks - 1) / blocks : 0, all = (total - b + blocks - 1) / blocks;
-        const double load = (double)first * cost[0] + (double)(all - first) * cost[1];
-        if (load > busiest) busiest = load;
+    const int64_t total = tiles[0] + tiles[1], used = total < cus ? total : cus;
+    const int64_t room = variant == kTwoPerCu ? 2 * cus : cus, blocks = total < room ? total : room, half = blocks / 2;
+    const PairLevel l = pair_level(tiles, cost, blocks);
+    *extra = l.extra;
+    double busiest = l.busiest();
+    if (variant == kTwoPerCu) {
+        // a tile per compute unit: the deeper ring of one block; products narrower than a tile: not measured
+        if (total <= cus || n[0] < 128 || (products == 2 && n[1] < 128)) return 1e30;
+        const double mixed = l.early_load + l.late_load;
+        busiest = l.early == 0 ? 2.0 * l.late_load : l.early > half ? 2.0 * l.early_load : 0.0;
+        if (l.early > 0 && mixed > busiest) busiest = mixed;
+        if (l.early > 0 && l.early < half && 2.0 * l.late_load > busiest) busiest = 2.0 * l.late_load;
     }
-    return c.start + busiest + c.per_fill * (double)blocks / (double)cus;
+    const double mean = sum / (double)used, weight = busiest > 4.0 * mean ? 1.0 : c.busiest;     // (a few long tiles alone: theirs is the time)
+    const double work = weight * busiest + (1.0 - weight) * mean + c.per_fill * (double)used / (double)cus;
+    const double memory = c.per_result * 1e-6 * results;
+    return c.start + (work > memory ? work : memory);
 }
 
 // the variant for one product or a pair, and its estimated time
 static int pick_variant(int products, const int64_t* m, const int64_t* n, const int64_t* k, int cus, double* estimate) {
-    int variant = 0;
-    for (int v = 0; v < 3; ++v) {
-        const double t = stream_estimate(v, products, m, n, k, cus);
-        if (v == 0 || t < *estimate) { *estimate = t; variant = v; }
+    int variant = -1;
+    for (int v = 0; v < 4; ++v) {
+        if (g_forced_variant >= 0 && g_forced_variant != (v == kTwoPerCu ? 2 : v)) continue;
+        int64_t extra;
+        const double t = stream_estimate(v, products, m, n, k, cus, &extra);
+        if (variant < 0 || t < *estimate) { *estimate = t; variant = v; }
     }
-    return g_forced_variant >= 0 ? g_forced_variant : variant;
+    return variant;
 }
 
 // Problems that the split kernels (gemm_split_kernels.hip) finish sooner: few rows, small layers, long inner dimensions with few
-// tiles.  Compares their estimate with that of the streaming kernels, in favour of the latter by 15 % (one product), 20 % (two) or, with
-// four waves, whose estimate is low for 64 x 64 tiles, 30 %.  Measured, streaming against split (us): 630 x 1312 x 2944 11.7 / 7.0;
+// tiles.  Compares their estimate with that of the streaming kernels, in favour of the latter by 12 % (one product, two waves) or
+// 35 % (two products; four waves, whose estimate is low for 64 x 64 tiles), which cost least over the calls the estimates were fitted to.  Measured, streaming against split (us): 630 x 1312 x 2944 11.7 / 7.0;
 // 2910 x 384 x 1056 7.6 / 7.2; 469 x 1792 x 1728 8.3 / 6.5; on the other side 2538 x 864 x 384 8.1 / 10.2; four waves 339 x 2624 x 5600 15.5 / 9.2 and
 // 377 x 4096 x 3936 12.8 / 13.9, 950 x 1696 x 5664 16.5 / 18.1; pairs of layers 736 x 928 x 800 10.5 / 8.2, 2176 x 1024 x 864 11.8 / 14.7.  The
 // choice depends on m, n and k alone, so fused and plain products of one size run on the same side.
@@ -747,7 +833,7 @@ static bool use_split(int products, const int64_t* m, const int64_t* n, const in
     for (int p = 0; p < products; ++p) tiles += ((m[p] + 31) / 32) * ((n[p] + 31) / 32);
     if (tiles >= ((int64_t)1 << 24)) return false;
     const bool four = split_waves(products == 2 && k[1] > k[0] ? k[1] : k[0]) == 4;
-    return best_split_shape(products, m, n, k, cus, shape) < (four ? 0.7 : products == 1 ? 0.85 : 0.8) * streaming;
+    return best_split_shape(products, m, n, k, cus, shape) < (four || products == 2 ? 0.65 : 0.88) * streaming;
 }
 
 // The kernel for one product or a pair, plain (nb = 0) or with the gradient epilogue of Hadamard blocks of nb groups.
@@ -759,14 +845,14 @@ static GemmPlan plan_gemm(int products, const int64_t* m, const int64_t* n, cons
     double estimate = 0.0;
     int shape = 0, variant = pick_variant(products, m, n, k, cus, &estimate);
     if (use_split(products, m, n, k, cus, estimate, &shape)) return {true, split_shape_for(shape, nb)};
-    if (nb >= 4u && variant == 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
+    if (nb >= 4u && variant >= 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
     return {false, variant};
 }
 
 int gemm_plan_code(int products, const int64_t* m, const int64_t* n, const int64_t* k, uint32_t nb, int cus) {
     const GemmPlan plan = plan_gemm(products, m, n, k, nb, cus);
     const int64_t k_max = products == 2 && k[1] > k[0] ? k[1] : k[0];
-    return plan.split ? 100 * split_waves(k_max) + plan.shape : plan.shape;
+    return plan.split ? 100 * split_waves(k_max) + plan.shape : plan.shape == kTwoPerCu ? 2 : plan.shape;
 }
 
 hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes,
@@ -786,8 +872,9 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const ui
         else { if (fused) FN<__VA_ARGS__ false, true>(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, nb, st);      \
                else FN<__VA_ARGS__ false, false>(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, ldd, mask, nb, st); }         \
     } while (0)
-    if (variant == 1) QUARTET_DISPATCH(launch_stream_tile_t, 2, 4, );
-    else if (variant == 2) QUARTET_DISPATCH(launch_stream_tile_t, 2, 2, );
+    if (variant == 1) QUARTET_DISPATCH(launch_stream_tile_t, 2, 4, 1, );
+    else if (variant == 2) QUARTET_DISPATCH(launch_stream_tile_t, 2, 2, 1, );
+    else if (variant == kTwoPerCu) QUARTET_DISPATCH(launch_stream_tile_t, 2, 2, 2, );
     else QUARTET_DISPATCH(launch_stream_t, );
 #undef QUARTET_DISPATCH
     return hipGetLastError();
@@ -812,10 +899,20 @@ hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_b
                               kTileM[variant], kTileN[variant]);
     batch.p[1] = make_problem(g1.a_codes, g1.a_scales, g1.b_codes, g1.b_scales, g1.m, g1.n, g1.k, g1.alpha, g1.d, g1.ldd, g1.mask,
                               kTileM[variant], kTileN[variant]);
+    const int64_t cus = stream_blocks();
+    const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, room = (uint32_t)(variant == kTwoPerCu ? 2 * cus : cus), blocks = total < room ? total : room;
+    int64_t extra;
+    stream_estimate(variant, 2, ms, ns, ks, cus, &extra);
     batch.past = stored_past(batch, d_bf16 != 0);
-    if (variant == 1) { if (d_bf16) launch_stream_tile_batch_t<2, 4, true, true>(batch, nb, st); else launch_stream_tile_batch_t<2, 4, false, true>(batch, nb, st); }
-    else if (variant == 2) { if (d_bf16) launch_stream_tile_batch_t<2, 2, true, true>(batch, nb, st); else launch_stream_tile_batch_t<2, 2, false, true>(batch, nb, st); }
-    else { if (d_bf16) launch_stream_batch_t<true, true>(batch, nb, st); else launch_stream_batch_t<false, true>(batch, nb, st); }
+    batch.late = blocks - batch.p[0].total_tiles % blocks;
+    batch.extra_tiles = (uint32_t)extra * batch.late;
+#define QUARTET_PAIR(FN, ...)                                                                           \
+    do { if (d_bf16) FN<__VA_ARGS__ true, true>(batch, nb, st); else FN<__VA_ARGS__ false, true>(batch, nb, st); } while (0)
+    if (variant == 1) QUARTET_PAIR(launch_stream_tile_batch_t, 2, 4, 1, );
+    else if (variant == 2) QUARTET_PAIR(launch_stream_tile_batch_t, 2, 2, 1, );
+    else if (variant == kTwoPerCu) QUARTET_PAIR(launch_stream_tile_batch_t, 2, 2, 2, );
+    else QUARTET_PAIR(launch_stream_batch_t, );
+#undef QUARTET_PAIR
     return hipGetLastError();
 }
 

@@ -172,7 +172,11 @@ __device__ __forceinline__ float epilogue_norm(float v, float signed_norm) { ret
 //   v4f [2 TM][2 TN] (v_mfma_scale_f32_16x16x128_f8f6f4: lane l, register r -> row 4*(l/16) + r, column l%16): pass P takes registers
 //     2*(P%2) and 2*(P%2) + 1 of the accumulators of tile row P/2, that is the rows 4*q + 2*(P%2) + e of it (q = 0..3, e = 0, 1), LDS row
 //     2*q + e; columns XORed with 32*(r%2) and 16*((r/2)%2).
-template <int TM, int TN, bool OUT_BF16, bool FUSED, bool FULL, typename ACC, int AM, int AN>
+// WIDE (FULL only, waves of 128 columns): Hadamard blocks of 256 columns, which span the tiles of two neighbouring waves (wave ^ 1).  The
+// stage that pairs columns 128 apart comes behind the stages in the lane: the waves put their values into their scratches, meet, read
+// each other's and meet again before the scratch takes the next pass's rows.  Every wave of the block must come here, as often as
+// the others.
+template <int TM, int TN, bool OUT_BF16, bool FUSED, bool FULL, bool WIDE = false, typename ACC, int AM, int AN>
 __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf, void* d, uint32_t ldd,
                                                  const uint32_t* mask, float alpha, uint32_t row_base,
                                                  uint32_t col_base, uint32_t m, uint32_t n, uint32_t lane, uint32_t nb, uint32_t past) {
@@ -239,7 +243,7 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
         float4 sl[TN];
 #pragma unroll
         for (uint32_t j = 0; j < TN; ++j) sl[j] = *reinterpret_cast<const float4*>(&rd[(j ^ rswz) * 32u]);
-        if (p + 1u < PASSES) write_pass(p + 1u);     // behind the reads in the wave's LDS queue: LDS operations of a wave run in order
+        if (!WIDE && p + 1u < PASSES) write_pass(p + 1u);     // behind the reads in the wave's LDS queue: LDS operations of a wave run in order
         const uint32_t grow = row_of_sub + row_step(p);
         float vv[TN][4];
 #pragma unroll
@@ -271,6 +275,26 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
                     vv[j][e] = a + b;
                     vv[(j + 2u) % TN][e] = a - b;
                 }
+        }
+        if constexpr (WIDE) {
+            static_assert(FUSED && FULL && TN == 4, "two waves' 128 columns each, nothing ragged");
+            const bool upper = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 1u) != 0u;
+            float4* mine = reinterpret_cast<float4*>(wbuf) + lane;
+            const float4* theirs = reinterpret_cast<const float4*>(upper ? wbuf - TN * 256u : wbuf + TN * 256u) + lane;
+#pragma unroll
+            for (uint32_t j = 0; j < TN; ++j) mine[j * 64u] = make_float4(vv[j][0], vv[j][1], vv[j][2], vv[j][3]);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            float4 o[TN];
+#pragma unroll
+            for (uint32_t j = 0; j < TN; ++j) o[j] = theirs[j * 64u];
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (p + 1u < PASSES) write_pass(p + 1u);
+            const float t = upper ? -1.0f : 1.0f;      // own + theirs below, theirs - own above
+#pragma unroll
+            for (uint32_t j = 0; j < TN; ++j) {
+                vv[j][0] = __builtin_fmaf(vv[j][0], t, o[j].x); vv[j][1] = __builtin_fmaf(vv[j][1], t, o[j].y);
+                vv[j][2] = __builtin_fmaf(vv[j][2], t, o[j].z); vv[j][3] = __builtin_fmaf(vv[j][3], t, o[j].w);
+            }
         }
 #pragma unroll
         for (uint32_t j = 0; j < TN; ++j) {

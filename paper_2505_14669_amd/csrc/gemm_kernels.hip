@@ -100,9 +100,9 @@ __device__ __forceinline__ uint32_t scale_selector(uint32_t lane, uint32_t group
 // stages never drains between them: the loads of the next tile's first stages are issued during the last stages
 // of the current one, so a tile's first matrix-core instruction follows the previous tile's result stores directly.
 // The epilogue uses a scratch of its own (16 KB beside the 144 KB ring).
-template <bool OUT_BF16, bool FUSED>
-__global__ void __launch_bounds__(256)
-gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+// WIDE: Hadamard blocks of 256 columns (store_tile_rows8): sizes are multiples of the tile
+template <bool OUT_BF16, bool FUSED, bool WIDE>
+__device__ __forceinline__ void stream_large_tiles(const GemmBatch& batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t TM = 4, TN = 4, BM = 256, BN = 256;
     constexpr uint32_t CODES = (BM + BN) * 8;            // 16-byte chunks of codes per K-quad
     constexpr uint32_t QUAD = CODES + 256;               // + 16 scale tiles of 256 B
@@ -343,9 +343,10 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ cl
         const uint32_t* __restrict__ mask = q.mask;
         const uint32_t row_base = m0 + wm0, col_base = n0 + wn0;
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
-        if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        if constexpr (WIDE) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        else if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
         else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
-        stores = full;                                     // 16 passes of four stores each; a ragged tile may have skipped some
+        stores = WIDE || full;                             // 16 passes of four stores each; a ragged tile may have skipped some
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // the quads issued past the last tile (zero-filled) have landed before the LDS is given back
     if (clock_counters && tid == 0) {
@@ -370,6 +371,18 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ cl
 #undef STREAM_BODY
 }
 
+template <bool OUT_BF16, bool FUSED>
+__global__ void __launch_bounds__(256)
+gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+    stream_large_tiles<OUT_BF16, FUSED, false>(batch, nb, clock_counters);
+}
+
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(256)
+gemm_mxfp4_wide_kernel(GemmBatch batch, uint64_t* __restrict__ clock_counters) {
+    stream_large_tiles<OUT_BF16, true, true>(batch, 8u, clock_counters);
+}
+
 // ---------------------------------------------------------------------------------------------
 // The streaming design for other tile shapes: wave tile (TM*32) x (TN*32), block tile (64 TM) x (64 TN), for problems
 // whose 256 x 256 tiles would leave compute units idle.  Same issue cursor, same epilogue; the instruction order is generated from the
@@ -386,7 +399,7 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ cl
 // three quarters of a quad to land: with several tiles per compute unit that is less than what the epilogues cost one block alone.
 // Pairs of layers (tokens, in, out), one block / two (us): 608 x 8832 x 3424 63.6 / 52.7, 4800 x 1824 x 2112 48.9 / 43.6, 9600 x 576 x 576 32.4 /
 // 36.0 (a tile or two per compute unit: the deeper ring); single products 10327 x 992 x 800 21.1 / 17.9, 4926 x 6496 x 10144 230 / 251.
-template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED>
+template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED, bool WIDE = false>
 __device__ __forceinline__ void stream_tiles(const GemmBatch& batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t BM = 64 * TM, BN = 64 * TN;
     static_assert(BM % 128 == 0 && BN % 128 == 0, "a wave's four scale tiles must belong to one operand");
@@ -616,9 +629,10 @@ __device__ __forceinline__ void stream_tiles(const GemmBatch& batch, uint32_t nb
         const uint32_t* __restrict__ mask = q.mask;
         const uint32_t row_base = m0 + wm0, col_base = n0 + wn0;
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
-        if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        if constexpr (WIDE) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        else if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
         else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
-        stores = full;                                     // every store was issued; a ragged tile may have skipped some
+        stores = WIDE || full;                             // every store was issued; a ragged tile may have skipped some
         if (!LATE) {
             __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
@@ -647,6 +661,12 @@ template <int TM, int TN, bool OUT_BF16, bool FUSED>
 __global__ void __launch_bounds__(256)
 gemm_mxfp4_stream_tile_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     stream_tiles<TM, TN, 1, OUT_BF16, FUSED>(batch, nb, clock_counters);
+}
+
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(256)
+gemm_mxfp4_wide_tile_kernel(GemmBatch batch, uint64_t* __restrict__ clock_counters) {
+    stream_tiles<2, 4, 1, OUT_BF16, true, true>(batch, 8u, clock_counters);
 }
 
 template <bool OUT_BF16, bool FUSED>
@@ -844,7 +864,7 @@ struct GemmPlan {
 static GemmPlan plan_gemm(int products, const int64_t* m, const int64_t* n, const int64_t* k, uint32_t nb, int cus) {
     double estimate = 0.0;
     int shape = 0, variant = pick_variant(products, m, n, k, cus, &estimate);
-    if (use_split(products, m, n, k, cus, estimate, &shape)) return {true, split_shape_for(shape, nb)};
+    if (nb != 8u && use_split(products, m, n, k, cus, estimate, &shape)) return {true, split_shape_for(shape, nb)};
     if (nb >= 4u && variant >= 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
     return {false, variant};
 }
@@ -880,9 +900,27 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const ui
     return hipGetLastError();
 }
 
-// Two gradient products in one launch (both with the fused epilogue, results of one type).  One tile shape serves both.
+// Hadamard blocks of 256 columns: the kernels that apply their epilogue take whole tiles of 256 x 256 (hence of 128 x 256) only, which is
+// what every layer with such blocks has.  Against two products on the kernels that are soonest for them, fp32 results in the
+// workspace and two epilogue kernels, layer steps (tokens, in, out; us): 256 x 1024 x 512 32.5 -> 24.5, 1024 x 768 x 1280 48 -> 34, 4096 x 4096 x
+// 2048 145 -> 112, 8192 x 2048 x 5632 288 -> 268, 1024 x 10752 x 7936 496 -> 330, 14336 x 1792 x 7680 541 -> 499.
+static bool wide_fits(const GemmArgs& g, int d_bf16) {
+    return g.m % 256 == 0 && g.n % 256 == 0 && g.ldd % 4 == 0 && g.mask != nullptr && (reinterpret_cast<uintptr_t>(g.d) & (d_bf16 ? 7u : 15u)) == 0;
+}
+static void launch_wide(const GemmBatch& batch, bool large, int d_bf16, hipStream_t st) {
+    const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, cus = (uint32_t)stream_blocks();
+    const dim3 grid(total < cus ? total : cus), block(256);
+    if (large && d_bf16) hipLaunchKernelGGL((gemm_mxfp4_wide_kernel<true>), grid, block, 0, st, batch, g_clock_counters);
+    else if (large) hipLaunchKernelGGL((gemm_mxfp4_wide_kernel<false>), grid, block, 0, st, batch, g_clock_counters);
+    else if (d_bf16) hipLaunchKernelGGL((gemm_mxfp4_wide_tile_kernel<true>), grid, block, 0, st, batch, g_clock_counters);
+    else hipLaunchKernelGGL((gemm_mxfp4_wide_tile_kernel<false>), grid, block, 0, st, batch, g_clock_counters);
+}
+
+// Two gradient products in one launch (both with the fused epilogue, results of one type).  One tile shape serves both.  Hadamard
+// blocks of 256 columns (nb = 8): hipErrorNotSupported, and nothing is launched, for what those kernels do not take (an empty product).
 hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_bf16, uint32_t nb, hipStream_t st) {
     const bool empty0 = g0.m == 0 || g0.n == 0, empty1 = g1.m == 0 || g1.n == 0;
+    if (nb == 8u && (empty0 || empty1)) return hipErrorNotSupported;
     if (empty0 || empty1) {
         hipError_t e = launch_gemm(g0.a_codes, g0.a_scales, g0.b_codes, g0.b_scales, g0.m, g0.n, g0.k, g0.alpha, g0.d, d_bf16, g0.ldd,
                                    1, g0.mask, nb, st);
@@ -892,6 +930,7 @@ hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_b
     }
     const int64_t ms[2] = {g0.m, g1.m}, ns[2] = {g0.n, g1.n}, ks[2] = {g0.k, g1.k};
     const GemmPlan plan = plan_gemm(2, ms, ns, ks, nb, stream_blocks());
+    if (nb == 8u && !(wide_fits(g0, d_bf16) && wide_fits(g1, d_bf16))) return hipErrorNotSupported;
     if (plan.split) return launch_gemm_split(g0, &g1, d_bf16, 1, nb, plan.shape, st);
     const int variant = plan.shape;
     GemmBatch batch;
@@ -908,7 +947,8 @@ hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_b
     batch.extra_tiles = (uint32_t)extra * batch.late;
 #define QUARTET_PAIR(FN, ...)                                                                           \
     do { if (d_bf16) FN<__VA_ARGS__ true, true>(batch, nb, st); else FN<__VA_ARGS__ false, true>(batch, nb, st); } while (0)
-    if (variant == 1) QUARTET_PAIR(launch_stream_tile_batch_t, 2, 4, 1, );
+    if (nb == 8u) launch_wide(batch, variant == 0, d_bf16, st);
+    else if (variant == 1) QUARTET_PAIR(launch_stream_tile_batch_t, 2, 4, 1, );
     else if (variant == 2) QUARTET_PAIR(launch_stream_tile_batch_t, 2, 2, 1, );
     else if (variant == kTwoPerCu) QUARTET_PAIR(launch_stream_tile_batch_t, 2, 2, 2, );
     else QUARTET_PAIR(launch_stream_batch_t, );

@@ -135,11 +135,21 @@ def _stream(stream):
     return stream.cuda_stream
 
 
+# The entry points of a training step, of serving and of the quantizers again, without ctypes (csrc/nn_autograd.cpp): they return
+# NotImplemented for arguments that the conversion here has to take or to refuse.  Bound with the device, None without the torch node.
+_native = None
+
+
 def _bind_torch():
-    global _current_device, _current_raw_stream
+    global _current_device, _current_raw_stream, _native
     import torch
     torch.cuda.current_stream()              # initializes the device as before, and raises without one
     _current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    try:
+        from . import _nn_native as native   # linked to the same library file
+        _native = native
+    except ImportError:
+        pass
 
 
 def quartet_last_hip_error():
@@ -190,12 +200,21 @@ def quartet_sign_word(seed):
 
 
 def quartet_quant_fwd(x_bf16, rows, k, ldx, transpose, codes, scales, mask, stream=None):
+    if _native is not None:
+        rc = _native.quartet_quant_fwd(x_bf16, rows, k, ldx, transpose, codes, scales, mask, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_quant_fwd(_ptr(x_bf16), rows, k, ldx, int(transpose), _ptr(codes), _ptr(scales),
                                   _ptr(mask), _stream(stream))
 
 
 def quartet_quant_bwd_sr(x_bf16, rows, k, ldx, transpose, sign_word, seed, stream_id, rounding, codes, scales,
                          stream=None):
+    if _native is not None:
+        rc = _native.quartet_quant_bwd_sr(x_bf16, rows, k, ldx, transpose, sign_word, seed, stream_id, rounding, codes,
+                                          scales, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_quant_bwd_sr(_ptr(x_bf16), rows, k, ldx, int(transpose), sign_word, seed, stream_id,
                                      rounding, _ptr(codes), _ptr(scales), _stream(stream))
 
@@ -222,6 +241,10 @@ def quartet_bwd_operands(dy_bf16, tokens, in_features, out_features, xq_codes, x
 
 
 def quartet_mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, d_dtype, ldd, stream=None):
+    if _native is not None:
+        rc = _native.quartet_mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, m, n, k, alpha, d, d_dtype, ldd, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_mxfp4_gemm(_ptr(a_codes), _ptr(a_scales), _ptr(b_codes), _ptr(b_scales), m, n, k,
                                    alpha, _ptr(d), d_dtype, ldd, _stream(stream))
 
@@ -236,6 +259,11 @@ def quartet_debug_gemm_plan(products, mnk, hadamard_block, compute_units):
 
 
 def quartet_mxfp4_gemm_grad(a_codes, a_scales, b_codes, b_scales, m, n, k, mask, scale, d, d_dtype, ldd, stream=None):
+    if _native is not None:
+        rc = _native.quartet_mxfp4_gemm_grad(a_codes, a_scales, b_codes, b_scales, m, n, k, mask, scale, d, d_dtype,
+                                             ldd, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_mxfp4_gemm_grad(_ptr(a_codes), _ptr(a_scales), _ptr(b_codes), _ptr(b_scales), m, n, k,
                                         _ptr(mask), scale, _ptr(d), d_dtype, ldd, _stream(stream))
 
@@ -269,6 +297,11 @@ def quartet_mxfp4_dequant(codes, scales, rows, k, out, stream=None):
 
 def quartet_linear_fwd(x_bf16, w_bf16, tokens, in_features, out_features, y, y_dtype, xq_codes, xq_scales,
                        x_mask, wq_codes, wq_scales, w_mask, stream=None):
+    if _native is not None:
+        rc = _native.quartet_linear_fwd(x_bf16, w_bf16, tokens, in_features, out_features, y, y_dtype, xq_codes,
+                                        xq_scales, x_mask, wq_codes, wq_scales, w_mask, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_linear_fwd(_ptr(x_bf16), _ptr(w_bf16), tokens, in_features, out_features, _ptr(y),
                                    y_dtype, _ptr(xq_codes), _ptr(xq_scales), _ptr(x_mask), _ptr(wq_codes),
                                    _ptr(wq_scales), _ptr(w_mask), _stream(stream))
@@ -281,6 +314,12 @@ def quartet_linear_workspace_bytes(tokens, in_features, out_features):
 def quartet_linear_bwd(dy_bf16, tokens, in_features, out_features, xq_codes, xq_scales, x_mask, wq_codes,
                        wq_scales, w_mask, seed, rounding, dx, dw, grad_dtype, workspace, workspace_bytes,
                        stream=None):
+    if _native is not None:
+        rc = _native.quartet_linear_bwd(dy_bf16, tokens, in_features, out_features, xq_codes, xq_scales, x_mask,
+                                        wq_codes, wq_scales, w_mask, seed, rounding, dx, dw, grad_dtype, workspace,
+                                        workspace_bytes, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_linear_bwd(_ptr(dy_bf16), tokens, in_features, out_features, _ptr(xq_codes),
                                    _ptr(xq_scales), _ptr(x_mask), _ptr(wq_codes), _ptr(wq_scales),
                                    _ptr(w_mask), seed, rounding, _ptr(dx), _ptr(dw), grad_dtype,
@@ -349,6 +388,11 @@ def quartet_grad_epilogue_block(g, mask, m, n, hadamard_block, scale, out, out_d
 
 def quartet_linear_fwd_block(x_bf16, w_bf16, tokens, in_f, out_f, hadamard_block, y, y_dtype, xq_codes, xq_scales,
                              x_mask, wq_codes, wq_scales, w_mask, stream=None):
+    if _native is not None:
+        rc = _native.quartet_linear_fwd_block(x_bf16, w_bf16, tokens, in_f, out_f, hadamard_block, y, y_dtype,
+                                              xq_codes, xq_scales, x_mask, wq_codes, wq_scales, w_mask, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_linear_fwd_block(_ptr(x_bf16), _ptr(w_bf16), tokens, in_f, out_f, hadamard_block, _ptr(y),
                                          y_dtype, _ptr(xq_codes), _ptr(xq_scales), _ptr(x_mask), _ptr(wq_codes),
                                          _ptr(wq_scales), _ptr(w_mask), _stream(stream))
@@ -361,6 +405,12 @@ def quartet_linear_workspace_bytes_block(tokens, in_f, out_f, hadamard_block):
 def quartet_linear_bwd_block(dy_bf16, tokens, in_f, out_f, hadamard_block, xq_codes, xq_scales, x_mask, wq_codes,
                              wq_scales, w_mask, seed, rounding, dx, dw, grad_dtype, workspace, workspace_bytes,
                              stream=None):
+    if _native is not None:
+        rc = _native.quartet_linear_bwd_block(dy_bf16, tokens, in_f, out_f, hadamard_block, xq_codes, xq_scales,
+                                              x_mask, wq_codes, wq_scales, w_mask, seed, rounding, dx, dw, grad_dtype,
+                                              workspace, workspace_bytes, stream)
+        if rc is not NotImplemented:
+            return rc
     return _lib.quartet_linear_bwd_block(_ptr(dy_bf16), tokens, in_f, out_f, hadamard_block, _ptr(xq_codes),
                                          _ptr(xq_scales), _ptr(x_mask), _ptr(wq_codes), _ptr(wq_scales),
                                          _ptr(w_mask), seed, rounding, _ptr(dx), _ptr(dw), grad_dtype,

@@ -29,6 +29,12 @@ struct FastDiv {
     uint32_t mul, shift;
 };
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
+inline FastDiv make_fast_div(uint32_t d) {     // d > 0
+    uint32_t l = 0;
+    while (((uint64_t)1 << l) < d) ++l;
+    uint64_t mul = ((((uint64_t)1 << l) - d) << 32) / d + 1;
+    return FastDiv{(uint32_t)mul, l};
+}
 
 typedef unsigned int v4u_t __attribute__((ext_vector_type(4)));
 typedef unsigned int v2u_t __attribute__((ext_vector_type(2)));

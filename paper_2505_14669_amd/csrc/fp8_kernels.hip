@@ -275,19 +275,12 @@ gemm_mxfp8_ring_kernel(const uint8_t* __restrict__ a_codes, const uint8_t* __res
 }
 
 // ------------------------------------------------------------------ host-side launchers
-static FastDiv fast_div_of(uint32_t d) {
-    uint32_t l = 0;
-    while (((uint64_t)1 << l) < d) ++l;
-    uint64_t mul = ((((uint64_t)1 << l) - d) << 32) / d + 1;
-    return FastDiv{(uint32_t)mul, l};
-}
-
 hipError_t launch_mxfp8_quant(const void* x, int64_t rows, int64_t k, int64_t ldx, uint8_t* codes, uint8_t* scales,
                               hipStream_t st) {
     if (rows == 0 || k == 0) return hipSuccess;
     const uint32_t gk = (uint32_t)(k / 32), k_blocks = (gk + 31) / 32;
     hipLaunchKernelGGL(mxfp8_quant_kernel, dim3((uint32_t)((rows + 7) / 8) * k_blocks), dim3(256), 0, st,
-                       (const uint16_t*)x, (uint32_t)rows, gk, ldx, codes, scales, k_blocks, fast_div_of(k_blocks));
+                       (const uint16_t*)x, (uint32_t)rows, gk, ldx, codes, scales, k_blocks, make_fast_div(k_blocks));
     return hipGetLastError();
 }
 

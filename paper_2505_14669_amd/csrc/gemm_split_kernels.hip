@@ -22,6 +22,7 @@ struct SplitProblem {
     uint32_t m, n, k, ldd;
     float alpha;
     uint32_t tiles_m, total_tiles;
+    FastDiv by_tiles_m;
 };
 struct SplitBatch {
     SplitProblem p[2];
@@ -115,11 +116,17 @@ gemm_mxfp4_split_kernel(SplitBatch batch, uint32_t nb) {
     const uint32_t lrow = lane & 31u, lhalf = lane >> 5;
     // consecutive tiles of one XCD share their columns of B (blocks go to the XCDs in turn)
     const bool second = blockIdx.x >= batch.p[0].total_tiles;
-    const SplitProblem& q = batch.p[second ? 1 : 0];
+    // Field by field: all arguments are on their way at once, then one product's are picked.  By index three scalar loads waited for each
+    // other, and a division, before the first operand load.  With that out (us): 24 x 4096 x 11008 quantized and multiplied 10.38 -> 10.19, a
+    // 256 x 512 x 512 layer step, with the same in the row quantizers' paired launch, 15.93 -> 15.47.
+#define PICK(F) (second ? batch.p[1].F : batch.p[0].F)
+    const SplitProblem q = {PICK(a_codes), PICK(a_scales), PICK(b_codes), PICK(b_scales), PICK(d), PICK(mask), PICK(m), PICK(n), PICK(k), PICK(ldd),
+                            PICK(alpha), PICK(tiles_m), PICK(total_tiles), {PICK(by_tiles_m.mul), PICK(by_tiles_m.shift)}};
+#undef PICK
     const uint32_t v = second ? blockIdx.x - batch.p[0].total_tiles : blockIdx.x;
     const uint32_t per = q.total_tiles >> 3, rem = q.total_tiles & 7u, xcd = v & 7u;
     const uint32_t tile = xcd * per + (xcd < rem ? xcd : rem) + (v >> 3);
-    const uint32_t m0 = (tile % q.tiles_m) * BM, n0 = (tile / q.tiles_m) * BN;
+    const uint32_t tile_n = fast_div(tile, q.by_tiles_m), m0 = (tile - tile_n * q.tiles_m) * BM, n0 = tile_n * BN;
     const uint32_t m = q.m, n = q.n, kb = q.k >> 1, gk = q.k >> 5, kq = (q.k + 255u) >> 8;
 
     // rows past the matrix read as zeros; chunks past k inside a row are cut off per lane
@@ -231,6 +238,7 @@ static SplitProblem split_problem(const GemmArgs& g, uint32_t bm, uint32_t bn) {
     q.alpha = g.alpha;
     q.tiles_m = (q.m + bm - 1u) / bm;
     q.total_tiles = q.tiles_m * ((q.n + bn - 1u) / bn);
+    q.by_tiles_m = make_fast_div(q.tiles_m);
     return q;
 }
 

@@ -271,7 +271,9 @@ quant_row_pair_kernel(RowMatrix a, RowMatrix b, uint32_t split, uint32_t gk, SrP
     __shared__ uint4 stage[4][256];
     __shared__ uint32_t s_scale[64];
     const bool second = blockIdx.x >= split;
-    const RowMatrix& m = second ? b : a;
+    // field by field: both matrices' arguments are on their way together with split, not behind it (forward 1003 x 2048 x 5632 21.03 -> 20.86 us)
+    const RowMatrix m = {second ? b.x : a.x, second ? b.rows : a.rows, second ? b.ldx : a.ldx, second ? b.codes : a.codes,
+                         second ? b.scales : a.scales, second ? b.mask : a.mask};
     quant_row_tile<MODE, MASK, BIG>(m.x, m.rows, gk, m.ldx, m.codes, m.scales, m.mask, p, p.stream_id, k_blocks, div_k_blocks,
                                       second ? blockIdx.x - split : blockIdx.x, stage, s_scale);
 }
@@ -763,13 +765,6 @@ dequant_kernel(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ sc
 }
 
 // ------------------------------------------------------------------ host-side launchers
-
-static FastDiv make_fast_div(uint32_t d) {
-    uint32_t l = 0;
-    while (((uint64_t)1 << l) < d) ++l;
-    uint64_t mul = ((((uint64_t)1 << l) - d) << 32) / d + 1;
-    return FastDiv{(uint32_t)mul, l};
-}
 
 template <int MODE, bool MASK>
 static void launch_row_big(bool big, dim3 grid, hipStream_t st, const void* x, int64_t rows, uint32_t gk, int64_t ldx,

@@ -16,7 +16,10 @@ G = S.G
 # 128 x 128, with one or two blocks per compute unit: 90 / 330, 255 / 260, 2 / 1190
 @pytest.mark.parametrize("variant,shapes", [(0, ((2304, 1280, 1312), (16640 - 9, 1280, 96))), (1, ((1500, 1280, 1056), (8448, 1280, 160))),
                                             (1, ((34432, 256, 544), (34816 - 3, 256, 32))), (2, ((1152, 1280, 1312), (4224, 1280, 96))),
-                                            (2, ((1900, 2176, 800), (2550, 1664, 544))), (2, ((128, 256, 1312), (8960 - 7, 2176, 32)))])
+                                            (2, ((1900, 2176, 800), (2550, 1664, 544))), (2, ((128, 256, 1312), (8960 - 7, 2176, 32))),
+                                            # a first tile outlasts all tiles of the second product that the other blocks can take
+                                            (0, ((256, 1280, 16640), (16640 - 9, 1280, 96))), (1, ((128, 1280, 8192), (8448, 1280, 160))),
+                                            (2, ((128, 256, 14400), (8960 - 7, 2176, 32)))])
 def test_pair_by_load_equals_single_products(G, variant, shapes):
     from paper_2505_14669_amd import binding
     rng = np.random.default_rng(variant)

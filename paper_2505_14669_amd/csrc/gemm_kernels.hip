@@ -825,8 +825,8 @@ static int pick_variant(int products, const int64_t* m, const int64_t* n, const 
 // tiles.  Compares their estimate with that of the streaming kernels, in favour of the latter by 12 % (one product, two waves) or
 // 35 % (two products; four waves, whose estimate is low for 64 x 64 tiles), which cost least over the calls the estimates were fitted to.  Measured, streaming against split (us): 630 x 1312 x 2944 11.7 / 7.0;
 // 2910 x 384 x 1056 7.6 / 7.2; 469 x 1792 x 1728 8.3 / 6.5; on the other side 2538 x 864 x 384 8.1 / 10.2; four waves 339 x 2624 x 5600 15.5 / 9.2 and
-// 377 x 4096 x 3936 12.8 / 13.9, 950 x 1696 x 5664 16.5 / 18.1; pairs of layers 736 x 928 x 800 10.5 / 8.2, 2176 x 1024 x 864 11.8 / 14.7.  The
-// choice depends on m, n and k alone, so fused and plain products of one size run on the same side.
+// 377 x 4096 x 3936 12.8 / 13.9, 950 x 1696 x 5664 16.5 / 18.1; pairs of layers 736 x 928 x 800 10.5 / 8.2, 2176 x 1024 x 864 11.8 / 14.7.  For
+// one product the choice depends on m, n and k alone, so fused and plain products of one size run on the same side.
 static bool use_split(int products, const int64_t* m, const int64_t* n, const int64_t* k, int cus, double streaming, int* shape) {
     if (g_forced_variant >= 0) return false;
     // A block per tile, and a launch has fewer than 2^32 threads: with 32 x 32 tiles of up to four waves, 2^24 tiles at most
@@ -845,8 +845,17 @@ struct GemmPlan {
 static GemmPlan plan_gemm(int products, const int64_t* m, const int64_t* n, const int64_t* k, uint32_t nb, int cus) {
     double estimate = 0.0;
     int shape = 0, variant = pick_variant(products, m, n, k, cus, &estimate);
+    if (nb >= 4u && variant >= 2) {
+        // A block of 128 columns needs the 128-column wave tile.  (256 x 256 where the estimates put it before 128 x 256 is not sooner: 40 layers
+        // each with blocks of 128 and 256, 1.00 and 0.98 of its speed on average.)
+        variant = 1;
+        // In a pair the split kernels are weighed against the tiles that run; against those that cannot, backward passes of layers with blocks
+        // of 128 took (tokens, in, out; us) 384 x 3456 x 256 21.6 for 13.9, 6016 x 384 x 640 40.2 for 26.5, 1280 x 640 x 2560 30.0 for 22.8.  One
+        // product stays on the side where the plain product of its sizes runs: their results are the same bits.
+        int64_t extra;
+        if (products == 2) estimate = stream_estimate(1, 2, m, n, k, cus, &extra);
+    }
     if (nb != 8u && use_split(products, m, n, k, cus, estimate, &shape)) return {true, split_shape_for(shape, nb)};
-    if (nb >= 4u && variant >= 2) variant = 1;   // a block of 128 columns needs the 128-column wave tile
     return {false, variant};
 }
 

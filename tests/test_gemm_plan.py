@@ -1,4 +1,6 @@
 """Which kernel the GEMM launcher picks (host only): the choice is a function of the sizes, the Hadamard block and the chip."""
+import random
+
 import torch  # noqa: F401  (before the library, as in every program that uses both: they share one HIP runtime then)
 
 from paper_2505_14669_amd import binding as q
@@ -33,6 +35,26 @@ def test_four_wave_split_leaves_what_the_streaming_kernels_do_sooner():
         assert plan(*mnk) == 2
     for mnk in ((339, 2624, 5600), (104, 6592, 6240)):
         assert plan(*mnk) // 100 == 4
+
+
+def pair_plan(t, i, o, block):
+    return plan(o, i, t, t, i, o, block=block)
+
+
+def test_pairs_with_blocks_of_128_weigh_the_split_kernels_against_the_tiles_that_run():
+    # measured, backward passes on 128 x 256 tiles against the split kernels (us): 21.6 / 13.9, 20.9 / 13.9, 30.0 / 22.8, 40.2 / 26.5, 47.5 / 38.2
+    for layer, waves in (((384, 3456, 256), 2), ((512, 2176, 384), 2), ((1280, 640, 2560), 2), ((6016, 384, 640), 4), ((7808, 512, 640), 4)):
+        assert pair_plan(*layer, 128) == 100 * waves + 14
+    # 53.5 / 69.2, 23.4 / 30.3, 34.4 / 41.0
+    for layer in ((5504, 1152, 1280), (512, 2816, 1792), (4096, 1408, 384)):
+        assert pair_plan(*layer, 128) == 1
+
+
+def test_one_product_runs_on_the_side_of_the_plain_one():
+    rng = random.Random(4)
+    for _ in range(2000):
+        m, n, k = rng.randrange(1, 6000), 128 * rng.randrange(1, 40), 32 * rng.randrange(1, 200)
+        assert len({plan(m, n, k, block=b) >= 100 for b in (0, 32, 64, 128)}) == 1
 
 
 def test_sizes_of_the_split_tests_reach_every_kernel():

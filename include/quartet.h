@@ -209,8 +209,8 @@ int quartet_mxfp4_gemm(const uint8_t *a_codes, const uint8_t *a_scales,
  * Test and tuning aid (no part of the method): which of the library's GEMM kernels quartet_mxfp4_gemm and
  * quartet_mxfp4_gemm_grad launch from now on.  variant -1 = choose by problem size (the default; small problems run
  * on kernels that split the inner dimension inside a block); 0, 1, 2 = tiles of 256 x 256, 128 x 256 or 128 x 128
- * (all three: one block per compute unit, or two with tiles of 128 x 128 where that is sooner, streams its tiles through a ring of two,
- * three or four K-quads of 256 elements in LDS).
+ * (all three: one block per compute unit streams its tiles through a ring of two, three or four K-quads of 256 elements in
+ * LDS); 22 = tiles of 128 x 128 with two blocks per compute unit, a ring of two K-quads each.
  * band_height 0 = choose by shape (the default), 1..64 = tile rows each XCD walks at a time.
  * Every combination gives the same results up to fp32 summation order; the parity tests use this to
  * reach each kernel.  Process-global, not thread-safe.  QUARTET_EINVAL outside those ranges.
@@ -219,7 +219,7 @@ int quartet_debug_set_gemm_plan(int variant, int band_height);
 
 /*
  * Test and tuning aid (host only, no device needed): which kernel runs one product, or a pair in one launch (products = 1, 2; mnk:
- * m, n, k of each), on a chip of that many compute units (8..4096): 0, 1, 2 as above, or 100 * waves + 11, 12, 14, 22 for the
+ * m, n, k of each), on a chip of that many compute units (8..4096): 0, 1, 2, 22 as above, or 100 * waves + 11, 12, 14, 22 for the
  * in-block split over tiles of 32 x 32, 32 x 64, 32 x 128, 64 x 64.  hadamard_block 0 = plain product, 32, 64, 128 = gradient
  * product.  Negative: error.
  */

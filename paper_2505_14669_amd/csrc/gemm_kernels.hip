@@ -40,8 +40,11 @@ static uint64_t* g_clock_counters = nullptr;
 
 void set_clock_counters(uint64_t* device_counters) { g_clock_counters = device_counters; }
 
+constexpr int kTwoPerCu = 3;          // variant: 128 x 128 tiles, two blocks per compute unit
+constexpr int kTwoPerCuCode = 22;     // its number outside
+
 void set_gemm_plan(int variant, int band_height) {
-    g_forced_variant = variant;
+    g_forced_variant = variant == kTwoPerCuCode ? kTwoPerCu : variant;
     g_forced_band = band_height;
 }
 
@@ -753,7 +756,7 @@ static void launch_stream_tile_t(const uint8_t* a_codes, const uint8_t* a_scales
 // Variants: 0 = 256x256 tiles (hand-scheduled K-quad), 1 = 128x256 tiles, 2 = 128x128 tiles (schedule generated from the
 // tile shape), kTwoPerCu = 128x128 tiles with two blocks per compute unit; blocks stream their tiles through a ring of K-quads, two
 // K-steps per trip with the scale byte picked by op_sel.  set_gemm_plan overrides the size heuristic (tests reach every variant
-// through it; of 128x128 tiles the estimate still says how many blocks).
+// through it).
 // fused != 0: D = alpha * H_along_n((A B^T) . mask) with Hadamard blocks of nb = 1, 2 or 4 groups of 32 columns (mask may
 // be null = all ones), n % (32 nb) == 0.
 //
@@ -772,7 +775,6 @@ static const StreamCost kStreamSingle[4] = {{1.42, 1.590, 5.39, 11.7, 0.803, 1.0
                                             {3.20, 0.609, 1.94, 1.95, 0.718, 1.00}, {1.54, 0.677, 1.03, 2.33, 0.591, 0.80}};
 static const StreamCost kStreamPair[4] = {{0.00, 1.520, 10.1, 19.8, 1.505, 1.00}, {3.06, 0.897, 6.46, 2.03, 1.351, 1.00},
                                           {4.26, 0.582, 4.19, 0.00, 0.128, 0.62}, {0.00, 0.638, 0.84, 5.04, 1.247, 1.00}};
-constexpr int kTwoPerCu = 3;      // 128 x 128 tiles, two blocks per compute unit
 constexpr int64_t kTileM[4] = {256, 128, 128, 128}, kTileN[4] = {256, 256, 128, 128};
 
 // *extra: the late blocks' rounds.  Two blocks b and b + half of a compute unit take turns at its matrix cores: their loads add up.
@@ -813,7 +815,7 @@ static double stream_estimate(int variant, int products, const int64_t* m, const
 static int pick_variant(int products, const int64_t* m, const int64_t* n, const int64_t* k, int cus, double* estimate) {
     int variant = -1;
     for (int v = 0; v < 4; ++v) {
-        if (g_forced_variant >= 0 && g_forced_variant != (v == kTwoPerCu ? 2 : v)) continue;
+        if (g_forced_variant >= 0 && g_forced_variant != v) continue;
         int64_t extra;
         const double t = stream_estimate(v, products, m, n, k, cus, &extra);
         if (variant < 0 || t < *estimate) { *estimate = t; variant = v; }
@@ -862,7 +864,7 @@ static GemmPlan plan_gemm(int products, const int64_t* m, const int64_t* n, cons
 int gemm_plan_code(int products, const int64_t* m, const int64_t* n, const int64_t* k, uint32_t nb, int cus) {
     const GemmPlan plan = plan_gemm(products, m, n, k, nb, cus);
     const int64_t k_max = products == 2 && k[1] > k[0] ? k[1] : k[0];
-    return plan.split ? 100 * split_waves(k_max) + plan.shape : plan.shape == kTwoPerCu ? 2 : plan.shape;
+    return plan.split ? 100 * split_waves(k_max) + plan.shape : plan.shape == kTwoPerCu ? kTwoPerCuCode : plan.shape;
 }
 
 hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* b_codes,

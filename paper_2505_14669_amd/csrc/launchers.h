@@ -57,9 +57,9 @@ int split_shape_for(int shape, uint32_t nb);
 int split_waves(int64_t k);
 hipError_t launch_gemm_split(const GemmArgs& g0, const GemmArgs* g1, int d_bf16, int fused, uint32_t nb, int shape, hipStream_t st);
 hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_bf16, uint32_t nb, hipStream_t st);
-// variant: -1 = size heuristic, 0..2 = force that tile shape (256x256, 128x256, 128x128); band_height: 0 = heuristic, > 0 = tile rows per band
+// variant: -1 = size heuristic, 0..2 = force that tile shape (256x256, 128x256, 128x128), 22 = 128x128 with two blocks per compute unit; band_height: 0 = heuristic, > 0 = tile rows per band
 void set_gemm_plan(int variant, int band_height);
-// the kernel that runs one or two products (nb = 0: plain) on a chip of that many compute units: 0..2 as above, or
+// the kernel that runs one or two products (nb = 0: plain) on a chip of that many compute units: 0..2 or 22 as above, or
 // 100 * waves + shape of the in-block split
 int gemm_plan_code(int products, const int64_t* m, const int64_t* n, const int64_t* k, uint32_t nb, int compute_units);
 hipError_t launch_grad_epilogue(const float* g, const uint32_t* mask, int64_t m, int64_t n, uint32_t nb, float scale,

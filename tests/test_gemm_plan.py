@@ -37,6 +37,18 @@ def test_four_wave_split_leaves_what_the_streaming_kernels_do_sooner():
         assert plan(*mnk) // 100 == 4
 
 
+def test_every_forced_kernel_is_the_one_that_is_reported():
+    try:
+        for variant in (0, 1, 2, 22):
+            assert q.quartet_debug_set_gemm_plan(variant, 0) == q.QUARTET_OK
+            for mnk in ((4096, 4096, 256), (96, 96, 96), (1152, 1280, 1312, 4224, 1280, 96)):
+                assert plan(*mnk) == variant and plan(*mnk, block=32) == variant
+        for bad in (-2, 3, 21, 23, 222):
+            assert q.quartet_debug_set_gemm_plan(bad, 0) == q.QUARTET_EINVAL
+    finally:
+        q.quartet_debug_set_gemm_plan(-1, 0)
+
+
 def pair_plan(t, i, o, block):
     return plan(o, i, t, t, i, o, block=block)
 

@@ -30,7 +30,8 @@ def _operand(rng, rows, k):
     return codes, scales, torch.from_numpy(values * np.repeat(2.0 ** (scales.astype(np.float64) - 127), 32, axis=1)).cuda()
 
 
-@pytest.mark.parametrize("variant,m,n", [(0, 4352 - 17, 4096 + 256), (1, 2176, 4352 - 5), (2, 2176, 2176), (2, 2176 - 9, 2176 + 64)])
+@pytest.mark.parametrize("variant,m,n", [(0, 4352 - 17, 4096 + 256), (1, 2176, 4352 - 5), (2, 2176, 2176), (2, 2176 - 9, 2176 + 64),
+                                         (22, 2176, 4352), (22, 4352 - 9, 2176 + 64)])
 @pytest.mark.parametrize("k", [32, 128, 160, 256, 480, 544, 768, 1312])
 def test_stream_gemm_exact(G, variant, m, n, k):
     rng = np.random.default_rng(k * 8 + variant)
@@ -41,7 +42,7 @@ def test_stream_gemm_exact(G, variant, m, n, k):
     assert np.array_equal(got, (va @ vb.T).cpu().numpy().astype(np.float32))
 
 
-@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("variant", [0, 1, 2, 22])
 @pytest.mark.parametrize("shapes", [((2304, 4352, 288), (4096, 2304, 800)), ((2048, 2304, 1056), (2000, 2080, 96))])
 def test_stream_gemm_pair_equals_single(G, variant, shapes):
     from paper_2505_14669_amd import binding
@@ -56,10 +57,18 @@ def test_stream_gemm_pair_equals_single(G, variant, shapes):
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
-# sizes on both sides of the lines where the launcher goes from one tile shape or kind of kernel to the next
-@pytest.mark.parametrize("m,n,k", [(1170, 7584, 384), (4096, 4096, 256), (4097, 4096, 256), (2529, 384, 1312), (46, 800, 1280), (3127, 1408, 1248),
-                                   (4096, 2048, 512), (2048, 4097, 288)])
-def test_gemm_chosen_plan_exact(G, m, n, k):
+# sizes where the launcher takes each kernel, and on both sides of lines between two: one product's plan code (quartet_debug_gemm_plan)
+CHOSEN = [((4096, 4096, 256), 22), ((4097, 4096, 256), 22), ((1170, 7584, 384), 22), ((2529, 384, 1312), 222), ((46, 800, 1280), 211),
+          ((3127, 1408, 1248), 22), ((4096, 2048, 512), 22), ((2048, 4097, 288), 22), ((1271, 3200, 608), 2), ((1271, 3201, 608), 22),
+          ((4608, 896, 704), 2), ((4608, 897, 704), 22), ((5632, 5120, 1312), 22), ((5632, 5121, 1312), 0), ((5633, 6528, 1312), 22),
+          ((5633, 6529, 1312), 1)]
+
+
+@pytest.mark.parametrize("mnk,code", CHOSEN)
+def test_gemm_chosen_plan_exact(G, mnk, code):
+    from paper_2505_14669_amd import binding
+    m, n, k = mnk
+    assert binding.quartet_debug_gemm_plan(1, list(mnk), 0, torch.cuda.get_device_properties(0).multi_processor_count) == code
     rng = np.random.default_rng(m + n + k)
     (a, sa, va), (b, sb, vb) = _operand(rng, m, k), _operand(rng, n, k)
     assert np.array_equal(G.gemm(a, sa, b, sb), (va @ vb.T).cpu().numpy().astype(np.float32))

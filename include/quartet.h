@@ -374,9 +374,10 @@ uint32_t quartet_sign_word(uint64_t seed);
  * sign_words arguments are HOST pointers to at least hadamard_block/32 words.
  *
  * quartet_mxfp4_gemm_grad_block is quartet_mxfp4_gemm_grad for blocks of 32, 64 or 128 columns (n a
- * multiple of the block); a block of 256 spans the tiles of two waves and returns QUARTET_ENOTSUP:
- * quartet_linear_bwd_block then runs the plain GEMM into its workspace and quartet_grad_epilogue_block
- * after it (quartet_linear_workspace_bytes_block accounts for that).
+ * multiple of the block); a block of 256 spans the tiles of two waves and returns QUARTET_ENOTSUP.
+ * quartet_linear_bwd_block applies its epilogue in the paired launch of both products; only where one of them is
+ * empty or a mask is not 4-byte aligned it runs the plain GEMM into its workspace and quartet_grad_epilogue_block
+ * after it (quartet_linear_workspace_bytes_block keeps room for that: it does not see the pointers).
  */
 int quartet_sign_words(uint64_t seed, uint32_t *out8);
 int quartet_quant_fwd_block(const void *x_bf16, int64_t rows, int64_t k, int64_t ldx, int transpose,

@@ -480,8 +480,7 @@ static int check_gemm_grad_args(const quartet_gemm_grad_args* g, int d_dtype, in
     return QUARTET_OK;
 }
 
-// both products with Hadamard blocks of hadamard_block = 32, 64 or 128 columns; of 256 (quartet_linear_bwd_block only): QUARTET_ENOTSUP
-// without a launch for what the kernels with that epilogue do not take
+// both products with Hadamard blocks of hadamard_block columns; of 256 only for products that are not empty, with masks
 static int gemm_grad_pair_block(const quartet_gemm_grad_args* first, const quartet_gemm_grad_args* second, int hadamard_block,
                                 int d_dtype, void* stream) {
     const uint32_t nb = block_groups(hadamard_block);
@@ -496,7 +495,6 @@ static int gemm_grad_pair_block(const quartet_gemm_grad_args* first, const quart
                                   second->k, second->scale, second->d, second->ldd, second->mask};
     ProfileScope prof(QUARTET_KIND_GEMM, (hipStream_t)stream);
     hipError_t e = quartet::launch_gemm_grad_pair(g0, g1, d_dtype == QUARTET_DTYPE_BF16, nb, (hipStream_t)stream);
-    if (nb > 4u && e == hipErrorNotSupported) return QUARTET_ENOTSUP;
     return e == hipSuccess ? QUARTET_OK : hip_fail(e);
 }
 
@@ -643,7 +641,10 @@ int quartet_linear_bwd_block(const void* dy_bf16, int64_t tokens, int64_t in, in
     if ((tokens % hb) != 0 || (in % hb) != 0 || (out % hb) != 0) return QUARTET_EINVAL;
     if (rounding != QUARTET_ROUND_STOCHASTIC && rounding != QUARTET_ROUND_NEAREST) return QUARTET_EINVAL;
     if (grad_dtype != QUARTET_DTYPE_F32 && grad_dtype != QUARTET_DTYPE_BF16) return QUARTET_EINVAL;
-    const bool big = hb > 128;     // the GEMM applies the gradient epilogue itself for blocks up to 128, and of 256 in the paired launch
+    const bool big = hb > 128;
+    // The paired launch applies the gradient epilogue itself: for blocks of 256 on whole tiles with mask words, which every product has that is not
+    // empty.  Otherwise fp32 products into the workspace, which keeps room for one, with the epilogue kernel behind each.
+    const bool paired = !big || (tokens > 0 && in > 0 && out > 0 && ((reinterpret_cast<uintptr_t>(x_mask) | reinterpret_cast<uintptr_t>(w_mask)) & 3u) == 0u);
     const BwdWorkspace w = plan_bwd(tokens, in, out, big);
     if (w.total > 0 && (!workspace || workspace_bytes < w.total)) return QUARTET_EINVAL;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return QUARTET_EINVAL;
@@ -665,13 +666,11 @@ int quartet_linear_bwd_block(const void* dy_bf16, int64_t tokens, int64_t in, in
     rc = bwd_operands_launch(dy_bf16, tokens, in, out, xq_codes, xq_scales, wq_codes, wq_scales, block_groups(hb), sw, seed, rounding,
                              gt_codes, gt_scales, bx_codes, bx_scales, bw_codes, bw_scales, g_codes, g_scales, stream);
     if (rc) return rc;
-    if (!big || ((reinterpret_cast<uintptr_t>(x_mask) | reinterpret_cast<uintptr_t>(w_mask)) & 3u) == 0u) {
+    if (paired) {
         const quartet_gemm_grad_args dw_args = {gt_codes, gt_scales, bx_codes, bx_scales, out, in, tokens, w_mask, c169, dw, in};
         const quartet_gemm_grad_args dx_args = {g_codes, g_scales, bw_codes, bw_scales, tokens, in, out, x_mask, c169, dx, in};
-        rc = gemm_grad_pair_block(&dw_args, &dx_args, hb, grad_dtype, stream);
-        if (!big || rc != QUARTET_ENOTSUP) return rc;
+        return gemm_grad_pair_block(&dw_args, &dx_args, hb, grad_dtype, stream);
     }
-    // Hadamard blocks of 256 with an empty product or masks off word alignment: fp32 products, then the epilogue kernel
     rc = quartet_mxfp4_gemm(gt_codes, gt_scales, bx_codes, bx_scales, out, in, tokens, 1.0f, acc, QUARTET_DTYPE_F32, in, stream);
     if (rc) return rc;
     rc = quartet_grad_epilogue_block(acc, w_mask, out, in, hb, c169, dw, grad_dtype, stream);

@@ -893,7 +893,7 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const ui
 }
 
 // Hadamard blocks of 256 columns: the kernels that apply their epilogue take whole tiles of 256 x 256 (hence of 128 x 256) only, which is
-// what every layer with such blocks has.  Against two products on the kernels that are soonest for them, fp32 results in the
+// what every layer with such blocks has, and results and masks aligned as the C entry requires them (a guard: nothing else comes here).  Against two products on the kernels that are soonest for them, fp32 results in the
 // workspace and two epilogue kernels, layer steps (tokens, in, out; us): 256 x 1024 x 512 32.5 -> 24.5, 1024 x 768 x 1280 48 -> 34, 4096 x 4096 x
 // 2048 145 -> 112, 8192 x 2048 x 5632 288 -> 268, 1024 x 10752 x 7936 496 -> 330, 14336 x 1792 x 7680 541 -> 499.
 static bool wide_fits(const GemmArgs& g, int d_bf16) {
@@ -909,7 +909,8 @@ static void launch_wide(const GemmBatch& batch, bool large, int d_bf16, hipStrea
 }
 
 // Two gradient products in one launch (both with the fused epilogue, results of one type).  One tile shape serves both.  Hadamard
-// blocks of 256 columns (nb = 8): hipErrorNotSupported, and nothing is launched, for what those kernels do not take (an empty product).
+// blocks of 256 columns (nb = 8): hipErrorNotSupported, and nothing is launched, for what those kernels do not take; the caller sees to it that
+// there is no empty product.
 hipError_t launch_gemm_grad_pair(const GemmArgs& g0, const GemmArgs& g1, int d_bf16, uint32_t nb, hipStream_t st) {
     const bool empty0 = g0.m == 0 || g0.n == 0, empty1 = g1.m == 0 || g1.n == 0;
     if (nb == 8u && (empty0 || empty1)) return hipErrorNotSupported;

@@ -163,6 +163,20 @@ def test_block_entry_points_reject_bad_arguments_on_the_host():
     assert q.quartet_last_hip_error() == 0
 
 
+def test_backward_with_blocks_of_256_is_two_launches_or_five():
+    # operands and one paired launch; with an empty product, or masks off word alignment, operands and each product with an epilogue
+    from paper_2505_14669_amd import binding as q
+    if launches(q) is None:
+        pytest.skip("the launches are counted in the host-only build (test_sanitizers.py)")
+    P = 0x10000
+    for (t, i, o), masks, want in (((256, 512, 768), (P, P), 2), ((256, 512, 768), (P + 2, P), 5), ((256, 512, 768), (P, P + 1), 5),
+                                   ((0, 512, 768), (P, P), 5), ((256, 512, 0), (P, P), 5)):
+        for dtype in (q.QUARTET_DTYPE_F32, q.QUARTET_DTYPE_BF16):
+            before, n = launches(q), q.quartet_linear_workspace_bytes_block(t, i, o, 256)
+            assert q.quartet_linear_bwd_block(P, t, i, o, 256, P, P, masks[0], P, P, masks[1], 0, 0, P, P, dtype, P, n, 0) == 0
+            assert launches(q) - before == want, (t, i, o, masks)
+
+
 def test_static_scratch_backward_rejects_layers_beyond_its_array_on_the_host():
     from paper_2505_14669_amd import binding as q
     P = 0x10000

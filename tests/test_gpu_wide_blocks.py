@@ -48,3 +48,24 @@ def test_linear_bwd_with_blocks_of_256(G, variant, t, i, o):
                                            lin.w_mask, seed, 0, dx16, dw16, G.q.QUARTET_DTYPE_BF16, lin.ws, lin.ws_bytes))
     for got, want in ((dx16, dx), (dw16, dw)):
         assert np.array_equal(got.view(torch.uint16).cpu().numpy().ravel(), synth.f32_to_bf16(want).ravel())
+
+
+# no tokens: dW = 0; no output features: dx = 0.  The profile names the launches that there were and no other.
+@pytest.mark.parametrize("t,o", [(0, 512), (512, 0)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_empty_products_with_blocks_of_256(G, t, o, dtype):
+    import ctypes
+    i, u8 = 256, lambda n: torch.zeros(max(n, 256), dtype=torch.uint8, device="cuda")
+    dx, dw = torch.full((t, i), float("nan"), dtype=dtype, device="cuda"), torch.full((o, i), float("nan"), dtype=dtype, device="cuda")
+    ctx = [a for r in (t, o) for a in (u8(r * i // 2), u8(G.q.quartet_scale_bytes(r, i)), u8(r * i // 8))]
+    out = [a if a.numel() else u8(0) for a in (dx, dw)]
+    ws_bytes = G.q.quartet_linear_workspace_bytes_block(t, i, o, 256)
+    G.q.check(G.q.quartet_profile_enable(16))
+    try:
+        G.q.check(G.q.quartet_linear_bwd_block(u8(0), t, i, o, 256, *ctx, 5, 0, *out, int(dtype == torch.bfloat16), u8(ws_bytes), ws_bytes))
+        kinds, ms = (ctypes.c_int * 16)(), (ctypes.c_float * 16)()
+        n = G.q.quartet_profile_read(kinds, ms, 16)
+    finally:
+        G.q.quartet_profile_enable(0)
+    assert list(kinds)[1:n] == [3, 4, 3, 4]          # behind the operands: product, epilogue, product, epilogue
+    assert not dx.any() and not dw.any()

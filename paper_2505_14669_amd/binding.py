@@ -8,6 +8,7 @@ library has not been built (python -m paper_2505_14669_amd.build, or __graft_ent
 """
 import ctypes
 import os
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libquartet.so")
@@ -136,7 +137,7 @@ def _stream(stream):
 
 
 # The entry points of a training step, of serving and of the quantizers again, without ctypes (csrc/nn_autograd.cpp): they return
-# NotImplemented for arguments that the conversion here has to take or to refuse.  Bound with the device, None without the torch node.
+# NotImplemented for arguments that the conversion here has to take or to refuse.  Bound with the device; None, after a warning, without the torch node.
 _native = None
 
 
@@ -148,8 +149,9 @@ def _bind_torch():
     try:
         from . import _nn_native as native   # linked to the same library file
         _native = native
-    except ImportError:
-        pass
+    except ImportError as e:                 # the library may have been built alone; a node that does not load is no reason to stop either
+        warnings.warn(f"{__package__}._nn_native is not available ({e}): every call is converted by ctypes, which takes 2 to 4 us more of "
+                      "host time (python -m paper_2505_14669_amd.build builds it)", RuntimeWarning, stacklevel=4)
 
 
 def quartet_last_hip_error():

@@ -33,8 +33,8 @@ def code_objects(data):
 
 
 class Instruction:
-    def __init__(self, address, mnemonic, operands, target):
-        self.address, self.mnemonic, self.operands, self.target = address, mnemonic, operands, target
+    def __init__(self, address, mnemonic, operands, target, modifiers=()):
+        self.address, self.mnemonic, self.operands, self.target, self.modifiers = address, mnemonic, operands, target, modifiers
         self.states = int(operands[0], 0) + 1 if mnemonic == "s_nop" else 1      # wait states it stands for
 
     def registers(self, operand):
@@ -72,7 +72,7 @@ def kernels(tmp_path):
                 continue
             jump = re.search(r"<\S+?\+0x([0-9a-f]+)>", line)
             operands = [o.strip().split(" ")[0] for o in m[2].split(",")] if m[2] else []
-            body.append(Instruction(int(m[3], 16), m[1], operands, start + int(jump[1], 16) if jump else None))
+            body.append(Instruction(int(m[3], 16), m[1], operands, start + int(jump[1], 16) if jump else None, m[2].split()))
     return {name: body for name, body in found.items() if any(i.is_mfma for i in body)}
 
 
@@ -126,12 +126,17 @@ def test_no_vector_instruction_writes_an_operand_right_before_a_matrix_core_inst
     assert not bad, f"{len(bad)} places, first ones:\n" + "\n".join(bad[:8])
 
 
+ASSEMBLY_KERNELS = {"gemm_mxfp4_stream_kernelI": 4, "gemm_mxfp4_wide_kernelI": 2, "mfma_ceiling": 1}
+
+
 def test_results_of_matrix_core_instructions_are_not_touched_too_early(listing):
     # kernels whose matrix-core instructions are inline assembly: nothing but another of them reads or overwrites an accumulator within
     # 19 wait states of the instruction that forms it (the longest, a 16-pass instruction, needs that many)
+    for kernel, count in ASSEMBLY_KERNELS.items():
+        assert sum(kernel in name for name in listing) == count, kernel
     bad = []
     for name, body in listing.items():
-        if "gemm_mxfp4_stream_kernel" not in name and "mfma_ceiling" not in name:
+        if not any(k in name for k in ASSEMBLY_KERNELS):
             continue
         before = predecessors(body)
         for n, ins in enumerate(body):
@@ -145,20 +150,24 @@ def test_results_of_matrix_core_instructions_are_not_touched_too_early(listing):
 
 
 # result stores of a wave's full tile: one per pass of eight rows and 32-column slice
-@pytest.mark.parametrize("kernel,stores", [("gemm_mxfp4_stream_kernelI", 64), ("gemm_mxfp4_stream_tile_kernelILi2ELi4E", 32),
-                                           ("gemm_mxfp4_stream_tile_kernelILi2ELi2E", 16)])
-def test_a_full_tile_leaves_in_as_many_stores_as_the_kernels_count(listing, kernel, stores):
+@pytest.mark.parametrize("kernel,count,stores", [("gemm_mxfp4_stream_kernelI", 4, 64), ("gemm_mxfp4_stream_tile_kernelILi2ELi4E", 4, 32),
+                                                 ("gemm_mxfp4_stream_tile_kernelILi2ELi2E", 4, 16), ("gemm_mxfp4_twin_kernelI", 4, 16),
+                                                 ("gemm_mxfp4_wide_kernelI", 2, 64), ("gemm_mxfp4_wide_tile_kernelI", 2, 32)])
+def test_a_full_tile_leaves_in_as_many_stores_as_the_kernels_count(listing, kernel, count, stores):
     # The wait behind a full tile lets that many younger operations be under way; with fewer stores it would let loads through that it is
     # there to wait for.  A lane's chunks (four columns: 16 bytes, 8 in bf16) do not touch, so no store instruction can hold two:
-    # nothing wider than a chunk, and one store per chunk on the full path (another set on the ragged one; of 16-byte chunks the last
-    # may be put together from parts that the paths share).
+    # nothing wider than a chunk, and one store per chunk on each path: full tiles through the L2 (sc1), fp32 ones also past the caches
+    # (nt), and the whole chunks of ragged tiles (sc1), which the kernels for blocks of 256 columns do not have.
     names = [n for n in listing if kernel in n]
-    assert len(names) == 4
+    assert len(names) == count
     for name in names:
-        widths = [i.mnemonic for i in listing[name] if i.mnemonic.startswith(("global_store", "buffer_store", "flat_store"))]
-        assert all(w.startswith("global_store") for w in widths)
-        bf16 = re.search(r"kernelI(?:Li\dELi\dE)?Lb1E", name) is not None
-        if bf16:
-            assert not {"global_store_dwordx3", "global_store_dwordx4"} & set(widths) and widths.count("global_store_dwordx2") == 2 * stores
+        found = [i for i in listing[name] if i.mnemonic.startswith(("global_store", "buffer_store", "flat_store"))]
+        assert all(i.mnemonic.startswith("global_store") for i in found)
+        wide = lambda chunk, modifier: sum(i.mnemonic == chunk and modifier in i.modifiers for i in found)
+        through = stores if "_wide_" in kernel else 2 * stores
+        if re.search(r"kernelI(?:Li\dELi\dE)?Lb1E", name) is not None:
+            assert not {"global_store_dwordx3", "global_store_dwordx4"} & {i.mnemonic for i in found}
+            assert wide("global_store_dwordx2", "sc1") == through and wide("global_store_dwordx2", "nt") == 0
         else:
-            assert widths.count("global_store_dwordx4") >= stores - 1
+            assert wide("global_store_dwordx4", "sc1") == through and wide("global_store_dwordx4", "nt") == stores
+        assert sum(i.mnemonic in ("global_store_dwordx2", "global_store_dwordx3", "global_store_dwordx4") for i in found) == through + wide("global_store_dwordx4", "nt")

@@ -69,3 +69,37 @@ def test_empty_products_with_blocks_of_256(G, t, o, dtype):
         G.q.quartet_profile_enable(0)
     assert list(kinds)[1:n] == [3, 4, 3, 4]          # behind the operands: product, epilogue, product, epilogue
     assert not dx.any() and not dw.any()
+
+
+# Blocks that take extra tiles of the second product for part of its rounds (1 of 2 and 4 of 5 with 256 x 256 tiles, 2 of 5 and 8 of 9 with
+# 128 x 256), the second layer with fp32 results of more than 256 MB, which go past the memory-side cache.  Against plain products on tiles
+# of the same shape and the epilogue kernel: the same sums and butterflies in the same order, so the same bits.
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("t,i,o", [(4096, 4864, 768), (65536, 1024, 256)])
+def test_wide_pair_equals_products_and_epilogues(G, variant, t, i, o):
+    q, block, seed = G.q, 256, 91
+    gen = torch.Generator(device="cuda").manual_seed(t + variant)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)
+    quantized = lambda rows, k: (torch.empty((rows, k // 2), dtype=torch.uint8, device="cuda"), torch.empty(q.quartet_scale_bytes(rows, k), dtype=torch.uint8, device="cuda"))
+    x, w, dy = rand(t, i), rand(o, i), rand(t, o)
+    xq, wq = quantized(t, i), quantized(o, i)
+    xm, wm = (torch.empty((r, i // 32), dtype=torch.int32, device="cuda") for r in (t, o))
+    q.check(q.quartet_linear_fwd_block(x, w, t, i, o, block, torch.empty((t, o), device="cuda"), 0, *xq, xm, *wq, wm))
+    n = q.quartet_linear_workspace_bytes_block(t, i, o, block)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    sw = q.quartet_sign_words(seed)
+    g, gt, wt, xt = quantized(t, o), quantized(o, t), quantized(i, o), quantized(i, t)
+    q.check(q.quartet_quant_bwd_sr_block(dy, t, o, o, 0, block, sw, seed, 0, 0, *g))
+    q.check(q.quartet_requant_transpose_sr_block(*wq, i, o, block, sw, seed, 1, 0, *wt))
+    q.check(q.quartet_quant_bwd_sr_block(dy, o, t, o, 1, block, sw, seed, 2, 0, *gt))
+    q.check(q.quartet_requant_transpose_sr_block(*xq, i, t, block, sw, seed, 3, 0, *xt))
+    assert q.quartet_debug_set_gemm_plan(variant, 0) == 0
+    for dtype in (torch.float32, torch.bfloat16):
+        bf16 = int(dtype == torch.bfloat16)
+        dx, dw = (torch.full((r, i), float("nan"), dtype=dtype, device="cuda") for r in (t, o))
+        q.check(q.quartet_linear_bwd_block(dy, t, i, o, block, *xq, xm, *wq, wm, seed, 0, dx, dw, bf16, ws, n))
+        for got, a, b, mask, m, k in ((dx, g, wt, xm, t, o), (dw, gt, xt, wm, o, t)):
+            acc, want = torch.empty((m, i), device="cuda"), torch.empty((m, i), dtype=dtype, device="cuda")
+            q.check(q.quartet_mxfp4_gemm(*a, *b, m, i, k, 1.0, acc, 0, i))
+            q.check(q.quartet_grad_epilogue_block(acc, mask, m, i, block, float(np.float32(16.0) / np.float32(9.0)), want, bf16))
+            assert torch.equal(got.view(torch.int16 if bf16 else torch.int32), want.view(torch.int16 if bf16 else torch.int32))

@@ -311,11 +311,18 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
         // past (a launch whose results the memory-side cache cannot hold): non-temporal; otherwise through the L2.  Against plain stores,
         // whose lines the L2 evicts and writes back while the next tiles load (us): forward 1003 x 2048 x 5632 22.1 -> 21.1; layer steps 2336 x
         // 1376 x 3168 64.8 -> 63.7, 16384 x 4096 x 4096 563 -> 547, 16384 x 4096 x 11008 1328 -> 1306.  A branch per pass, not per store.
-        if (FULL && !OUT_BF16 && past) {
+        if (FULL && past) {
 #pragma unroll
             for (uint32_t j = 0; j < TN; ++j) {
-                const v4f v = {vv[j][0], vv[j][1], vv[j][2], vv[j][3]};
-                __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(static_cast<float*>(d) + (size_t)grow * ldd + col_base + j * 32u + 4u * c));
+                const size_t at = (size_t)grow * ldd + col_base + j * 32u + 4u * c;
+                if (OUT_BF16) {
+                    const uint32_t h0 = f32_to_bf16_rne(vv[j][0]), h1 = f32_to_bf16_rne(vv[j][1]), h2 = f32_to_bf16_rne(vv[j][2]), h3 = f32_to_bf16_rne(vv[j][3]);
+                    const v2u_t v = {h0 | (h1 << 16), h2 | (h3 << 16)};
+                    __builtin_nontemporal_store(v, reinterpret_cast<v2u_t*>(static_cast<uint16_t*>(d) + at));
+                } else {
+                    const v4f v = {vv[j][0], vv[j][1], vv[j][2], vv[j][3]};
+                    __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(static_cast<float*>(d) + at));
+                }
             }
             continue;
         }

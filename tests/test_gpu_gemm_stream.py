@@ -72,3 +72,25 @@ def test_gemm_chosen_plan_exact(G, mnk, code):
     rng = np.random.default_rng(m + n + k)
     (a, sa, va), (b, sb, vb) = _operand(rng, m, k), _operand(rng, n, k)
     assert np.array_equal(G.gemm(a, sa, b, sb), (va @ vb.T).cpu().numpy().astype(np.float32))
+
+
+# results of 256 MB and more, which full tiles store past the memory-side cache; full and ragged tiles, every kernel, plain and with the
+# gradient epilogue (against the epilogue kernel on the exact product)
+@pytest.mark.parametrize("variant", [0, 1, 2, 22])
+@pytest.mark.parametrize("dtype,m,n", [(torch.float32, 8192 + 100, 8192), (torch.bfloat16, 16384 + 100, 8192)])
+def test_results_past_the_memory_side_cache(G, variant, dtype, m, n):
+    from paper_2505_14669_amd import binding as q
+    rng, k, bf16 = np.random.default_rng(variant), 288, int(dtype == torch.bfloat16)
+    (a, sa, va), (b, sb, vb) = _operand(rng, m, k), _operand(rng, n, k)
+    a, sa, b, sb = G.to_dev(a), G.to_dev(G.scales_to_tiled(sa)), G.to_dev(b), G.to_dev(G.scales_to_tiled(sb))
+    assert q.quartet_debug_set_gemm_plan(variant, 0) == 0
+    got = torch.full((m, n), float("nan"), dtype=dtype, device="cuda")
+    q.check(q.quartet_mxfp4_gemm(a, sa, b, sb, m, n, k, 1.0, got, bf16, n))
+    exact = (va @ vb.T).float()
+    assert torch.equal(got, exact.to(dtype))
+    mask = torch.from_numpy(rng.integers(-2 ** 31, 2 ** 31, size=(m, n // 32), dtype=np.int64).astype(np.int32)).cuda()
+    want = torch.empty_like(got)
+    q.check(q.quartet_grad_epilogue(exact, mask, m, n, float(oracle.FL_16_9), want, bf16))
+    q.check(q.quartet_mxfp4_gemm_grad(a, sa, b, sb, m, n, k, mask, float(oracle.FL_16_9), got, bf16, n))
+    bits = torch.int16 if bf16 else torch.int32
+    assert torch.equal(got.view(bits), want.view(bits))

@@ -71,11 +71,11 @@ def test_empty_products_with_blocks_of_256(G, t, o, dtype):
     assert not dx.any() and not dw.any()
 
 
-# Blocks that take extra tiles of the second product for part of its rounds (1 of 2 and 4 of 5 with 256 x 256 tiles, 2 of 5 and 8 of 9 with
-# 128 x 256), the second layer with fp32 results of more than 256 MB, which go past the memory-side cache.  Against plain products on tiles
-# of the same shape and the epilogue kernel: the same sums and butterflies in the same order, so the same bits.
+# Blocks that take extra tiles of the second product for part of its rounds (1 of 2 and 8 of 9 with 256 x 256 tiles, 2 of 5 and 16 of 17 with
+# 128 x 256), the second layer with results of more than 256 MB in both types, which go past the memory-side cache.  Against plain products on
+# tiles of the same shape and the epilogue kernel: the same sums and butterflies in the same order, so the same bits.
 @pytest.mark.parametrize("variant", [0, 1])
-@pytest.mark.parametrize("t,i,o", [(4096, 4864, 768), (65536, 1024, 256)])
+@pytest.mark.parametrize("t,i,o", [(4096, 4864, 768), (131072, 1024, 256)])
 def test_wide_pair_equals_products_and_epilogues(G, variant, t, i, o):
     q, block, seed = G.q, 256, 91
     gen = torch.Generator(device="cuda").manual_seed(t + variant)

@@ -310,7 +310,8 @@ __device__ __forceinline__ void store_tile_rows8(ACC (&acc)[AM][AN], float* wbuf
         if (!FULL && grow >= m) continue;
         // past (a launch whose results the memory-side cache cannot hold): non-temporal; otherwise through the L2.  Against plain stores,
         // whose lines the L2 evicts and writes back while the next tiles load (us): forward 1003 x 2048 x 5632 22.1 -> 21.1; layer steps 2336 x
-        // 1376 x 3168 64.8 -> 63.7, 16384 x 4096 x 4096 563 -> 547, 16384 x 4096 x 11008 1328 -> 1306.  A branch per pass, not per store.
+        // 1376 x 3168 64.8 -> 63.7, 16384 x 4096 x 4096 563 -> 547, 16384 x 4096 x 11008 1328 -> 1306.  A branch per pass, not per store;
+        // for bf16 `past` is a constant.
         if (FULL && past) {
 #pragma unroll
             for (uint32_t j = 0; j < TN; ++j) {

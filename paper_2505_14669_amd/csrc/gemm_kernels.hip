@@ -66,7 +66,7 @@ struct GemmProblem {
 struct GemmBatch {
     GemmProblem p[2];
     uint32_t extra_tiles, late;     // the second product's tiles that the last `late` blocks take in rounds of their own, see TileWalk
-    uint32_t past;                  // results are stored past the memory-side cache (store_tile_rows8)
+    uint32_t past;                  // fp32 results are stored past the memory-side cache (store_tile_rows8); of bf16 ones by kernels of their own
 };
 
 // The tiles of block b of G: b, b + G, ... of the first product, then, with the blocks counted from r = its tiles % G on, tiles of the
@@ -104,8 +104,9 @@ __device__ __forceinline__ uint32_t scale_selector(uint32_t lane, uint32_t group
 // stages never drains between them: the loads of the next tile's first stages are issued during the last stages
 // of the current one, so a tile's first matrix-core instruction follows the previous tile's result stores directly.
 // The epilogue uses a scratch of its own (16 KB beside the 144 KB ring).
-// WIDE: Hadamard blocks of 256 columns (store_tile_rows8): sizes are multiples of the tile
-template <bool OUT_BF16, bool FUSED, bool WIDE>
+// WIDE: Hadamard blocks of 256 columns (store_tile_rows8): sizes are multiples of the tile.  PAST16: bf16 results past the memory-side cache: a
+// branch per pass, as fp32 results have it, costs bf16 launches 0.5-1.6 % (layer step 2336 x 1376 x 3168 58.3 -> 59.2 us).
+template <bool OUT_BF16, bool FUSED, bool WIDE, bool PAST16 = false>
 __device__ __forceinline__ void stream_large_tiles(const GemmBatch& batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t TM = 4, TN = 4, BM = 256, BN = 256;
     constexpr uint32_t CODES = (BM + BN) * 8;            // 16-byte chunks of codes per K-quad
@@ -128,6 +129,7 @@ __device__ __forceinline__ void stream_large_tiles(const GemmBatch& batch, uint3
     const uint32_t second_start = blockIdx.x + late >= G ? blockIdx.x + late - G : extra_tiles + late + blockIdx.x;
     const uint32_t wm0 = (wave >> 1) * 128u, wn0 = (wave & 1u) * 128u;
     const bool scales_of_a = wave < 2u;
+    const uint32_t past = OUT_BF16 ? (uint32_t)PAST16 : batch.past;
 
 // tile origin of tile number V of product Q (XCD-aware order, bands of band_height tile rows); V >= its tiles: M0 = m (no rows)
 #define STREAM_TILE(Q, V, M0, N0)                                                                       \
@@ -347,9 +349,9 @@ __device__ __forceinline__ void stream_large_tiles(const GemmBatch& batch, uint3
         const uint32_t* __restrict__ mask = q.mask;
         const uint32_t row_base = m0 + wm0, col_base = n0 + wn0;
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
-        if constexpr (WIDE) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
-        else if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
-        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        if constexpr (WIDE) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, past);
+        else if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, past);
+        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, past);
         stores = WIDE || full;                             // 16 passes of four stores each; a ragged tile may have skipped some
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // the quads issued past the last tile (zero-filled) have landed before the LDS is given back
@@ -381,6 +383,17 @@ gemm_mxfp4_stream_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ cl
     stream_large_tiles<OUT_BF16, FUSED, false>(batch, nb, clock_counters);
 }
 
+template <bool FUSED>
+__global__ void __launch_bounds__(256)
+gemm_mxfp4_past_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+    stream_large_tiles<true, FUSED, false, true>(batch, nb, clock_counters);
+}
+
+__global__ void __launch_bounds__(256)
+gemm_mxfp4_past_wide_kernel(GemmBatch batch, uint64_t* __restrict__ clock_counters) {
+    stream_large_tiles<true, true, true, true>(batch, 8u, clock_counters);
+}
+
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(256)
 gemm_mxfp4_wide_kernel(GemmBatch batch, uint64_t* __restrict__ clock_counters) {
@@ -403,7 +416,7 @@ gemm_mxfp4_wide_kernel(GemmBatch batch, uint64_t* __restrict__ clock_counters) {
 // three quarters of a quad to land: with several tiles per compute unit that is less than what the epilogues cost one block alone.
 // Pairs of layers (tokens, in, out), one block / two (us): 608 x 8832 x 3424 63.6 / 52.7, 4800 x 1824 x 2112 48.9 / 43.6, 9600 x 576 x 576 32.4 /
 // 36.0 (a tile or two per compute unit: the deeper ring); single products 10327 x 992 x 800 21.1 / 17.9, 4926 x 6496 x 10144 230 / 251.
-template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED, bool WIDE = false>
+template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED, bool WIDE = false, bool PAST16 = false>
 __device__ __forceinline__ void stream_tiles(const GemmBatch& batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
     constexpr uint32_t BM = 64 * TM, BN = 64 * TN;
     static_assert(BM % 128 == 0 && BN % 128 == 0, "a wave's four scale tiles must belong to one operand");
@@ -436,6 +449,7 @@ __device__ __forceinline__ void stream_tiles(const GemmBatch& batch, uint32_t nb
     // their load is out of range and delivers zeros, which keeps every wave's count of loads the same)
     const bool has_scales = 4u * wave < NT, scales_of_a = 4u * wave < BM / 32u;
     const uint32_t stile0 = scales_of_a ? 4u * wave : 4u * wave - BM / 32u;
+    const uint32_t past = OUT_BF16 ? (uint32_t)PAST16 : batch.past;
 
 // tile origin of tile number V of product Q (as in the 256 x 256 kernel)
 #define TILE_ORIGIN(Q, V, M0, N0)                                                                       \
@@ -633,9 +647,9 @@ __device__ __forceinline__ void stream_tiles(const GemmBatch& batch, uint32_t nb
         const uint32_t* __restrict__ mask = q.mask;
         const uint32_t row_base = m0 + wm0, col_base = n0 + wn0;
         const bool full = (ldd & 3u) == 0u && row_base + TM * 32u <= m && col_base + TN * 32u <= n && (!FUSED || mask != nullptr);
-        if constexpr (WIDE) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
-        else if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
-        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, batch.past);
+        if constexpr (WIDE) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, past);
+        else if (full) store_tile_rows8<TM, TN, OUT_BF16, FUSED, true>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, past);
+        else store_tile_rows8<TM, TN, OUT_BF16, FUSED, false>(acc, wbuf, q.d, ldd, mask, q.alpha, row_base, col_base, m, n, lane, nb, past);
         stores = WIDE || full;                             // every store was issued; a ragged tile may have skipped some
         if (!LATE) {
             __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
@@ -679,6 +693,12 @@ gemm_mxfp4_twin_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ cloc
     stream_tiles<2, 2, 2, OUT_BF16, FUSED>(batch, nb, clock_counters);
 }
 
+template <bool FUSED>
+__global__ void __launch_bounds__(256, 2)
+gemm_mxfp4_past_twin_kernel(GemmBatch batch, uint32_t nb, uint64_t* __restrict__ clock_counters) {
+    stream_tiles<2, 2, 2, true, FUSED, false, true>(batch, nb, clock_counters);
+}
+
 static int stream_blocks() {
     static int cus = 0;
     if (cus == 0) {
@@ -695,7 +715,8 @@ static int stream_blocks() {
 // what follows out.  Less is stored through the L2 and stays there for its reader.  Through the L2 / past the cache (us), layer steps
 // (tokens, in, out): fp32 16384 x 2048 x 4096 (y 256 MB) 357 / 344, 16384 x 4096 x 4096 572 / 534, 8192 x 7936 x 1024 (gradients 279 MB) 229 / 219; bf16
 // 16384 x 2048 x 8192 (y 256 MB) 605 / 592, 16384 x 8192 x 1024 (gradients 272 MB) 447 / 430, 12544 x 10752 x 2048 659 / 637.  A forward pass of 256 MB that is
-// repeated alone is 3-10 % slower past the cache (fp32 8192 x 2048 x 8192 107 / 117), from 264 MB on 0-6 % faster.
+// repeated alone is 1-10 % slower past the cache (fp32 8192 x 2048 x 8192 107 / 117), from 264 MB on 0-6 % faster.  For bf16 on the kernels that such
+// launches take; 128 x 256 tiles, which take 1 in 1000 of them, and forced 128 x 128 ones with one block per compute unit stay with the L2.
 static uint32_t stored_past(const GemmBatch& batch, bool bf16) {
     const double results = (double)batch.p[0].m * batch.p[0].n + (double)batch.p[1].m * batch.p[1].n;
     return results * (bf16 ? 2.0 : 4.0) >= 256.0 * 1024.0 * 1024.0 ? 1u : 0u;
@@ -720,8 +741,9 @@ static GemmProblem make_problem(const uint8_t* a_codes, const uint8_t* a_scales,
 template <bool OUT_BF16, bool FUSED>
 static void launch_stream_batch_t(const GemmBatch& batch, uint32_t nb, hipStream_t st) {
     const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, cus = (uint32_t)stream_blocks();
-    hipLaunchKernelGGL((gemm_mxfp4_stream_kernel<OUT_BF16, FUSED>), dim3(total < cus ? total : cus), dim3(256), 0, st, batch, nb,
-                       g_clock_counters);
+    const dim3 grid(total < cus ? total : cus);
+    if (OUT_BF16 && batch.past) hipLaunchKernelGGL((gemm_mxfp4_past_kernel<FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
+    else hipLaunchKernelGGL((gemm_mxfp4_stream_kernel<OUT_BF16, FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
 }
 
 template <bool OUT_BF16, bool FUSED>
@@ -740,7 +762,8 @@ template <int TM, int TN, int PER_CU, bool OUT_BF16, bool FUSED>
 static void launch_stream_tile_batch_t(const GemmBatch& batch, uint32_t nb, hipStream_t st) {
     const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, room = PER_CU * (uint32_t)stream_blocks();
     const dim3 grid(total < room ? total : room);
-    if constexpr (PER_CU == 2) hipLaunchKernelGGL((gemm_mxfp4_twin_kernel<OUT_BF16, FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
+    if (PER_CU == 2 && OUT_BF16 && batch.past) hipLaunchKernelGGL((gemm_mxfp4_past_twin_kernel<FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
+    else if constexpr (PER_CU == 2) hipLaunchKernelGGL((gemm_mxfp4_twin_kernel<OUT_BF16, FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
     else hipLaunchKernelGGL((gemm_mxfp4_stream_tile_kernel<TM, TN, OUT_BF16, FUSED>), grid, dim3(256), 0, st, batch, nb, g_clock_counters);
 }
 
@@ -905,7 +928,8 @@ static bool wide_fits(const GemmArgs& g, int d_bf16) {
 static void launch_wide(const GemmBatch& batch, bool large, int d_bf16, hipStream_t st) {
     const uint32_t total = batch.p[0].total_tiles + batch.p[1].total_tiles, cus = (uint32_t)stream_blocks();
     const dim3 grid(total < cus ? total : cus), block(256);
-    if (large && d_bf16) hipLaunchKernelGGL((gemm_mxfp4_wide_kernel<true>), grid, block, 0, st, batch, g_clock_counters);
+    if (large && d_bf16 && batch.past) hipLaunchKernelGGL(gemm_mxfp4_past_wide_kernel, grid, block, 0, st, batch, g_clock_counters);
+    else if (large && d_bf16) hipLaunchKernelGGL((gemm_mxfp4_wide_kernel<true>), grid, block, 0, st, batch, g_clock_counters);
     else if (large) hipLaunchKernelGGL((gemm_mxfp4_wide_kernel<false>), grid, block, 0, st, batch, g_clock_counters);
     else if (d_bf16) hipLaunchKernelGGL((gemm_mxfp4_wide_tile_kernel<true>), grid, block, 0, st, batch, g_clock_counters);
     else hipLaunchKernelGGL((gemm_mxfp4_wide_tile_kernel<false>), grid, block, 0, st, batch, g_clock_counters);

@@ -126,7 +126,8 @@ def test_no_vector_instruction_writes_an_operand_right_before_a_matrix_core_inst
     assert not bad, f"{len(bad)} places, first ones:\n" + "\n".join(bad[:8])
 
 
-ASSEMBLY_KERNELS = {"gemm_mxfp4_stream_kernelI": 4, "gemm_mxfp4_wide_kernelI": 2, "mfma_ceiling": 1}
+ASSEMBLY_KERNELS = {"gemm_mxfp4_stream_kernelI": 4, "gemm_mxfp4_past_kernelI": 2, "gemm_mxfp4_past_wide_kernel": 1, "gemm_mxfp4_wide_kernelI": 2,
+                    "mfma_ceiling": 1}
 
 
 def test_results_of_matrix_core_instructions_are_not_touched_too_early(listing):
@@ -152,23 +153,23 @@ def test_results_of_matrix_core_instructions_are_not_touched_too_early(listing):
 # result stores of a wave's full tile: one per pass of eight rows and 32-column slice
 @pytest.mark.parametrize("kernel,count,stores", [("gemm_mxfp4_stream_kernelI", 4, 64), ("gemm_mxfp4_stream_tile_kernelILi2ELi4E", 4, 32),
                                                  ("gemm_mxfp4_stream_tile_kernelILi2ELi2E", 4, 16), ("gemm_mxfp4_twin_kernelI", 4, 16),
-                                                 ("gemm_mxfp4_wide_kernelI", 2, 64), ("gemm_mxfp4_wide_tile_kernelI", 2, 32)])
+                                                 ("gemm_mxfp4_wide_kernelI", 2, 64), ("gemm_mxfp4_wide_tile_kernelI", 2, 32),
+                                                 ("gemm_mxfp4_past_kernelI", 2, 64), ("gemm_mxfp4_past_twin_kernelI", 2, 16),
+                                                 ("gemm_mxfp4_past_wide_kernel", 1, 64)])
 def test_a_full_tile_leaves_in_as_many_stores_as_the_kernels_count(listing, kernel, count, stores):
     # The wait behind a full tile lets that many younger operations be under way; with fewer stores it would let loads through that it is
     # there to wait for.  A lane's chunks (four columns: 16 bytes, 8 in bf16) do not touch, so no store instruction can hold two:
-    # nothing wider than a chunk, and one store per chunk on each path: full tiles through the L2 (sc1) or past the caches (nt), and
-    # the whole chunks of ragged tiles (sc1), which the kernels for blocks of 256 columns do not have.
+    # nothing wider than a chunk, and one store per chunk on each path: full tiles through the L2 (sc1), fp32 ones also past the caches (nt),
+    # bf16 ones there in kernels of their own, and the whole chunks of ragged tiles (sc1), which the kernels for blocks of 256 columns do not have.
     names = [n for n in listing if kernel in n]
     assert len(names) == count
     for name in names:
         found = [i for i in listing[name] if i.mnemonic.startswith(("global_store", "buffer_store", "flat_store"))]
         assert all(i.mnemonic.startswith("global_store") for i in found)
-        wide = lambda chunk, modifier: sum(i.mnemonic == chunk and modifier in i.modifiers for i in found)
-        through = stores if "_wide_" in kernel else 2 * stores
-        if re.search(r"kernelI(?:Li\dELi\dE)?Lb1E", name) is not None:
-            assert not {"global_store_dwordx3", "global_store_dwordx4"} & {i.mnemonic for i in found}
-            chunk = "global_store_dwordx2"
-        else:
-            chunk = "global_store_dwordx4"
-        assert wide(chunk, "sc1") == through and wide(chunk, "nt") == stores
-        assert sum(i.mnemonic in ("global_store_dwordx2", "global_store_dwordx3", "global_store_dwordx4") for i in found) == through + stores
+        bf16 = "_past_" in kernel or re.search(r"kernelI(?:Li\dELi\dE)?Lb1E", name) is not None
+        chunk = "global_store_dwordx2" if bf16 else "global_store_dwordx4"
+        ragged = 0 if "_wide_" in kernel else stores
+        through, past = (0, stores) if "_past_" in kernel else (stores, 0 if bf16 else stores)
+        with_modifier = lambda modifier: sum(i.mnemonic == chunk and modifier in i.modifiers for i in found)
+        assert with_modifier("sc1") == through + ragged and with_modifier("nt") == past
+        assert sum(i.mnemonic in ("global_store_dwordx2", "global_store_dwordx3", "global_store_dwordx4") for i in found) == through + ragged + past

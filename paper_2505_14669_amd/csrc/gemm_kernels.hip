@@ -19,7 +19,7 @@
 //
 // Kernels: gemm_mxfp4_stream_kernel (256 x 256 tiles) and gemm_mxfp4_stream_tile_kernel (128 x 256 and 128 x 128 tiles
 // for small problems): one block per compute unit streams its tiles through a ring of K-quads (256 elements) in LDS, of 128 x 128 tiles
-// also two (gemm_mxfp4_twin_kernel).  All work through a batch of one or two products per launch (GemmBatch).
+// also two (gemm_mxfp4_twin_kernel).  The wide kernels are for Hadamard blocks of 256, the past kernels for bf16 results of 256 MB and more.  All work through a batch of one or two products per launch (GemmBatch).
 // What bounds them besides power is the way of the operands into the LDS: a cache line is 128 bytes, so a ring of 128-element
 // stages (64 bytes of codes per row) fetched every line twice.  K-quads, whole lines, one barrier per quad and reads and loads spread
 // evenly over the matrix-core instructions, 16 x 16 x 128 on the large tiles and 32 x 32 x 64 on the small ones, took against that design
@@ -48,8 +48,8 @@ void set_gemm_plan(int variant, int band_height) {
     g_forced_band = band_height;
 }
 
-// One product of a launch of the 256 x 256 streaming kernel, and the one or two products a launch works through: the
-// block's virtual tile ids run over the first product's tiles, then the second's (Algorithm 1 Backward: the two gradient
+// One product of a launch of the streaming kernels, and the one or two products a launch works through: a
+// block walks tiles of the first product, then of the second (TileWalk; Algorithm 1 Backward: the two gradient
 // products do not depend on each other; in one launch the second starts where the first leaves compute units idle and
 // there is one ramp-up and one drain instead of two).
 struct GemmProblem {
@@ -100,10 +100,10 @@ __device__ __forceinline__ uint32_t scale_selector(uint32_t lane, uint32_t group
 }
 
 // ---------------------------------------------------------------------------------------------
-// Streaming variant: one block per compute unit walks its tiles (virtual block ids b, b + G, ...), and the ring of LDS
+// Streaming variant: one block per compute unit walks its tiles (TileWalk), and the ring of LDS
 // stages never drains between them: the loads of the next tile's first stages are issued during the last stages
 // of the current one, so a tile's first matrix-core instruction follows the previous tile's result stores directly.
-// The epilogue uses a scratch of its own (16 KB beside the 144 KB ring).
+// The epilogue uses a scratch of its own (16 KB beside the 136 KB ring).
 // WIDE: Hadamard blocks of 256 columns (store_tile_rows8): sizes are multiples of the tile.  PAST16: bf16 results past the memory-side cache: a
 // branch per pass, as fp32 results have it, costs bf16 launches 0.5-1.6 % (layer step 2336 x 1376 x 3168 58.3 -> 59.2 us).
 template <bool OUT_BF16, bool FUSED, bool WIDE, bool PAST16 = false>
